@@ -495,6 +495,8 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         p.tpos[i] = c->tpos[i]; p.tneg[i] = c->tneg[i]; p.bin_sc[i] = c->bin_sc[i]; p.bin_off[i] = c->bin_off[i];
         p.bin_lo[i] = c->bin_lo[i]; p.bin_hi[i] = c->bin_hi[i];
         p.gid_w |= (unsigned)c->gid[i] << (4 * i);
+        if ((i & 1) && c->gid[i] == c->gid[i - 1]) p.second_mask |= 1u << i;
+        if ((i & 3) == 3 && c->gid[i] == c->gid[i - 1] && c->gid[i] == c->gid[i - 2] && c->gid[i] == c->gid[i - 3]) p.second_mask |= 1u << (i - 1);
         if (c->mirror[i]) p.mirror_mask |= 1u << i;
         if (c->selfsym[i]) p.selfsym_mask |= 1u << i;
         p.nent[i] = (unsigned char)c->nent[i];
@@ -557,7 +559,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     }
     // one workgroup of 4*occ wavefronts per compute unit; each takes a contiguous range of (strip,row) steps
     const long long waves_per_wg = 4 * occ;
-    long long wg = std::min<long long>(c->n_cu, (p.total_units + waves_per_wg - 1) / waves_per_wg);
+    long long wg = std::min<long long>(c->n_cu, (p.total_units + 3) / 4);
     wg = std::max<long long>(wg, 1);
     p.n_waves = wg * waves_per_wg;
     if (!launch) return SOP_OK;

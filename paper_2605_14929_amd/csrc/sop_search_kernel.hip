@@ -47,27 +47,33 @@
 
 namespace sopk {
 
-__device__ __forceinline__ float xor_lanes(float v, int mask) { return __shfl_xor(v, mask, 64); }
+// value of the lane's partner under lane ^ MASK (1 or 2): a data-parallel-primitive move inside quads of lanes, on the vector
+// ALU (a general exchange goes through LDS, which the element passes keep busy).  Used where all 64 lanes are active.
+template <int MASK> __device__ __forceinline__ float xor_lanes(float v)
+{
+    static_assert(MASK == 1 || MASK == 2, "exchange inside a quad");
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), MASK == 1 ? 0xB1 : 0x4E, 0xF, 0xF, false));   // quad_perm [1,0,3,2] / [2,3,0,1]
+}
 
 template <int LPB> __device__ __forceinline__ float group_max(float v)
 {
-    if (LPB >= 2) v = fmaxf(v, xor_lanes(v, 1));
-    if (LPB >= 4) v = fmaxf(v, xor_lanes(v, 2));
+    if (LPB >= 2) v = fmaxf(v, xor_lanes<1>(v));
+    if (LPB >= 4) v = fmaxf(v, xor_lanes<2>(v));
     return v;
 }
 // balanced tree over the lanes of a block, in lane (= index) order; both partners compute the
 // same rounded sum because addition commutes
 template <int LPB> __device__ __forceinline__ float group_sum(float v)
 {
-    if (LPB >= 2) v = v + xor_lanes(v, 1);
-    if (LPB >= 4) v = v + xor_lanes(v, 2);
+    if (LPB >= 2) v = v + xor_lanes<1>(v);
+    if (LPB >= 4) v = v + xor_lanes<2>(v);
     return v;
 }
 
 // wave-uniform switches of the row loop
 struct Switches {
     int A;
-    uint32_t pair_mask, flip_mask, gid, unit_tpos, unit_tneg, wide, mirror, selfsym;
+    uint32_t pair_mask, flip_mask, gid, unit_tpos, unit_tneg, wide, mirror, selfsym, second;
 };
 
 // round a non-negative fp32 to the scale word: nearest, ties to the lower code, saturating
@@ -82,8 +88,8 @@ __device__ __forceinline__ int encode_scale(float sp, const KParams& p)
     const bool sub = E < 128 - p.bias;
     if (__any(sub)) {
         // subnormal range of the target (or zero): quantum 2^(1-bias-y)
-        const int Ee = E > 0 ? E : 1;
-        const uint32_t m = (u & 0x7FFFFFu) | (E > 0 ? 0x800000u : 0u);
+        const int Ee = max(E, 1);
+        const uint32_t m = (u & 0x7FFFFFu) | ((uint32_t)min(E, 1) << 23);
         int S = 151 - p.bias - y - Ee;
         S = S > 31 ? 31 : S;
         const uint32_t qs = S > 0 ? ((m + ((1u << (S - 1)) - 1u)) >> S) : 0u;
@@ -226,6 +232,22 @@ struct Sums {
     float err;    // decision score of metrics WSE / MSE (and the blk_err output)
     float wd;     // RESIDUAL form: <w,d>_c;  DIRECT form: numerator sum
     float ew;     // RESIDUAL form with metric MSE: c-weighted ||d||^2;  DIRECT form: denominator sum
+    float rn = 0.0f, rd = 0.0f; // RESIDUAL form with RANK: numerator and denominator sums of the ranking score (the DIRECT form's)
+};
+
+// One element's share of the ranking score's sums (chunks of 8 and the tree, as the DIRECT form)
+template <int EPL>
+struct RankSums {
+    float n0 = 0.0f, n1 = 0.0f, d0 = 0.0f, d1 = 0.0f;
+    __device__ __forceinline__ void add(int i, float w, float c, float ss, float yv)
+    {
+        const float what = ss * yv;
+        const float cw = c * w, cwh = c * what;
+        if (i < 8) { n0 = __fmaf_rn(cw, what, n0); d0 = __fmaf_rn(cwh, what, d0); }
+        else       { n1 = __fmaf_rn(cw, what, n1); d1 = __fmaf_rn(cwh, what, d1); }
+    }
+    __device__ __forceinline__ float num() const { return EPL == 16 ? n0 + n1 : n0; }
+    __device__ __forceinline__ float den() const { return EPL == 16 ? d0 + d1 : d0; }
 };
 
 // One bin record read: boundary, value below, value above (and the lower code when codes are wanted).
@@ -272,11 +294,12 @@ __device__ __forceinline__ void put_code(uint32_t (&codes)[EPL / 4], int i, uint
 // where a codebook under the negative scale sign and its sign-negated copy under the positive sign part ways).  The
 // comparison writes a scalar lane mask and the masks are joined on the scalar unit: one vector instruction per
 // element.  (-0 and +0 compare equal, so a boundary at zero is seen from either side.)
-template <int EPL, int METRIC, bool CODES, bool TIES = false, class SRC>
+template <int EPL, int METRIC, bool CODES, bool TIES = false, bool RANK = false, class SRC>
 __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float (&cb)[EPL], const SRC& src, float ss, int a,
                                               bool wide_codes, uint32_t (&codes)[EPL / 4], unsigned long long* tie = nullptr)
 {
     float e0 = 0.0f, e1 = 0.0f, wd = 0.0f, ew = 0.0f;
+    RankSums<EPL> rk;
     if (CODES) {
 #pragma unroll
         for (int j = 0; j < EPL / 4; ++j) codes[j] = 0;
@@ -303,14 +326,87 @@ __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float
             if (i < 8) e0 = __fmaf_rn(dd, d, e0); else e1 = __fmaf_rn(dd, d, e1);
             wd = __fmaf_rn(cd, w[i], wd);
             if (METRIC == 2) ew = __fmaf_rn(cd, d, ew);
+            if constexpr (RANK) rk.add(i, w[i], cb[i], ss, yv);
             put_code<EPL, CODES>(codes, i, (uint32_t)r[j].clo + (up ? 1u : 0u), wide_codes);
+        }
+        // (one chunk's look-ups in flight at a time where the pass keeps many sums: a register budget, not an order)
+        if constexpr (RANK) {
+            asm volatile("" : "+v"(e0), "+v"(e1), "+v"(wd), "+v"(rk.n0), "+v"(rk.n1), "+v"(rk.d0), "+v"(rk.d1));
+            if constexpr (METRIC == 2) asm volatile("" : "+v"(ew));
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     Sums s;
     s.err = EPL == 16 ? e0 + e1 : e0;
     s.wd = wd;
     s.ew = ew;
+    if constexpr (RANK) { s.rn = rk.num(); s.rd = rk.den(); }
     return s;
+}
+
+// Element pass of N atoms of one scale group at once (slots a .. a+N-1; metrics WSE and MSE): the scaled weight and its
+// table address are formed once per element, used for every atom and dropped, so no array of either is ever held.  Same
+// arithmetic, in the same order, as eval_residual.  CODES: one atom (N = 1).
+template <int EPL, int METRIC, int N, bool CODES, bool RANK, bool KEEPCW, class SRC>
+__device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const float (&cb)[EPL], const SRC& src, float ss, int a, Sums (&out)[N],
+                                                    bool wide_codes, uint32_t (&codes)[EPL / 4])
+{
+    static_assert(N == 1 || !CODES, "codes are formed atom by atom");
+    constexpr int CH = N > 2 || (N > 1 && RANK) ? 2 : 4;                  // elements whose look-ups are in flight
+    float e0[N], e1[N], wd[N], ew[N];
+    RankSums<EPL> rk[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) e0[n] = e1[n] = wd[n] = ew[n] = 0.0f;
+    if (CODES) {
+#pragma unroll
+        for (int j = 0; j < EPL / 4; ++j) codes[j] = 0;
+    }
+#pragma unroll
+    for (int i0 = 0; i0 < EPL; i0 += CH) {
+        Rec r[N][CH];
+        float xe[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            uint32_t bo;
+            src.get(i0 + j, xe[j], bo);
+#pragma unroll
+            for (int n = 0; n < N; ++n) r[n][j] = read_rec<CODES, CODES>(bo, a + n);
+        }
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const int i = i0 + j;
+                const bool up = xe[j] > r[n][j].thr;
+                const float yv = up ? r[n][j].yhi : r[n][j].ylo;
+                const float d = __fmaf_rn(-ss, yv, w[i]);
+                const float cd = cb[i] * d;
+                const float dd = METRIC == 2 ? d : cd;
+                if (i < 8) e0[n] = __fmaf_rn(dd, d, e0[n]); else e1[n] = __fmaf_rn(dd, d, e1[n]);
+                wd[n] = __fmaf_rn(cd, w[i], wd[n]);
+                if (METRIC == 2) ew[n] = __fmaf_rn(cd, d, ew[n]);
+                if constexpr (RANK) {
+                    float wi = w[i];
+                    if constexpr (!KEEPCW) asm volatile("" : "+v"(wi));       // (c w is formed again for every atom rather than kept: 16 registers)
+                    rk[n].add(i, wi, cb[i], ss, yv);
+                }
+                put_code<EPL, CODES>(codes, i, (uint32_t)r[n][j].clo + (up ? 1u : 0u), wide_codes);
+            }
+        }
+        // one chunk's look-ups in flight at a time: four wavefronts per SIMD hide them, and more in flight would cost the fourth
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            asm volatile("" : "+v"(e0[n]), "+v"(e1[n]), "+v"(wd[n]));
+            if constexpr (METRIC == 2) asm volatile("" : "+v"(ew[n]));
+            if constexpr (RANK) asm volatile("" : "+v"(rk[n].n0), "+v"(rk[n].n1), "+v"(rk[n].d0), "+v"(rk[n].d1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        out[n].err = EPL == 16 ? e0[n] + e1[n] : e0[n]; out[n].wd = wd[n]; out[n].ew = ew[n];
+        if constexpr (RANK) { out[n].rn = rk[n].num(); out[n].rd = rk[n].den(); }
+    }
 }
 
 // Element pass, DIRECT form with the decision sums of metric COS:
@@ -376,8 +472,12 @@ __device__ __forceinline__ void direct_cosine_sums(const float (&cb)[EPL], const
         src.get(i, xe, bo);
         const Rec r = read_rec<THR, false>(bo, a);
         const float yv = xe > r.thr ? r.yhi : r.ylo;
-        ny = __fmaf_rn(cb[i] * w[i], yv, ny);
+        // (a rare path: the products c w of the block statistics are formed again rather than kept for it in registers)
+        float wi = w[i];
+        asm volatile("" : "+v"(wi));
+        ny = __fmaf_rn(cb[i] * wi, yv, ny);
         dy = __fmaf_rn(cb[i], yv * yv, dy);
+        if (i % 4 == 3) { asm volatile("" : "+v"(ny), "+v"(dy)); __builtin_amdgcn_sched_barrier(0); }
     }
     const float nsum = group_sum<LPB>(negative ? -ny : ny), dsum = group_sum<LPB>(dy);
     ny_out = nonzero ? nsum : 0.0f;                    // a zero scale reconstructs nothing
@@ -472,22 +572,25 @@ __device__ __forceinline__ void all_pairs(const KParams& p, const Switches& sw, 
 // The weights one lane reads per step, as they come from memory
 template <bool BF16, int EPL> struct RawBlk { uint4 v[BF16 ? EPL / 8 : EPL / 4]; };
 
+// Strip and row are the same in every lane: the address is a scalar base plus the lane's own 32-bit offset.  `lanes`: lanes
+// of the strip that hold weights (64 but for the last strip of a row); a full strip is loaded without a lane mask.
 template <bool BF16, int EPL>
-__device__ __forceinline__ RawBlk<BF16, EPL> load_raw(const void* W, long long ldw, long long K, long long strip, long long m, int lane)
+__device__ __forceinline__ RawBlk<BF16, EPL> load_raw(const void* W, long long ldw, unsigned int strip, unsigned int m, unsigned int lanes, unsigned int lane)
 {
     RawBlk<BF16, EPL> r;
-    const long long col0 = (strip * 64 + lane) * EPL;
-    const bool valid = col0 < K;
     constexpr int NV = BF16 ? EPL / 8 : EPL / 4;
-    const char* src = reinterpret_cast<const char*>(W) + (m * ldw + col0) * (BF16 ? 2 : 4);
+    constexpr unsigned int esz = BF16 ? 2u : 4u;
+    const char* row = reinterpret_cast<const char*>(W) + ((long long)m * ldw + (long long)strip * (64 * EPL)) * esz;
+    const unsigned int off = lane * (EPL * esz);
+    if (lanes == 64u) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) r.v[i] = valid ? reinterpret_cast<const uint4*>(src)[i] : make_uint4(0, 0, 0, 0);
+        for (int i = 0; i < NV; ++i) r.v[i] = *reinterpret_cast<const uint4*>(row + off + 16 * i);
+    } else {
+        const bool valid = lane < lanes;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) r.v[i] = valid ? *reinterpret_cast<const uint4*>(row + off + 16 * i) : make_uint4(0, 0, 0, 0);
+    }
     return r;
-}
-template <bool BF16, int EPL>
-__device__ __forceinline__ RawBlk<BF16, EPL> load_raw(const KParams& p, long long strip, long long m, int lane)
-{
-    return load_raw<BF16, EPL>(p.W, p.ldw, p.K, strip, m, lane);
 }
 
 template <bool BF16, int EPL>
@@ -512,6 +615,31 @@ __device__ __forceinline__ void widen(const RawBlk<BF16, EPL>& r, float (&w)[EPL
     }
 }
 
+template <int V> struct ic { constexpr operator int() const { return V; } };      // a compile-time integer as an argument
+
+// Ranking score of step 2 of the per-layer search: a decision quantity, formed in binary32 from the block's tree sums
+// num = <w,w^>_c, den = ||w^||_c^2 (chunks of 8, balanced tree) and wn = ||w||_c^2:
+// fl(fl(num / wn) * fl(|num| / den)), 1 for a block without weighted norm, 0 for a zero reconstruction
+__device__ __forceinline__ float rank_score(float num, float dn, float wn)
+{
+    return wn > 0.0f ? (dn > 0.0f ? (num / wn) * (fabsf(num) / dn) : 0.0f) : 1.0f;
+}
+
+// the codes of the lane's elements into the atom's plane (two codes per byte, or one for atoms of more than 16 entries)
+template <int EPL>
+__device__ __forceinline__ void store_codes(const KParams& p, const Switches& sw, int a, long long row, long long col0, const uint32_t (&codes)[EPL / 4])
+{
+    if (!((sw.wide >> a) & 1u)) {
+        uint8_t* dst = p.codes + p.code_off[a] + (row * p.K + col0) / 2;
+#pragma unroll
+        for (int j = 0; j < EPL / 8; ++j) reinterpret_cast<uint32_t*>(dst)[j] = codes[j];
+    } else {
+        uint8_t* dst = p.codes + p.code_off[a] + row * p.K + col0;
+#pragma unroll
+        for (int j = 0; j < EPL / 4; ++j) reinterpret_cast<uint32_t*>(dst)[j] = codes[j];
+    }
+}
+
 // NA: atoms the kernel is unrolled for (2, 6 or 8).  OCC: wavefronts per SIMD the register budget is set
 // for; a workgroup is 4*OCC wavefronts and fills one compute unit on its own (one copy of the tables in
 // LDS per compute unit, one ticket per compute unit in the layer reduction).
@@ -527,6 +655,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 {
     static_assert(!MULTI || !EMIT, "the model-wide kernel searches only");
     constexpr bool SIGNED = SIGNMODE == 1, ARGMAX = SIGNMODE == 2;
+    constexpr bool GROUPED = SIGNMODE == 0 && METRIC != 1 && EPL == 16;   // atoms of a scale group are evaluated two at a time
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
     // LDS: bin table | (scale, reciprocal) table | group parameters | reduction scratch
@@ -594,8 +723,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // the share's range of steps in a layer of total_units steps
     auto share_of = [&](long long total_units, unsigned int& first, unsigned int& count) {
         const long long g0 = total_units * blockIdx.x / gridDim.x, g1 = total_units * (blockIdx.x + 1) / gridDim.x;
-        first = (unsigned int)(g0 + (g1 - g0) * simd / 4);
-        count = (unsigned int)(g0 + (g1 - g0) * (simd + 1) / 4) - first;
+        first = (unsigned int)__builtin_amdgcn_readfirstlane((int)(g0 + (g1 - g0) * simd / 4));
+        count = (unsigned int)__builtin_amdgcn_readfirstlane((int)(g0 + (g1 - g0) * (simd + 1) / 4)) - first;
     };
     // Request side (the row loads run one step ahead of the arithmetic): the layer the next requested step
     // lies in.  One layer: sb, cnt are the share's range.  MULTI: the shares of all layers follow one another
@@ -642,9 +771,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         if (lane == 0) v = atomicAdd(&s_next[simd], 1u);
         return (unsigned int)__builtin_amdgcn_readfirstlane((int)v);
     };
+    // lanes of a strip that hold weights (row length K, below 2^31 * 64 * EPL as there are fewer than 2^31 strip rows)
+    auto lanes_of = [&](unsigned int st, long long K) -> unsigned int {
+        const unsigned int full = (unsigned int)((unsigned long long)K / (64u * EPL));
+        return st < full ? 64u : (unsigned int)((unsigned long long)K % (64u * EPL)) / EPL;
+    };
     // step number -> (strip, row): steps run down the rows of a strip; division by multiplication with
     // floor(2^32 / M), one correction (scalar arithmetic)
-    auto locate = [&](unsigned int u, long long& st, long long& row) {
+    auto locate = [&](unsigned int u, unsigned int& st, unsigned int& row) {
         const unsigned int magic = MULTI ? rq_magic : p.m_magic, rows = MULTI ? rq_M32 : p.M32;
         unsigned int q = __umulhi(u, magic);
         unsigned int r = u - q * rows;
@@ -653,7 +787,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     };
 
     // running sums of 1 - cos in units of 2^-22 (integers: exact, so their order does not matter): atoms,
-    // pairs, and the lanes whose block has zero norm
+    // pairs, and the number of steps in which the lane's block had zero norm
     int acca[SOP_K_MAXA], accp[SOP_K_MAXP], accz = 0;
 #pragma unroll
     for (int i = 0; i < SOP_K_MAXA; ++i) acca[i] = 0;
@@ -688,7 +822,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 #pragma unroll
         for (int i = 0; i < SOP_K_MAXP; ++i)
             if (kPairTab.second[i] < NA) { col_of[n] = SOP_K_MAXA + i; val[n] = accp[i]; accp[i] = 0; ++n; }
-        col_of[n] = SOP_K_ZCOL; val[n] = accz; accz = 0; ++n;
+        col_of[n] = SOP_K_ZCOL; val[n] = accz << 22; accz = 0; ++n;
         // four columns at a time: their chains of moves are independent and fill each other's wait states,
         // and few values are live at once
         constexpr int B = 4;
@@ -723,8 +857,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     long long lc_K = 0, lc_Bk = 0;
     unsigned int lc_Kc = 1u;
 
-    long long strip = 0, m = 0;
-    long long cur_strip = -1;
+    unsigned int strip = 0u, m = 0u;
+    unsigned int cur_strip = 0xFFFFFFFFu;
     float cb[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) cb[i] = 0.0f;
@@ -732,7 +866,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     RawBlk<BF16, EPL> nxt;
     bool ok_cur = seek(i_cur);
     int l_nxt = rq_l;                              // layer of the row in nxt
-    if (ok_cur) { locate(sb + (i_cur - rq_base), strip, m); nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, MULTI ? rq_K : p.K, strip, m, lane); }
+    if (ok_cur) { locate(sb + (i_cur - rq_base), strip, m); nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, strip, m, lanes_of(strip, MULTI ? rq_K : p.K), (unsigned int)lane); }
     int since_flush = 0;
 
     while (ok_cur) {
@@ -748,7 +882,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 lc_K = (long long)uni((unsigned int)d.K); lc_Bk = (long long)uni((unsigned int)d.Bk);
                 lc_Kc = uni((unsigned int)d.Kc);
                 cur_strip = strip;
-                const long long c0 = (strip * 64 + lane) * EPL;
+                const long long c0 = ((long long)strip * 64 + lane) * EPL;
 #pragma unroll
                 for (int i = 0; i < EPL; i += 4) {
                     float4 t = c0 < lc_K ? *reinterpret_cast<const float4*>(lc_c + (unsigned int)c0 % lc_Kc + i) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -760,12 +894,13 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         }
         // The uniform switches below are re-read every row.  Left loop-invariant, each test would be
         // hoisted out of the loop as a 64-bit lane mask and the hundred-odd masks would spill.
-        Switches sw = {p.A, p.pair_mask, p.flip_mask, p.gid_w, p.unit_tpos, p.unit_tneg, p.wide_mask, p.mirror_mask, p.selfsym_mask};
+        Switches sw = {p.A, p.pair_mask, p.flip_mask, p.gid_w, p.unit_tpos, p.unit_tneg, p.wide_mask, p.mirror_mask, p.selfsym_mask, p.second_mask};
         asm volatile("" : "+s"(sw.A), "+s"(sw.pair_mask), "+s"(sw.flip_mask), "+s"(sw.gid), "+s"(sw.unit_tpos), "+s"(sw.unit_tneg), "+s"(sw.wide));
         if constexpr (SIGNED) asm volatile("" : "+s"(sw.mirror), "+s"(sw.selfsym));
-        const long long cm = m, cs = strip;
-        const long long col0 = (cs * 64 + lane) * EPL;
-        const bool valid = col0 < (MULTI ? lc_K : p.K);
+        if constexpr (GROUPED) asm volatile("" : "+s"(sw.second));
+        const unsigned int cm32 = m, cs = strip;
+        const long long cm = cm32, col0 = ((long long)cs * 64 + lane) * EPL;
+        const bool valid = (unsigned int)lane < lanes_of(cs, MULTI ? lc_K : p.K);
         if (cs != cur_strip) {
             cur_strip = cs;
 #pragma unroll
@@ -778,9 +913,15 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // ---- the block: one read from HBM, requested one step ahead ----
         float w[EPL];
         widen<BF16, EPL>(nxt, w);
+        // (widened before the next row is asked for: its registers take that row)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) asm volatile("" : "+v"(w[i]));
         const bool ok_nxt = seek(i_nxt);
         l_nxt = rq_l;
-        if (ok_nxt) { locate(sb + (i_nxt - rq_base), strip, m); nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, MULTI ? rq_K : p.K, strip, m, lane); }
+        // (after the last step its row is read once more: a load on every path leaves the rows in place, where a
+        // conditional one costs a copy of them per step)
+        if (ok_nxt) locate(sb + (i_nxt - rq_base), strip, m);
+        nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, strip, m, lanes_of(strip, MULTI ? rq_K : p.K), (unsigned int)lane);
         // the next step opens another layer: its channel norms are asked for now (one word per lane brings
         // every cache line of the strip's norms in), so that the loads at the top of that step find them
         // near; the value is only held until the end of this step
@@ -788,7 +929,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         if constexpr (MULTI) {
             if (ok_nxt && l_nxt != cl) {
                 const float* cn = reinterpret_cast<const float*>(uni64((unsigned long long)reinterpret_cast<uintptr_t>(p.layers[l_nxt].c)));
-                const long long tc = (strip * 64 + lane) * EPL;
+                const long long tc = ((long long)strip * 64 + lane) * EPL;
                 if (tc < rq_K) c_touch = cn[(unsigned int)tc % uni((unsigned int)p.layers[l_nxt].Kc)];
             }
         }
@@ -815,7 +956,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         pmax = valid ? pmax : 1.0f;
         nmax = valid ? nmax : 1.0f;
         const float wn = group_sum<LPB>(EPL == 16 ? wn0 + wn1 : wn0);
-        accz += wn > 0.0f ? 0 : (1 << 22);
+        accz += wn > 0.0f ? 0 : 1;
         // power of two that brings ||w||^2 into [1, 2) (exponent fields 1 .. 253: norms within 2^-126 .. 2^126)
         NormScale nsc;
         {
@@ -826,7 +967,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             nsc.qwns = 0.25f * nsc.wns;
         }
 
-        const long long blk_in_row = (cs * 64 + lane) / LPB;
+        const long long blk_in_row = ((long long)cs * 64 + lane) / LPB;
         const long long blk = cm * (MULTI ? lc_Bk : p.Bk) + blk_in_row;
         const bool leader = valid && (lane % LPB == 0);
 
@@ -840,7 +981,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         int gq = 0;
         float gss = 0.0f;                              // twice the scale (the table holds halved codebook values)
         bool gnz = false, gneg = false;
-        constexpr bool FLY = SIGNED && EPL == 16;       // (a lane of 8 elements has the registers for both signs' arrays)
+        constexpr bool FLY = GROUPED || (SIGNED && EPL == 16);       // (a lane of 8 elements has the registers for both signs' arrays)
         float gx[FLY ? 1 : EPL], gx2[(SIGNED && !FLY) ? EPL : 1];
         uint32_t gboff[FLY ? 1 : EPL], gboff2[(SIGNED && !FLY) ? EPL : 1];
         ScalePrep spP = {0, 0.0f, 0.0f, false, false}, spM = {0, 0.0f, 0.0f, false, false};
@@ -861,6 +1002,115 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         bool pv_tie = true;                            // wave-uniform: the kept candidates may not be taken over
         bool pv_raw0 = false, pv_raw1 = false;         // wave-uniform: the kept cosine sums are the direct ones (not scaled)
 
+        if constexpr (GROUPED) {
+            uint32_t weak_atoms = 0u;                  // wave-uniform: atoms whose residual form some lane does not trust
+            ScalePrep sp = {0, 0.0f, 0.0f, false, false};
+            uint32_t codes[EPL / 4];
+            const bool want_rank = EMIT && p.blk_rank, want_codes = EMIT && p.codes;      // wave-uniform
+            // the atom's share of the outputs: decision score, deficit 1 - cos in units of 2^-22 (see below), planes
+            auto settle = [&](int a, const Sums& s, bool have_codes) __attribute__((always_inline)) {
+                const Cand t = finish_residual<LPB, METRIC>(s, nsc);
+                score[a] = t.err; den[a] = 1.0f;
+                const float rs = __frsqrt_rn(__fmaf_rn(nsc.wns, t.dy, 1.0e-37f));
+                dlt[a] = (int)__float_as_uint(__fmaf_rn(-t.ny, rs, 3.0f)) - 0x40000000;
+                acca[a] += dlt[a];
+                if (__builtin_expect(__any(t.weak) != 0, 0)) weak_atoms |= 1u << a;
+                if constexpr (EMIT) {
+                    const long long ua = p.uidx[a];
+                    if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)sp.q;
+                    if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = t.err;
+                    if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-t.ny, rs, 1.0f) : 1.0f;
+                    if (want_rank) {
+                        const float r = rank_score(group_sum<LPB>(s.rn), group_sum<LPB>(s.rd), wn);
+                        if (leader) p.blk_rank[ua * p.Nb + blk] = r;
+                    }
+                    if (have_codes && valid) store_codes<EPL>(p, sw, a, cm, col0, codes);
+                }
+            };
+            auto scale_of = [&](int a) __attribute__((always_inline)) {
+                const int gid = (int)((sw.gid >> (4 * a)) & 15u);
+                if (gid != cur_gid) { cur_gid = gid; sp = prepare_scale(pmax, nmax, false, a, p, sw, s_tab, s_gpar); }
+            };
+            // N atoms of the current scale group (CL: scaled weights clamped into the table's range, CD: codes, RK: ranking sums)
+            auto pass = [&](auto n_, auto cl_, auto cd_, auto rk_, int a) __attribute__((always_inline)) {
+                constexpr int N = n_;
+                constexpr bool CL = cl_, CD = cd_, RK = rk_;
+                const float4 gpar = s_gpar[2 * a];
+                float lo = 0.0f, hi = 0.0f;
+                if (CL) { const float4 g2 = s_gpar[2 * a + 1]; lo = g2.x; hi = g2.y; }
+                Sums sn[N];
+                eval_residual_group<EPL, METRIC, N, CD, RK, NA == 2>(w, cb, FlySrc<EPL, CL>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
+#pragma unroll
+                for (int n = 0; n < N; ++n) settle(a + n, sn[n], CD && want_codes);
+            };
+            // one atom on its own
+            auto one = [&](int a) __attribute__((always_inline)) {
+                scale_of(a);
+                // the table covers a scale rounded down by up to the factor SOP_K_BIN_SAFE; beyond it (the scale word
+                // saturated) the whole wavefront clamps its scaled weights into the table's range
+                if (__builtin_expect(__any(sp.beyond) != 0, 0)) pass(ic<1>(), ic<1>(), ic<EMIT>(), ic<EMIT>(), a);
+                else if constexpr (!EMIT) pass(ic<1>(), ic<0>(), ic<0>(), ic<0>(), a);
+                else if (want_codes) { if (want_rank) pass(ic<1>(), ic<0>(), ic<1>(), ic<1>(), a); else pass(ic<1>(), ic<0>(), ic<1>(), ic<0>(), a); }
+                else if (want_rank) pass(ic<1>(), ic<0>(), ic<0>(), ic<1>(), a);
+                else pass(ic<1>(), ic<0>(), ic<0>(), ic<0>(), a);
+            };
+            // two atoms: together when they are of one group (and no codes are wanted), else one after the other
+            auto two = [&](auto a_) __attribute__((always_inline)) {
+                constexpr int a = a_;
+                score[a] = score[a + 1] = 0.0f; den[a] = den[a + 1] = 1.0f; dlt[a] = dlt[a + 1] = 0;
+                if (__builtin_expect(a < sw.A, 1)) {
+                    bool joint = ((sw.second >> (a + 1)) & 1u) && !want_codes;
+                    if (joint) {
+                        scale_of(a);
+                        joint = __any(sp.beyond) == 0;
+                    }
+                    if (joint) {
+                        if constexpr (!EMIT) pass(ic<2>(), ic<0>(), ic<0>(), ic<0>(), a);
+                        else if (want_rank) pass(ic<2>(), ic<0>(), ic<0>(), ic<1>(), a);
+                        else pass(ic<2>(), ic<0>(), ic<0>(), ic<0>(), a);
+                    } else {
+                        one(a);
+                        if (a + 1 < sw.A) one(a + 1);
+                    }
+                }
+            };
+            // four atoms: together when they are of one group (the bit of the third one) and no planes are wanted
+            auto four = [&](auto a_) __attribute__((always_inline)) {
+                constexpr int a = a_;
+                bool joint = !EMIT && ((sw.second >> (a + 2)) & 1u);
+                if (joint) {
+                    scale_of(a);
+                    joint = __any(sp.beyond) == 0;
+                }
+                if (joint) pass(ic<4>(), ic<0>(), ic<0>(), ic<0>(), a);
+                else { two(ic<a>()); two(ic<a + 2>()); }
+            };
+            if constexpr (NA == 2) two(ic<0>());
+            else {
+                four(ic<0>());
+                if constexpr (NA == 6) two(ic<4>()); else four(ic<4>());
+            }
+            // the residual form is accurate while the reconstruction carries a fair share of the block's norm; otherwise
+            // the whole wavefront recomputes the atom's cosine directly
+            while (__builtin_expect(weak_atoms != 0u, 0)) {
+                const int wa = __builtin_ctz(weak_atoms);
+                weak_atoms &= weak_atoms - 1u;
+                const ScalePrep sq = prepare_scale(pmax, nmax, false, wa, p, sw, s_tab, s_gpar);
+                const float4 gpar = s_gpar[2 * wa], g2 = s_gpar[2 * wa + 1];
+                float ny1, dy1;
+                direct_cosine_sums<EPL, LPB, EMIT>(cb, w, FlySrc<EPL, true>{w, sq.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg}, sq.nonzero, false, wa, ny1, dy1);
+                // (direct sums go with the raw norm, which is the scaled one times the inverse power of two, exactly)
+                const float wnr = nsc.wns * __uint_as_float((254u << 23) - __float_as_uint(nsc.sc));
+                const float rs = __frsqrt_rn(__fmaf_rn(wnr, dy1, 1.0e-37f));
+                const int ia = (int)__float_as_uint(__fmaf_rn(-ny1, rs, 3.0f)) - 0x40000000;
+#pragma unroll
+                for (int a = 0; a < NA; ++a)
+                    if (a == wa) { acca[a] += ia - dlt[a]; dlt[a] = ia; }
+                if constexpr (EMIT) {
+                    if (p.blk_cos && leader) p.blk_cos[(long long)p.uidx[wa] * p.Nb + blk] = wnr > 0.0f ? 1.0f - __fmaf_rn(-ny1, rs, 1.0f) : 1.0f;
+                }
+            }
+        } else {
 #pragma unroll
         for (int a = 0; a < NA; ++a) {
             score[a] = 0.0f; den[a] = 1.0f; dlt[a] = 0;
@@ -917,7 +1167,15 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                             auto run = [&](const auto& src) {
                                 Cand t;
                                 if constexpr (METRIC == 1) t = finish_direct<LPB>(eval_direct<EPL, EMIT, EMIT, true>(w, cb, src, sp.ss, a, wide, cds, &tie));
-                                else t = finish_residual<LPB, METRIC>(eval_residual<EPL, METRIC, EMIT, true>(w, cb, src, sp.ss, a, wide, cds, &tie), nsc);
+                                else {
+                                    // (the ranking score's sums, where wanted, are formed in the same pass)
+                                    Sums s;
+                                    if (EMIT && p.blk_rank) {
+                                        s = eval_residual<EPL, METRIC, EMIT, true, EMIT>(w, cb, src, sp.ss, a, wide, cds, &tie);
+                                        rn = group_sum<LPB>(s.rn); rd = group_sum<LPB>(s.rd);
+                                    } else s = eval_residual<EPL, METRIC, EMIT, true>(w, cb, src, sp.ss, a, wide, cds, &tie);
+                                    t = finish_residual<LPB, METRIC>(s, nsc);
+                                }
                                 err = t.err; ny = t.ny; dy = t.dy;
                                 rawf = METRIC == 1;
                                 if constexpr (METRIC != 1) {
@@ -928,16 +1186,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                                         rawf = true;
                                     }
                                 }
-                                if constexpr (EMIT) {
-                                    if (p.blk_rank) {
-                                        if constexpr (METRIC == 1) { rn = t.ny; rd = t.dy; }
-                                        else {
-                                            uint32_t nocodes[EPL / 4];
-                                            const Cand c1 = finish_direct<LPB>(eval_direct<EPL, false, false>(w, cb, src, sp.ss, a, false, nocodes));
-                                            rn = c1.ny; rd = c1.dy;
-                                        }
-                                    }
-                                }
+                                if constexpr (EMIT && METRIC == 1) { rn = t.ny; rd = t.dy; }
                             };
                             // the table covers a scale rounded down by up to the factor SOP_K_BIN_SAFE; beyond it (the scale word
                             // saturated) the whole wavefront clamps its scaled weights into the table's range
@@ -1010,9 +1259,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     raw = true;
                 } else {
                     // (emit mode without a code plane, as when only the ranking scores are wanted: the pass that forms no codes
-                    // and reads no boundaries)
-                    if (!EMIT || p.codes) best = finish_residual<LPB, METRIC>(eval_residual<EPL, METRIC, EMIT>(w, cb, ArrSrc<EPL>{gx, gboff}, gss, a, wide, codes), nsc);
-                    else best = finish_residual<LPB, METRIC>(eval_residual<EPL, METRIC, false>(w, cb, ArrSrc<EPL>{gx, gboff}, gss, a, wide, codes), nsc);
+                    // and reads no boundaries; the ranking score's sums are formed in the same pass)
+                    const ArrSrc<EPL> src{gx, gboff};
+                    Sums s;
+                    if constexpr (!EMIT) s = eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
+                    else if (p.codes) s = p.blk_rank ? eval_residual<EPL, METRIC, true, false, true>(w, cb, src, gss, a, wide, codes) : eval_residual<EPL, METRIC, true>(w, cb, src, gss, a, wide, codes);
+                    else s = p.blk_rank ? eval_residual<EPL, METRIC, false, false, true>(w, cb, src, gss, a, wide, codes) : eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
+                    best = finish_residual<LPB, METRIC>(s, nsc);
+                    if (EMIT) { rk_num = group_sum<LPB>(s.rn); rk_dn = group_sum<LPB>(s.rd); }
                     // the residual form is accurate while the reconstruction carries a fair share of
                     // the block's norm; otherwise the whole wavefront recomputes this atom directly
                     if (__builtin_expect(__any(best.weak) != 0, 0)) {
@@ -1043,33 +1297,13 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = best.err;
                     if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-best.ny, rs, 1.0f) : 1.0f;
                     if (p.blk_rank) {
-                        // ranking score of step 2 of the per-layer search: a decision quantity, formed in binary32 from
-                        // the block's tree sums num = <w,w^>_c, den = ||w^||_c^2 (chunks of 8, balanced tree) and wn:
-                        // fl(fl(num / wn) * fl(|num| / den)), 1 for a block without weighted norm, 0 for a zero reconstruction
-                        float num, dn;
-                        if constexpr (SIGNED) { num = rk_num; dn = rk_dn; }
-                        else if constexpr (METRIC == 1) { num = ny_raw; dn = dy_raw; }
-                        else {
-                            uint32_t nocodes[EPL / 4];
-                            const Cand c1 = finish_direct<LPB>(eval_direct<EPL, false, false>(w, cb, ArrSrc<EPL>{gx, gboff}, gss, a, false, nocodes));
-                            num = c1.ny; dn = c1.dy;
-                        }
-                        const float rank = wn > 0.0f ? (dn > 0.0f ? (num / wn) * (fabsf(num) / dn) : 0.0f) : 1.0f;
+                        const float rank = METRIC == 1 && !SIGNED ? rank_score(ny_raw, dy_raw, wn) : rank_score(rk_num, rk_dn, wn);
                         if (leader) p.blk_rank[ua * p.Nb + blk] = rank;
                     }
-                    if (p.codes && valid) {
-                        if (!wide) {
-                            uint8_t* dst = p.codes + p.code_off[a] + (cm * p.K + col0) / 2;
-#pragma unroll
-                            for (int j = 0; j < EPL / 8; ++j) reinterpret_cast<uint32_t*>(dst)[j] = codes[j];
-                        } else {
-                            uint8_t* dst = p.codes + p.code_off[a] + cm * p.K + col0;
-#pragma unroll
-                            for (int j = 0; j < EPL / 4; ++j) reinterpret_cast<uint32_t*>(dst)[j] = codes[j];
-                        }
-                    }
+                    if (p.codes && valid) store_codes<EPL>(p, sw, a, cm, col0, codes);
                 }
             }
+        }
         }
         // ---- selector of every requested pair: one word per block ----
         uint32_t bits = 0;
@@ -1192,19 +1426,23 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 
 // ---- kernel table of this part ----
 namespace {
-// wavefronts per SIMD each variant is built for: the largest number its register need allows (a lane
-// owning 8 elements needs far fewer registers than one owning 16; trying both signs, emitting codes and
-// eight atoms each need more; measured on the 4096 x 11008 layer where two choices were close)
-constexpr int occ_for(int epl, int sign_mode, bool emit, int na, int metric)
+// Wavefronts per SIMD each variant is built for: the largest number its register need allows without spilling (512 / occ
+// registers a lane).  The passes that evaluate a scale group's atoms together (16 elements a lane, positive scale, metrics WSE and
+// MSE) hold neither scaled weights nor table addresses and fit one wavefront more than the others: the headline layer
+// (4096 x 11008, six atoms) takes 72.6 us at four against 78.6 with the arrays at three, a 28672 x 8192 layer with seven atoms
+// 530 us at three against 640 at two.  fp32 weights keep 8 more registers of requested rows: one wavefront less where that is the difference.
+constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int metric)
 {
-    if (na == 2) {                                   // one or two atoms: fewer registers
-        if (epl == 8) return (sign_mode == 1 && emit) ? 3 : 4;
-        return emit ? 2 : 3;                           // (with the per-block planes a lane of 16 elements needs more than 168 registers)
-    }
     if (epl == 8) {
+        if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;
         if (sign_mode == 1) return emit ? 2 : 3;
         return (emit || na == 8) ? 3 : 4;
     }
+    if (sign_mode == 0 && metric != 1) {
+        if (!emit) return na == 8 ? 3 : (na == 2 || bf16) ? 4 : 3;
+        return na == 2 || (na == 6 && bf16) ? 3 : 2;
+    }
+    if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : 3;
     if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 ? 2 : 3);
     if (emit) return 2;
     return (na == 8 || metric == 1) ? 2 : 3;        // the cosine metric keeps two more sums per candidate alive
@@ -1217,7 +1455,7 @@ template <bool BF16, int EPL, int LPB, int S, bool E, int NA>
 const void* variant(int mode, int* occ, int* mode_out)
 {
     constexpr int MT = SOPK_PART_METRIC;
-    constexpr int O = occ_for(EPL, S, E, NA, MT);
+    constexpr int O = occ_for(BF16, EPL, S, E, NA, MT);
     *occ = O;
     *mode_out = 0;
     if constexpr (!E && NA != 2) {
