@@ -16,11 +16,17 @@
 // plane's histograms: the weights are read, normalised and binned once.
 //
 // Work mapping as in the search kernel: a lane owns min(g,16) consecutive elements of a row, a
-// wavefront walks down the rows of a 64-lane strip.  Each workgroup (16 wavefronts, one per compute
-// unit) finds cmax itself, accumulates into its own LDS histogram with 64-bit LDS atomics and adds
-// that to the layer's running histogram (kept in the context, zero between calls) with 64-bit global
-// atomics; the workgroup that finishes last moves the result to the caller's buffer and leaves
-// zeros behind.  One kernel per call.
+// wavefront walks down the rows of a 64-lane strip, the next row requested a step ahead.  Each workgroup (16 wavefronts,
+// one per compute unit) finds cmax itself, accumulates in LDS and adds its histogram to the layer's running histogram (kept in
+// the context, zero between calls) with 64-bit global atomics; the workgroup that finishes last moves the result to
+// the caller's buffer and leaves zeros behind.  One kernel per call.
+//
+// In LDS a weight costs one 32-bit add.  The pass is bound by those adds (a wavefront's 64 lanes fall on random bins: bank
+// conflicts) beside the read of the layer, and a 64-bit add takes twice the bank cycles.  The 32-bit counts sit in p.n_repl
+// replicas, each shared by 16 / n_repl wavefronts, and never wrap: a step adds at most S = the sum of the masses of the
+// strip's columns to any one word, and a wavefront that has added as much as its share of 2^32 - 1 since it last emptied its
+// replica empties it (exchange with zero, word by word) into the 64-bit histogram first.  Heavy-tailed channel norms have S near
+// 2^25 and are hardly ever emptied before the end; with equal norms S is 2^30 and a private replica is emptied every third row.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,16 +34,32 @@
 
 namespace sopk {
 
+// floor of a non-negative value as an unsigned integer; values below zero and NaN give 0, values past 2^32 the largest integer
+// (the hardware's conversion saturates; the language leaves such conversions undefined)
+__device__ __forceinline__ unsigned int cvt_floor(float v)
+{
+    unsigned int r;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 template <bool BF16, int EPL, int LPB>
 __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParams p)
 {
-    extern __shared__ __align__(16) unsigned long long s_hist[];      // [H]
+    extern __shared__ __align__(16) unsigned long long s_hist[];      // [H] 64-bit sums, then n_repl x [H] 32-bit counts
     __shared__ float s_max[SOP_K_DD_THREADS / 64];
     __shared__ unsigned int s_flag;
+    constexpr int NW = SOP_K_DD_THREADS / 64, NV = BF16 ? EPL / 8 : EPL / 4;
+    constexpr int PRE = 4;                                            // level planes whose bytes are requested a step ahead
     const int HB = p.n_bins;                                          // bins of one histogram
     const int NP = p.n_levels > 0 ? p.n_planes : 1;                   // level planes
     const int H = p.n_bins * (p.n_levels > 0 ? p.n_levels : 1) * NP;  // words of all the histograms of the call
-    for (int i = threadIdx.x; i < H; i += SOP_K_DD_THREADS) s_hist[i] = 0ull;
+    unsigned int* s_cnt = reinterpret_cast<unsigned int*>(s_hist + H);
+    {
+        uint4* z = reinterpret_cast<uint4*>(s_hist);                  // (H is a multiple of 64)
+        const int n16 = (H / 4) * (2 + p.n_repl);
+        for (int i = threadIdx.x; i < n16; i += SOP_K_DD_THREADS) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     // cmax = max_k c_k (order-independent), found by every workgroup for itself
     float cmax = 1.0f;
     if (p.c) {
@@ -61,29 +83,51 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     if (p.c) {
         cmax = s_max[0];
 #pragma unroll
-        for (int i = 1; i < SOP_K_DD_THREADS / 64; ++i) cmax = fmaxf(cmax, s_max[i]);
+        for (int i = 1; i < NW; ++i) cmax = fmaxf(cmax, s_max[i]);
     }
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const long long wave = (long long)blockIdx.x * (SOP_K_DD_THREADS / 64) + wv;
+    const long long wave = (long long)blockIdx.x * NW + wv;
     const long long u0 = p.total_units * wave / p.n_waves;
-    const long long u1 = p.total_units * (wave + 1) / p.n_waves;
+    const int n_steps = __builtin_amdgcn_readfirstlane((int)(p.total_units * (wave + 1) / p.n_waves - u0));
     const float cs = cmax > 0.0f ? 1048576.0f / cmax : 0.0f;      // all-zero channel norms: an empty histogram
     const float half = 0.5f * (float)HB;
+    unsigned int* const cnt = s_cnt + (wv % p.n_repl) * H;        // this wavefront's replica
+    const unsigned int budget = 0xFFFFFFFFu / (unsigned int)(NW / p.n_repl);
+    unsigned int spent = 0u, per_step = 0u;                       // added to any one word since the last emptying, at most; by one step, at most
 
-    long long strip = u0 / p.Ms;
-    long long m = u0 - strip * p.Ms;              // index among the sampled rows
-    long long cur_strip = -1;
+    // request side: (strip, row) of the next step, kept on the scalar unit
+    unsigned int rs = (unsigned int)__builtin_amdgcn_readfirstlane((int)(u0 / p.Ms));
+    long long rm = (long long)__builtin_amdgcn_readfirstlane((int)(u0 - (long long)rs * p.Ms));      // index among the sampled rows
+    uint4 raw[NV];
+    int lvl[PRE];
+    auto request = [&]() __attribute__((always_inline)) {
+        const long long c0 = (long long)rs * (64 * EPL), room = p.K - c0;
+        const bool valid = (long long)lane * EPL < room;
+        const char* src = reinterpret_cast<const char*>(p.W) + (rm * p.row_step * p.ldw + c0 + lane * EPL) * (BF16 ? 2 : 4);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) raw[i] = valid ? reinterpret_cast<const uint4*>(src)[i] : make_uint4(0u, 0u, 0u, 0u);
+        if (p.block_mask) {
+            const long long blk = rm * p.row_step * p.Bk + ((long long)rs * 64 + lane) / LPB;
+#pragma unroll
+            for (int pl = 0; pl < PRE; ++pl) lvl[pl] = pl < NP && valid ? p.block_mask[(long long)pl * p.plane_stride + blk] : 0;
+        }
+    };
+    if (n_steps > 0) request();
+    unsigned int cur_strip = 0xFFFFFFFFu;
     unsigned int mass[EPL]; // rint(fl(c*cs)) of the owned columns
 #pragma unroll
     for (int i = 0; i < EPL; ++i) mass[i] = 0u;
 
-    for (long long u = u0; u < u1; ++u) {
-        const long long col0 = (strip * 64 + lane) * EPL;
+    for (int u = 0; u < n_steps; ++u) {
+        const unsigned int strip = rs;
+        const long long m = rm;
+        const long long col0 = ((long long)strip * 64 + lane) * EPL;
         const bool valid = col0 < p.K;
         if (strip != cur_strip) {
             cur_strip = strip;
+            unsigned int sum = 0u;                                // at most 16 * 2^20 a lane
 #pragma unroll
             for (int i = 0; i < EPL; i += 4) {
                 float4 t = make_float4(1.f, 1.f, 1.f, 1.f);
@@ -92,78 +136,72 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     mass[i + j] = (unsigned int)__float2int_rn(cv[j] * cs);
+                    sum += mass[i + j];
                 }
             }
+#pragma unroll
+            for (int st = 1; st < 64; st <<= 1) sum += (unsigned int)__shfl_xor((int)sum, st, 64);
+            per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30
+        }
+        // a step that alone exceeds the wavefront's share (a shared replica under near-equal norms) adds to the 64-bit words
+        const bool wide = per_step > budget;
+        if (!wide) {
+            if (per_step > budget - spent) {
+                for (int i = lane; i < H; i += 64) {
+                    const unsigned int v = atomicExch(&cnt[i], 0u);
+                    if (v) atomicAdd(&s_hist[i], (unsigned long long)v);
+                }
+                spent = 0u;
+            }
+            spent += per_step;
         }
         float w[EPL];
-        if (BF16) {
-            const uint16_t* src = reinterpret_cast<const uint16_t*>(p.W) + m * p.row_step * p.ldw + col0;
 #pragma unroll
-            for (int i = 0; i < EPL; i += 8) {
-                uint4 t = valid ? *reinterpret_cast<const uint4*>(src + i) : make_uint4(0, 0, 0, 0);
-                const uint32_t v[4] = {t.x, t.y, t.z, t.w};
+        for (int i = 0; i < NV; ++i) {
+            const uint32_t v[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    w[i + 2 * j] = __uint_as_float(v[j] << 16);
-                    w[i + 2 * j + 1] = __uint_as_float(v[j] & 0xFFFF0000u);
-                }
-            }
-        } else {
-            const float* src = reinterpret_cast<const float*>(p.W) + m * p.row_step * p.ldw + col0;
-#pragma unroll
-            for (int i = 0; i < EPL; i += 4) {
-                float4 t = valid ? *reinterpret_cast<const float4*>(src + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                w[i] = t.x; w[i + 1] = t.y; w[i + 2] = t.z; w[i + 3] = t.w;
+            for (int j = 0; j < 4; ++j) {
+                if (BF16) { w[8 * i + 2 * j] = __uint_as_float(v[j] << 16); w[(8 * i + 2 * j + 1) % EPL] = __uint_as_float(v[j] & 0xFFFF0000u); }
+                else w[4 * i + j] = __uint_as_float(v[j]);
             }
         }
+        int lv_now[PRE];
+#pragma unroll
+        for (int pl = 0; pl < PRE; ++pl) lv_now[pl] = lvl[pl];
+        if (++rm == p.Ms) { rm = 0; ++rs; }
+        if (u + 1 < n_steps) request();
         float a = 0.0f;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) a = fmaxf(a, fabsf(w[i]));
         if (LPB >= 2) a = fmaxf(a, __shfl_xor(a, 1, 64));
         if (LPB >= 4) a = fmaxf(a, __shfl_xor(a, 2, 64));
-        bool take = valid && a > 0.0f;
-        if (NP > 1) {
-            // several level planes: the bins are found once, every plane adds the block to the histogram of its level
-            if (take) {
-                const float r = 1.0f / a;
-                int bin[EPL];
-#pragma unroll
-                for (int i = 0; i < EPL; ++i) {
-                    const float x = w[i] * r;
-                    const int b = (int)floorf(x * half + half);
-                    bin[i] = b < 0 ? 0 : (b > HB - 1 ? HB - 1 : b);
-                }
-                const long long blk = m * p.row_step * p.Bk + (strip * 64 + lane) / LPB;
-                for (int pl = 0; pl < NP; ++pl) {
-                    const int lv = p.block_mask[(long long)pl * p.plane_stride + blk];
-                    if (lv != 0) {
-                        const int hb = (pl * p.n_levels + min(lv, p.n_levels) - 1) * HB;
-#pragma unroll
-                        for (int i = 0; i < EPL; ++i) atomicAdd(&s_hist[hb + bin[i]], (unsigned long long)mass[i]);
-                    }
-                }
-            }
-            if (++m == p.Ms) { m = 0; ++strip; }
-            continue;
-        }
-        int hbase = 0;                              // first word of the block's histogram
-        if (p.block_mask && take) {                 // only the blocks of the pool enter
-            const long long blk = m * p.row_step * p.Bk + (strip * 64 + lane) / LPB;
-            const int lv = p.block_mask[blk];
-            take = lv != 0;
-            if (p.n_levels > 0) hbase = (min(lv, p.n_levels) - 1) * HB;
-        }
-        if (take) {
+        if (valid && a > 0.0f) {
             const float r = 1.0f / a;
+            unsigned int bin[EPL];
 #pragma unroll
             for (int i = 0; i < EPL; ++i) {
                 const float x = w[i] * r;
-                int bin = (int)floorf(x * half + half);          // x*half is exact: the sum rounds once
-                bin = bin < 0 ? 0 : (bin > HB - 1 ? HB - 1 : bin);
-                atomicAdd(&s_hist[hbase + bin], (unsigned long long)mass[i]);
+                // x*half is exact: the fma rounds the sum once; the conversion truncates, takes what is below zero to 0 and NaN to 0
+                bin[i] = min(cvt_floor(__fmaf_rn(x, half, half)), (unsigned int)(HB - 1));
+            }
+            auto add = [&](int hb) __attribute__((always_inline)) {
+                if (!wide) {
+#pragma unroll
+                    for (int i = 0; i < EPL; ++i) atomicAdd(&cnt[hb + bin[i]], mass[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < EPL; ++i) atomicAdd(&s_hist[hb + bin[i]], (unsigned long long)mass[i]);
+                }
+            };
+            if (!p.block_mask) add(0);
+            else {
+                for (int pl = 0; pl < NP; ++pl) {                 // several level planes: the bins are found once
+                    int lv = pl == 0 ? lv_now[0] : pl == 1 ? lv_now[1] : pl == 2 ? lv_now[2] : lv_now[3];
+                    if (pl >= PRE) lv = p.block_mask[(long long)pl * p.plane_stride + m * p.row_step * p.Bk + ((long long)strip * 64 + lane) / LPB];
+                    if (lv != 0) add(p.n_levels > 0 ? (pl * p.n_levels + min(lv, p.n_levels) - 1) * HB : 0);
+                }
             }
         }
-        if (++m == p.Ms) { m = 0; ++strip; }
     }
     __syncthreads();
     // the workgroup's histogram joins the layer's through 64-bit integer atomics; their returned
@@ -176,7 +214,8 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             const int i = threadIdx.x + j * SOP_K_DD_THREADS;
             before[j] = 0ull;
             if (i < H) {
-                const unsigned long long v = s_hist[i];
+                unsigned long long v = s_hist[i];
+                for (int r = 0; r < p.n_repl; ++r) v += s_cnt[r * H + i];
                 if (v) before[j] = atomicAdd(p.acc + i, v);
             }
         }
@@ -225,9 +264,15 @@ extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, voi
 {
     DdParams p = *pp;
     hipStream_t st = (hipStream_t)stream;
-    const size_t lds = (size_t)p.n_bins * (size_t)(p.n_levels > 0 ? p.n_levels * p.n_planes : 1) * sizeof(unsigned long long);
+    // replicas of the 32-bit counts: one per wavefront where they take at most 64 KiB, else as many as fit beside the 64-bit sums
+    const size_t words = (size_t)p.n_bins * (size_t)(p.n_levels > 0 ? p.n_levels * p.n_planes : 1);
+    p.n_repl = SOP_K_DD_THREADS / 64;
+    while (p.n_repl > 1 && words * p.n_repl * 4 > (64u << 10)) p.n_repl /= 2;
+    const size_t lds = words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);
     const dim3 grid((unsigned)(p.n_waves / (SOP_K_DD_THREADS / 64))), block(SOP_K_DD_THREADS);
-#define SOPK_DD(B, E, L) hipLaunchKernelGGL((sopk::dd_hist_kernel<B, E, L>), grid, block, lds, st, p)
+#define SOPK_DD(B, E, L) do { \
+        if (lds > 48 * 1024) { const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sopk::dd_hist_kernel<B, E, L>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); if (e != hipSuccess) return e; } \
+        hipLaunchKernelGGL((sopk::dd_hist_kernel<B, E, L>), grid, block, lds, st, p); } while (0)
     if (is_bf16) {
         if (g == 8) SOPK_DD(true, 8, 1); else if (g == 16) SOPK_DD(true, 16, 1); else if (g == 32) SOPK_DD(true, 16, 2); else SOPK_DD(true, 16, 4);
     } else {

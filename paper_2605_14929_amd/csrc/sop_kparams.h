@@ -143,6 +143,7 @@ struct DdParams {
     long long row_step, Ms;          // every row_step-th row is used: Ms = ceil(M / row_step) rows
     long long strips, total_units, n_waves;  // total_units = strips * Ms
     int n_bins;
+    int n_repl;                      // copies of the 32-bit counts in a workgroup's LDS (set by the launch: 1, 2, 4, 8 or 16)
     unsigned long long* acc;         // [n_bins] running histogram of the layer (zero between calls)
     unsigned int* done;              // workgroups finished
     long long* hist;                 // [n_bins] output

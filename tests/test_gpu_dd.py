@@ -140,3 +140,22 @@ def test_grid_constrained_dd4_joins_the_alphabet():
     # among codebooks that live on the E4M3 grid, the one selected on the grid serves the layer best
     # (the unconstrained NF4 table, which no E4M3 LUT can hold, is better still)
     assert gpu["acos_atom"][1] > gpu["acos_atom"][2] and gpu["acos_atom"][1] > gpu["acos_atom"][3]
+
+
+@pytest.mark.parametrize("H", [64, 1024, 4096, 8192])
+@pytest.mark.parametrize("norms", ["ones", "none", "mixed"])
+def test_counts_past_32_bits_on_one_bin(H, norms):
+    """Every weight of a block at its maximum: whole rows fall on one bin, twelve rows a wavefront, so the 32-bit counts have
+    to be emptied on the way (at 8192 bins a single step exceeds the wavefront's share of them).  Expected in closed form."""
+    import torch
+    M, K, g = 12 * 4096, 1024, 16
+    Wt = torch.full((M, K), 0.5, dtype=torch.bfloat16, device="cuda")
+    Wt[:, 512:] = -0.25
+    c = None if norms == "none" else torch.ones(K, device="cuda")
+    if norms == "mixed":
+        c[::2] = 0.5
+    h = ctx().dd_histogram(Wt, c, g, H).cpu().numpy()
+    per_half = M * (512 if norms != "mixed" else 384) << 20
+    want = np.zeros(H, dtype=np.int64)
+    want[H - 1], want[0] = per_half, per_half
+    assert np.array_equal(h, want)
