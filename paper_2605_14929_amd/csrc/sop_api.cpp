@@ -44,6 +44,11 @@ struct ScaleSlot { std::tuple<int, int, int, int, int> key; bool used = false; u
 }  // namespace
 
 static constexpr int kLanes = 2;          // streams of its own that sop_pair_search_layers deals the layers out to
+// scratch of the layer-scope passes, in 64-bit words: workgroup partials, running maxima, tickets (every copy and ticket counter in a
+// 128-byte line of its own)
+static constexpr size_t kLsMax = 3 * SOP_K_LS_MAXWG + 16;
+static constexpr size_t kLsDone = kLsMax + 16 * SOP_K_LS_MAXREP;
+static constexpr size_t kLsWords = kLsDone + 17 * SOP_K_LS_DONE_STRIDE / 2;
 static constexpr int kMaxLayers = 1024;  // layers of one launch of the model-wide kernel (more are dealt with in several launches)
 static constexpr int kStabSlots = 160;   // (scale, reciprocal) tables kept on the device: more than the layer shifts one call can name (129)
 static constexpr size_t kSumsWords = SOP_K_REPL * SOP_K_NCOL + SOP_K_REPL + 1;   // one set of layer sums and tickets, in 64-bit words
@@ -119,7 +124,7 @@ struct sop_ctx {
     char* h_res = nullptr;                // pinned staging for its results
     hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
     bool stage_pending = false;
-    unsigned long long* d_ls = nullptr;   // [3*SOP_K_LS_MAXWG] workgroup partials, one spare word, 17 ticket counters (u32) from word 3*MAXWG+1, then SOP_K_LS_MAXREP copies of the layer maxima (2 x u32 each, 128 bytes apart) from word 3*MAXWG+16; zero between calls
+    unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
     unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] running DD histogram + (one word further) its finished-workgroup counter; zero between calls
     unsigned int* d_sel = nullptr;        // [2][3][SOP_K_SEL_BINS] two sets of digit counts of the block ranking: a call counts into set sel_set and clears the other
     int sel_set = 0;
@@ -194,8 +199,8 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
         delete c;
         return hipfail(nullptr, e, "hipMalloc(histogram)");
     }
-    if ((e = hipMalloc((void**)&c->d_ls, sizeof(unsigned long long) * (3 * SOP_K_LS_MAXWG + 2 + 9 + 5 + 16 * SOP_K_LS_MAXREP))) != hipSuccess ||
-        (e = hipMemset(c->d_ls, 0, sizeof(unsigned long long) * (3 * SOP_K_LS_MAXWG + 2 + 9 + 5 + 16 * SOP_K_LS_MAXREP))) != hipSuccess) {
+    if ((e = hipMalloc((void**)&c->d_ls, sizeof(unsigned long long) * kLsWords)) != hipSuccess ||
+        (e = hipMemset(c->d_ls, 0, sizeof(unsigned long long) * kLsWords)) != hipSuccess) {
         (void)hipFree(c->d_bins); (void)hipFree(c->d_sums); (void)hipFree(c->d_ddacc); if (c->d_ls) (void)hipFree(c->d_ls);
         delete c;
         return hipfail(nullptr, e, "hipMalloc(partials)");
@@ -885,14 +890,18 @@ extern "C" sop_status sop_layer_scope_error(sop_ctx* c, const void* W, sop_dtype
     p.W = W; p.c = cn; p.M = M; p.K = K; p.ldw = ldw;
     p.strips = (K / epl + 63) / 64;
     p.total_units = p.strips * M;
-    long long wg = std::min<long long>(std::min<long long>((long long)c->n_cu * 4, SOP_K_LS_MAXWG), (p.total_units + 3) / 4);
+    // the maxima pass: sixteen workgroups of four wavefronts per compute unit.  The rounding pass: eight, which its registers allow
+    // (62 of 64) and which covers its loads and its arithmetic better than four (SOP_K_LS_MAXWG partials at most)
+    const long long fine = (p.total_units + 3) / 4;
+    p.max_waves = std::max<long long>(4 * std::min<long long>(std::min<long long>((long long)c->n_cu * 4, SOP_K_LS_MAXWG), fine), 1) * 4;
+    long long wg = std::min<long long>(std::min<long long>((long long)c->n_cu * 8, SOP_K_LS_MAXWG), fine);
     p.n_waves = std::max<long long>(wg, 1) * 4;
     p.w_man = rw.y; p.w_bias = rw.bias; p.w_max_code = rw.max_code;
     p.s_man = rs.y; p.s_bias = rs.bias; p.s_max_code = rs.max_code;
     p.k = k; p.pow2k = std::ldexp(1.0f, k);
     p.part = c->d_ls;
-    p.maxbits = reinterpret_cast<unsigned int*>(c->d_ls + 3 * SOP_K_LS_MAXWG + 16);   // 128-byte aligned: one cache line per copy
-    p.done = reinterpret_cast<unsigned int*>(c->d_ls + 3 * SOP_K_LS_MAXWG + 1);
+    p.maxbits = reinterpret_cast<unsigned int*>(c->d_ls + kLsMax);
+    p.done = reinterpret_cast<unsigned int*>(c->d_ls + kLsDone);
     p.out = out; p.codes = codes;
     DeviceGuard guard(c->device);
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
@@ -943,7 +952,7 @@ extern "C" sop_status sop_sum_f32(sop_ctx* c, const float* x, int64_t n, double*
     long long wg = std::min<long long>(std::min<long long>((long long)c->n_cu * 4, SOP_K_LS_MAXWG), (n + 255) / 256);
     p.n_waves = std::max<long long>(wg, 1) * 4;
     p.part = c->d_ls;
-    p.done = reinterpret_cast<unsigned int*>(c->d_ls + 3 * SOP_K_LS_MAXWG + 1);
+    p.done = reinterpret_cast<unsigned int*>(c->d_ls + kLsDone);
     p.out = out;
     DeviceGuard guard(c->device);
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");

@@ -170,18 +170,20 @@ struct FlParams {
 /* Layer-scope weight formats and the binary64 sum */
 #define SOP_K_LS_MAXWG 2048
 #define SOP_K_LS_MAXREP 64           /* copies of the running layer maxima */
+#define SOP_K_LS_DONE_STRIDE 32      /* words between ticket counters: a 128-byte line each */
 struct LsParams {
     const void*  W;                  // weights (or the binary32 array of the sum kernel)
     const float* c;                  // null: c = 1
     long long M, K, ldw;
     long long strips, total_units, n_waves;   // sum kernel: total_units = number of elements
+    long long max_waves;             // wavefronts of the maxima pass
     int w_man, w_bias, w_max_code;   // weight grid ExMy
     int s_man, s_bias, s_max_code;   // scale word
     int k;
     float pow2k;
     unsigned int* maxbits;           // [SOP_K_LS_MAXREP][32], two words used: bit patterns of the largest positive / negative weight (zero between calls)
     unsigned long long* part;        // [SOP_K_LS_MAXWG][3] workgroup partials (bit patterns of doubles)
-    unsigned int* done;              // [17] tickets: over the groups, then per group of workgroups
+    unsigned int* done;              // [17] tickets, SOP_K_LS_DONE_STRIDE words apart: over the groups, then per group of workgroups
     double* out;                     // [4] weighted error, plain error, ||W||_c^2, scale code   (sum kernel: [1])
     uint16_t* codes;                 // optional [M*K] index into the ascending signed grid
 };
