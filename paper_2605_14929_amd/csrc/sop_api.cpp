@@ -1020,7 +1020,10 @@ static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t 
     const long long quads = std::max<long long>((n_blocks / 4 + SOP_K_SEL_THREADS - 1) / SOP_K_SEL_THREADS, 1);
     const int n_wg = (int)std::min<long long>((long long)c->n_cu * 4, quads);
     const long long cquads = std::max<long long>((n_blocks / 4 + SOP_K_CNT_THREADS - 1) / SOP_K_CNT_THREADS, 1);
-    const int n_wg_count = (int)std::min<long long>(std::max(c->n_cu / 2, 1), cquads);
+    // counting workgroups per plane: half the compute units (each adds its whole histogram to the plane's with atomics), and over
+    // all planes no more than are resident at once (two of 1024 threads per compute unit): a second, half-empty round of
+    // workgroups cost six planes a quarter of the pass
+    const int n_wg_count = (int)std::min<long long>(std::max(std::min(c->n_cu / 2, 2 * c->n_cu / std::max(n_planes, 1)), 1), cquads);
     DeviceGuard guard(c->device);
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
     hipError_t e = sopk_selm_launch(&p, n_wg_count, n_wg, stream);

@@ -219,8 +219,13 @@ __global__ __launch_bounds__(SOP_K_CNT_THREADS) void rank_count_multi_kernel(con
     const bool higher = p.higher != 0;
     const long long n4 = p.n >> 2;
     const float4* s4 = reinterpret_cast<const float4*>(p.score);
-    for (long long i = (long long)blockIdx.x * SOP_K_CNT_THREADS + threadIdx.x; i < n4; i += (long long)gridDim.x * SOP_K_CNT_THREADS) {
-        const float4 v = s4[i];
+    // (the next four scores are asked for before the current ones are counted)
+    const long long step = (long long)gridDim.x * SOP_K_CNT_THREADS;
+    long long i = (long long)blockIdx.x * SOP_K_CNT_THREADS + threadIdx.x;
+    float4 nv = i < n4 ? s4[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (; i < n4; i += step) {
+        const float4 v = nv;
+        if (i + step < n4) nv = s4[i + step];
         const float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
