@@ -918,9 +918,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         for (int i = 0; i < EPL; ++i) asm volatile("" : "+v"(w[i]));
         const bool ok_nxt = seek(i_nxt);
         l_nxt = rq_l;
-        // (after the last step its row is read once more: a load on every path leaves the rows in place, where a
-        // conditional one costs a copy of them per step)
+        // (after the last step the first row of the layer the request side is in is read and not used: a load on every path
+        // leaves the rows in place, where a conditional one costs a copy of them per step.  That layer can be a later one, with
+        // fewer rows than the one at hand, when the share has no steps in it: the position at hand may lie outside it.)
         if (ok_nxt) locate(sb + (i_nxt - rq_base), strip, m);
+        else { strip = 0u; m = 0u; }
         nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, strip, m, lanes_of(strip, MULTI ? rq_K : p.K), (unsigned int)lane);
         // the next step opens another layer: its channel norms are asked for now (one word per lane brings
         // every cache line of the strip's norms in), so that the loads at the top of that step find them

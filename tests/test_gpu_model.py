@@ -161,3 +161,22 @@ def test_random_lists_of_layers(seed):
             o = cx.pair_search(layers[l][0], layers[l][1], g, fmt, k=shifts[l], metric=metric)
             torch.cuda.synchronize()
             assert np.array_equal(o.acos_atom.cpu().numpy(), ta[l]) and (P == 0 or np.array_equal(o.acos_pair.cpu().numpy()[:P], tp[l])), l
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_small_layers_after_and_between_large_ones(bf16):
+    """Lists in which most shares have no step in some layers, at the list's end, its start and in between (a wavefront's
+    last requests then belong to a layer with fewer rows than the one at hand): every layer against a search of its own."""
+    import torch
+    cx, fmt = ctx(), sop.fmt_by_name("UE4M4")
+    cx.set_alphabet(_alphabet()); cx.set_pairs(None)
+    shapes = [(3, 1024), (600, 2048), (1, 64), (2, 512), (300, 3072), (1, 16), (5, 1040), (1, 1024)]
+    layers = []
+    for i, (M, K) in enumerate(shapes):
+        W = torch.from_numpy(si.student_t_weights(M, K, 5.0, 800 + i)).cuda()
+        layers.append((W.to(torch.bfloat16) if bf16 else W, torch.from_numpy(si.channel_norms(K, 1.0, 820 + i)).cuda()))
+    tp, ta, sels = cx.pair_search_layers(layers, 16, fmt, want_sel=True)
+    for i, (W, c) in enumerate(layers):
+        one = cx.pair_search(W, c, 16, fmt)
+        assert torch.equal(tp[i], one.acos_pair[:15]) and torch.equal(ta[i], one.acos_atom), shapes[i]
+        assert torch.equal(sels[i].view(-1), one.sel_words.view(-1)), shapes[i]
