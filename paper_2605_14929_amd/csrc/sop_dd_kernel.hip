@@ -279,7 +279,8 @@ extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, voi
     hipStream_t st = (hipStream_t)stream;
     // replicas of the 32-bit counts: one per wavefront where they take at most 64 KiB, else as many as fit beside the 64-bit sums
     const size_t words = (size_t)p.n_bins * (size_t)(p.n_levels > 0 ? p.n_levels * p.n_planes : 1);
-    p.n_repl = SOP_K_DD_THREADS / 64;
+    // (a quarter of them for a layer of few steps a wavefront, which would spend its time clearing and joining replicas)
+    p.n_repl = p.total_units >= 8 * p.n_waves ? SOP_K_DD_THREADS / 64 : SOP_K_DD_THREADS / 256;
     while (p.n_repl > 1 && words * p.n_repl * 4 > (64u << 10)) p.n_repl /= 2;
     const size_t lds = words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);
     const dim3 grid((unsigned)(p.n_waves / (SOP_K_DD_THREADS / 64))), block(SOP_K_DD_THREADS);
