@@ -92,6 +92,9 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     const long long u0 = p.total_units * wave / p.n_waves;
     const int n_steps = __builtin_amdgcn_readfirstlane((int)(p.total_units * (wave + 1) / p.n_waves - u0));
     const float cs = cmax > 0.0f ? 1048576.0f / cmax : 0.0f;      // all-zero channel norms: an empty histogram
+    // cs overflows for norms below 2^20 / FLT_MAX: the conversion below then gives 2^31 - 1 for every non-zero norm, and a step's
+    // additions to one word do not fit 32 bits
+    const bool huge = !(cs < INFINITY);
     const float half = 0.5f * (float)HB;
     unsigned int* const cnt = s_cnt + (wv % p.n_repl) * H;        // this wavefront's replica
     const unsigned int budget = 0xFFFFFFFFu / (unsigned int)(NW / p.n_repl);
@@ -151,10 +154,10 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             }
 #pragma unroll
             for (int st = 1; st < 64; st <<= 1) sum += (unsigned int)__shfl_xor((int)sum, st, 64);
-            per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30
+            per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30 (not used where `huge`)
         }
         // a step that alone exceeds the wavefront's share (a shared replica under near-equal norms) adds to the 64-bit words
-        const bool wide = per_step > budget;
+        const bool wide = huge || per_step > budget;
         if (!wide) {
             if (per_step > budget - spent) {
                 for (int i = lane; i < H; i += 64) {

@@ -159,3 +159,20 @@ def test_counts_past_32_bits_on_one_bin(H, norms):
     want = np.zeros(H, dtype=np.int64)
     want[H - 1], want[0] = per_half, per_half
     assert np.array_equal(h, want)
+
+
+@pytest.mark.parametrize("H,cols", [(64, 1024), (1024, 1024), (2048, 6), (4096, 1024)])
+def test_norms_below_the_range_of_the_mass_scale(H, cols):
+    """Largest channel norm below 2^20 / FLT_MAX: the scale to integer masses overflows and every non-zero norm counts as the
+    largest 32-bit integer.  A step's additions then exceed 32 bits; the sums are exact all the same.  Expected in closed form."""
+    import torch
+    M, K, g = 12 * 4096, 1024, 16
+    Wt = torch.full((M, K), 0.5, dtype=torch.bfloat16, device="cuda")
+    Wt[:, 512:] = -0.25
+    c = torch.zeros(K, device="cuda")
+    c[:cols // 2] = 1e-36
+    c[K - cols // 2:] = 1e-36
+    h = ctx().dd_histogram(Wt, c, g, H).cpu().numpy()
+    want = np.zeros(H, dtype=np.int64)
+    want[H - 1] = want[0] = M * (cols // 2) * (2 ** 31 - 1)
+    assert np.array_equal(h, want)
