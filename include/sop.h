@@ -386,7 +386,8 @@ sop_status sop_read_probe(sop_ctx* ctx, const void* x_dev, int64_t n_bytes, uint
 sop_status sop_issue_probe(sop_ctx* ctx, int kind, int waves_per_simd, int iters, float a, float b,
                            float* out_dev, int* n_out, void* hip_stream);
 
-/* out_dev[0] = sum of the n binary32 values at x_dev, accumulated in binary64 in a fixed order. */
+/* out_dev[0] = sum of the n binary32 values at x_dev, accumulated in binary64 in a fixed order, which depends on n and the
+ * device alone: the same values give the same bits wherever x_dev (4-byte aligned) lies. */
 sop_status sop_sum_f32(sop_ctx* ctx, const float* x_dev, int64_t n, double* out_dev, void* hip_stream);
 
 /* ---- block ranking and pools (Section "Per-Layer Pair Search", step 2: every block is scored

@@ -81,6 +81,21 @@ def test_sum_kernel():
         assert abs(got.item() - ref) <= 1e-12 * float(np.abs(x).astype(np.float64).sum())
 
 
+@pytest.mark.parametrize("n", [1, 3, 257, 4097, 16385, 1_000_003])
+def test_sum_kernel_order_does_not_depend_on_the_address(n):
+    """The additions follow the element numbers: the same values give the same bits at every offset from a 16-byte boundary."""
+    import torch
+    rng = np.random.default_rng(10 + n)
+    x = torch.from_numpy((rng.standard_normal(n) * 10.0 ** rng.uniform(-6, 6, size=n)).astype(np.float32)).cuda()
+    buf = torch.empty(n + 8, device="cuda")
+    assert x.data_ptr() % 16 == 0 and buf.data_ptr() % 16 == 0
+    want = ctx().sum_f32(x).item()
+    for off in (1, 2, 3, 4, 5):
+        view = buf[off:off + n]
+        view.copy_(x)
+        assert ctx().sum_f32(view).item() == want, off
+
+
 def test_fp6_block_scaled_versus_fp8_layer_scaled_full_layer():
     # the paper's operating-point comparison on the 70B-shaped layer of configuration 5:
     # E2M3sUE4M4 (g = 16, 6.5 bpw) against E4M3^0sUE8M0 (8.0 bpw), weighted reconstruction error
