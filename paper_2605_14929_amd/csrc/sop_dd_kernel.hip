@@ -26,7 +26,9 @@
 // replicas, each shared by 16 / n_repl wavefronts, and never wrap: a step adds at most S = the sum of the masses of the
 // strip's columns to any one word, and a wavefront that has added as much as its share of 2^32 - 1 since it last emptied its
 // replica empties it (exchange with zero, word by word) into the 64-bit histogram first.  Heavy-tailed channel norms have S near
-// 2^25 and are hardly ever emptied before the end; with equal norms S is 2^30 and a private replica is emptied every third row.
+// 2^25 and are hardly ever emptied before the end.  With norms near their maximum (S up to 2^30) many words and shared
+// replicas would be emptied at every other step, at several times the cost of the step's own adds: a wavefront whose strip's S
+// is above p.dear_mass (dd_dear_mass()) and which cannot get through its steps without emptying adds to the 64-bit sums.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -129,6 +131,7 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     };
     if (n_steps > 0) request();
     unsigned int cur_strip = 0xFFFFFFFFu;
+    bool wide = false;                            // this strip's steps add to the 64-bit sums
     unsigned int mass[EPL]; // rint(fl(c*cs)) of the owned columns
 #pragma unroll
     for (int i = 0; i < EPL; ++i) mass[i] = 0u;
@@ -155,9 +158,10 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
 #pragma unroll
             for (int st = 1; st < 64; st <<= 1) sum += (unsigned int)__shfl_xor((int)sum, st, 64);
             per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30 (not used where `huge`)
+            // (a step that alone exceeds the wavefront's share, as in a shared replica under near-equal norms, goes there too)
+            wide = huge || per_step > budget ||
+                   (per_step > p.dear_mass && (unsigned long long)per_step * (unsigned int)(n_steps - u) > budget - spent);
         }
-        // a step that alone exceeds the wavefront's share (a shared replica under near-equal norms) adds to the 64-bit words
-        const bool wide = huge || per_step > budget;
         if (!wide) {
             if (per_step > budget - spent) {
                 for (int i = lane; i < H; i += 64) {
@@ -285,6 +289,7 @@ extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, voi
     // (a quarter of them for a layer of few steps a wavefront, which would spend its time clearing and joining replicas)
     p.n_repl = p.total_units >= 8 * p.n_waves ? SOP_K_DD_THREADS / 64 : SOP_K_DD_THREADS / 256;
     while (p.n_repl > 1 && words * p.n_repl * 4 > (64u << 10)) p.n_repl /= 2;
+    p.dear_mass = dd_dear_mass((unsigned int)words, g < 16 ? g : 16, p.n_repl);
     const size_t lds = words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);
     const dim3 grid((unsigned)(p.n_waves / (SOP_K_DD_THREADS / 64))), block(SOP_K_DD_THREADS);
 #define SOPK_DD(B, E, L) do { \

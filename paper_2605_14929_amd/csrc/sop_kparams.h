@@ -144,10 +144,24 @@ struct DdParams {
     long long strips, total_units, n_waves;  // total_units = strips * Ms
     int n_bins;
     int n_repl;                      // copies of the 32-bit counts in a workgroup's LDS (set by the launch: 1, 2, 4, 8 or 16)
+    unsigned int dear_mass;          // a strip whose columns' masses sum to more is not worth emptying replicas for (dd_dear_mass)
     unsigned long long* acc;         // [n_bins] running histogram of the layer (zero between calls)
     unsigned int* done;              // workgroups finished
     long long* hist;                 // [n_bins] output
 };
+
+/* Largest sum of a strip's column masses for which 32-bit counts that have to be emptied on the way pay.  A wavefront empties its
+ * replica (one of n_repl, shared by the others of the workgroup's wavefronts) every budget / sum steps: words / 64 exchanges a
+ * lane, each followed by a 64-bit add, against weights_per_lane adds a step, of which each saves about a quarter of the cost
+ * of such a pair.  Measured at 4096 x 11008, bf16, 16 weights a lane, 64-bit adds -> 32-bit: 1024 words 31 us -> 27 where
+ * nothing is emptied, 31 where every third step is; 4096 words 34 -> 40 at every fifth step, 80 at every second. */
+inline unsigned int dd_dear_mass(unsigned int words, unsigned int weights_per_lane, unsigned int n_repl)
+{
+    const unsigned int waves_per_repl = SOP_K_DD_THREADS / 64 / n_repl;
+    const unsigned long long budget = 0xFFFFFFFFull / waves_per_repl;
+    const unsigned long long m = budget * weights_per_lane * 64u / (4ull * words);
+    return m < 0xFFFFFFFFull ? (unsigned int)m : 0xFFFFFFFFu;
+}
 
 /* Statistics pass of the per-layer scale shift */
 #define SOP_K_FL_THREADS 1024
