@@ -45,7 +45,9 @@ __device__ __forceinline__ unsigned int cvt_floor(float v)
     return r;
 }
 
-template <bool BF16, int EPL, int LPB>
+// REPL: 32-bit counts in replicas; else every weight adds to the 64-bit sums (dd_replicas()).  AHEAD: the next row is requested a
+// step ahead; without it for layers that give no wavefront a second step (a smaller kernel: 256 x 1024, 1024 bins, 6.0 us -> 5.8)
+template <bool BF16, int EPL, int LPB, bool REPL, bool AHEAD>
 __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParams p)
 {
     extern __shared__ __align__(16) unsigned long long s_hist[];      // [H] 64-bit sums, then n_repl x [H] 32-bit counts
@@ -59,7 +61,7 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     unsigned int* s_cnt = reinterpret_cast<unsigned int*>(s_hist + H);
     {
         uint4* z = reinterpret_cast<uint4*>(s_hist);                  // (H is a multiple of 64)
-        const int n16 = (H / 4) * (2 + p.n_repl);
+        const int n16 = (H / 4) * (REPL ? 2 + p.n_repl : 2);
         for (int i = threadIdx.x; i < n16; i += SOP_K_DD_THREADS) z[i] = make_uint4(0u, 0u, 0u, 0u);
     }
     // cmax = max_k c_k (order-independent), found by every workgroup for itself
@@ -90,31 +92,46 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const long long wave = (long long)blockIdx.x * NW + wv;
-    const long long u0 = p.total_units * wave / p.n_waves;
-    const int n_steps = __builtin_amdgcn_readfirstlane((int)(p.total_units * (wave + 1) / p.n_waves - u0));
+    // this wavefront's steps: floor(T b / G) = (T / G) b + (T % G) b / G with the first two from the host, all of it in 32 bits but
+    // for a product (64-bit divisions took a few tenths of a microsecond of a small layer's six)
+    const unsigned int wave = blockIdx.x * NW + (unsigned int)wv, n_waves = (unsigned int)p.n_waves;
+    const unsigned int r0 = p.units_r * wave / n_waves, r1 = p.units_r * (wave + 1u) / n_waves;       // (G below 2^16)
+    const long long u0 = p.units_q * wave + r0;
+    const int n_steps = __builtin_amdgcn_readfirstlane((int)p.units_q + (int)(r1 - r0));
     const float cs = cmax > 0.0f ? 1048576.0f / cmax : 0.0f;      // all-zero channel norms: an empty histogram
     // cs overflows for norms below 2^20 / FLT_MAX: the conversion below then gives 2^31 - 1 for every non-zero norm, and a step's
     // additions to one word do not fit 32 bits
     const bool huge = !(cs < INFINITY);
     const float half = 0.5f * (float)HB;
-    unsigned int* const cnt = s_cnt + (wv % p.n_repl) * H;        // this wavefront's replica
-    const unsigned int budget = 0xFFFFFFFFu / (unsigned int)(NW / p.n_repl);
+    unsigned int* const cnt = s_cnt + (REPL ? (wv & (p.n_repl - 1)) * H : 0);                         // this wavefront's replica
+    const unsigned int budget = REPL ? 0xFFFFFFFFu / (unsigned int)(NW / p.n_repl) : 0u;
     unsigned int spent = 0u, per_step = 0u;                       // added to any one word since the last emptying, at most; by one step, at most
 
     // request side: band, strip and row of the next step, kept on the scalar unit.  Steps run down the BAND rows of a strip, then
     // through the strips of the band, then through the bands: the wavefronts of a workgroup stay
     // within a few megabytes of the layer, where a walk down whole strips spreads them over all of it, a row's stride between any
-    // two reads (28672 x 8192: 108 us, 92 in bands of 32 or 128 rows; a 90 MB layer is the same either way).
+    // two reads (28672 x 8192: 108 us, 92 in bands of 32 or 128 rows; 4096 x 11008, a third of a band a workgroup: 30.1 us, 30.7).
     constexpr unsigned int BAND = 128;
     const unsigned int strips = (unsigned int)p.strips;
-    const long long per_band = (long long)BAND * p.strips;
-    long long rb = (long long)__builtin_amdgcn_readfirstlane((int)(u0 / per_band)) * BAND;           // first row of the band
     auto rows_of = [&](long long b) -> unsigned int { return (unsigned int)min((long long)BAND, p.Ms - b); };
-    unsigned int rh = rows_of(rb);                                                                    // rows of the band
-    const unsigned int rem = (unsigned int)__builtin_amdgcn_readfirstlane((int)(u0 - rb / BAND * per_band));
-    unsigned int rs = n_steps > 0 ? (unsigned int)__builtin_amdgcn_readfirstlane((int)(rem / rh)) : 0u;
-    long long rm = rb + (n_steps > 0 ? rem - rs * rh : 0u);                                           // index among the sampled rows
+    long long rb = 0, rm = 0;                     // first row of the band; row of the step: indices among the sampled rows
+    unsigned int rh = 0u, rs = 0u;                // rows of the band; strip
+    if (n_steps > 0) {
+        if (p.total_units < (1ll << 31) && strips <= (1u << 24)) {
+            const unsigned int u = (unsigned int)__builtin_amdgcn_readfirstlane((int)u0), band = u / (BAND * strips);
+            rb = (long long)__builtin_amdgcn_readfirstlane((int)(band * BAND));
+            rh = rows_of(rb);
+            const unsigned int rem = u - band * (BAND * strips);
+            rs = (unsigned int)__builtin_amdgcn_readfirstlane((int)(rem / rh));
+            rm = rb + (rem - rs * rh);
+        } else {
+            const long long per_band = (long long)BAND * p.strips, band = u0 / per_band, rem = u0 - band * per_band;
+            rb = band * BAND;
+            rh = rows_of(rb);
+            rs = (unsigned int)(rem / rh);
+            rm = rb + (rem - (long long)rs * rh);
+        }
+    }
     uint4 raw[NV];
     int lvl[PRE];
     auto request = [&]() __attribute__((always_inline)) {
@@ -129,9 +146,9 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             for (int pl = 0; pl < PRE; ++pl) lvl[pl] = pl < NP && valid ? p.block_mask[(long long)pl * p.plane_stride + blk] : 0;
         }
     };
-    if (n_steps > 0) request();
+    if (AHEAD && n_steps > 0) request();
     unsigned int cur_strip = 0xFFFFFFFFu;
-    bool wide = false;                            // this strip's steps add to the 64-bit sums
+    bool wide = !REPL;                            // this strip's steps add to the 64-bit sums
     unsigned int mass[EPL]; // rint(fl(c*cs)) of the owned columns
 #pragma unroll
     for (int i = 0; i < EPL; ++i) mass[i] = 0u;
@@ -155,14 +172,16 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
                     sum += mass[i + j];
                 }
             }
+            if constexpr (REPL) {
 #pragma unroll
-            for (int st = 1; st < 64; st <<= 1) sum += (unsigned int)__shfl_xor((int)sum, st, 64);
-            per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30 (not used where `huge`)
-            // (a step that alone exceeds the wavefront's share, as in a shared replica under near-equal norms, goes there too)
-            wide = huge || per_step > budget ||
-                   (per_step > p.dear_mass && (unsigned long long)per_step * (unsigned int)(n_steps - u) > budget - spent);
+                for (int st = 1; st < 64; st <<= 1) sum += (unsigned int)__shfl_xor((int)sum, st, 64);
+                per_step = (unsigned int)__builtin_amdgcn_readfirstlane((int)sum);       // at most 2^30 (not used where `huge`)
+                // (a step that alone exceeds the wavefront's share, as in a shared replica under near-equal norms, goes there too)
+                wide = huge || per_step > budget ||
+                       (per_step > p.dear_mass && (unsigned long long)per_step * (unsigned int)(n_steps - u) > budget - spent);
+            }
         }
-        if (!wide) {
+        if (REPL && !wide) {
             if (per_step > budget - spent) {
                 for (int i = lane; i < H; i += 64) {
                     const unsigned int v = atomicExch(&cnt[i], 0u);
@@ -172,6 +191,7 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             }
             spent += per_step;
         }
+        if (!AHEAD) request();
         float w[EPL];
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -189,7 +209,7 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             if (++rs == strips) { rs = 0u; rb += BAND; rh = rows_of(rb); }
             rm = rb;
         }
-        if (u + 1 < n_steps) request();
+        if (AHEAD && u + 1 < n_steps) request();
         float a = 0.0f;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) a = fmaxf(a, fabsf(w[i]));
@@ -205,7 +225,7 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
                 bin[i] = min(cvt_floor(__fmaf_rn(x, half, half)), (unsigned int)(HB - 1));
             }
             auto add = [&](int hb) __attribute__((always_inline)) {
-                if (!wide) {
+                if (REPL && !wide) {
 #pragma unroll
                     for (int i = 0; i < EPL; ++i) atomicAdd(&cnt[hb + bin[i]], mass[i]);
                 } else {
@@ -235,7 +255,8 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             before[j] = 0ull;
             if (i < H) {
                 unsigned long long v = s_hist[i];
-                for (int r = 0; r < p.n_repl; ++r) v += s_cnt[r * H + i];
+                if (REPL)
+                    for (int r = 0; r < p.n_repl; ++r) v += s_cnt[r * H + i];
                 if (v) before[j] = atomicAdd(p.acc + i, v);
             }
         }
@@ -284,22 +305,27 @@ extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, voi
 {
     DdParams p = *pp;
     hipStream_t st = (hipStream_t)stream;
-    // replicas of the 32-bit counts: one per wavefront where they take at most 64 KiB, else as many as fit beside the 64-bit sums
-    const size_t words = (size_t)p.n_bins * (size_t)(p.n_levels > 0 ? p.n_levels * p.n_planes : 1);
-    // (a quarter of them for a layer of few steps a wavefront, which would spend its time clearing and joining replicas)
-    p.n_repl = p.total_units >= 8 * p.n_waves ? SOP_K_DD_THREADS / 64 : SOP_K_DD_THREADS / 256;
-    while (p.n_repl > 1 && words * p.n_repl * 4 > (64u << 10)) p.n_repl /= 2;
-    p.dear_mass = dd_dear_mass((unsigned int)words, g < 16 ? g : 16, p.n_repl);
-    const size_t lds = words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);
+    const unsigned int words = (unsigned int)p.n_bins * (unsigned int)(p.n_levels > 0 ? p.n_levels * p.n_planes : 1);
+    const unsigned int wpl = (unsigned int)(g < 16 ? g : 16);
+    p.n_repl = (int)dd_replicas(words, wpl, p.n_levels > 0, p.c == nullptr, p.total_units, p.n_waves);
+    p.dear_mass = p.n_repl ? dd_dear_mass(words, wpl, (unsigned int)p.n_repl) : 0u;
+    p.units_q = p.total_units / p.n_waves;
+    p.units_r = (unsigned int)(p.total_units % p.n_waves);
+    const size_t lds = (size_t)words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);
     const dim3 grid((unsigned)(p.n_waves / (SOP_K_DD_THREADS / 64))), block(SOP_K_DD_THREADS);
+#define SOPK_DDR(B, E, L, R, N) do { \
+        if (lds > 48 * 1024) { const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sopk::dd_hist_kernel<B, E, L, R, N>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); if (e != hipSuccess) return e; } \
+        hipLaunchKernelGGL((sopk::dd_hist_kernel<B, E, L, R, N>), grid, block, lds, st, p); } while (0)
 #define SOPK_DD(B, E, L) do { \
-        if (lds > 48 * 1024) { const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sopk::dd_hist_kernel<B, E, L>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); if (e != hipSuccess) return e; } \
-        hipLaunchKernelGGL((sopk::dd_hist_kernel<B, E, L>), grid, block, lds, st, p); } while (0)
+        if (p.n_repl) SOPK_DDR(B, E, L, true, true); \
+        else if (p.total_units > p.n_waves) SOPK_DDR(B, E, L, false, true); \
+        else SOPK_DDR(B, E, L, false, false); } while (0)
     if (is_bf16) {
         if (g == 8) SOPK_DD(true, 8, 1); else if (g == 16) SOPK_DD(true, 16, 1); else if (g == 32) SOPK_DD(true, 16, 2); else SOPK_DD(true, 16, 4);
     } else {
         if (g == 8) SOPK_DD(false, 8, 1); else if (g == 16) SOPK_DD(false, 16, 1); else if (g == 32) SOPK_DD(false, 16, 2); else SOPK_DD(false, 16, 4);
     }
 #undef SOPK_DD
+#undef SOPK_DDR
     return hipGetLastError();
 }

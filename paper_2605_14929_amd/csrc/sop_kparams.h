@@ -141,9 +141,11 @@ struct DdParams {
     long long plane_stride;          // wanted): one pass over the weights fills P * L histograms, laid out [plane][level][bin]
     long long M, K, ldw, Bk;
     long long row_step, Ms;          // every row_step-th row is used: Ms = ceil(M / row_step) rows
-    long long strips, total_units, n_waves;  // total_units = strips * Ms
+    long long strips, total_units, n_waves;  // total_units = strips * Ms; n_waves below 2^16
+    long long units_q;               // total_units = units_q * n_waves + units_r
+    unsigned int units_r;
     int n_bins;
-    int n_repl;                      // copies of the 32-bit counts in a workgroup's LDS (set by the launch: 1, 2, 4, 8 or 16)
+    int n_repl;                      // copies of the 32-bit counts in a workgroup's LDS (set by the launch: 0, 1, 2, 4, 8 or 16)
     unsigned int dear_mass;          // a strip whose columns' masses sum to more is not worth emptying replicas for (dd_dear_mass)
     unsigned long long* acc;         // [n_bins] running histogram of the layer (zero between calls)
     unsigned int* done;              // workgroups finished
@@ -161,6 +163,21 @@ inline unsigned int dd_dear_mass(unsigned int words, unsigned int weights_per_la
     const unsigned long long budget = 0xFFFFFFFFull / waves_per_repl;
     const unsigned long long m = budget * weights_per_lane * 64u / (4ull * words);
     return m < 0xFFFFFFFFull ? (unsigned int)m : 0xFFFFFFFFu;
+}
+
+/* Replicas of the 32-bit counts: one per wavefront where they take at most 64 KiB, else as many as fit; none (every weight adds to the
+ * 64-bit sums) where they do not pay:
+ *  - fewer than eight steps a wavefront: clearing and joining the replicas costs more than the cheaper adds save (64-bit -> 32-bit:
+ *    768 x 2048, a step a wavefront, 8.8 us -> 10.4; 4096 x 4096, four steps, 18.9 -> 18.9; 8192 x 4096, eight, 25.1 -> 23.6);
+ *  - level planes: part of the blocks add, to as many times the words (4 x 1024, 4096 x 11008: 31.6 -> 33.6);
+ *  - no norms: every strip's mass is the largest there is, above dd_dear_mass() for all but a few bins. */
+inline unsigned int dd_replicas(unsigned int words, unsigned int weights_per_lane, bool levels, bool no_norms, long long total_units, long long n_waves)
+{
+    if (levels || total_units < 8 * n_waves) return 0u;
+    unsigned int n = SOP_K_DD_THREADS / 64;
+    while (n > 1u && words * n * 4u > (64u << 10)) n /= 2u;
+    if (no_norms && (64u * weights_per_lane << 20) > dd_dear_mass(words, weights_per_lane, n)) return 0u;
+    return n;
 }
 
 /* Statistics pass of the per-layer scale shift */
