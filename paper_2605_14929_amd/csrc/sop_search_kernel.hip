@@ -460,7 +460,9 @@ __device__ __forceinline__ Sums eval_direct(const float (&w)[EPL], const float (
 // Cosine inputs straight from the codebook values in the scaled domain, where the block scale
 // cancels: cos = sign(s) <w,y>_c / sqrt(||w||_c^2 ||y||_c^2).  Used when the residual form would cancel.
 // (y is read as the table holds it, halved: the ratio does not change.)
-template <int EPL, int LPB, bool THR, class SRC>
+// LEAN: the products c w of the block statistics are formed again rather than kept for it in registers, and four look-ups are in
+// flight at a time.
+template <int EPL, int LPB, bool THR, bool LEAN, class SRC>
 __device__ __forceinline__ void direct_cosine_sums(const float (&cb)[EPL], const float (&w)[EPL], const SRC& src, bool nonzero, bool negative,
                                                    int a, float& ny_out, float& dy_out)
 {
@@ -472,12 +474,13 @@ __device__ __forceinline__ void direct_cosine_sums(const float (&cb)[EPL], const
         src.get(i, xe, bo);
         const Rec r = read_rec<THR, false>(bo, a);
         const float yv = xe > r.thr ? r.yhi : r.ylo;
-        // (a rare path: the products c w of the block statistics are formed again rather than kept for it in registers)
         float wi = w[i];
-        asm volatile("" : "+v"(wi));
+        if constexpr (LEAN) asm volatile("" : "+v"(wi));
         ny = __fmaf_rn(cb[i] * wi, yv, ny);
         dy = __fmaf_rn(cb[i], yv * yv, dy);
-        if (i % 4 == 3) { asm volatile("" : "+v"(ny), "+v"(dy)); __builtin_amdgcn_sched_barrier(0); }
+        if constexpr (LEAN) {
+            if (i % 4 == 3) { asm volatile("" : "+v"(ny), "+v"(dy)); __builtin_amdgcn_sched_barrier(0); }
+        }
     }
     const float nsum = group_sum<LPB>(negative ? -ny : ny), dsum = group_sum<LPB>(dy);
     ny_out = nonzero ? nsum : 0.0f;                    // a zero scale reconstructs nothing
@@ -656,6 +659,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     static_assert(!MULTI || !EMIT, "the model-wide kernel searches only");
     constexpr bool SIGNED = SIGNMODE == 1, ARGMAX = SIGNMODE == 2;
     constexpr bool GROUPED = SIGNMODE == 0 && METRIC != 1 && EPL == 16;   // atoms of a scale group are evaluated two at a time
+    // the direct cosine sums outside the grouped passes: in the form that keeps registers low for the six-atom variants only (the others
+    // have registers left, and the form's scheduling fences cost the signed eight-atom search a sixth: 4096 x 4096, 77 us -> 92)
+    constexpr bool LEAN = NA == 6;
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
     // LDS: bin table | (scale, reciprocal) table | group parameters | reduction scratch
@@ -1100,7 +1106,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 const ScalePrep sq = prepare_scale(pmax, nmax, false, wa, p, sw, s_tab, s_gpar);
                 const float4 gpar = s_gpar[2 * wa], g2 = s_gpar[2 * wa + 1];
                 float ny1, dy1;
-                direct_cosine_sums<EPL, LPB, EMIT>(cb, w, FlySrc<EPL, true>{w, sq.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg}, sq.nonzero, false, wa, ny1, dy1);
+                direct_cosine_sums<EPL, LPB, EMIT, true>(cb, w, FlySrc<EPL, true>{w, sq.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg}, sq.nonzero, false, wa, ny1, dy1);
                 // (direct sums go with the raw norm, which is the scaled one times the inverse power of two, exactly)
                 const float wnr = nsc.wns * __uint_as_float((254u << 23) - __float_as_uint(nsc.sc));
                 const float rs = __frsqrt_rn(__fmaf_rn(wnr, dy1, 1.0e-37f));
@@ -1184,7 +1190,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                                     // the residual form is accurate while the reconstruction carries a fair share of the block's
                                     // norm; otherwise the whole wavefront recomputes this candidate's cosine sums directly
                                     if (__builtin_expect(__any(t.weak) != 0, 0)) {
-                                        direct_cosine_sums<EPL, LPB, true>(cb, w, src, sp.nonzero, sgn, a, ny, dy);
+                                        direct_cosine_sums<EPL, LPB, true, LEAN>(cb, w, src, sp.nonzero, sgn, a, ny, dy);
                                         rawf = true;
                                     }
                                 }
@@ -1273,7 +1279,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     // the block's norm; otherwise the whole wavefront recomputes this atom directly
                     if (__builtin_expect(__any(best.weak) != 0, 0)) {
                         float ny1, dy1;
-                        direct_cosine_sums<EPL, LPB, EMIT>(cb, w, ArrSrc<EPL>{gx, gboff}, gnz, ARGMAX ? gneg : false, a, ny1, dy1);
+                        direct_cosine_sums<EPL, LPB, EMIT, LEAN>(cb, w, ArrSrc<EPL>{gx, gboff}, gnz, ARGMAX ? gneg : false, a, ny1, dy1);
                         best.ny = ny1;
                         best.dy = dy1;
                         raw = true;
