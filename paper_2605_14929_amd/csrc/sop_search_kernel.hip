@@ -662,6 +662,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // the direct cosine sums outside the grouped passes: in the form that keeps registers low for the six-atom variants only (the others
     // have registers left, and the form's scheduling fences cost the signed eight-atom search a sixth: 4096 x 4096, 77 us -> 92)
     constexpr bool LEAN = NA == 6;
+    // ranking sums in a pass of their own where eight atoms of 8-element lanes leave no registers for them in the one element pass (up to
+    // 17 spilled; argmax rule, metric MSE, fp32, 4096 x 4096, every plane: 157 us in one pass, 127 in two)
+    constexpr bool SPLIT_RANK = EMIT && EPL == 8 && NA == 8;
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
     // LDS: bin table | (scale, reciprocal) table | group parameters | reduction scratch
@@ -1271,10 +1274,20 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     const ArrSrc<EPL> src{gx, gboff};
                     Sums s;
                     if constexpr (!EMIT) s = eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
+                    else if constexpr (SPLIT_RANK) {
+                        if (p.codes) s = eval_residual<EPL, METRIC, true>(w, cb, src, gss, a, wide, codes);
+                        else s = eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
+                    }
                     else if (p.codes) s = p.blk_rank ? eval_residual<EPL, METRIC, true, false, true>(w, cb, src, gss, a, wide, codes) : eval_residual<EPL, METRIC, true>(w, cb, src, gss, a, wide, codes);
                     else s = p.blk_rank ? eval_residual<EPL, METRIC, false, false, true>(w, cb, src, gss, a, wide, codes) : eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
                     best = finish_residual<LPB, METRIC>(s, nsc);
-                    if (EMIT) { rk_num = group_sum<LPB>(s.rn); rk_dn = group_sum<LPB>(s.rd); }
+                    if constexpr (SPLIT_RANK) {
+                        if (p.blk_rank) {
+                            uint32_t nocodes[EPL / 4];
+                            const Cand c1 = finish_direct<LPB>(eval_direct<EPL, false, false>(w, cb, src, gss, a, false, nocodes));
+                            rk_num = c1.ny; rk_dn = c1.dy;
+                        }
+                    } else if (EMIT) { rk_num = group_sum<LPB>(s.rn); rk_dn = group_sum<LPB>(s.rd); }
                     // the residual form is accurate while the reconstruction carries a fair share of
                     // the block's norm; otherwise the whole wavefront recomputes this atom directly
                     if (__builtin_expect(__any(best.weak) != 0, 0)) {
