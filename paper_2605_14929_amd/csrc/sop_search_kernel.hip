@@ -1447,11 +1447,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 
 // ---- kernel table of this part ----
 namespace {
-// Wavefronts per SIMD each variant is built for: the largest number its register need allows without spilling (512 / occ
-// registers a lane).  The passes that evaluate a scale group's atoms together (16 elements a lane, positive scale, metrics WSE and
-// MSE) hold neither scaled weights nor table addresses and fit one wavefront more than the others: the headline layer
-// (4096 x 11008, six atoms) takes 72.6 us at four against 78.6 with the arrays at three, a 28672 x 8192 layer with seven atoms
-// 530 us at three against 640 at two.  fp32 weights keep 8 more registers of requested rows: one wavefront less where that is the difference.
+// Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling, or
+// one more where it measured better with a few spilled: the signed six-atom cosine search with bf16 weights (18 to 61 spilled:
+// 4096 x 4096, g = 16, 51.6 us at three, 57.3 at two; with fp32 weights, 65 spilled, 62.5 at three, 59.1 at two), and
+// every plane of eight atoms in 8-element lanes under the cosine metric (5 to 11 spilled).  The passes that
+// evaluate a scale group's atoms together (16 elements a lane, positive scale, metrics WSE and MSE) hold neither scaled weights
+// nor table addresses and fit one wavefront more than the others: the headline layer (4096 x 11008, six atoms) takes 75.7 us at
+// four against 78.4 with the arrays at three, a 28672 x 8192 layer with seven atoms 530 us at three against 640 at two.  fp32
+// weights keep 8 more registers of requested rows: one wavefront less where that is the difference.
 constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int metric)
 {
     if (epl == 8) {
@@ -1464,7 +1467,7 @@ constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int 
         return na == 2 || (na == 6 && bf16) ? 3 : 2;
     }
     if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : 3;
-    if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 ? 2 : 3);
+    if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 || (metric == 1 && !bf16)) ? 2 : 3;
     if (emit) return 2;
     return (na == 8 || metric == 1) ? 2 : 3;        // the cosine metric keeps two more sums per candidate alive
 }
