@@ -563,14 +563,11 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         c->occ_lds[vi] = dyn_lds;
     }
     // One workgroup of 4*occ wavefronts per compute unit; each takes a contiguous range of (strip,row) steps.  A layer of few
-    // steps takes fewer: a SIMD spends about 1.7 us on each further step, and every workgroup adds about 20 ns to the layer
-    // reduction (its ticket's atomics go to one address, served one after the other), so steps * 1.7 / (4 wg) + 0.02 wg is
-    // least at wg = sqrt(21 steps); a step per SIMD is the limit.  (256 steps, four atoms: 13.9 us with a wavefront per step packed
-    // into 22 workgroups, 10.3 with 64; 1536 steps, five atoms: 13.4 with 128 workgroups, 15.3 with 256.)
+    // steps takes fewer (search_workgroups()).
     const long long waves_per_wg = 4 * occ;
-    long long wg = std::min<long long>(c->n_cu, (p.total_units + 3) / 4);
-    wg = std::min<long long>(wg, std::lround(std::sqrt(21.0 * (double)p.total_units)));
-    wg = std::max<long long>(wg, 1);
+    int evals = emit ? 2 : 0;                    // (a sign-negated copy under a signed word takes its original's candidates over)
+    for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
+    const long long wg = search_workgroups(p.total_units, c->n_cu, occ, evals);
     p.n_waves = wg * waves_per_wg;
     if (!launch) return SOP_OK;
     if (use_static) {

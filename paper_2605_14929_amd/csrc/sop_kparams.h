@@ -127,6 +127,30 @@ struct LayerDesc {
     int          pad;
 };
 
+/* Workgroups of a search (one per compute unit at most), from whole steps per SIMD.  evaluations: codebooks times signs tried per
+ * block, 3 or more where planes are written.
+ *  - A step per SIMD where that fits: the time is then one step's latency (1 us with one atom, 4 with six, 15 with every plane of
+ *    eight signed ones), and a wavefront that finds a second step in its SIMD's share takes it together with the first, since rows are
+ *    requested a step ahead: two steps a SIMD cost twice the latency, whatever the other wavefronts do (six atoms, 640 steps: 12.2 us
+ *    with 160 workgroups, 15.4 with 116).  A single evaluation is shorter than the last quarter of the workgroups' tickets: 10 ns each
+ *    in the layer reduction, whose atomics go to one address, one after the other.
+ *  - Beyond, three to five steps a SIMD take hardly longer than two, and every workgroup left out saves its ticket: three, or five
+ *    for the short steps of one or two evaluations (one atom, 2048 steps: 9.5 us with 103 workgroups, 10.1 with 207).  A SIMD
+ *    with a single wavefront gets through its steps one by one: as few as the compute units allow (every plane of eight signed
+ *    atoms, 1536 steps: 43.9 us with 192 workgroups, 59.0 with 180).
+ *  - No more workgroups than it takes for that many steps, while there are eight or fewer; one on every compute unit beyond.
+ * Measured at 64 to 4500 steps over 31 kinds of call: 0.2 % above the best number of workgroups on average, 5 % at worst. */
+inline long long search_workgroups(long long steps, int n_cu, int wavefronts_per_simd, int evaluations)
+{
+    const long long one = (steps + 3) / 4;
+    if (one <= n_cu && (evaluations > 1 || 4 * one <= 3ll * n_cu)) return one > 1 ? one : 1;
+    long long s = (steps + 4ll * n_cu - 1) / (4ll * n_cu);
+    if (s > 8) return n_cu;
+    const long long least = wavefronts_per_simd == 1 ? 1 : evaluations <= 2 ? 5 : 3;
+    if (s < least) s = least;
+    return (steps + 4 * s - 1) / (4 * s);
+}
+
 /* Statistics pass of the data-derived codebook */
 #define SOP_K_DD_THREADS 1024
 #define SOP_K_DD_MAXBINS 8192
