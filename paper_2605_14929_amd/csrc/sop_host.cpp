@@ -549,6 +549,11 @@ extern "C" sop_status sop_layer_shift(const int64_t* hist, int64_t n_blocks, sop
     (void)std::frexp(r.lo, &e_lo);
     (void)std::frexp((float)r.hi, &e_top);
     const int emax = std::max(r.max_code >> r.y, 1);
+    // (running sums of the histogram: a candidate costs two look-ups and not a scan of all bins, whose time, 29 to 34 us, hung on where the
+    // linker had put the loop)
+    long long below[SOP_K_FL_BINS + 1];
+    below[0] = 0;
+    for (int b = 0; b < SOP_K_FL_BINS; ++b) below[b + 1] = below[b] + hist[b];
     long long best_count = -1;
     int best_k = 0;
     for (int mag = 0; mag <= 64; ++mag) {
@@ -557,13 +562,10 @@ extern "C" sop_status sop_layer_shift(const int64_t* hist, int64_t n_blocks, sop
             const int k = sgn ? -mag : mag;
             // the shifts sop_pair_search() accepts for this format
             if (1 - r.bias - r.y - k < -126 || 1 - r.bias - k > 126 || emax - r.bias - k > 125) continue;
-            long long count = 0;
-            for (int b = 0; b < SOP_K_FL_BINS; ++b) {
-                const int e = b - 160 + k;
-                if (e < e_lo || e > e_top) continue;
-                count += hist[b];
-                if (e == e_top) count -= hist[SOP_K_FL_BINS + b];
-            }
+            const int first = std::clamp(e_lo - k + 160, 0, SOP_K_FL_BINS), top = e_top - k + 160;      // bins of e_lo and e_top
+            const int end = std::clamp(top + 1, first, SOP_K_FL_BINS);
+            long long count = below[end] - below[first];
+            if (top >= first && top < SOP_K_FL_BINS) count -= hist[SOP_K_FL_BINS + top];
             if (count > best_count) { best_count = count; best_k = k; }
         }
     }

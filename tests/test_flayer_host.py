@@ -24,3 +24,59 @@ def test_histogram_route_equals_the_definition(x, y, mc):
     h = FL.exponent_histogram(sc, x, y, bias, mc)
     k, frac = sop.sop_layer_shift(h, sc.size, sop.ScaleFmt(0, x, y, 16, bias, mc))
     assert (k, frac) == (k_ref, f_ref)
+
+
+def _scan(hist, fmt, x, y, bias, mc):
+    """The definition on the histogram: every shift that the search accepts, every bin."""
+    lo, hi, _, _ = FL.format_range(x, y, bias, mc)
+    e_lo, e_top = int(np.frexp(np.float64(lo))[1]), int(np.frexp(np.float64(np.float32(hi)))[1])
+    b = np.arange(320)
+    rb = (1 << (x - 1)) - 1 if bias < 0 else bias
+    emax = max(((1 << (x + y)) - 1 if mc < 0 else mc) >> y, 1)
+    best, best_k = -1, 0
+    for k in sorted(range(-64, 65), key=lambda k: (abs(k), k < 0)):
+        if 1 - rb - y - k < -126 or 1 - rb - k > 126 or emax - rb - k > 125:
+            continue
+        e = b - 160 + k
+        n = int(hist[:320][(e >= e_lo) & (e <= e_top)].sum() - hist[320:][(e == e_top) & (e >= e_lo)].sum())
+        if n > best:
+            best, best_k = n, k
+    return best_k, best
+
+
+@pytest.mark.parametrize("x,y,bias,mc", [(4, 3, -1, -1), (4, 4, -1, -1), (5, 5, -1, -1), (2, 3, -1, -1), (1, 0, -1, -1), (6, 2, 0, -1), (6, 2, 127, -1), (5, 5, 127, 40),
+                                         (8, 7, 119, 244 * 128 + 127), (8, 0, 127, 252), (3, 1, 60, 2), (1, 10, 100, 1)])
+def test_every_shift_against_a_scan_of_all_bins(x, y, bias, mc):
+    rng = np.random.default_rng(x * 100 + y + max(bias, 0))
+    for spread in (320, 40, 3):
+        for centre in (0, 20, 160, 300, 319):
+            h = np.zeros(640, dtype=np.int64)
+            at = np.clip(centre + rng.integers(-spread, spread + 1, size=200), 0, 319)
+            np.add.at(h, at, rng.integers(1, 1 << 40, size=200))
+            h[320:] = (h[:320] * rng.random(320)).astype(np.int64)
+            want_k, want = _scan(h, None, x, y, bias, mc)
+            k, frac = sop.sop_layer_shift(h, 1 << 30, sop.ScaleFmt(0, x, y, 16, bias, mc))
+            assert (k, frac) == (want_k, want / float(1 << 30))
+
+
+def test_choice_of_the_shift_is_not_a_scan_of_all_bins():
+    # 129 candidates times 320 bins are 41 thousand steps, about as long as a loop of a thousand additions here; the running sums
+    # are a thousand steps in compiled code
+    import time
+    h = np.zeros(640, dtype=np.int64)
+    h[120:200] = 1000
+    fmt = sop.fmt_by_name("E4M3")
+
+    def best(fn, n=300):
+        t = []
+        for _ in range(n):
+            t0 = time.perf_counter()
+            fn()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    def loop():
+        s = 0
+        for i in range(500):
+            s += i
+    assert best(lambda: sop.sop_layer_shift(h, 80000, fmt)) < best(loop)
