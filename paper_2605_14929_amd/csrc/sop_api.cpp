@@ -565,9 +565,10 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     // One workgroup of 4*occ wavefronts per compute unit; each takes a contiguous range of (strip,row) steps.  A layer of few
     // steps takes fewer (search_workgroups()).
     const long long waves_per_wg = 4 * occ;
-    int evals = emit ? 2 : 0;                    // (a sign-negated copy under a signed word takes its original's candidates over)
+    int evals = 0;                               // (a sign-negated copy under a signed word takes its original's candidates over)
     for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
-    const long long wg = search_workgroups(p.total_units, c->n_cu, occ, evals);
+    const long long wg = search_workgroups(p.total_units, c->n_cu, emit ? 2 * evals : evals);
+    p.deal = p.total_units <= 4ll * SOP_K_SHORT_SHARE * c->n_cu ? 1u : 0u;
     p.n_waves = wg * waves_per_wg;
     if (!launch) return SOP_OK;
     if (use_static) {

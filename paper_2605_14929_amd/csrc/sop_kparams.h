@@ -77,6 +77,7 @@ struct KParams {
     float bin_lo[SOP_K_MAXA], bin_hi[SOP_K_MAXA];  // range of x the table covers (clamped path)
     unsigned int gid_w;                            // 4 bits per atom: its scale group (atoms of a group are adjacent)
     unsigned int second_mask;                      // bit a (a odd): atoms a-1 and a are of one scale group (search mode evaluates them together)
+    unsigned int deal;                             // 1: the shares are short (SOP_K_SHORT_SHARE), their wavefronts' first steps are dealt out
     unsigned int mirror_mask;                      // bit a: atom a is the sign-negated copy of atom a-1 (signed scale words take its candidates over)
     unsigned int selfsym_mask;                     // bit a: atom a is its own sign-negated copy
     alignas(8) unsigned char nent[SOP_K_MAXA];     // entries of the atom
@@ -127,28 +128,24 @@ struct LayerDesc {
     int          pad;
 };
 
-/* Workgroups of a search (one per compute unit at most), from whole steps per SIMD.  evaluations: codebooks times signs tried per
- * block, 3 or more where planes are written.
- *  - A step per SIMD where that fits: the time is then one step's latency (1 us with one atom, 4 with six, 15 with every plane of
- *    eight signed ones), and a wavefront that finds a second step in its SIMD's share takes it together with the first, since rows are
- *    requested a step ahead: two steps a SIMD cost twice the latency, whatever the other wavefronts do (six atoms, 640 steps: 12.2 us
- *    with 160 workgroups, 15.4 with 116).  A single evaluation is shorter than the last quarter of the workgroups' tickets: 10 ns each
- *    in the layer reduction, whose atomics go to one address, one after the other.
- *  - Beyond, three to five steps a SIMD take hardly longer than two, and every workgroup left out saves its ticket: three, or five
- *    for the short steps of one or two evaluations (one atom, 2048 steps: 9.5 us with 103 workgroups, 10.1 with 207).  A SIMD
- *    with a single wavefront gets through its steps one by one: as few as the compute units allow (every plane of eight signed
- *    atoms, 1536 steps: 43.9 us with 192 workgroups, 59.0 with 180).
- *  - No more workgroups than it takes for that many steps, while there are eight or fewer; one on every compute unit beyond.
- * Measured at 64 to 4500 steps over 31 kinds of call: 0.2 % above the best number of workgroups on average, 5 % at worst. */
-inline long long search_workgroups(long long steps, int n_cu, int wavefronts_per_simd, int evaluations)
+/* Workgroups of a search, one per compute unit at most, from whole steps per SIMD.  A step more on every SIMD costs about
+ * 0.3 us + 0.1 us per evaluation (evaluations: codebooks times signs tried, twice that where planes are written), a workgroup
+ * more 10 ns in the layer reduction (the tickets' atomics go to one address, one after the other).  Beyond SOP_K_SHORT_SHARE steps
+ * a SIMD every compute unit has a workgroup.  Measured at 64 to 4500 steps over 31 kinds of call against every number of
+ * workgroups that changes the steps per SIMD: 0.1 % above the best on average, 3 % at worst (one atom, 1024 steps: 8.5 us with
+ * 86 workgroups, 9.7 with 256; six atoms, 1536: 13.6 with 192, 14.3 with 128 or 256; every plane of six signed ones, 1536: 24.3 with
+ * 192, 33.7 with 128). */
+#define SOP_K_SHORT_SHARE 8
+inline long long search_workgroups(long long steps, int n_cu, int evaluations)
 {
-    const long long one = (steps + 3) / 4;
-    if (one <= n_cu && (evaluations > 1 || 4 * one <= 3ll * n_cu)) return one > 1 ? one : 1;
-    long long s = (steps + 4ll * n_cu - 1) / (4ll * n_cu);
-    if (s > 8) return n_cu;
-    const long long least = wavefronts_per_simd == 1 ? 1 : evaluations <= 2 ? 5 : 3;
-    if (s < least) s = least;
-    return (steps + 4 * s - 1) / (4 * s);
+    const long long least = (steps + 4ll * n_cu - 1) / (4ll * n_cu);
+    if (least > SOP_K_SHORT_SHARE) return n_cu;
+    long long best = 0, best_ns = 0;
+    for (long long s = least; s <= SOP_K_SHORT_SHARE; ++s) {
+        const long long wg = (steps + 4 * s - 1) / (4 * s), ns = s * (300 + 100 * evaluations) + 10 * wg;
+        if (best == 0 || ns < best_ns) { best = wg; best_ns = ns; }
+    }
+    return best;
 }
 
 /* Statistics pass of the data-derived codebook */

@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     if (i0 + j * NT < nt) s_tab[i0 + j * NT] = t[j];
             }
         }
-        if (threadIdx.x < 4) s_next[threadIdx.x] = 0u;
+        if (threadIdx.x < 4) s_next[threadIdx.x] = !MULTI && p.deal ? (unsigned int)OCC : 0u;
         for (int i = threadIdx.x; i < n_acc; i += NT) s_acc[i] = 0ull;
         // (static indices: a lane-dependent index into the kernel arguments would copy them to scratch memory)
 #pragma unroll
@@ -872,7 +872,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     float cb[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) cb[i] = 0.0f;
-    unsigned int i_cur = grab(), i_nxt = grab();
+    // Short shares: the first step of each wavefront is its own and the others come from the counter (all from the counter, the first
+    // two steps of a share went to its first wavefront, one after the other, while the others had none: six atoms, 1536 steps, 16.4 us
+    // -> 13.6).  Long ones take every step from the counter: wavefronts that start in step stay in step, and use the units by
+    // turns less well (six model layers of 2048 x 2048: 57 us -> 59 with the first steps dealt out).
+    unsigned int i_cur = !MULTI && p.deal ? (unsigned int)wv >> 2 : grab(), i_nxt = grab();
     RawBlk<BF16, EPL> nxt;
     bool ok_cur = seek(i_cur);
     int l_nxt = rq_l;                              // layer of the row in nxt

@@ -13,11 +13,10 @@ SRC = r"""
 int main()
 {
     for (int n_cu : {1, 38, 256})
-        for (int w = 1; w <= 4; ++w)
-            for (int e = 1; e < 4; ++e)
-                for (long long steps = 1; steps < 40000; steps += steps < 5000 ? 1 : 997)
-                    std::printf("%d %d %d %lld %lld\n", n_cu, w, e, steps, search_workgroups(steps, n_cu, w, e));
-    std::printf("256 4 3 %lld %lld\n", (1ll << 31) - 1, search_workgroups((1ll << 31) - 1, 256, 4, 3));
+        for (int e : {1, 2, 6, 16})
+            for (long long steps = 1; steps < 40000; steps += steps < 3000 ? 7 : 997)
+                std::printf("%d %d %lld %lld\n", n_cu, e, steps, search_workgroups(steps, n_cu, e));
+    std::printf("256 6 %lld %lld\n", (1ll << 31) - 1, search_workgroups((1ll << 31) - 1, 256, 6));
 }
 """
 
@@ -39,14 +38,21 @@ def _most(steps, wg):
 
 
 def test_grid_is_within_the_device(grid):
-    for n_cu, w, evals, steps, wg in grid:
+    for n_cu, evals, steps, wg in grid:
         assert 1 <= wg <= n_cu
 
 
-def test_steps_per_simd(grid):
-    for n_cu, w, evals, steps, wg in grid:
-        best = _most(steps, n_cu)
-        if w == 1 and evals > 1 or best > 8 or best == 1 and (evals > 1 or wg == -(-steps // 4)):
-            assert _most(steps, wg) == best                   # as few as the device allows
-        else:
-            assert _most(steps, wg) <= max(best, 5 if evals <= 2 else 3)
+def test_grid_is_the_cheapest_of_all(grid):
+    for n_cu, evals, steps, wg in grid:
+        least = _most(steps, n_cu)
+        if least > 8:
+            assert wg == n_cu
+            continue
+        cost = lambda w: _most(steps, w) * (300 + 100 * evals) + 10 * w
+        assert cost(wg) <= min(cost(w) for w in range(1, n_cu + 1) if _most(steps, w) <= 8)
+
+
+def test_wavefronts_of_dear_steps_get_one_each_where_they_can(grid):
+    for n_cu, evals, steps, wg in grid:
+        if evals == 16 and steps <= 4 * n_cu:
+            assert _most(steps, wg) == 1
