@@ -76,7 +76,8 @@ struct KParams {
     float bin_sc[SOP_K_MAXA], bin_off[SOP_K_MAXA]; // bin = bits(fma(x, sc, off)) - bits(magic)
     float bin_lo[SOP_K_MAXA], bin_hi[SOP_K_MAXA];  // range of x the table covers (clamped path)
     unsigned int gid_w;                            // 4 bits per atom: its scale group (atoms of a group are adjacent)
-    unsigned int second_mask;                      // bit a (a odd): atoms a-1 and a are of one scale group (search mode evaluates them together)
+    unsigned int second_mask;                      // odd bit a: atoms a-1 and a are of one scale group (evaluated together, also where planes but no codes
+                                                   // are written); bits 2 and 6: atoms 0..3 and 4..7 are (evaluated together in search mode)
     unsigned int deal;                             // 1: the shares are short (SOP_K_SHORT_SHARE), their wavefronts' first steps are dealt out
     unsigned int mirror_mask;                      // bit a: atom a is the sign-negated copy of atom a-1 (signed scale words take its candidates over)
     unsigned int selfsym_mask;                     // bit a: atom a is its own sign-negated copy

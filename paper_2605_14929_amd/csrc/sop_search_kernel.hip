@@ -658,7 +658,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 {
     static_assert(!MULTI || !EMIT, "the model-wide kernel searches only");
     constexpr bool SIGNED = SIGNMODE == 1, ARGMAX = SIGNMODE == 2;
-    constexpr bool GROUPED = SIGNMODE == 0 && METRIC != 1 && EPL == 16;   // atoms of a scale group are evaluated two at a time
+    constexpr bool GROUPED = SIGNMODE == 0 && METRIC != 1 && EPL == 16;   // atoms of a scale group are evaluated four or two at a time
     // the direct cosine sums outside the grouped passes: in the form that keeps registers low for the variants that are short of them
     // (the others have some left, and the form's scheduling fences cost the signed eight-atom search a sixth: 4096 x 4096, 77 us
     // -> 92; the signed one-atom search with every plane, g = 32, takes 33.4 us with it and 35.0 without)

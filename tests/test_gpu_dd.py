@@ -220,3 +220,30 @@ def test_time_does_not_depend_on_the_spread_of_the_norms(H):
             best = min(best, e0.elapsed_time(e1))
         t[sigma] = best
     assert max(t.values()) < 2.0 * t[1.0], t
+
+
+@pytest.mark.parametrize("Ms,K", [(129, 1040), (255, 3072), (300, 5024), (1531, 3072), (4097, 16384)])
+@pytest.mark.parametrize("form", ["plain", "row_step", "mask", "levels"])
+def test_bands_of_rows_with_a_short_last_one(Ms, K, form):
+    """Layers of full bands of 128 rows and a shorter one, several strips a row: wavefronts that begin and end anywhere in them,
+    with one step each, with several, and (the last size) with enough for 32-bit counts."""
+    import torch
+    g, H, bf16 = 16, 1024, K != 3072
+    step = 3 if form == "row_step" else 1
+    M = Ms * step - (step - 1)                                        # Ms sampled rows
+    W = si.student_t_weights(M, K, 4.0, 960 + Ms, row_sigma=0.5)
+    if bf16:
+        W = si.bf16_round(W)
+    c = si.channel_norms(K, 1.0, 961)
+    rng = np.random.default_rng(962 + Ms)
+    if form == "mask":
+        mask = (rng.random(M * K // g) < 0.4).astype(np.uint8)
+        assert np.array_equal(gpu_hist(W, c, g, H, bf16, mask=mask), DD.histogram(W, c, g, H, block_mask=mask))
+    elif form == "levels":
+        lv = rng.integers(0, 4, M * K // g).astype(np.uint8)
+        Wt = torch.from_numpy(W).cuda()
+        h = ctx().dd_histogram_levels(Wt.to(torch.bfloat16) if bf16 else Wt, torch.from_numpy(c).cuda(), g, torch.from_numpy(lv).cuda(), 3, H).cpu().numpy()
+        for j in range(3):
+            assert np.array_equal(h[j], DD.histogram(W, c, g, H, block_mask=(lv > j).astype(np.uint8)))
+    else:
+        assert np.array_equal(gpu_hist(W, c, g, H, bf16, row_step=step), DD.histogram(W[::step], c, g, H))
