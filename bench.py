@@ -236,7 +236,7 @@ def bench_dd(args):
         "roofline": {"bound": "hbm", "achieved": alg_bytes / (ev_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": alg_bytes / (ev_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
                      "algorithmic_bytes_per_launch": alg_bytes, "kernel": "sopk::dd_hist_kernel", "event_ms_per_launch": ev_ms,
-                     "note": "the pass is held back by LDS atomic throughput (one 64-bit LDS atomic per weight), not by HBM"},
+                     "note": "the pass is held back by LDS atomic throughput (one LDS atomic per weight), not by HBM"},
     }
     if not args.no_cpu_baseline:
         from oracle import dd as DD
