@@ -495,6 +495,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     // code planes are laid out in the caller's atom order
     long long plane_off[SOP_K_MAXA], off = 0;
     for (int a = 0; a < A; ++a) { plane_off[a] = off; off += c->tables[a].size() <= 16 ? Mu * Ku / 2 : Mu * Ku; }
+    const int na_class = A > 6 ? 2 : (A > 2 ? 1 : 0), na = na_class == 2 ? 8 : na_class == 1 ? 6 : 2;      // the atoms the variant is unrolled for
     int internal_of[SOP_K_MAXA];
     for (int i = 0; i < A; ++i) {
         p.tpos[i] = c->tpos[i]; p.tneg[i] = c->tneg[i]; p.bin_sc[i] = c->bin_sc[i]; p.bin_off[i] = c->bin_off[i];
@@ -518,7 +519,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         p.pair_mask |= 1u << pi;
         if (ia > ib) { p.flip_mask |= 1u << pi; p.flip_slots |= 1u << q; }
         p.pair_slot_w[pi / 4] |= (unsigned)q << (8 * (pi % 4));
-        p.pair_pi[q] = (unsigned char)pi;
+        p.pair_col[q] = (unsigned char)(na + i * (2 * na - i - 1) / 2 + (j - i - 1));
     }
     p.sums = use_static ? reinterpret_cast<unsigned long long*>(c->static_scratch) : c->d_sums + (size_t)sums_set * kSumsWords;
     p.done = reinterpret_cast<unsigned int*>(p.sums + SOP_K_REPL * SOP_K_NCOL);
@@ -540,13 +541,12 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         p.stab = t.dev;
         p.n_tab_codes = t.n;
     }
-    const int na_class = A > 6 ? 2 : (A > 2 ? 1 : 0);
     const int sign_mode = c->scale_rule == 1 ? 2 : w;
     int occ = 1, mode = 0;
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
     const size_t dyn_lds = (((size_t)p.n_bins * SOP_K_BIN_BYTES + 15) & ~(size_t)15) + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15) +
-                           2 * SOP_K_MAXA * sizeof(float4) + (1 + 2 * SOP_K_NCOL) * sizeof(unsigned long long);
+                           2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_NCOL + search_slots(na)) * sizeof(unsigned long long);
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds;
     hipError_t e = hipSuccess;
@@ -657,7 +657,7 @@ extern "C" sop_status sop_pair_search_layers(sop_ctx* c, const sop_layer* layers
         int occ = 1, mode = 0;
         const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, 0, na_class, 2, &occ, &mode);
         const size_t lds0 = by_shift.begin()->second.second;          // (the same for every shift: table sizes do not depend on it)
-        const size_t per_layer = SOP_K_NCOL * sizeof(unsigned long long), slack = 256;     // (the kernel's few static words)
+        const size_t per_layer = search_slots(na_class == 2 ? 8 : na_class == 1 ? 6 : 2) * sizeof(unsigned long long), slack = 256;     // (the kernel's few static words)
         const long long room = c->lds_max > lds0 + slack ? (long long)((c->lds_max - lds0 - slack) / per_layer) : 0;
         const int chunk = (int)std::min<long long>(kMaxLayers, room);
         if (mode == 2 && chunk >= 2) {

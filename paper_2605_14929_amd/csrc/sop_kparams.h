@@ -6,7 +6,7 @@
 #define SOP_K_MAXA 8                 /* atoms                                        */
 #define SOP_K_MAXP 28                /* pairs i < j among SOP_K_MAXA atoms           */
 #define SOP_K_NCOL (SOP_K_MAXA + SOP_K_MAXP + 1)   /* sum columns: atoms, pairs, zero-norm lane count */
-#define SOP_K_ZCOL (SOP_K_MAXA + SOP_K_MAXP)
+#define SOP_K_FLUSH_STEPS 60         /* steps a lane's running sums are kept before they join the workgroup's (4 * 60 * 2^23 < 2^31) */
 #define SOP_K_REPL 8                 /* replicas of the layer sums (spreads same-address atomics) */
 #define SOP_K_MAXBINS 1024           /* bins of the element-search table                        */
 #define SOP_K_MAXTABCODES 2048       /* scale codes whose (scale, reciprocal) pair is tabulated */
@@ -31,6 +31,11 @@ struct float2 { float x, y; };       /* (host-only translation units see the lau
 
 /* position of (i,j), i < j, in the lexicographic list of all pairs of SOP_K_MAXA atoms */
 SOP_K_HD constexpr int pair_index(int i, int j) { return i * (2 * SOP_K_MAXA - i - 1) / 2 + (j - i - 1); }
+
+/* Sum columns of a variant unrolled for na atoms: atoms, pairs i < j of them (lexicographic), count of zero-norm lanes; and the same
+ * rounded up to the four columns that a wavefront adds up together */
+SOP_K_HD constexpr int search_cols(int na) { return na + na * (na - 1) / 2 + 1; }
+SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 * 4; }
 
 /* One bin of the element-search table.  For every atom the bin holds at most one code boundary.
  * The two values are stored HALVED (exactly; the element passes multiply by twice the block scale): the boundary
@@ -91,7 +96,7 @@ struct KParams {
     unsigned int flip_slots;                          // bit q: output pair q is such a swapped pair
     // (byte arrays sit on 8-byte boundaries so that the kernels fetch them with scalar loads)
     unsigned int pair_slot_w[SOP_K_MAXP / 4];          // byte pi%4 of word pi/4: output index of pair pi = pair_index(i,j)
-    alignas(8) unsigned char pair_pi[SOP_K_MAXP + 4];  // pair_index(i,j) of output o
+    alignas(8) unsigned char pair_col[SOP_K_MAXP + 4]; // sum column of output pair o (in the variant's own numbering, see search_cols)
     // outputs
     // layer sums of 1-cos in fixed point (2^-22 units): every workgroup adds its share with integer
     // atomics (order-independent, so the result is reproducible); the workgroup that finishes last

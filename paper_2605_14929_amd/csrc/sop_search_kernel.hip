@@ -449,6 +449,9 @@ __device__ __forceinline__ Sums eval_direct(const float (&w)[EPL], const float (
             }
             put_code<EPL, CODES>(codes, i, (uint32_t)r[j].clo + (up ? 1u : 0u), wide_codes);
         }
+        // (a register budget, not an order: with the chunks apart the signed six-atom search keeps 139 registers, without 168 and up to 60 spilled;
+        // every plane of eight atoms of 8-element lanes 162 to 167, without 168 and up to 12 spilled)
+        if constexpr ((TIES && !CODES && EPL == 16) || (EPL == 8 && CODES)) asm volatile("" : "+v"(n0), "+v"(n1), "+v"(d0), "+v"(d1));
     }
     Sums s;
     s.err = EPL == 16 ? e0 + e1 : e0;
@@ -675,8 +678,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     float4* s_gpar = reinterpret_cast<float4*>(s_mem + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
     // reduction scratch: flag word, the final gather's totals, the workgroup's own totals (64-bit integers)
     unsigned long long* s_red = reinterpret_cast<unsigned long long*>(s_gpar + 2 * SOP_K_MAXA);
-    unsigned long long* s_acc = s_red + 1 + SOP_K_NCOL;                           // [SOP_K_NCOL] this workgroup's sums (MULTI: per layer)
-    const int n_acc = MULTI ? p.n_layers * SOP_K_NCOL : SOP_K_NCOL;
+    constexpr int NLIVE = search_cols(NA), NSLOT = search_slots(NA);              // sum columns of this variant: atoms, pairs, count column
+    unsigned long long* s_acc = s_red + 1 + SOP_K_NCOL;                           // [NSLOT] this workgroup's sums (MULTI: per layer)
+    const int n_acc = MULTI ? p.n_layers * NSLOT : NSLOT;
     __shared__ unsigned int s_next[4];                                            // next step of each SIMD's share
     {
         // 16 bytes per lane and four loads in flight before the first LDS write: a loop of one load, wait,
@@ -803,12 +807,17 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     for (int i = 0; i < SOP_K_MAXA; ++i) acca[i] = 0;
 #pragma unroll
     for (int i = 0; i < SOP_K_MAXP; ++i) accp[i] = 0;
-    // Lane sums of a column, exact.  A row of 16 lanes is added up with data-parallel-primitive moves on the
-    // vector ALU (quads, half rows, rows: every lane of the row then holds the row's sum), and the first lane
-    // of each row adds its row's sum to the workgroup's 64-bit sum in LDS: four lanes to one word per column.
-    // (This translation unit is compiled
-    // with the compiler's atomic optimizer off: it would turn each of these adds into a loop over the
-    // active lanes.)
+    // Lane sums of every column, exact.  Four columns at a time: exchanges of half and quarter wavefronts (gfx950's lane swaps)
+    // leave one column's sums over four lanes in each row of 16 lanes, the row is added up with data-parallel-primitive moves
+    // (quads, half rows, rows: every lane of the row then holds the column's sum), and the first lane of each row adds it to
+    // the workgroup's 64-bit sum in LDS: one add of four lanes to four different words for four columns.  (Rows summed for every
+    // column on its own, four lanes to one word: 88 moves and 22 adds for six atoms against 66 and 6, and the adds of four lanes to
+    // one word are served one after the other, with every wavefront's.)
+    // Range: a step adds at most 2^23 to a lane, so SOP_K_FLUSH_STEPS = 60 steps of four lanes stay below 2^31; the sum is split
+    // at bit 15 and both halves are added over the row (below 2^19 and 2^20), then joined in 64 bits.  A lane's sum can be a few units below
+    // zero: all of it is signed.
+    // (This translation unit is compiled with the compiler's atomic optimizer off: it would turn each of these adds into a
+    // loop over the active lanes.)
     auto row_sum = [](int x) -> int {
         x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
         x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);      // quad_perm [2,3,0,1]
@@ -816,49 +825,29 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, false);     // row_mirror
         return x;
     };
+    // a's sums of lanes l and l + 32 in the lower half, b's in the upper half; the same with rows 0, 1 and 2, 3
+    auto fold_halves = [](int a, int b) -> int { const auto t = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false); return (int)(t[0] + t[1]); };
+    auto fold_rows = [](int a, int b) -> int { const auto t = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false); return (int)(t[0] + t[1]); };
     int cl = MULTI ? -1 : 0;                       // the layer the arithmetic is in
-    // few: the lanes hold at most 15 steps (a wavefront's share of a layer of a few thousand rows: the rule at
-    // a change of layer in the model-wide kernel, and at the end of a single call on such a layer).  Then a
-    // lane holds at most 15 * 2^23 and a row of 16 lanes less than 2^31: one 32-bit pass per column.  In
-    // general a lane holds at most 128 steps x 2^23 < 2^31: the value is split at bit 15 and both halves are
-    // added over the row (below 2^19 and 2^20), then joined in 64 bits.
-    auto flush = [&](int layer, bool few) {
-        const int c0 = MULTI ? layer * SOP_K_NCOL : 0;
-        const bool row_lead = (lane & 15) == 0;
-        constexpr int NCOLS = SOP_K_MAXA + SOP_K_MAXP + 1;
-        int col_of[NCOLS], val[NCOLS], n = 0;        // the live columns of this variant (compile-time list)
+    auto flush = [&](int layer) {
+        int fl = lane;
+        asm volatile("" : "+v"(fl));                 // (the address is formed here, not kept in a register through the row loop)
+        unsigned long long* dst = s_acc + (MULTI ? layer * NSLOT : 0) + (fl >> 4);
+        int val[NSLOT], n = 0;                       // the live columns of this variant (compile-time list)
 #pragma unroll
-        for (int i = 0; i < NA; ++i) { col_of[n] = i; val[n] = acca[i]; acca[i] = 0; ++n; }
+        for (int i = 0; i < NA; ++i) { val[n++] = acca[i]; acca[i] = 0; }
 #pragma unroll
         for (int i = 0; i < SOP_K_MAXP; ++i)
-            if (kPairTab.second[i] < NA) { col_of[n] = SOP_K_MAXA + i; val[n] = accp[i]; accp[i] = 0; ++n; }
-        col_of[n] = SOP_K_ZCOL; val[n] = accz << 22; accz = 0; ++n;
-        // four columns at a time: their chains of moves are independent and fill each other's wait states,
-        // and few values are live at once
-        constexpr int B = 4;
-        if (few) {
+            if (kPairTab.second[i] < NA) { val[n++] = accp[i]; accp[i] = 0; }
+        val[n++] = accz << 22; accz = 0;
 #pragma unroll
-            for (int j0 = 0; j0 < NCOLS; j0 += B) {
-                int rs[B];
+        for (int i = NLIVE; i < NSLOT; ++i) val[i] = 0;
 #pragma unroll
-                for (int j = 0; j < B; ++j) if (j0 + j < n) rs[j] = row_sum(val[j0 + j]);
-                if (row_lead) {
-#pragma unroll
-                    for (int j = 0; j < B; ++j) if (j0 + j < n) atomicAdd(&s_acc[c0 + col_of[j0 + j]], (unsigned long long)(long long)rs[j]);   // (a lane's sum can be a few units below zero: sign-extended)
-                }
-            }
-            return;
-        }
-#pragma unroll
-        for (int j0 = 0; j0 < NCOLS; j0 += B) {
-            int rl[B], rh[B];
-#pragma unroll
-            for (int j = 0; j < B; ++j) if (j0 + j < n) { rl[j] = row_sum(val[j0 + j] & 0x7FFF); rh[j] = row_sum(val[j0 + j] >> 15); }
-            if (row_lead) {
-#pragma unroll
-                for (int j = 0; j < B; ++j)
-                    if (j0 + j < n) atomicAdd(&s_acc[c0 + col_of[j0 + j]], (unsigned long long)(((long long)rh[j] << 15) + (long long)rl[j]));
-            }
+        for (int j = 0; j < NSLOT; j += 4) {
+            // (row r of the result holds column j + r)
+            const int t = fold_rows(fold_halves(val[j], val[j + 2]), fold_halves(val[j + 1], val[j + 3]));
+            const int rl = row_sum(t & 0x7FFF), rh = row_sum(t >> 15);
+            if ((fl & 15) == 0) atomicAdd(dst + j, (unsigned long long)(((long long)rh << 15) + (long long)rl));
         }
     };
     // what the arithmetic needs of its layer
@@ -902,7 +891,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     float4 t = c0 < lc_K ? *reinterpret_cast<const float4*>(lc_c + (unsigned int)c0 % lc_Kc + i) : make_float4(0.f, 0.f, 0.f, 0.f);
                     cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
                 }
-                if (left >= 0) flush(left, since_flush <= 15);
+                if (left >= 0) flush(left);
                 since_flush = 0;
             }
         }
@@ -917,10 +906,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         const bool valid = (unsigned int)lane < lanes_of(cs, MULTI ? lc_K : p.K);
         if (cs != cur_strip) {
             cur_strip = cs;
+            // (rows may have been folded, see KParams::Kc: the channel of a column is its index modulo the true row length; hidden from the
+            // compiler, which would keep the division's reciprocal in a vector register through the loop)
+            unsigned int kc = MULTI ? lc_Kc : (unsigned int)p.Kc;
+            asm volatile("" : "+s"(kc));
+            const unsigned int ch0 = (unsigned int)col0 % kc;
 #pragma unroll
             for (int i = 0; i < EPL; i += 4) {
-                // (rows may have been folded, see KParams::Kc: the channel of a column is its index modulo the true row length)
-                float4 t = valid ? *reinterpret_cast<const float4*>((MULTI ? lc_c : p.c) + (unsigned int)col0 % (MULTI ? lc_Kc : (unsigned int)p.Kc) + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+                float4 t = valid ? *reinterpret_cast<const float4*>((MULTI ? lc_c : p.c) + ch0 + i) : make_float4(0.f, 0.f, 0.f, 0.f);
                 cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
             }
         }
@@ -1344,11 +1337,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         i_cur = i_nxt;
         ok_cur = ok_nxt;
         i_nxt = i_nn;
-        if (++since_flush == 128) { flush(cl, false); since_flush = 0; }   // a step adds at most 2^23: a lane's sums stay below 2^31
+        if (++since_flush == SOP_K_FLUSH_STEPS) { flush(cl); since_flush = 0; }
     }
 
     // ---- per-workgroup sums: what the lanes still hold joins the workgroup's integer sums in LDS ----
-    if (!MULTI || cl >= 0) flush(cl, since_flush <= 15);      // (since_flush: steps since the last flush)
+    if (!MULTI || cl >= 0) flush(cl);
     __syncthreads();
     if constexpr (MULTI) {
         // every layer's sums of this workgroup join the layer's replica; eight adds of a thread are in
@@ -1361,14 +1354,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 before[j] = 0ull;
                 if (idx < n_acc) {
                     const unsigned long long v = s_acc[idx];
-                    const int layer = idx / SOP_K_NCOL, col = idx - layer * SOP_K_NCOL;
+                    const int layer = idx / NSLOT, col = idx - layer * NSLOT;
                     if (v != 0ull) before[j] = atomicAdd(p.sums + ((size_t)layer * SOP_K_REPL + blockIdx.x % SOP_K_REPL) * SOP_K_NCOL + col, v);
                 }
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) asm volatile("" :: "v"(before[j]) : "memory");
         }
-    } else if ((int)threadIdx.x < SOP_K_NCOL) {
+    } else if ((int)threadIdx.x < NLIVE) {
         const int i = threadIdx.x;
         const unsigned long long v = s_acc[i];
         if (v != 0ull) {
@@ -1398,7 +1391,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             // (the exchanges leave zeros for the next call), then one ACos per (layer, atom or pair)
             __syncthreads();
             for (int idx = threadIdx.x; idx < n_acc; idx += NT) {
-                const int layer = idx / SOP_K_NCOL, col = idx - layer * SOP_K_NCOL;
+                const int layer = idx / NSLOT, col = idx - layer * NSLOT;
+                if (col >= NLIVE) continue;
                 unsigned long long* src = p.sums + (size_t)layer * SOP_K_REPL * SOP_K_NCOL + col;
                 unsigned long long part[SOP_K_REPL];
 #pragma unroll
@@ -1416,9 +1410,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 double* dst;
                 const size_t row = (size_t)p.layers[layer].out_row;
                 if (q < p.A) { col = q; dst = p.acos_atom ? p.acos_atom + row * p.A + p.uidx[q] : nullptr; }
-                else { col = SOP_K_MAXA + p.pair_pi[q - p.A]; dst = p.acos_pair ? p.acos_pair + row * p.P + (q - p.A) : nullptr; }
-                const long long z = (long long)s_acc[layer * SOP_K_NCOL + SOP_K_ZCOL];
-                const long long t = (long long)s_acc[layer * SOP_K_NCOL + col];
+                else { col = p.pair_col[q - p.A]; dst = p.acos_pair ? p.acos_pair + row * p.P + (q - p.A) : nullptr; }
+                const long long z = (long long)s_acc[layer * NSLOT + NLIVE - 1];
+                const long long t = (long long)s_acc[layer * NSLOT + col];
                 if (dst) *dst = 1.0 - ((double)(t - z) * (1.0 / 4194304.0)) / ((double)p.layers[layer].Nb * (double)p.lpb);
             }
         }
@@ -1435,13 +1429,13 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         __syncthreads();
         // lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1
         // to every column; the count column takes them out again
-        const long long z = (long long)s_tot[SOP_K_ZCOL];
+        const long long z = (long long)s_tot[NLIVE - 1];
         const int o = threadIdx.x;                 // 0..A-1 atoms (internal order), then pairs by output index
         if (o < p.A + p.P) {
             int col;
             double* dst;
             if (o < p.A) { col = o; dst = p.acos_atom ? p.acos_atom + p.uidx[o] : nullptr; }
-            else { col = SOP_K_MAXA + p.pair_pi[o - p.A]; dst = p.acos_pair ? p.acos_pair + (o - p.A) : nullptr; }
+            else { col = p.pair_col[o - p.A]; dst = p.acos_pair ? p.acos_pair + (o - p.A) : nullptr; }
             const long long t = (long long)s_tot[col];
             if (dst) *dst = 1.0 - ((double)(t - z) * (1.0 / 4194304.0)) / ((double)p.Nb * (double)p.lpb);
         }
@@ -1452,10 +1446,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 
 // ---- kernel table of this part ----
 namespace {
-// Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling, or
-// one more where it measured better with a few spilled: the signed six-atom cosine search with bf16 weights (18 to 61 spilled:
-// 4096 x 4096, g = 16, 51.6 us at three, 57.3 at two; with fp32 weights, 65 spilled, 62.5 at three, 59.1 at two), and
-// every plane of eight atoms in 8-element lanes under the cosine metric (5 to 11 spilled).  The passes that
+// Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling (the
+// signed cosine search, with its chunks of look-ups kept apart, at three: 4096 x 4096, six atoms, g = 16, bf16, 47.8 us against 51.6
+// with 18 to 61 registers spilled, fp32 52.8 at three against 59.5 at two, eight atoms 67.6 against 76.8).  The passes that
 // evaluate a scale group's atoms together (16 elements a lane, positive scale, metrics WSE and MSE) hold neither scaled weights
 // nor table addresses and fit one wavefront more than the others: the headline layer (4096 x 11008, six atoms) takes 75.7 us at
 // four against 78.4 with the arrays at three, a 28672 x 8192 layer with seven atoms 530 us at three against 640 at two.  fp32
@@ -1472,7 +1465,7 @@ constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int 
         return na == 2 || (na == 6 && bf16) ? 3 : 2;
     }
     if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : 3;
-    if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 || (metric == 1 && !bf16)) ? 2 : 3;
+    if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 && metric != 1) ? 2 : 3;
     if (emit) return 2;
     return (na == 8 || metric == 1) ? 2 : 3;        // the cosine metric keeps two more sums per candidate alive
 }
