@@ -427,6 +427,9 @@ static sop_status scale_table(sop_ctx* c, int x, int y, int bias, int max_code, 
     return SOP_OK;
 }
 
+// ceil(2^32 / n) for a launch of n workgroups (KParams::grid_magic): floor(a b / n) for a, b <= n < 2^10
+static unsigned int grid_magic(long long n) { return n == 1 ? 0xFFFFFFFFu : (unsigned int)(((1ull << 32) + (unsigned long long)n - 1) / (unsigned long long)n); }
+
 // launch == false: validate everything and prepare the tables the call needs, but launch nothing
 static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, int64_t M, int64_t K, int64_t ldw,
                                    const float* cn, int g, sop_scale_fmt fmt, int k, sop_metric metric,
@@ -498,8 +501,8 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     const int na_class = A > 6 ? 2 : (A > 2 ? 1 : 0), na = na_class == 2 ? 8 : na_class == 1 ? 6 : 2;      // the atoms the variant is unrolled for
     int internal_of[SOP_K_MAXA];
     for (int i = 0; i < A; ++i) {
-        p.tpos[i] = c->tpos[i]; p.tneg[i] = c->tneg[i]; p.bin_sc[i] = c->bin_sc[i]; p.bin_off[i] = c->bin_off[i];
-        p.bin_lo[i] = c->bin_lo[i]; p.bin_hi[i] = c->bin_hi[i];
+        const float gpar[8] = {c->tpos[i], c->tneg[i], c->bin_sc[i], c->bin_off[i], c->bin_lo[i], c->bin_hi[i], 0.0f, 0.0f};
+        std::memcpy(p.gpar[i], gpar, sizeof(gpar));
         p.gid_w |= (unsigned)c->gid[i] << (4 * i);
         if ((i & 1) && c->gid[i] == c->gid[i - 1]) p.second_mask |= 1u << i;
         if ((i & 3) == 3 && c->gid[i] == c->gid[i - 1] && c->gid[i] == c->gid[i - 2] && c->gid[i] == c->gid[i - 3]) p.second_mask |= 1u << (i - 1);
@@ -564,12 +567,12 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     }
     // One workgroup of 4*occ wavefronts per compute unit; each takes a contiguous range of (strip,row) steps.  A layer of few
     // steps takes fewer (search_workgroups()).
-    const long long waves_per_wg = 4 * occ;
     int evals = 0;                               // (a sign-negated copy under a signed word takes its original's candidates over)
     for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
     const long long wg = search_workgroups(p.total_units, c->n_cu, emit ? 2 * evals : evals);
     p.deal = p.total_units <= 4ll * SOP_K_SHORT_SHARE * c->n_cu ? 1u : 0u;
-    p.n_waves = wg * waves_per_wg;
+    p.units_q = (unsigned int)(p.total_units / wg); p.units_r = (unsigned int)(p.total_units % wg);
+    p.grid_magic = grid_magic(wg);
     if (!launch) return SOP_OK;
     if (use_static) {
         const int n_words = (int)kSumsWords, n_thr = std::max(n_words, p.n_tab_codes);
@@ -686,8 +689,9 @@ extern "C" sop_status sop_pair_search_layers(sop_ctx* c, const sop_layer* layers
                         d.out_row = l;
                         d.M32 = (unsigned int)Mf;
                         d.m_magic = Mf == 1 ? 0xFFFFFFFFu : (unsigned int)((1ull << 32) / (unsigned long long)Mf);
-                        d.K = (int)Kf; d.Kc = (int)L.K; d.pad = 0;
-                        d.total_units = (unsigned int)(((Kf / epl + 63) / 64) * Mf);
+                        d.K = (int)Kf; d.Kc = (int)L.K;
+                        const long long units = ((Kf / epl + 63) / 64) * Mf;
+                        d.units_q = (unsigned int)(units / c->n_cu); d.units_r = (unsigned int)(units % c->n_cu);
                     }
                     if ((e = hipMemcpyAsync(c->d_ldesc, h, sizeof(LayerDesc) * n, hipMemcpyHostToDevice, (hipStream_t)stream)) != hipSuccess ||
                         (e = hipEventRecord(c->ldesc_copied[turn], (hipStream_t)stream)) != hipSuccess)
@@ -697,6 +701,7 @@ extern "C" sop_status sop_pair_search_layers(sop_ctx* c, const sop_layer* layers
                     p.W = nullptr; p.c = nullptr; p.sel_words = nullptr;
                     p.layers = c->d_ldesc;
                     p.n_layers = n;
+                    p.grid_magic = grid_magic(c->n_cu);
                     p.sums = c->d_msums;
                     p.done = reinterpret_cast<unsigned int*>(c->d_msums + (size_t)kMaxLayers * SOP_K_REPL * SOP_K_NCOL);
                     p.acos_pair = c->n_pairs > 0 ? acos_pair_table : nullptr;

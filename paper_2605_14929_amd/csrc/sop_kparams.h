@@ -67,7 +67,8 @@ struct KParams {
     long long Nb;                    // blocks in the layer
     long long strips;                // 64-lane strips per row
     long long total_units;           // strips * M
-    long long n_waves;               // wavefronts launched (multiple of 4)
+    unsigned int units_q, units_r;   // total_units = units_q * workgroups + units_r
+    unsigned int grid_magic;         // ceil(2^32 / workgroups) (2^32 - 1 for one): a product of two numbers up to the workgroups, divided by them
     unsigned int M32, m_magic;       // M, and floor(2^32 / M) (2^32 - 1 for M = 1): step number -> (strip, row)
     int A, P, lpb;
     int n_bins;
@@ -77,9 +78,8 @@ struct KParams {
     float pow2k;                     // 2^k
     float sub_quantum;               // 2^(1-bias-man_bits-k)
     // atoms, internal order
-    float tpos[SOP_K_MAXA], tneg[SOP_K_MAXA];      // t+ and -t-
-    float bin_sc[SOP_K_MAXA], bin_off[SOP_K_MAXA]; // bin = bits(fma(x, sc, off)) - bits(magic)
-    float bin_lo[SOP_K_MAXA], bin_hi[SOP_K_MAXA];  // range of x the table covers (clamped path)
+    alignas(16) float gpar[SOP_K_MAXA][8];         // t+, -t-, bin scale and offset (bin = bits(fma(x, sc, off)) - bits(magic)), range of x the table covers
+                                                   // (clamped path, low and high), 0, 0: two 16-byte words an atom, copied to LDS as they are
     unsigned int gid_w;                            // 4 bits per atom: its scale group (atoms of a group are adjacent)
     unsigned int second_mask;                      // odd bit a: atoms a-1 and a are of one scale group (evaluated together, also where planes but no codes
                                                    // are written); bits 2 and 6: atoms 0..3 and 4..7 are (evaluated together in search mode)
@@ -129,9 +129,8 @@ struct LayerDesc {
     int          out_row;            // row of the ACos tables this layer's results go to
     unsigned int M32, m_magic;       // rows, floor(2^32 / rows)
     int          K;
-    unsigned int total_units;        // strips * rows
+    unsigned int units_q, units_r;   // strips * rows = units_q * workgroups + units_r
     int          Kc;                 // true row length (rows may be folded as in KParams)
-    int          pad;
 };
 
 /* Workgroups of a search, one per compute unit at most, from whole steps per SIMD.  A step more on every SIMD costs about

@@ -682,43 +682,6 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     unsigned long long* s_acc = s_red + 1 + SOP_K_NCOL;                           // [NSLOT] this workgroup's sums (MULTI: per layer)
     const int n_acc = MULTI ? p.n_layers * NSLOT : NSLOT;
     __shared__ unsigned int s_next[4];                                            // next step of each SIMD's share
-    {
-        // 16 bytes per lane and four loads in flight before the first LDS write: a loop of one load, wait,
-        // one write would spend a round trip to L2 per word and cost more than ten microseconds per launch
-        // (the table has a multiple of four bins, so its size is a multiple of 16 bytes)
-        const int n16 = p.n_bins * (SOP_K_BIN_BYTES / 4) / 4;
-        const uint4* src = reinterpret_cast<const uint4*>(p.bins);
-        uint4* dst = reinterpret_cast<uint4*>(s_bins);
-        for (int i0 = threadIdx.x; i0 < n16; i0 += 4 * NT) {
-            uint4 t[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = i0 + j * NT < n16 ? src[i0 + j * NT] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (i0 + j * NT < n16) dst[i0 + j * NT] = t[j];
-        }
-        {
-            float2 t[3];                                // at most 2048 codes: three per thread are enough for 768 threads or more
-            const int nt = p.n_tab_codes;
-            for (int i0 = threadIdx.x; i0 < nt; i0 += 3 * NT) {
-#pragma unroll
-                for (int j = 0; j < 3; ++j) t[j] = i0 + j * NT < nt ? p.stab[i0 + j * NT] : make_float2(0.f, 0.f);
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    if (i0 + j * NT < nt) s_tab[i0 + j * NT] = t[j];
-            }
-        }
-        if (threadIdx.x < 4) s_next[threadIdx.x] = !MULTI && p.deal ? (unsigned int)OCC : 0u;
-        for (int i = threadIdx.x; i < n_acc; i += NT) s_acc[i] = 0ull;
-        // (static indices: a lane-dependent index into the kernel arguments would copy them to scratch memory)
-#pragma unroll
-        for (int a = 0; a < SOP_K_MAXA; ++a)
-            if ((int)threadIdx.x == a) {
-                s_gpar[2 * a] = make_float4(p.tpos[a], p.tneg[a], p.bin_sc[a], p.bin_off[a]);
-                s_gpar[2 * a + 1] = make_float4(p.bin_lo[a], p.bin_hi[a], 0.0f, 0.0f);
-            }
-    }
-    __syncthreads();
     const uint32_t lds_neg = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_bins + SOP_K_BIN_NEGC;
 
     const int lane = threadIdx.x & 63;
@@ -734,11 +697,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // SIMD's rate, for a fifth of the kernel.  Which wavefront takes which step does not change any
     // result: all sums are integers.
     const int simd = wv & 3;
-    // the share's range of steps in a layer of total_units steps
-    auto share_of = [&](long long total_units, unsigned int& first, unsigned int& count) {
-        const long long g0 = total_units * blockIdx.x / gridDim.x, g1 = total_units * (blockIdx.x + 1) / gridDim.x;
-        first = (unsigned int)__builtin_amdgcn_readfirstlane((int)(g0 + (g1 - g0) * simd / 4));
-        count = (unsigned int)__builtin_amdgcn_readfirstlane((int)(g0 + (g1 - g0) * (simd + 1) / 4)) - first;
+    // the share's range of the steps of a layer of uq * gridDim.x + ur (rest ur below gridDim.x, which is below 2^10)
+    auto share_of = [&](unsigned int uq, unsigned int ur, unsigned int& first, unsigned int& count) {
+        const unsigned int b = blockIdx.x, g0 = uq * b + __umulhi(ur * b, p.grid_magic), g1 = uq * (b + 1u) + __umulhi(ur * (b + 1u), p.grid_magic);
+        first = g0 + (g1 - g0) * (unsigned int)simd / 4u;
+        count = g0 + (g1 - g0) * (unsigned int)(simd + 1) / 4u - first;
     };
     // Request side (the row loads run one step ahead of the arithmetic): the layer the next requested step
     // lies in.  One layer: sb, cnt are the share's range.  MULTI: the shares of all layers follow one another
@@ -748,25 +711,19 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     unsigned int rq_base = 0u, rq_M32 = 0u, rq_magic = 0u;
     const void* rq_W = nullptr;
     long long rq_ldw = 0, rq_K = 0;
-    // (everything here is the same in all lanes; saying so keeps it in scalar registers: the range's
-    // divisions run on the vector unit, in 32 bits: T*b/G = (T/G)*b + (T%G)*b/G with G, b below 2^16)
+    // (everything here is the same in all lanes; saying so keeps it in scalar registers)
     auto uni = [](unsigned int x) { return (unsigned int)__builtin_amdgcn_readfirstlane((int)x); };
     auto uni64 = [&](unsigned long long x) { return ((unsigned long long)uni((unsigned int)(x >> 32)) << 32) | uni((unsigned int)x); };
     auto rq_enter = [&](int l) {
         const LayerDesc& d = p.layers[l];
-        const unsigned int T = uni(d.total_units), G = gridDim.x, b = blockIdx.x;
-        const unsigned int tq = T / G, tr = T - tq * G;
-        const unsigned int g0 = tq * b + tr * b / G, g1 = tq * (b + 1u) + tr * (b + 1u) / G;
-        const unsigned int first = g0 + (g1 - g0) * (unsigned int)simd / 4u;
-        sb = uni(first);
-        cnt = uni(g0 + (g1 - g0) * (unsigned int)(simd + 1) / 4u - first);
+        share_of(uni(d.units_q), uni(d.units_r), sb, cnt);
         rq_W = reinterpret_cast<const void*>(uni64((unsigned long long)reinterpret_cast<uintptr_t>(d.W)));
         rq_ldw = (long long)uni64((unsigned long long)d.ldw);
         rq_K = (long long)uni((unsigned int)d.K);
         rq_M32 = uni(d.M32); rq_magic = uni(d.m_magic);
     };
     if constexpr (MULTI) rq_enter(0);
-    else share_of(p.total_units, sb, cnt);          // (the layer's own values are read from the kernel arguments where used)
+    else share_of(p.units_q, p.units_r, sb, cnt);   // (the layer's own values are read from the kernel arguments where used)
     // is step v of the sequence there?  (MULTI: moves the request side on to its layer; v never decreases)
     auto seek = [&](unsigned int v) -> bool {
         if constexpr (!MULTI) return v < cnt;
@@ -861,15 +818,82 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     float cb[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) cb[i] = 0.0f;
+    // channel norms of the lane's columns (rows may have been folded, see KParams::Kc: the channel of a column is its index modulo the true
+    // row length; hidden from the compiler, which would keep the division's reciprocal in a vector register through the loop)
+    auto load_norms = [&](const float* c, unsigned int kc, long long col0, bool valid) {
+        asm volatile("" : "+s"(kc));
+        const unsigned int ch0 = (unsigned int)col0 % kc;
+#pragma unroll
+        for (int i = 0; i < EPL; i += 4) {
+            const float4 t = valid ? *reinterpret_cast<const float4*>(c + ch0 + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+            cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
+        }
+    };
     // Short shares: the first step of each wavefront is its own and the others come from the counter (all from the counter, the first
     // two steps of a share went to its first wavefront, one after the other, while the others had none: six atoms, 1536 steps, 16.4 us
-    // -> 13.6).  Long ones take every step from the counter: wavefronts that start in step stay in step, and use the units by
-    // turns less well (six model layers of 2048 x 2048: 57 us -> 59 with the first steps dealt out).
-    unsigned int i_cur = !MULTI && p.deal ? (unsigned int)wv >> 2 : grab(), i_nxt = grab();
+    // -> 13.6), and its row and channel norms are asked for ahead of everything else.  Long ones take every step from the counter:
+    // wavefronts that start in step stay in step, and use the units by turns less well (six model layers of 2048 x 2048: 57 us ->
+    // 59 with the first steps dealt out).
+    const bool dealt = !MULTI && p.deal;
+    unsigned int i_cur = 0u;
     RawBlk<BF16, EPL> nxt;
-    bool ok_cur = seek(i_cur);
+    bool ok_cur = false;
+    auto first_row = [&]() {
+        ok_cur = seek(i_cur);
+        if (ok_cur) { locate(sb + (i_cur - rq_base), strip, m); nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, strip, m, lanes_of(strip, MULTI ? rq_K : p.K), (unsigned int)lane); }
+    };
+    if (dealt) {
+        i_cur = (unsigned int)wv >> 2;
+        first_row();
+        if (ok_cur) {
+            cur_strip = strip;
+            load_norms(p.c, (unsigned int)p.Kc, ((long long)strip * 64 + lane) * EPL, (unsigned int)lane < lanes_of(strip, p.K));
+        }
+    }
+    // Tables into LDS: the first 16 bytes of the bin table for four in flight per thread, the scale table and the group parameters are all asked
+    // for before the first of them is waited for; a loop of one load, wait, one write would spend a round trip to L2 per word (the bin
+    // table has a multiple of four bins, so its size is a multiple of 16 bytes)
+    {
+        const int n16 = p.n_bins * (SOP_K_BIN_BYTES / 4) / 4, nt = p.n_tab_codes, tid = (int)threadIdx.x;
+        const uint4* src = reinterpret_cast<const uint4*>(p.bins);
+        uint4* dst = reinterpret_cast<uint4*>(s_bins);
+        constexpr int NB = MULTI ? 1 : 2, NS = NB;      // words of the bin table and of the scale table in the first round
+        uint4 t[NB];
+        float2 u[NS];
+        float4 gp = make_float4(0.f, 0.f, 0.f, 0.f);
+        // (a uniform test skips what is not there; indices past the end read the last word again)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) { t[j] = make_uint4(0, 0, 0, 0); if (j * NT < n16) t[j] = src[min(tid + j * NT, n16 - 1)]; }
+#pragma unroll
+        for (int j = 0; j < NS; ++j) { u[j] = make_float2(0.f, 0.f); if (j * NT < nt) u[j] = p.stab[min(tid + j * NT, nt - 1)]; }
+        if (tid < 2 * SOP_K_MAXA) gp = reinterpret_cast<const float4*>(p.gpar)[tid];
+        if (tid < 4) s_next[tid] = dealt ? (unsigned int)OCC : 0u;
+        for (int i = tid; i < n_acc; i += NT) s_acc[i] = 0ull;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) if (tid + j * NT < n16) dst[tid + j * NT] = t[j];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) if (tid + j * NT < nt) s_tab[tid + j * NT] = u[j];
+        if (tid < 2 * SOP_K_MAXA) s_gpar[tid] = gp;
+        for (int i0 = tid + NB * NT; i0 < n16; i0 += 4 * NT) {
+            uint4 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = src[min(i0 + j * NT, n16 - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) if (i0 + j * NT < n16) dst[i0 + j * NT] = v[j];
+        }
+        for (int i0 = tid + NS * NT; i0 < nt; i0 += 2 * NT) {
+            float2 v[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[j] = p.stab[min(i0 + j * NT, nt - 1)];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) if (i0 + j * NT < nt) s_tab[i0 + j * NT] = v[j];
+        }
+    }
+    __syncthreads();
+    if (!dealt) { i_cur = grab(); }
+    unsigned int i_nxt = grab();
+    if (!dealt) first_row();
     int l_nxt = rq_l;                              // layer of the row in nxt
-    if (ok_cur) { locate(sb + (i_cur - rq_base), strip, m); nxt = load_raw<BF16, EPL>(MULTI ? rq_W : p.W, MULTI ? rq_ldw : p.ldw, strip, m, lanes_of(strip, MULTI ? rq_K : p.K), (unsigned int)lane); }
     int since_flush = 0;
 
     while (ok_cur) {
@@ -886,11 +910,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 lc_Kc = uni((unsigned int)d.Kc);
                 cur_strip = strip;
                 const long long c0 = ((long long)strip * 64 + lane) * EPL;
-#pragma unroll
-                for (int i = 0; i < EPL; i += 4) {
-                    float4 t = c0 < lc_K ? *reinterpret_cast<const float4*>(lc_c + (unsigned int)c0 % lc_Kc + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
-                }
+                load_norms(lc_c, lc_Kc, c0, c0 < lc_K);
                 if (left >= 0) flush(left);
                 since_flush = 0;
             }
@@ -906,16 +926,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         const bool valid = (unsigned int)lane < lanes_of(cs, MULTI ? lc_K : p.K);
         if (cs != cur_strip) {
             cur_strip = cs;
-            // (rows may have been folded, see KParams::Kc: the channel of a column is its index modulo the true row length; hidden from the
-            // compiler, which would keep the division's reciprocal in a vector register through the loop)
-            unsigned int kc = MULTI ? lc_Kc : (unsigned int)p.Kc;
-            asm volatile("" : "+s"(kc));
-            const unsigned int ch0 = (unsigned int)col0 % kc;
-#pragma unroll
-            for (int i = 0; i < EPL; i += 4) {
-                float4 t = valid ? *reinterpret_cast<const float4*>((MULTI ? lc_c : p.c) + ch0 + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
-            }
+            load_norms(MULTI ? lc_c : p.c, MULTI ? lc_Kc : (unsigned int)p.Kc, col0, valid);
         }
         // ---- the block: one read from HBM, requested one step ahead ----
         float w[EPL];
