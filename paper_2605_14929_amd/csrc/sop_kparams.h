@@ -7,7 +7,7 @@
 #define SOP_K_MAXP 28                /* pairs i < j among SOP_K_MAXA atoms           */
 #define SOP_K_NCOL (SOP_K_MAXA + SOP_K_MAXP + 1)   /* sum columns: atoms, pairs, zero-norm lane count */
 #define SOP_K_FLUSH_STEPS 60         /* steps a lane's running sums are kept before they join the workgroup's (4 * 60 * 2^23 < 2^31) */
-#define SOP_K_REPL 8                 /* replicas of the layer sums (spreads same-address atomics) */
+#define SOP_K_REPL 8                 /* rows of layer sums (spread same-address atomics): replicas, the last one of a single layer's the totals of the others */
 #define SOP_K_MAXBINS 1024           /* bins of the element-search table                        */
 #define SOP_K_MAXTABCODES 2048       /* scale codes whose (scale, reciprocal) pair is tabulated */
 #define SOP_K_BIN_WORDS (4 * SOP_K_MAXA + 1)   /* words of one bin record (odd: conflict-free banks)  */
@@ -100,7 +100,7 @@ struct KParams {
     // outputs
     // layer sums of 1-cos in fixed point (2^-22 units): every workgroup adds its share with integer
     // atomics (order-independent, so the result is reproducible); the workgroup that finishes last
-    // turns them into the ACos outputs and leaves sums and counter at zero for the next call
+    // turns them into the ACos outputs and leaves the sums (and the model-wide kernel's counter) at zero for the next call
     unsigned long long* sums;        // [SOP_K_REPL][SOP_K_NCOL]
     unsigned int* done;              // workgroups finished (zero between calls; room for 1 + SOP_K_REPL words)
     double*   acos_pair;
@@ -135,7 +135,8 @@ struct LayerDesc {
 
 /* Workgroups of a search, one per compute unit at most, from whole steps per SIMD.  A step more on every SIMD costs about
  * 0.3 us + 0.1 us per evaluation (evaluations: codebooks times signs tried, twice that where planes are written), a workgroup
- * more 10 ns in the layer reduction (the tickets' atomics go to one address, one after the other).  Beyond SOP_K_SHORT_SHARE steps
+ * more 10 ns in the layer reduction (about 3 ns since the reduction counts its workgroups in the sums themselves: the launch states its evaluations
+ * accordingly, see pair_search_impl).  Beyond SOP_K_SHORT_SHARE steps
  * a SIMD every compute unit has a workgroup.  Measured at 64 to 4500 steps over 31 kinds of call against every number of
  * workgroups that changes the steps per SIMD: 0.1 % above the best on average, 3 % at worst (one atom, 1024 steps: 8.5 us with
  * 86 workgroups, 9.7 with 256; six atoms, 1536: 13.6 with 192, 14.3 with 128 or 256; every plane of six signed ones, 1536: 24.3 with

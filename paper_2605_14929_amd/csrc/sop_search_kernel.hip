@@ -678,6 +678,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     float4* s_gpar = reinterpret_cast<float4*>(s_mem + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
     // reduction scratch: flag word, the final gather's totals, the workgroup's own totals (64-bit integers)
     unsigned long long* s_red = reinterpret_cast<unsigned long long*>(s_gpar + 2 * SOP_K_MAXA);
+    unsigned int* s_out = reinterpret_cast<unsigned int*>(s_red + 1);             // (not MULTI) output: its sum column, and from bit 8 its place in the table
     constexpr int NLIVE = search_cols(NA), NSLOT = search_slots(NA);              // sum columns of this variant: atoms, pairs, count column
     unsigned long long* s_acc = s_red + 1 + SOP_K_NCOL;                           // [NSLOT] this workgroup's sums (MULTI: per layer)
     const int n_acc = MULTI ? p.n_layers * NSLOT : NSLOT;
@@ -867,6 +868,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 #pragma unroll
         for (int j = 0; j < NS; ++j) { u[j] = make_float2(0.f, 0.f); if (j * NT < nt) u[j] = p.stab[min(tid + j * NT, nt - 1)]; }
         if (tid < 2 * SOP_K_MAXA) gp = reinterpret_cast<const float4*>(p.gpar)[tid];
+        if (!MULTI && tid < p.A + p.P) s_out[tid] = tid < p.A ? (unsigned)tid | (unsigned)p.uidx[tid] << 8 : (unsigned)p.pair_col[tid - p.A] | (unsigned)(tid - p.A) << 8;
         if (tid < 4) s_next[tid] = dealt ? (unsigned int)OCC : 0u;
         for (int i = tid; i < n_acc; i += NT) s_acc[i] = 0ull;
 #pragma unroll
@@ -1354,6 +1356,43 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // ---- per-workgroup sums: what the lanes still hold joins the workgroup's integer sums in LDS ----
     if (!MULTI || cl >= 0) flush(cl);
     __syncthreads();
+    if constexpr (!MULTI) {
+        // ---- layer reduction, one thread per output ----
+        // A word of the layer's sums counts in its top bits the workgroups that have added to it, so the one that adds last knows by the value it
+        // gets back that it holds the total: no ticket is taken and nothing is read afterwards.  Atomics to one address are served
+        // one after the other (about 20 ns each), so a workgroup adds to one of seven words, chosen by its number, and the last of each adds
+        // that total to the eighth: two round trips to memory on the last workgroup's path (sums, a ticket and the reading of the sums were
+        // three, with up to 256 tickets on one address; six atoms: 256 x 1024 10.3 us -> 9.5, 1024 x 4096 16.7 -> 13.8, 4096 x 11008
+        // 72.0 -> 69.8).  All adds are of integers: their order does not matter.
+        // Counts in units of 2^56 (up to 255 workgroups a word) and 2^60; the sums stay below 2^54 and 2^58 (2^37 lane steps of at most
+        // 2^23 are more than the card's memory holds); a bias keeps each above zero (a lane's sum can be a few units below).
+        // Lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1 to every column; the count column
+        // takes them out again.
+        const int o = threadIdx.x;
+        if (o < p.A + p.P) {
+            const unsigned int oc = s_out[o], G = gridDim.x;
+            double* const to = o < p.A ? p.acos_atom : p.acos_pair;
+            if (to) {
+                constexpr unsigned int R = SOP_K_REPL - 1;
+                const unsigned int r = blockIdx.x % R, members = (G - r + R - 1u) / R, used = G < R ? G : R;
+                const long long v = (long long)(s_acc[oc & 0xFFu] - s_acc[NLIVE - 1]);
+                constexpr unsigned long long one1 = (1ull << 56) + (1ull << 40), one2 = (1ull << 60) + (1ull << 48);
+                unsigned long long* const w1 = p.sums + r * SOP_K_NCOL + o;
+                unsigned long long* const w2 = p.sums + R * SOP_K_NCOL + o;
+                const unsigned long long s1 = atomicAdd(w1, one1 + (unsigned long long)v) + one1 + (unsigned long long)v;
+                if ((s1 >> 56) == members) {
+                    __hip_atomic_store(w1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // (zero for the next call)
+                    const unsigned long long add = one2 + (s1 - members * one1);
+                    const unsigned long long s2 = atomicAdd(w2, add) + add;
+                    if ((s2 >> 60) == used) {
+                        __hip_atomic_store(w2, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        to[oc >> 8] = 1.0 - ((double)(long long)(s2 - used * one2) * (1.0 / 4194304.0)) / ((double)p.Nb * (double)p.lpb);
+                    }
+                }
+            }
+        }
+        return;
+    }
     if constexpr (MULTI) {
         // every layer's sums of this workgroup join the layer's replica; eight adds of a thread are in
         // flight before their returned values are consumed (see below for why they are consumed)
@@ -1372,22 +1411,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 #pragma unroll
             for (int j = 0; j < 8; ++j) asm volatile("" :: "v"(before[j]) : "memory");
         }
-    } else if ((int)threadIdx.x < NLIVE) {
-        const int i = threadIdx.x;
-        const unsigned long long v = s_acc[i];
-        if (v != 0ull) {
-            // Atomics to one address are served one after the other (about 20 ns each), so the sums
-            // are kept in SOP_K_REPL replicas chosen by workgroup number.  The returned value is
-            // consumed so that the add has completed at the memory side before this workgroup
-            // announces itself below (all traffic here is atomic: no cache write-back, which a fence
-            // would cost on every workgroup, is needed).
-            const unsigned long long before = atomicAdd(p.sums + (blockIdx.x % SOP_K_REPL) * SOP_K_NCOL + i, v);
-            asm volatile("" :: "v"(before) : "memory");
-        }
     }
-    // ---- layer reduction: every workgroup takes a ticket; the one that takes the last finishes the
-    //      layer.  (One counter: the workgroups do not end at the same instant, and a second level of
-    //      counters only put one more round trip to memory on the last workgroup's path.) ----
+    // every workgroup takes a ticket; the one that takes the last finishes the layers of the launch
     __syncthreads();
     unsigned int* s_flag = reinterpret_cast<unsigned int*>(s_red);
     if (threadIdx.x == 0) {
@@ -1426,29 +1451,6 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 const long long t = (long long)s_acc[layer * NSLOT + col];
                 if (dst) *dst = 1.0 - ((double)(t - z) * (1.0 / 4194304.0)) / ((double)p.layers[layer].Nb * (double)p.lpb);
             }
-        }
-    } else if (*s_flag) {
-        // gather the replicas (exact integer adds in LDS; the exchanges leave zeros for the next call)
-        unsigned long long* s_tot = s_red + 1;
-        __syncthreads();
-        if ((int)threadIdx.x < SOP_K_NCOL) s_tot[threadIdx.x] = 0ull;
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < SOP_K_REPL * SOP_K_NCOL; idx += NT) {
-            const unsigned long long v = atomicExch(p.sums + idx, 0ull);
-            if (v) atomicAdd(&s_tot[idx % SOP_K_NCOL], v);
-        }
-        __syncthreads();
-        // lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1
-        // to every column; the count column takes them out again
-        const long long z = (long long)s_tot[NLIVE - 1];
-        const int o = threadIdx.x;                 // 0..A-1 atoms (internal order), then pairs by output index
-        if (o < p.A + p.P) {
-            int col;
-            double* dst;
-            if (o < p.A) { col = o; dst = p.acos_atom ? p.acos_atom + p.uidx[o] : nullptr; }
-            else { col = p.pair_col[o - p.A]; dst = p.acos_pair ? p.acos_pair + (o - p.A) : nullptr; }
-            const long long t = (long long)s_tot[col];
-            if (dst) *dst = 1.0 - ((double)(t - z) * (1.0 / 4194304.0)) / ((double)p.Nb * (double)p.lpb);
         }
     }
 }
