@@ -451,7 +451,7 @@ __device__ __forceinline__ Sums eval_direct(const float (&w)[EPL], const float (
         }
         // (a register budget, not an order: with the chunks apart the signed six-atom search keeps 139 registers, without 168 and up to 60 spilled;
         // every plane of eight atoms of 8-element lanes 162 to 167, without 168 and up to 12 spilled)
-        if constexpr ((TIES && !CODES && EPL == 16) || (EPL == 8 && CODES)) asm volatile("" : "+v"(n0), "+v"(n1), "+v"(d0), "+v"(d1));
+        if constexpr ((TIES && !CODES && EPL == 16) || (CODES && (EPL == 8 || !TIES))) asm volatile("" : "+v"(n0), "+v"(n1), "+v"(d0), "+v"(d1));
     }
     Sums s;
     s.err = EPL == 16 ? e0 + e1 : e0;
@@ -579,7 +579,8 @@ __device__ __forceinline__ void all_pairs(const KParams& p, const Switches& sw, 
 template <bool BF16, int EPL> struct RawBlk { uint4 v[BF16 ? EPL / 8 : EPL / 4]; };
 
 // Strip and row are the same in every lane: the address is a scalar base plus the lane's own 32-bit offset.  `lanes`: lanes
-// of the strip that hold weights (64 but for the last strip of a row); a full strip is loaded without a lane mask.
+// of the strip that hold weights (64 but for the last strip of a row); the others lie past the end the load is given and read zeros.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16, int EPL>
 __device__ __forceinline__ RawBlk<BF16, EPL> load_raw(const void* W, long long ldw, unsigned int strip, unsigned int m, unsigned int lanes, unsigned int lane)
 {
@@ -587,14 +588,11 @@ __device__ __forceinline__ RawBlk<BF16, EPL> load_raw(const void* W, long long l
     constexpr int NV = BF16 ? EPL / 8 : EPL / 4;
     constexpr unsigned int esz = BF16 ? 2u : 4u;
     const char* row = reinterpret_cast<const char*>(W) + ((long long)m * ldw + (long long)strip * (64 * EPL)) * esz;
-    const unsigned int off = lane * (EPL * esz);
-    if (lanes == 64u) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), 0, (int)(lanes * (EPL * esz)), 0x00027000);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) r.v[i] = *reinterpret_cast<const uint4*>(row + off + 16 * i);
-    } else {
-        const bool valid = lane < lanes;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) r.v[i] = valid ? *reinterpret_cast<const uint4*>(row + off + 16 * i) : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < NV; ++i) {
+        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * (EPL * esz) + 16u * i, 0, 0);
+        r.v[i] = make_uint4(t.x, t.y, t.z, t.w);
     }
     return r;
 }
@@ -821,14 +819,19 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     for (int i = 0; i < EPL; ++i) cb[i] = 0.0f;
     // channel norms of the lane's columns (rows may have been folded, see KParams::Kc: the channel of a column is its index modulo the true
     // row length; hidden from the compiler, which would keep the division's reciprocal in a vector register through the loop)
-    auto load_norms = [&](const float* c, unsigned int kc, long long col0, bool valid) {
+    auto load_norms = [&](const float* c, unsigned int kc, unsigned int col0, bool valid) {
         asm volatile("" : "+s"(kc));
-        const unsigned int ch0 = (unsigned int)col0 % kc;
+        const unsigned int ch0 = col0 % kc;
 #pragma unroll
         for (int i = 0; i < EPL; i += 4) {
             const float4 t = valid ? *reinterpret_cast<const float4*>(c + ch0 + i) : make_float4(0.f, 0.f, 0.f, 0.f);
             cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
         }
+    };
+    // (norms are waited for where they are asked for, not at their first use, which lies behind the request of the next row)
+    auto norms_here = [&]() {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) asm volatile("" : "+v"(cb[i]));
     };
     // Short shares: the first step of each wavefront is its own and the others come from the counter (all from the counter, the first
     // two steps of a share went to its first wavefront, one after the other, while the others had none: six atoms, 1536 steps, 16.4 us
@@ -848,7 +851,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         first_row();
         if (ok_cur) {
             cur_strip = strip;
-            load_norms(p.c, (unsigned int)p.Kc, ((long long)strip * 64 + lane) * EPL, (unsigned int)lane < lanes_of(strip, p.K));
+            load_norms(p.c, (unsigned int)p.Kc, (strip * 64u + (unsigned int)lane) * EPL, (unsigned int)lane < lanes_of(strip, p.K));
         }
     }
     // Tables into LDS: the first 16 bytes of the bin table for four in flight per thread, the scale table and the group parameters are all asked
@@ -897,6 +900,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     if (!dealt) first_row();
     int l_nxt = rq_l;                              // layer of the row in nxt
     int since_flush = 0;
+    // (the first row is waited for here: at the top of the loop the wait is then that of a step, whose row is older than its stores)
+    if (ok_cur) {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(nxt.v) / sizeof(nxt.v[0])); ++i) asm volatile("" : "+v"(nxt.v[i].x), "+v"(nxt.v[i].y), "+v"(nxt.v[i].z), "+v"(nxt.v[i].w));
+        norms_here();
+    }
 
     while (ok_cur) {
         if constexpr (MULTI) {
@@ -911,9 +920,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 lc_K = (long long)uni((unsigned int)d.K); lc_Bk = (long long)uni((unsigned int)d.Bk);
                 lc_Kc = uni((unsigned int)d.Kc);
                 cur_strip = strip;
-                const long long c0 = ((long long)strip * 64 + lane) * EPL;
-                load_norms(lc_c, lc_Kc, c0, c0 < lc_K);
+                load_norms(lc_c, lc_Kc, (strip * 64u + (unsigned int)lane) * EPL, (unsigned int)lane < lanes_of(strip, lc_K));
                 if (left >= 0) flush(left);
+                norms_here();
                 since_flush = 0;
             }
         }
@@ -924,11 +933,13 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         if constexpr (SIGNED) asm volatile("" : "+s"(sw.mirror), "+s"(sw.selfsym));
         if constexpr (GROUPED) asm volatile("" : "+s"(sw.second));
         const unsigned int cm32 = m, cs = strip;
-        const long long cm = cm32, col0 = ((long long)cs * 64 + lane) * EPL;
-        const bool valid = (unsigned int)lane < lanes_of(cs, MULTI ? lc_K : p.K);
+        const long long cm = cm32;
+        const unsigned int lanes_here = lanes_of(cs, MULTI ? lc_K : p.K);
+        const bool valid = (unsigned int)lane < lanes_here;
         if (cs != cur_strip) {
             cur_strip = cs;
-            load_norms(MULTI ? lc_c : p.c, MULTI ? lc_Kc : (unsigned int)p.Kc, col0, valid);
+            load_norms(MULTI ? lc_c : p.c, MULTI ? lc_Kc : (unsigned int)p.Kc, (cs * 64u + (unsigned int)lane) * EPL, valid);
+            norms_here();
         }
         // ---- the block: one read from HBM, requested one step ahead ----
         float w[EPL];
@@ -951,8 +962,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         if constexpr (MULTI) {
             if (ok_nxt && l_nxt != cl) {
                 const float* cn = reinterpret_cast<const float*>(uni64((unsigned long long)reinterpret_cast<uintptr_t>(p.layers[l_nxt].c)));
-                const long long tc = ((long long)strip * 64 + lane) * EPL;
-                if (tc < rq_K) c_touch = cn[(unsigned int)tc % uni((unsigned int)p.layers[l_nxt].Kc)];
+                if ((unsigned int)lane < lanes_of(strip, rq_K)) c_touch = cn[(strip * 64u + (unsigned int)lane) * EPL % uni((unsigned int)p.layers[l_nxt].Kc)];
             }
         }
         const unsigned int i_nn = grab();              // the step after the next one; used at the end of this step
@@ -989,9 +999,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             nsc.qwns = 0.25f * nsc.wns;
         }
 
-        const long long blk_in_row = ((long long)cs * 64 + lane) / LPB;
-        const long long blk = cm * (MULTI ? lc_Bk : p.Bk) + blk_in_row;
-        const bool leader = valid && (lane % LPB == 0);
+        const long long blk0 = cm * (MULTI ? lc_Bk : p.Bk) + (long long)cs * (64 / LPB), blk = blk0 + (unsigned int)lane / LPB;    // (the step's first block; the lane's)
+        const bool leader = valid && lane % LPB == 0;
 
         // per-block results of every atom that the pair stage needs: score = err (WSE / MSE) or
         // q = num*|num| (COS, 0 for a zero reconstruction), den (COS only, 1 for a zero reconstruction), 1 - cos
@@ -1039,14 +1048,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 if (__builtin_expect(__any(t.weak) != 0, 0)) weak_atoms |= 1u << a;
                 if constexpr (EMIT) {
                     const long long ua = p.uidx[a];
-                    if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)sp.q;
-                    if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = t.err;
-                    if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-t.ny, rs, 1.0f) : 1.0f;
+                    if (have_codes && valid) store_codes<EPL>(p, sw, a, cm, (long long)(cs * 64u + (unsigned int)lane) * EPL, codes);
                     if (want_rank) {
                         const float r = rank_score(group_sum<LPB>(s.rn), group_sum<LPB>(s.rd), wn);
                         if (leader) p.blk_rank[ua * p.Nb + blk] = r;
                     }
-                    if (have_codes && valid) store_codes<EPL>(p, sw, a, cm, col0, codes);
+                    if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)sp.q;
+                    if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-t.ny, rs, 1.0f) : 1.0f;
+                    if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = t.err;
                 }
             };
             auto scale_of = [&](int a) __attribute__((always_inline)) {
@@ -1325,14 +1334,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 acca[a] += ia;
                 if (EMIT) {
                     const long long ua = p.uidx[a];
-                    if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)(q | (neg ? 0x8000 : 0));
-                    if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = best.err;
-                    if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-best.ny, rs, 1.0f) : 1.0f;
+                    if (p.codes && valid) store_codes<EPL>(p, sw, a, cm, (long long)(cs * 64u + (unsigned int)lane) * EPL, codes);
                     if (p.blk_rank) {
                         const float rank = METRIC == 1 && !SIGNED ? rank_score(ny_raw, dy_raw, wn) : rank_score(rk_num, rk_dn, wn);
                         if (leader) p.blk_rank[ua * p.Nb + blk] = rank;
                     }
-                    if (p.codes && valid) store_codes<EPL>(p, sw, a, cm, col0, codes);
+                    if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)(q | (neg ? 0x8000 : 0));
+                    if (p.blk_cos && leader) p.blk_cos[ua * p.Nb + blk] = wn > 0.0f ? 1.0f - __fmaf_rn(-best.ny, rs, 1.0f) : 1.0f;
+                    if (p.blk_err && leader) p.blk_err[ua * p.Nb + blk] = best.err;
                 }
             }
         }
@@ -1342,10 +1351,21 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         all_pairs<0, NA, METRIC>(p, sw, score, den, dlt, accp, bits);
         bits ^= p.flip_slots;
         void* const sel_words = MULTI ? lc_sel : p.sel_words;
-        if (sel_words && leader) {
-            if (p.sel_u32) reinterpret_cast<uint32_t*>(sel_words)[blk] = bits;
-            else reinterpret_cast<uint16_t*>(sel_words)[blk] = (uint16_t)bits;
-        }
+        // One store without a branch ends every path of a step: lanes without a word to store, or all of them, lie past the end the store is given
+        // and are dropped by the hardware.  Behind a branch it may or may not be the last access, the compiler waits for every access in
+        // flight, and a step began with a wait for memory's answer to the words of the one before (4096 x 11008, six atoms, rows from HBM:
+        // 73.7 us -> 70.5; ragged fp32 layer 22.1 -> 20.8).  (The planes of emit mode keep their branches: a range to set up for each costs
+        // more than it saves, 4096 x 11008, two atoms, 67.8 us -> 72.7.)  32-bit words belong to more than sixteen pairs: of the two stores of eight atoms one
+        // has nothing to store.
+        unsigned int at = (unsigned int)lane;
+        asm volatile("" : "+v"(at));                   // (the offset is formed here rather than kept in a register)
+        at = at % LPB == 0u ? at / LPB : 0x20000000u;      // (past every end, counted in 16-bit words as in 32-bit ones)
+        const unsigned int n_here = lanes_here / LPB;
+        char* const sel_at = reinterpret_cast<char*>(sel_words);
+        const bool w32 = NA == 8 && p.sel_u32;
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)bits, __builtin_amdgcn_make_buffer_rsrc(sel_at + blk0 * 2, 0, sel_words && !w32 ? (int)(n_here * 2u) : 0, 0x00027000), at * 2u, 0, 0);
+        if constexpr (NA == 8)
+            __builtin_amdgcn_raw_buffer_store_b32(bits, __builtin_amdgcn_make_buffer_rsrc(sel_at + blk0 * 4, 0, sel_words && w32 ? (int)(n_here * 4u) : 0, 0x00027000), at * 4u, 0, 0);
         if constexpr (MULTI) asm volatile("" :: "v"(c_touch));
         i_cur = i_nxt;
         ok_cur = ok_nxt;
@@ -1356,6 +1376,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // ---- per-workgroup sums: what the lanes still hold joins the workgroup's integer sums in LDS ----
     if (!MULTI || cl >= 0) flush(cl);
     __syncthreads();
+    const int tid = wv * 64 + lane;                // (not kept through the row loop)
     if constexpr (!MULTI) {
         // ---- layer reduction, one thread per output ----
         // A word of the layer's sums counts in its top bits the workgroups that have added to it, so the one that adds last knows by the value it
@@ -1368,7 +1389,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // 2^23 are more than the card's memory holds); a bias keeps each above zero (a lane's sum can be a few units below).
         // Lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1 to every column; the count column
         // takes them out again.
-        const int o = threadIdx.x;
+        const int o = tid;
         if (o < p.A + p.P) {
             const unsigned int oc = s_out[o], G = gridDim.x;
             double* const to = o < p.A ? p.acos_atom : p.acos_pair;
@@ -1400,7 +1421,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             unsigned long long before[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int idx = base + j * NT + (int)threadIdx.x;
+                const int idx = base + j * NT + tid;
                 before[j] = 0ull;
                 if (idx < n_acc) {
                     const unsigned long long v = s_acc[idx];
@@ -1415,7 +1436,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // every workgroup takes a ticket; the one that takes the last finishes the layers of the launch
     __syncthreads();
     unsigned int* s_flag = reinterpret_cast<unsigned int*>(s_red);
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         unsigned int last = 0u;
         if (atomicAdd(p.done, 1u) == gridDim.x - 1) { atomicExch(p.done, 0u); last = 1u; }
         *s_flag = last;
@@ -1426,7 +1447,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             // totals of every (layer, column) over the replicas into LDS, in place of the workgroup's own sums
             // (the exchanges leave zeros for the next call), then one ACos per (layer, atom or pair)
             __syncthreads();
-            for (int idx = threadIdx.x; idx < n_acc; idx += NT) {
+            for (int idx = tid; idx < n_acc; idx += NT) {
                 const int layer = idx / NSLOT, col = idx - layer * NSLOT;
                 if (col >= NLIVE) continue;
                 unsigned long long* src = p.sums + (size_t)layer * SOP_K_REPL * SOP_K_NCOL + col;
@@ -1440,7 +1461,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             }
             __syncthreads();
             const int per = p.A + p.P;
-            for (int o = threadIdx.x; o < p.n_layers * per; o += NT) {
+            for (int o = tid; o < p.n_layers * per; o += NT) {
                 const int layer = o / per, q = o - layer * per;
                 int col;
                 double* dst;
