@@ -40,63 +40,40 @@ static int bin_of(float x, float xl, float xh, float sc, float off)
 // Fill atom slot `ia` of the bin records for the table range [xl, xh] (wider than the atom: values
 // beyond the atom's endpoints take its first / last entry); false when some bin would hold two code
 // boundaries or the binning leaves [0, n_bins).
+//
+// The binning is monotone in x, so the code of a bin's first float and of its last one follow from where the boundaries fall, without
+// looking for the bins' own ends: with m a boundary and m+ the next float, a float lies above m from m+ on.  Bins past that of m+ start
+// above m; the bin of m+ starts above m where m itself falls into an earlier bin; bins from that of m+ on end above m.
 static bool build_bins(const std::vector<float>& L, float xl, float xh, float sc, float off, int n_bins, int ia, BinRec* rec)
 {
     const int N = (int)L.size();
     const float inf = std::numeric_limits<float>::infinity();
-    std::vector<float> mid(N - 1);
-    for (int j = 0; j + 1 < N; ++j) mid[j] = (float)(((double)L[j] + (double)L[j + 1]) * 0.5);
-    auto code_of = [&](float x) { int c = 0; for (int j = 0; j + 1 < N; ++j) c += x > mid[j]; return c; };
     const int b_lo = bin_of(xl, xl, xh, sc, off), b_hi = bin_of(xh, xl, xh, sc, off);
     if (b_lo < 0 || b_hi >= n_bins || b_lo > b_hi) return false;
-    // Quick rejection (the caller tries bin counts in ascending order, and most fail): two neighbouring code
-    // boundaries with a float above the second one still in the first one's bin put two boundaries into
-    // that bin.  (Where this does not decide, the full construction below does.)
-    for (int j = 0; j + 2 < N; ++j) {
-        const int bj = bin_of(mid[j], xl, xh, sc, off);
-        if (mid[j] >= xl && mid[j + 1] < xh && bj > b_lo && bj < b_hi && bin_of(mid[j + 1], xl, xh, sc, off) == bj &&
-            bin_of(std::nextafter(mid[j + 1], inf), xl, xh, sc, off) == bj)
-            return false;
+    float mid[SOP_MAX_ENTRIES];
+    int at[SOP_MAX_ENTRIES], above[SOP_MAX_ENTRIES];                  // bin of a boundary, bin of the float above it
+    for (int j = 0; j + 1 < N; ++j) {
+        mid[j] = (float)(((double)L[j] + (double)L[j + 1]) * 0.5);
+        at[j] = bin_of(mid[j], xl, xh, sc, off);
+        above[j] = bin_of(std::nextafter(mid[j], inf), xl, xh, sc, off);
+        // (a bin that holds this boundary and the one before, with floats on either side of both)
+        if (j && above[j] == above[j - 1] && at[j - 1] == above[j - 1]) return false;
     }
-    // first[j] = smallest float in [xl, xh] whose bin is >= j (the binning is monotone in x)
-    std::vector<float> first(n_bins + 1, inf);
-    for (int j = 0; j <= b_lo; ++j) first[j] = xl;
-    for (int j = b_lo + 1; j <= b_hi; ++j) {
-        int64_t lo = ford(first[j - 1]), hi = ford(xh);              // bin(lo) < j <= bin(hi)
-        if (bin_of(funord(lo), xl, xh, sc, off) >= j) { first[j] = funord(lo); continue; }
-        // the bin changes where x*sc + off passes j - 1/2 above the constant: a bracket of a few floats around
-        // that x, used if it holds the change (the bisection then takes 7 steps instead of 30)
-        {
-            const float est = (float)(((double)j - 0.5 + ((double)SOP_K_BIN_MAGIC - (double)off)) / (double)sc);
-            if (std::isfinite(est)) {
-                const int64_t elo = std::max(lo, ford(est) - 64), ehi = std::min(hi, ford(est) + 64);
-                if (elo < ehi && bin_of(funord(elo), xl, xh, sc, off) < j && bin_of(funord(ehi), xl, xh, sc, off) >= j) { lo = elo; hi = ehi; }
-            }
-        }
-        while (hi - lo > 1) {
-            const int64_t m = lo + (hi - lo) / 2;
-            if (bin_of(funord(m), xl, xh, sc, off) >= j) hi = m; else lo = m;
-        }
-        first[j] = funord(hi);
-    }
+    int c0 = 0, c1 = 0;                                               // code of the bin's first and last float
     for (int j = 0; j < n_bins; ++j) {
-        // floats of bin j: [first[j], pred(first[j+1])]; everything below xl falls into bin(xl),
-        // everything above xh into bin(xh)
-        int c0 = 0, c1 = 0;
-        if (j < b_lo || j > b_hi || !(first[j] < first[j + 1])) {     // never addressed
-            c0 = c1 = 0;
-        } else {
-            c0 = j == b_lo ? 0 : code_of(first[j]);
-            c1 = j == b_hi ? N - 1 : code_of(std::nextafter(first[j + 1], -inf));
-        }
-        if (c1 - c0 > 1) return false;
-        rec[j].thr[ia] = c1 > c0 ? mid[c0] : inf;
-        rec[j].ylo[ia] = 0.5f * L[c0];               // halves (exact: plan_alphabet refuses entries whose half is not)
-        rec[j].yhi[ia] = 0.5f * L[c1];
-        rec[j].code_lo[ia] = c0;
+        while (c0 < N - 1 && (above[c0] < j || (above[c0] == j && at[c0] < j))) ++c0;
+        while (c1 < N - 1 && above[c1] <= j) ++c1;
+        const bool used = j >= b_lo && j <= b_hi;                     // (the others are never addressed)
+        if (used && c1 - c0 > 1) return false;
+        const int a = used ? c0 : 0, b = used ? c1 : 0;
+        rec[j].thr[ia] = b > a ? mid[a] : inf;
+        rec[j].ylo[ia] = 0.5f * L[a];                // halves (exact: plan_alphabet refuses entries whose half is not)
+        rec[j].yhi[ia] = 0.5f * L[b];
+        rec[j].code_lo[ia] = a;
     }
     return true;
 }
+
 
 
 // Validate the atoms, form the scale groups and build the bin table (host only).
@@ -365,6 +342,43 @@ extern "C" sop_status sop_atom_bof(int n_bits, const double* draws, int64_t n_dr
 }
 
 
+// The rounds of the fit.  A cell's last bin is looked for from where the midpoint lies, by the binary64 expression of the bin's
+// centre that defines the cell; a round that moves no entry is the last one that could.
+template <class U>
+static void dd_rounds(const int64_t* hist, int n_bins, int n_entries, int iters, std::vector<double>& cent, std::vector<double>& mids)
+{
+    std::vector<U> pm(n_bins + 1), pf(n_bins + 1);
+    pm[0] = 0; pf[0] = 0;
+    for (int b = 0; b < n_bins; ++b) {
+        pm[b + 1] = pm[b] + (U)hist[b];
+        pf[b + 1] = pf[b] + (U)hist[b] * (unsigned)(2 * b + 1);
+    }
+    const double inv = 1.0 / (double)n_bins;          // (exact: a power of two)
+    auto centre = [inv](int b) { return -1.0 + (2.0 * (double)b + 1.0) * inv; };
+    std::vector<double> before(n_entries);
+    for (int it = 0; it < iters; ++it) {
+        before = cent;
+        for (int j = 0; j + 1 < n_entries; ++j) mids[j] = 0.5 * (cent[j] + cent[j + 1]);
+        int lo_bin = 0;                               // first bin of the current cell
+        for (int j = 0; j < n_entries; ++j) {
+            int end = n_bins;                         // one past the last bin of cell j
+            if (j + 1 < n_entries) {
+                // smallest b >= lo_bin with mids[j] < centre(b): those bins belong to later cells
+                const double g = (mids[j] + 1.0) * (0.5 * (double)n_bins);
+                int b = g > (double)lo_bin ? (g < (double)n_bins ? (int)g : n_bins) : lo_bin;
+                while (b > lo_bin && mids[j] < centre(b - 1)) --b;
+                while (b < n_bins && !(mids[j] < centre(b))) ++b;
+                end = b;
+            }
+            const U mass = pm[end] - pm[lo_bin], first = pf[end] - pf[lo_bin];
+            if (mass > 0) cent[j] = ((double)first / (double)mass) / (double)n_bins - 1.0;
+            lo_bin = end;
+        }
+        std::sort(cent.begin(), cent.end());
+        if (cent == before) break;
+    }
+}
+
 extern "C" sop_status sop_dd_fit(const int64_t* hist, int n_bins, int n_entries, int iters, const float* init, float* out)
 {
     if (!hist || !init || !out) return soph::host_fail(SOP_EINVAL, "sop_dd_fit: NULL argument");
@@ -375,35 +389,13 @@ extern "C" sop_status sop_dd_fit(const int64_t* hist, int n_bins, int n_entries,
         if (!(cent[j] < cent[j + 1])) return soph::host_fail(SOP_EATOM, "sop_dd_fit: the start grid must be strictly ascending");
     // A bin stands for its centre -1 + (2b+1)/H and goes, whole, to that centre's cell (cell = number of
     // midpoints strictly below the centre).  The centres ascend with b, so a cell is a run of bins and its
-    // mass and first moment are differences of prefix sums (exact integers); the run's end for a midpoint is
-    // found by bisection on the same binary64 expression of the centre that defines the cell.
-    std::vector<unsigned __int128> pm(n_bins + 1), pf(n_bins + 1);
-    pm[0] = 0; pf[0] = 0;
-    for (int b = 0; b < n_bins; ++b) {
-        pm[b + 1] = pm[b] + (unsigned __int128)hist[b];
-        pf[b + 1] = pf[b] + (unsigned __int128)hist[b] * (unsigned)(2 * b + 1);
-    }
-    auto centre = [n_bins](int b) { return -1.0 + (2.0 * (double)b + 1.0) / (double)n_bins; };
-    for (int it = 0; it < iters; ++it) {
-        for (int j = 0; j + 1 < n_entries; ++j) mids[j] = 0.5 * (cent[j] + cent[j + 1]);
-        int lo_bin = 0;                               // first bin of the current cell
-        for (int j = 0; j < n_entries; ++j) {
-            int end = n_bins;                         // one past the last bin of cell j
-            if (j + 1 < n_entries) {
-                // smallest b >= lo_bin with mids[j] < centre(b): those bins belong to later cells
-                int lo = lo_bin, hi = n_bins;
-                while (lo < hi) {
-                    const int mid = (lo + hi) / 2;
-                    if (mids[j] < centre(mid)) hi = mid; else lo = mid + 1;
-                }
-                end = lo;
-            }
-            const unsigned __int128 mass = pm[end] - pm[lo_bin], first = pf[end] - pf[lo_bin];
-            if (mass > 0) cent[j] = ((double)first / (double)mass) / (double)n_bins - 1.0;
-            lo_bin = end;
-        }
-        std::sort(cent.begin(), cent.end());
-    }
+    // mass and first moment are differences of prefix sums (exact integers, of 64 bits where they fit).
+    unsigned long long total = 0;
+    bool wide = false;
+    for (int b = 0; b < n_bins; ++b) wide = __builtin_add_overflow(total, (unsigned long long)hist[b], &total) || wide;
+    wide = wide || total > (0x7FFFFFFFFFFFFFFFull >> 1) / (unsigned long long)n_bins;     // (the largest first moment is below 2 n_bins total)
+    if (wide) dd_rounds<unsigned __int128>(hist, n_bins, n_entries, iters, cent, mids);
+    else dd_rounds<unsigned long long>(hist, n_bins, n_entries, iters, cent, mids);
     for (int j = 0; j < n_entries; ++j) out[j] = (float)cent[j];
     for (int j = 0; j + 1 < n_entries; ++j)
         if (!(out[j] < out[j + 1])) return soph::host_fail(SOP_EATOM, "sop_dd_fit: the fitted grid is not strictly ascending in binary32 (too little data)");
