@@ -52,6 +52,7 @@ static constexpr size_t kLsWords = kLsDone + 17 * SOP_K_LS_DONE_STRIDE / 2;
 static constexpr int kMaxLayers = 1024;  // layers of one launch of the model-wide kernel (more are dealt with in several launches)
 static constexpr int kStabSlots = 160;   // (scale, reciprocal) tables kept on the device: more than the layer shifts one call can name (129)
 static constexpr size_t kSumsWords = SOP_K_REPL * SOP_K_NCOL + SOP_K_REPL + 1;   // one set of layer sums and tickets, in 64-bit words
+static constexpr size_t kDdWords = SOP_K_DD_MAXBINS + (1 + SOP_K_DD_ROWS) * SOP_K_DD_DONE_STRIDE / 2;       // running histograms and ticket counters of the statistics passes, in 64-bit words
 
 // ---- scratch of the entry point that allocates nothing (sop_pair_search_static) ----
 // One set of layer sums with its ticket counters, then the (scale, reciprocal) table of the call's scale
@@ -125,7 +126,7 @@ struct sop_ctx {
     hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
     bool stage_pending = false;
     unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
-    unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] running DD histogram + (one word further) its finished-workgroup counter; zero between calls
+    unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] rows of the running DD histogram and, behind them, the counters of finished workgroups; zero between calls
     unsigned int* d_sel = nullptr;        // [2][3][SOP_K_SEL_BINS] two sets of digit counts of the block ranking: a call counts into set sel_set and clears the other
     int sel_set = 0;
     unsigned int* d_selm = nullptr;       // [2][SOP_K_MAXA][SOP_K_SELM_WORDS] two sets of digit counts of the ranking with several thresholds (one per score plane of a launch)
@@ -193,8 +194,8 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
         delete c;
         return hipfail(nullptr, e, "hipMalloc(layer sums)");
     }
-    if ((e = hipMalloc((void**)&c->d_ddacc, sizeof(unsigned long long) * (SOP_K_DD_MAXBINS + 1))) != hipSuccess ||
-        (e = hipMemset(c->d_ddacc, 0, sizeof(unsigned long long) * (SOP_K_DD_MAXBINS + 1))) != hipSuccess) {
+    if ((e = hipMalloc((void**)&c->d_ddacc, sizeof(unsigned long long) * kDdWords)) != hipSuccess ||
+        (e = hipMemset(c->d_ddacc, 0, sizeof(unsigned long long) * kDdWords)) != hipSuccess) {
         (void)hipFree(c->d_bins); (void)hipFree(c->d_sums); if (c->d_ddacc) (void)hipFree(c->d_ddacc);
         delete c;
         return hipfail(nullptr, e, "hipMalloc(histogram)");

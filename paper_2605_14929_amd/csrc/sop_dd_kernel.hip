@@ -17,9 +17,15 @@
 //
 // Work mapping as in the search kernel: a lane owns min(g,16) consecutive elements of a row, a
 // wavefront walks down the rows of a 64-lane strip, the next row requested a step ahead.  Each workgroup (16 wavefronts,
-// one per compute unit) finds cmax itself, accumulates in LDS and adds its histogram to the layer's running histogram (kept in
-// the context, zero between calls) with 64-bit global atomics; the workgroup that finishes last moves the result to
+// one per compute unit) finds cmax itself, accumulates in LDS and adds its histogram to one of the layer's rows of running sums (kept in
+// the context, zero between calls; dd_rows()) with 64-bit global atomics; the workgroup that finishes last moves the result to
 // the caller's buffer and leaves zeros behind.  One kernel per call.
+//
+// What does not depend on the layer's size is most of a layer below 100 MB: launch, norms, first row, and then 256 workgroups that add to
+// the same words and take tickets.  First row, norms and the clearing of LDS overlap, the workgroups are divided among four rows of
+// sums, and each begins at a place of its own in its row (all in one order, they queued up on one line after the other).
+// bf16, 1024 bins: 2048 x 4096 15.1 us -> 11.3, 4096 x 4096 18.5 -> 14.6, 4096 x 11008 26.3 -> 23.2; 8192 words: 27.5 -> 23.8, 30 -> 26.9,
+// 39.8 -> 37; 28672 x 8192 88 before and after.
 //
 // In LDS a weight costs one 32-bit add.  The pass is bound by those adds (a wavefront's 64 lanes fall on random bins: bank
 // conflicts) beside the read of the layer, and a 64-bit add takes twice the bank cycles.  The 32-bit counts sit in p.n_repl
@@ -59,37 +65,6 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     const int NP = p.n_levels > 0 ? p.n_planes : 1;                   // level planes
     const int H = p.n_bins * (p.n_levels > 0 ? p.n_levels : 1) * NP;  // words of all the histograms of the call
     unsigned int* s_cnt = reinterpret_cast<unsigned int*>(s_hist + H);
-    {
-        uint4* z = reinterpret_cast<uint4*>(s_hist);                  // (H is a multiple of 64)
-        const int n16 = (H / 4) * (REPL ? 2 + p.n_repl : 2);
-        for (int i = threadIdx.x; i < n16; i += SOP_K_DD_THREADS) z[i] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    // cmax = max_k c_k (order-independent), found by every workgroup for itself
-    float cmax = 1.0f;
-    if (p.c) {
-        // 16 bytes per lane and four loads in flight (a loop of single dependent loads would spend a round
-        // trip to L2 per element); K is a multiple of 8 and c is 16-byte aligned
-        float v = 0.0f;
-        const long long k4 = p.K >> 2;
-        const float4* c4 = reinterpret_cast<const float4*>(p.c);
-        for (long long k0 = threadIdx.x; k0 < k4; k0 += 4 * SOP_K_DD_THREADS) {
-            float4 t[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) t[j] = k0 + j * SOP_K_DD_THREADS < k4 ? c4[k0 + j * SOP_K_DD_THREADS] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v = fmaxf(fmaxf(fmaxf(v, t[j].x), fmaxf(t[j].y, t[j].z)), t[j].w);
-        }
-#pragma unroll
-        for (int st = 1; st < 64; st <<= 1) v = fmaxf(v, __shfl_xor(v, st, 64));
-        if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = v;
-    }
-    __syncthreads();
-    if (p.c) {
-        cmax = s_max[0];
-#pragma unroll
-        for (int i = 1; i < NW; ++i) cmax = fmaxf(cmax, s_max[i]);
-    }
-
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // this wavefront's steps: floor(T b / G) = (T / G) b + (T % G) b / G with the first two from the host, all of it in 32 bits but
@@ -98,10 +73,6 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     const unsigned int r0 = p.units_r * wave / n_waves, r1 = p.units_r * (wave + 1u) / n_waves;       // (G below 2^16)
     const long long u0 = p.units_q * wave + r0;
     const int n_steps = __builtin_amdgcn_readfirstlane((int)p.units_q + (int)(r1 - r0));
-    const float cs = cmax > 0.0f ? 1048576.0f / cmax : 0.0f;      // all-zero channel norms: an empty histogram
-    // cs overflows for norms below 2^20 / FLT_MAX: the conversion below then gives 2^31 - 1 for every non-zero norm, and a step's
-    // additions to one word do not fit 32 bits
-    const bool huge = !(cs < INFINITY);
     const float half = 0.5f * (float)HB;
     unsigned int* const cnt = s_cnt + (REPL ? (wv & (p.n_repl - 1)) * H : 0);                         // this wavefront's replica
     const unsigned int budget = REPL ? 0xFFFFFFFFu / (unsigned int)(NW / p.n_repl) : 0u;
@@ -146,7 +117,57 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
             for (int pl = 0; pl < PRE; ++pl) lvl[pl] = pl < NP && valid ? p.block_mask[(long long)pl * p.plane_stride + blk] : 0;
         }
     };
-    if (AHEAD && n_steps > 0) request();
+    // channel norms of the lane's columns in strip st
+    float4 cv[EPL / 4];
+    auto load_norms = [&](unsigned int st) __attribute__((always_inline)) {
+        const long long col0 = ((long long)st * 64 + lane) * EPL;
+#pragma unroll
+        for (int i = 0; i < EPL / 4; ++i) {
+            cv[i] = make_float4(1.f, 1.f, 1.f, 1.f);
+            if (p.c) cv[i] = col0 < p.K ? reinterpret_cast<const float4*>(p.c + col0)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    // The first row and the first strip's norms are asked for ahead of everything that does not need them: the largest norm,
+    // the clearing of the sums and the barrier take as long as they travel.
+    if (n_steps > 0) {
+        if (AHEAD) request();
+        load_norms(rs);
+    }
+    {
+        uint4* z = reinterpret_cast<uint4*>(s_hist);                  // (H is a multiple of 64)
+        const int n16 = (H / 4) * (REPL ? 2 + p.n_repl : 2);
+        for (int i = threadIdx.x; i < n16; i += SOP_K_DD_THREADS) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    // cmax = max_k c_k (order-independent), found by every workgroup for itself
+    float cmax = 1.0f;
+    if (p.c) {
+        // 16 bytes per lane and four loads in flight (a loop of single dependent loads would spend a round
+        // trip to L2 per element); K is a multiple of 8 and c is 16-byte aligned
+        float v = 0.0f;
+        const long long k4 = p.K >> 2;
+        const float4* c4 = reinterpret_cast<const float4*>(p.c);
+        for (long long k0 = threadIdx.x; k0 < k4; k0 += 4 * SOP_K_DD_THREADS) {
+            float4 t[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[j] = k0 + j * SOP_K_DD_THREADS < k4 ? c4[k0 + j * SOP_K_DD_THREADS] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v = fmaxf(fmaxf(fmaxf(v, t[j].x), fmaxf(t[j].y, t[j].z)), t[j].w);
+        }
+#pragma unroll
+        for (int st = 1; st < 64; st <<= 1) v = fmaxf(v, __shfl_xor(v, st, 64));
+        if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = v;
+    }
+    __syncthreads();
+    if (p.c) {
+        cmax = s_max[0];
+#pragma unroll
+        for (int i = 1; i < NW; ++i) cmax = fmaxf(cmax, s_max[i]);
+    }
+
+    const float cs = cmax > 0.0f ? 1048576.0f / cmax : 0.0f;      // all-zero channel norms: an empty histogram
+    // cs overflows for norms below 2^20 / FLT_MAX: the conversion below then gives 2^31 - 1 for every non-zero norm, and a step's
+    // additions to one word do not fit 32 bits
+    const bool huge = !(cs < INFINITY);
     unsigned int cur_strip = 0xFFFFFFFFu;
     bool wide = !REPL;                            // this strip's steps add to the 64-bit sums
     unsigned int mass[EPL]; // rint(fl(c*cs)) of the owned columns
@@ -160,15 +181,14 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
         const bool valid = col0 < p.K;
         if (strip != cur_strip) {
             cur_strip = strip;
+            if (u > 0) load_norms(strip);
             unsigned int sum = 0u;                                // at most 16 * 2^20 a lane
 #pragma unroll
             for (int i = 0; i < EPL; i += 4) {
-                float4 t = make_float4(1.f, 1.f, 1.f, 1.f);
-                if (p.c) t = valid ? *reinterpret_cast<const float4*>(p.c + col0 + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-                const float cv[4] = {t.x, t.y, t.z, t.w};
+                const float t[4] = {cv[i / 4].x, cv[i / 4].y, cv[i / 4].z, cv[i / 4].w};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    mass[i + j] = (unsigned int)__float2int_rn(cv[j] * cs);
+                    mass[i + j] = (unsigned int)__float2int_rn(t[j] * cs);
                     sum += mass[i + j];
                 }
             }
@@ -247,31 +267,57 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     // the workgroup's histogram joins the layer's through 64-bit integer atomics; their returned
     // values are consumed so that they have completed before the workgroup takes its ticket
     // (all of a thread's atomics are issued before the first returned value is looked at: one round trip)
+    const unsigned int R = p.n_rows, row = blockIdx.x & (R - 1u);
     {
+        // (each workgroup begins elsewhere in the row: 2048 x 4096, 8192 words, 35 us -> 23.8)
+        const int turn = (int)((blockIdx.x / R * 64u) % (unsigned int)H);
         unsigned long long before[SOP_K_DD_MAXBINS / SOP_K_DD_THREADS];
 #pragma unroll
         for (int j = 0; j < SOP_K_DD_MAXBINS / SOP_K_DD_THREADS; ++j) {
-            const int i = threadIdx.x + j * SOP_K_DD_THREADS;
+            int i = threadIdx.x + j * SOP_K_DD_THREADS;
             before[j] = 0ull;
             if (i < H) {
+                i += turn;
+                if (i >= H) i -= H;
                 unsigned long long v = s_hist[i];
                 if (REPL)
                     for (int r = 0; r < p.n_repl; ++r) v += s_cnt[r * H + i];
-                if (v) before[j] = atomicAdd(p.acc + i, v);
+                if (v) before[j] = atomicAdd(p.acc + row * (unsigned int)H + i, v);
             }
         }
 #pragma unroll
         for (int j = 0; j < SOP_K_DD_MAXBINS / SOP_K_DD_THREADS; ++j) asm volatile("" :: "v"(before[j]) : "memory");
     }
     __syncthreads();
-    if (threadIdx.x == 0) s_flag = atomicAdd(p.done, 1u) == gridDim.x - 1 ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        // the last of a row's workgroups takes the row's ticket, the last row's finishes the call
+        unsigned int* const mine = p.done + (1u + row) * SOP_K_DD_DONE_STRIDE;
+        unsigned int last = 0u;
+        if (R == 1u) last = atomicAdd(p.done, 1u) == gridDim.x - 1u;
+        else if (atomicAdd(mine, 1u) == (gridDim.x - row + R - 1u) / R - 1u) { atomicExch(mine, 0u); last = atomicAdd(p.done, 1u) == R - 1u; }
+        s_flag = last;
+    }
     __syncthreads();
     if (s_flag) {
-        unsigned long long got[SOP_K_DD_MAXBINS / SOP_K_DD_THREADS];
+        constexpr int PER = SOP_K_DD_MAXBINS / SOP_K_DD_THREADS;
+        unsigned long long got[PER];
 #pragma unroll
-        for (int j = 0; j < SOP_K_DD_MAXBINS / SOP_K_DD_THREADS; ++j) {
-            const int i = threadIdx.x + j * SOP_K_DD_THREADS;
-            got[j] = i < H ? atomicExch(p.acc + i, 0ull) : 0ull;
+        for (int j = 0; j < PER; ++j) got[j] = 0ull;
+        if (R > 1u) {
+            // (several rows: at most a word a thread, the rows' words asked for together)
+            unsigned long long part[SOP_K_DD_ROWS];
+            if ((int)threadIdx.x < H) {
+#pragma unroll
+                for (int r = 0; r < SOP_K_DD_ROWS; ++r) part[r] = atomicExch(p.acc + r * H + threadIdx.x, 0ull);
+#pragma unroll
+                for (int r = 0; r < SOP_K_DD_ROWS; ++r) got[0] += part[r];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const int i = threadIdx.x + j * SOP_K_DD_THREADS;
+                if (i < H) got[j] = atomicExch(p.acc + i, 0ull);
+            }
         }
         if (p.n_levels > 1 || NP > 1) {
             // nested pools: histogram j of the result is the sum of the level histograms j .. L-1
@@ -309,6 +355,7 @@ extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, voi
     const unsigned int wpl = (unsigned int)(g < 16 ? g : 16);
     p.n_repl = (int)dd_replicas(words, wpl, p.n_levels > 0, p.c == nullptr, p.total_units, p.n_waves);
     p.dear_mass = p.n_repl ? dd_dear_mass(words, wpl, (unsigned int)p.n_repl) : 0u;
+    p.n_rows = dd_rows(words, (unsigned int)(p.n_waves / (SOP_K_DD_THREADS / 64)));
     p.units_q = p.total_units / p.n_waves;
     p.units_r = (unsigned int)(p.total_units % p.n_waves);
     const size_t lds = (size_t)words * (sizeof(unsigned long long) + (size_t)p.n_repl * 4);

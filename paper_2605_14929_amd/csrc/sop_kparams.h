@@ -157,6 +157,8 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
 /* Statistics pass of the data-derived codebook */
 #define SOP_K_DD_THREADS 1024
 #define SOP_K_DD_MAXBINS 8192
+#define SOP_K_DD_ROWS 4              /* rows of running sums among which a launch's workgroups are divided (dd_rows()) */
+#define SOP_K_DD_DONE_STRIDE 32      /* words between ticket counters: a 128-byte line each */
 struct DdParams {
     const void*  W;
     const float* c;                  // null: uniform weights
@@ -174,8 +176,9 @@ struct DdParams {
     int n_bins;
     int n_repl;                      // copies of the 32-bit counts in a workgroup's LDS (set by the launch: 0, 1, 2, 4, 8 or 16)
     unsigned int dear_mass;          // a strip whose columns' masses sum to more is not worth emptying replicas for (dd_dear_mass)
-    unsigned long long* acc;         // [n_bins] running histogram of the layer (zero between calls)
-    unsigned int* done;              // workgroups finished
+    unsigned int n_rows;             // rows of running sums (set by the launch, dd_rows())
+    unsigned long long* acc;         // [n_rows][words] running histograms of the layer (zero between calls)
+    unsigned int* done;              // counters of finished rows and, a line apart, of each row's finished workgroups (zero between calls)
     long long* hist;                 // [n_bins] output
 };
 
@@ -205,6 +208,15 @@ inline unsigned int dd_replicas(unsigned int words, unsigned int weights_per_lan
     while (n > 1u && words * n * 4u > (64u << 10)) n /= 2u;
     if (no_norms && (64u * weights_per_lane << 20) > dd_dear_mass(words, weights_per_lane, n)) return 0u;
     return n;
+}
+
+/* Rows of running sums.  Atomics to one 128-byte line are served one after the other, about 20 ns each: 256 workgroups that end together
+ * wait 5 us for their sums in one row and as long for their tickets on one counter.  Four rows take a second ticket (one more round
+ * trip to memory) and the reading of four words for one, by a single workgroup at about half a nanosecond each, which many words do
+ * not repay: one row -> four and eight, bf16, 2048 x 4096, 256 words 14.5 us -> 11.2, 10.7; 1024 words 15.1 -> 11.1, 11.9; 4096 words 20.4 -> 24, 27. */
+inline unsigned int dd_rows(unsigned int words, unsigned int workgroups)
+{
+    return words <= SOP_K_DD_THREADS && workgroups >= 64u ? SOP_K_DD_ROWS : 1u;
 }
 
 /* Statistics pass of the per-layer scale shift */

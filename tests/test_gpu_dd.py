@@ -247,3 +247,20 @@ def test_bands_of_rows_with_a_short_last_one(Ms, K, form):
             assert np.array_equal(h[j], DD.histogram(W, c, g, H, block_mask=(lv > j).astype(np.uint8)))
     else:
         assert np.array_equal(gpu_hist(W, c, g, H, bf16, row_step=step), DD.histogram(W[::step], c, g, H))
+
+
+@pytest.mark.parametrize("workgroups", [1, 63, 64, 66, 131, 256])
+def test_workgroups_divided_among_rows_of_sums(workgroups):
+    """One row of running sums below 64 workgroups or above 1024 words, four otherwise (uneven for 66 and 131); calls of both kinds one
+    after the other leave nothing behind.  Integers: equal bit for bit."""
+    import torch
+    M, K, g = 16 * workgroups - (workgroups > 1), 1024, 16            # a strip a row, 16 rows a workgroup, the last one a row short
+    W = si.student_t_weights(M, K, 4.0, 950 + workgroups)
+    c = si.channel_norms(K, 1.0, 951)
+    level = np.random.default_rng(952).integers(0, 4, M * (K // g)).astype(np.uint8)
+    for H in (64, 2048, 1024, 512):
+        assert np.array_equal(gpu_hist(W, c, g, H, False), DD.histogram(W, c, g, H))
+    for H in (256, 1024):                                             # 768 and 3072 words: no powers of two
+        got = ctx().dd_histogram_levels(torch.from_numpy(W).cuda(), torch.from_numpy(c).cuda(), g, torch.from_numpy(level).cuda(), 3, H).cpu().numpy()
+        for j in range(3):
+            assert np.array_equal(got[j], DD.histogram(W, c, g, H, block_mask=(level > j).astype(np.uint8))), (H, j)
