@@ -344,10 +344,11 @@ __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float
     return s;
 }
 
-// Element pass of N atoms of one scale group at once (slots a .. a+N-1; metrics WSE and MSE): the scaled weight and its
+// Element pass of N atoms of one scale group at once (slots a .. a+N-1): the scaled weight and its
 // table address are formed once per element, used for every atom and dropped, so no array of either is ever held.  Same
-// arithmetic, in the same order, as eval_residual.  CODES: one atom (N = 1).
-template <int EPL, int METRIC, int N, bool CODES, bool RANK, bool KEEPCW, class SRC>
+// arithmetic, in the same order, as eval_residual (metrics WSE and MSE) or eval_direct (metric COS; ERR: with the error sum).  CODES: one
+// atom (N = 1).
+template <int EPL, int METRIC, int N, bool CODES, bool RANK, bool KEEPCW, bool ERR, class SRC>
 __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const float (&cb)[EPL], const SRC& src, float ss, int a, Sums (&out)[N],
                                                     bool wide_codes, uint32_t (&codes)[EPL / 4])
 {
@@ -379,13 +380,15 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
                 const int i = i0 + j;
                 const bool up = xe[j] > r[n][j].thr;
                 const float yv = up ? r[n][j].yhi : r[n][j].ylo;
-                const float d = __fmaf_rn(-ss, yv, w[i]);
-                const float cd = cb[i] * d;
-                const float dd = METRIC == 2 ? d : cd;
-                if (i < 8) e0[n] = __fmaf_rn(dd, d, e0[n]); else e1[n] = __fmaf_rn(dd, d, e1[n]);
-                wd[n] = __fmaf_rn(cd, w[i], wd[n]);
-                if (METRIC == 2) ew[n] = __fmaf_rn(cd, d, ew[n]);
-                if constexpr (RANK) {
+                if constexpr (ERR) {
+                    const float d = __fmaf_rn(-ss, yv, w[i]);
+                    const float cd = cb[i] * d;
+                    const float dd = METRIC == 2 ? d : cd;
+                    if (i < 8) e0[n] = __fmaf_rn(dd, d, e0[n]); else e1[n] = __fmaf_rn(dd, d, e1[n]);
+                    if (METRIC != 1) wd[n] = __fmaf_rn(cd, w[i], wd[n]);
+                    if (METRIC == 2) ew[n] = __fmaf_rn(cd, d, ew[n]);
+                }
+                if constexpr (RANK || METRIC == 1) {
                     float wi = w[i];
                     if constexpr (!KEEPCW) asm volatile("" : "+v"(wi));       // (c w is formed again for every atom rather than kept: 16 registers)
                     rk[n].add(i, wi, cb[i], ss, yv);
@@ -396,14 +399,16 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
         // one chunk's look-ups in flight at a time: four wavefronts per SIMD hide them, and more in flight would cost the fourth
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            asm volatile("" : "+v"(e0[n]), "+v"(e1[n]), "+v"(wd[n]));
+            if constexpr (ERR) asm volatile("" : "+v"(e0[n]), "+v"(e1[n]));
+            if constexpr (METRIC != 1) asm volatile("" : "+v"(wd[n]));
             if constexpr (METRIC == 2) asm volatile("" : "+v"(ew[n]));
-            if constexpr (RANK) asm volatile("" : "+v"(rk[n].n0), "+v"(rk[n].n1), "+v"(rk[n].d0), "+v"(rk[n].d1));
+            if constexpr (RANK || METRIC == 1) asm volatile("" : "+v"(rk[n].n0), "+v"(rk[n].n1), "+v"(rk[n].d0), "+v"(rk[n].d1));
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int n = 0; n < N; ++n) {
+        if constexpr (METRIC == 1) { wd[n] = rk[n].num(); ew[n] = rk[n].den(); }
         out[n].err = EPL == 16 ? e0[n] + e1[n] : e0[n]; out[n].wd = wd[n]; out[n].ew = ew[n];
         if constexpr (RANK) { out[n].rn = rk[n].num(); out[n].rd = rk[n].den(); }
     }
@@ -659,7 +664,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 {
     static_assert(!MULTI || !EMIT, "the model-wide kernel searches only");
     constexpr bool SIGNED = SIGNMODE == 1, ARGMAX = SIGNMODE == 2;
-    constexpr bool GROUPED = SIGNMODE == 0 && METRIC != 1 && EPL == 16;   // atoms of a scale group are evaluated four or two at a time
+    // atoms of a scale group are evaluated four or two at a time.  (Not for the planes of more than two atoms under the cosine metric, whose sums
+    // leave two wavefronts either way: 4096 x 11008, six atoms, every plane, 182 us atom by atom, 217 in groups)
+    constexpr bool GROUPED = SIGNMODE == 0 && EPL == 16 && (METRIC != 1 || !EMIT || NA == 2);
     // the direct cosine sums outside the grouped passes: in the form that keeps registers low for the variants that are short of them
     // (the others have some left, and the form's scheduling fences cost the signed eight-atom search a sixth: 4096 x 4096, 77 us
     // -> 92; the signed one-atom search with every plane, g = 32, takes 33.4 us with it and 35.0 without)
@@ -1040,8 +1047,18 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             const bool want_rank = EMIT && p.blk_rank, want_codes = EMIT && p.codes;      // wave-uniform
             // the atom's share of the outputs: decision score, deficit 1 - cos in units of 2^-22 (see below), planes
             auto settle = [&](int a, const Sums& s, bool have_codes) __attribute__((always_inline)) {
-                const Cand t = finish_residual<LPB, METRIC>(s, nsc);
-                score[a] = t.err; den[a] = 1.0f;
+                Cand t;
+                float ny_raw = 0.0f, dy_raw = 0.0f;
+                if constexpr (METRIC == 1) {
+                    t = finish_direct<LPB>(s);
+                    score[a] = t.dy > 0.0f ? t.ny * fabsf(t.ny) : 0.0f;
+                    den[a] = t.dy > 0.0f ? t.dy : 1.0f;
+                    ny_raw = t.ny; dy_raw = t.dy;
+                    t.ny *= nsc.sc; t.dy *= nsc.sc;    // (the decision sums are raw: brought to the scaled norm's units)
+                } else {
+                    t = finish_residual<LPB, METRIC>(s, nsc);
+                    score[a] = t.err; den[a] = 1.0f;
+                }
                 const float rs = __frsqrt_rn(__fmaf_rn(nsc.wns, t.dy, 1.0e-37f));
                 dlt[a] = (int)__float_as_uint(__fmaf_rn(-t.ny, rs, 3.0f)) - 0x40000000;
                 acca[a] += dlt[a];
@@ -1050,7 +1067,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     const long long ua = p.uidx[a];
                     if (have_codes && valid) store_codes<EPL>(p, sw, a, cm, (long long)(cs * 64u + (unsigned int)lane) * EPL, codes);
                     if (want_rank) {
-                        const float r = rank_score(group_sum<LPB>(s.rn), group_sum<LPB>(s.rd), wn);
+                        const float r = METRIC == 1 ? rank_score(ny_raw, dy_raw, wn) : rank_score(group_sum<LPB>(s.rn), group_sum<LPB>(s.rd), wn);
                         if (leader) p.blk_rank[ua * p.Nb + blk] = r;
                     }
                     if (p.scale_code && leader) p.scale_code[ua * p.Nb + blk] = (uint16_t)sp.q;
@@ -1070,7 +1087,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 float lo = 0.0f, hi = 0.0f;
                 if (CL) { const float4 g2 = s_gpar[2 * a + 1]; lo = g2.x; hi = g2.y; }
                 Sums sn[N];
-                eval_residual_group<EPL, METRIC, N, CD, RK, NA == 2>(w, cb, FlySrc<EPL, CL>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
+                eval_residual_group<EPL, METRIC, N, CD, RK && METRIC != 1, NA == 2, METRIC != 1 || EMIT>(w, cb, FlySrc<EPL, CL>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
 #pragma unroll
                 for (int n = 0; n < N; ++n) settle(a + n, sn[n], CD && want_codes);
             };
@@ -1483,25 +1500,27 @@ namespace {
 // Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling (the
 // signed cosine search, with its chunks of look-ups kept apart, at three: 4096 x 4096, six atoms, g = 16, bf16, 47.8 us against 51.6
 // with 18 to 61 registers spilled, fp32 52.8 at three against 59.5 at two, eight atoms 67.6 against 76.8).  The passes that
-// evaluate a scale group's atoms together (16 elements a lane, positive scale, metrics WSE and MSE) hold neither scaled weights
+// evaluate a scale group's atoms together (16 elements a lane, positive scale) hold neither scaled weights
 // nor table addresses and fit one wavefront more than the others: the headline layer (4096 x 11008, six atoms) takes 75.7 us at
 // four against 78.4 with the arrays at three, a 28672 x 8192 layer with seven atoms 530 us at three against 640 at two.  fp32
-// weights keep 8 more registers of requested rows: one wavefront less where that is the difference.
-constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int metric)
+// weights keep 8 more registers of requested rows: one wavefront less where that is the difference.  Metric COS, from the arrays of one
+// atom at a time at two wavefronts: 4096 x 11008, bf16, 2 / 4 / 6 / 7 atoms 40.2 / 76.3 / 96.6 / 112 us -> 37.6 / 59.6 / 83 / 104.5, two atoms with every
+// plane 84 -> 72.7, fp32 4096 x 4096, six atoms 43.2 -> 37.4; the model-wide search of six atoms (bf16) spills a register at four wavefronts.
+constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int metric, bool multi)
 {
     if (epl == 8) {
         if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;
         if (sign_mode == 1) return emit ? 2 : 3;
         return (emit || na == 8) ? 3 : 4;
     }
-    if (sign_mode == 0 && metric != 1) {
-        if (!emit) return na == 8 ? 3 : (na == 2 || bf16) ? 4 : 3;
-        return na == 2 || (na == 6 && bf16) ? 3 : 2;
+    if (sign_mode == 0) {
+        if (!emit) return na == 8 || (na == 6 && metric == 1 && multi) ? 3 : (na == 2 || bf16) ? 4 : 3;
+        return na == 2 || (na == 6 && bf16 && metric != 1) ? 3 : 2;
     }
     if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : 3;
     if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 && metric != 1) ? 2 : 3;
     if (emit) return 2;
-    return (na == 8 || metric == 1) ? 2 : 3;        // the cosine metric keeps two more sums per candidate alive
+    return (na == 8 || metric == 1) ? 2 : 3;        // (argmax rule) the cosine metric keeps two more sums per candidate alive
 }
 
 // one variant: *occ = wavefronts per SIMD its registers allow (a workgroup has 4 * occ wavefronts).  mode 0: one
@@ -1511,13 +1530,15 @@ template <bool BF16, int EPL, int LPB, int S, bool E, int NA>
 const void* variant(int mode, int* occ, int* mode_out)
 {
     constexpr int MT = SOPK_PART_METRIC;
-    constexpr int O = occ_for(BF16, EPL, S, E, NA, MT);
+    constexpr int O = occ_for(BF16, EPL, S, E, NA, MT, false);
     *occ = O;
     *mode_out = 0;
     if constexpr (!E && NA != 2) {
         if (mode == 2) {
+            constexpr int OM = occ_for(BF16, EPL, S, E, NA, MT, true);
+            *occ = OM;
             *mode_out = 2;
-            return reinterpret_cast<const void*>(&sopk::search_kernel<BF16, EPL, LPB, S, MT, E, NA, O, true>);
+            return reinterpret_cast<const void*>(&sopk::search_kernel<BF16, EPL, LPB, S, MT, E, NA, OM, true>);
         }
     }
     return reinterpret_cast<const void*>(&sopk::search_kernel<BF16, EPL, LPB, S, MT, E, NA, O, false>);

@@ -79,3 +79,24 @@ def test_every_set_of_planes(planes, name, fmt_name, g):
     if "codes" in planes:
         for x, y in zip(full.code_planes, ref.codes):
             assert np.array_equal(x.cpu().numpy(), y)
+
+
+@pytest.mark.parametrize("name", PATTERNS)
+@pytest.mark.parametrize("g,bf16", [(16, True), (16, False), (32, False), (64, True)])
+def test_every_grouping_under_the_cosine_metric(name, g, bf16):
+    """The searches and the planes of one and two atoms evaluate groups of atoms; wider planes atom by atom.  The model-wide search gives the
+    single call's bits."""
+    import torch
+    tabs, fmt = _tabs(name), sop.fmt_by_name("UE4M4")
+    W, c = _weights(bf16, 41), si.channel_norms(K, 1.0, 42)
+    ref = ops.pair_search(W, c, tabs, g, oracle_fmt(fmt), metric=1, want_codes=True)
+    P = len(tabs) * (len(tabs) - 1) // 2
+    for emit in (False, True):
+        got = run_gpu(W, c, tabs, g, fmt, metric=1, bf16=bf16, emit=emit)
+        compare(got, ref, P, emit=emit)
+    Wt = torch.from_numpy(W).cuda()
+    pairs, atoms, _ = ctx().pair_search_layers([(Wt.to(torch.bfloat16) if bf16 else Wt, torch.from_numpy(c).cuda())] * 3, g, fmt, metric=1)
+    for l in range(3):
+        assert np.array_equal(atoms[l].cpu().numpy(), got["acos_atom"])
+        if P:
+            assert np.array_equal(pairs[l].cpu().numpy(), got["acos_pair"])
