@@ -1402,8 +1402,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // that total to the eighth: two round trips to memory on the last workgroup's path (sums, a ticket and the reading of the sums were
         // three, with up to 256 tickets on one address; six atoms: 256 x 1024 10.3 us -> 9.5, 1024 x 4096 16.7 -> 13.8, 4096 x 11008
         // 72.0 -> 69.8).  All adds are of integers: their order does not matter.
-        // Counts in units of 2^56 (up to 255 workgroups a word) and 2^60; the sums stay below 2^54 and 2^58 (2^37 lane steps of at most
-        // 2^23 are more than the card's memory holds); a bias keeps each above zero (a lane's sum can be a few units below).
+        // Counts in units of 2^56 (up to 255 workgroups a word) and 2^60.  A lane step reads 16 bytes or more, so the card's 288 GB hold fewer than 2^35 of
+        // at most 2^23 each: below 2^58 in all, and below 2^56 in a word that takes a seventh of the workgroups (with fewer than seven
+        // workgroups there are few steps); a bias keeps each above zero (a lane's sum can be a few units below).
         // Lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1 to every column; the count column
         // takes them out again.
         const int o = tid;

@@ -1,0 +1,28 @@
+"""The layer's sums count the workgroups that have added to them: few workgroups, as many as there are words to add to and one
+more or less, all of a card's; consecutive calls of different alphabets leave nothing behind."""
+import numpy as np
+import pytest
+
+import paper_2605_14929_amd as sop
+from oracle import atoms as OA, pairsearch as ops
+import sop_inputs as si
+from gpu_util import compare, oracle_fmt, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+NF, SH = OA.to_f32(OA.nf(4)), OA.to_f32(OA.sh(4))
+SETS = [[NF], [NF, SH, OA.to_f32(OA.negate(OA.nf(4)))], [OA.to_f32(OA.nf(5)), NF, SH, OA.to_f32(OA.sh(5)), OA.to_f32(OA.negate(OA.sh(4))), OA.to_f32(OA.negate(OA.nf(4))), OA.to_f32(OA.negate(OA.nf(5)))]]
+
+
+@pytest.mark.parametrize("M", [1, 3, 5, 23, 25, 28, 29, 33, 57, 257, 1023])     # (a step a row: a workgroup per one to four of them)
+def test_few_to_many_workgroups(M):
+    K, g, fmt = 1032, 8, sop.fmt_by_name("UE4M4")                    # 129 lanes: two full strips and one of a single lane
+    W, c = si.student_t_weights(M, K, 4.0, 7300 + M), si.channel_norms(K, 1.0, 7301)
+    W[0, :512] = 0.0                                                  # blocks without norm count 1
+    first = None
+    for tabs in SETS + SETS[:1]:
+        got = run_gpu(W, c, tabs, g, fmt, emit=False)
+        compare(got, ops.pair_search(W, c, tabs, g, oracle_fmt(fmt)), len(tabs) * (len(tabs) - 1) // 2, emit=False)
+        if first is None:
+            first = got
+    assert np.array_equal(got["acos_atom"], first["acos_atom"])       # (the last call repeats the first, bit for bit)
