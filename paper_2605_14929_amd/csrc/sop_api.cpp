@@ -572,10 +572,11 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
     // (3 e + 6: three times the cost of a step of e evaluations, since a workgroup of the present layer reduction costs about a third of the
     // 10 ns the rule weighs it with: a row of one atom and 1531 steps 6.7 us -> 6.2, 169 small calls 1.3 % faster, none slower)
-    const long long wg = search_workgroups(p.total_units, c->n_cu, 3 * (emit ? 2 * evals : evals) + 6);
+    const long long wg = search_workgroups(p.total_units, std::min(c->n_cu, SOP_K_SEARCH_MAXWG), 3 * (emit ? 2 * evals : evals) + 6);
     p.deal = p.total_units <= 4ll * SOP_K_SHORT_SHARE * c->n_cu ? 1u : 0u;
     p.units_q = (unsigned int)(p.total_units / wg); p.units_r = (unsigned int)(p.total_units % wg);
     p.grid_magic = grid_magic(wg);
+    p.sum_max = sum_max((unsigned int)wg);
     if (!launch) return SOP_OK;
     if (use_static) {
         const int n_words = (int)kSumsWords, n_thr = std::max(n_words, p.n_tab_codes);

@@ -103,6 +103,7 @@ struct KParams {
     // turns them into the ACos outputs and leaves the sums (and the model-wide kernel's counter) at zero for the next call
     unsigned long long* sums;        // [SOP_K_REPL][SOP_K_NCOL]
     unsigned int* done;              // workgroups finished (zero between calls; room for 1 + SOP_K_REPL words)
+    long long sum_max;               // (single search) the largest sum that a workgroup adds, sum_max(workgroups)
     double*   acos_pair;
     double*   acos_atom;
     void*     sel_words;             // [Nb] selector word of every block
@@ -153,6 +154,28 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
     }
     return best;
 }
+
+/* Layer sums of a single search.  A word of them counts in its top bits the workgroups that have added to it (units of 2^56 in the first
+ * SOP_K_REPL - 1 rows, of 2^60 in the last one, which takes those rows' totals).  A sum must never reach into its count or borrow from it,
+ * whatever the weights held: a word that misses its count is not cleared, and spoils the calls that follow.  A bias beside every one of a
+ * count keeps a word's sum above zero, and a workgroup's sum is cut to SOP_K_SUM_MIN .. sum_max() before it is added.
+ * That changes none of a valid layer: a lane step reads 16 bytes or more, so 288 GB hold fewer than 2^35 of at most 2^23 each, below 2^58 for the
+ * layer, and a large layer is spread evenly over all compute units (26 or more: sum_max(g) >= 2^58 / g); a lane's sum can be a few units below
+ * zero.  Where a block's own sums leave binary32's range the lanes' 32-bit sums wrap: a NaN deficit counts 2^30 - 2^22, four of them -2^24. */
+#define SOP_K_SEARCH_MAXWG 256       /* workgroups of a single search (one per compute unit) */
+#define SOP_K_SUM_MIN (-(1ll << 48))
+constexpr unsigned long long kSumOne1 = (1ull << 56) + (1ull << 49), kSumOne2 = (1ull << 60) + (1ull << 54);
+/* workgroups that add to first-row word r of a launch of g, and first-row words that g workgroups add to */
+SOP_K_HD constexpr unsigned int sum_members(unsigned int g, unsigned int r) { return (g - r + SOP_K_REPL - 2u) / (SOP_K_REPL - 1u); }
+SOP_K_HD constexpr unsigned int sum_rows_used(unsigned int g) { return g < SOP_K_REPL - 1u ? g : SOP_K_REPL - 1u; }
+/* largest sum that a workgroup of a launch of g adds */
+SOP_K_HD constexpr long long sum_max(unsigned int g) { return (45ll << 50) / sum_members(g, 0u); }
+/* what workgroup sum v adds to its first-row word; what a complete first-row word s (of m workgroups) adds to the last row's */
+SOP_K_HD constexpr unsigned long long sum_add1(long long v, long long max) { return kSumOne1 + (unsigned long long)(v < SOP_K_SUM_MIN ? SOP_K_SUM_MIN : v > max ? max : v); }
+SOP_K_HD constexpr unsigned long long sum_add2(unsigned long long s, unsigned int m) { return kSumOne2 + (s - m * kSumOne1); }
+constexpr long long kSumMostMembers = sum_members(SOP_K_SEARCH_MAXWG, 0u);
+static_assert((45ll << 50) + kSumMostMembers * (1ll << 49) < (1ll << 56) && SOP_K_SUM_MIN + (1ll << 49) > 0, "a first-row sum stays within its 56 bits");
+static_assert((SOP_K_REPL - 1) * ((45ll << 50) + (1ll << 54)) < (1ll << 60) && kSumMostMembers * SOP_K_SUM_MIN + (1ll << 54) > 0, "a last-row sum stays within its 60 bits");
 
 /* Statistics pass of the data-derived codebook */
 #define SOP_K_DD_THREADS 1024

@@ -1402,9 +1402,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // that total to the eighth: two round trips to memory on the last workgroup's path (sums, a ticket and the reading of the sums were
         // three, with up to 256 tickets on one address; six atoms: 256 x 1024 10.3 us -> 9.5, 1024 x 4096 16.7 -> 13.8, 4096 x 11008
         // 72.0 -> 69.8).  All adds are of integers: their order does not matter.
-        // Counts in units of 2^56 (up to 255 workgroups a word) and 2^60.  A lane step reads 16 bytes or more, so the card's 288 GB hold fewer than 2^35 of
-        // at most 2^23 each: below 2^58 in all, and below 2^56 in a word that takes a seventh of the workgroups (with fewer than seven
-        // workgroups there are few steps); a bias keeps each above zero (a lane's sum can be a few units below).
+        // (Range of the sums beside their counts: SOP_K_SUM_MIN and sum_max().)
         // Lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1 to every column; the count column
         // takes them out again.
         const int o = tid;
@@ -1413,19 +1411,18 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             double* const to = o < p.A ? p.acos_atom : p.acos_pair;
             if (to) {
                 constexpr unsigned int R = SOP_K_REPL - 1;
-                const unsigned int r = blockIdx.x % R, members = (G - r + R - 1u) / R, used = G < R ? G : R;
-                const long long v = (long long)(s_acc[oc & 0xFFu] - s_acc[NLIVE - 1]);
-                constexpr unsigned long long one1 = (1ull << 56) + (1ull << 40), one2 = (1ull << 60) + (1ull << 48);
+                const unsigned int r = blockIdx.x % R, members = sum_members(G, r), used = sum_rows_used(G);
                 unsigned long long* const w1 = p.sums + r * SOP_K_NCOL + o;
                 unsigned long long* const w2 = p.sums + R * SOP_K_NCOL + o;
-                const unsigned long long s1 = atomicAdd(w1, one1 + (unsigned long long)v) + one1 + (unsigned long long)v;
+                const unsigned long long add1 = sum_add1((long long)(s_acc[oc & 0xFFu] - s_acc[NLIVE - 1]), p.sum_max);
+                const unsigned long long s1 = atomicAdd(w1, add1) + add1;
                 if ((s1 >> 56) == members) {
                     __hip_atomic_store(w1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);       // (zero for the next call)
-                    const unsigned long long add = one2 + (s1 - members * one1);
-                    const unsigned long long s2 = atomicAdd(w2, add) + add;
+                    const unsigned long long add2 = sum_add2(s1, members);
+                    const unsigned long long s2 = atomicAdd(w2, add2) + add2;
                     if ((s2 >> 60) == used) {
                         __hip_atomic_store(w2, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        to[oc >> 8] = 1.0 - ((double)(long long)(s2 - used * one2) * (1.0 / 4194304.0)) / ((double)p.Nb * (double)p.lpb);
+                        to[oc >> 8] = 1.0 - ((double)(long long)(s2 - used * kSumOne2) * (1.0 / 4194304.0)) / ((double)p.Nb * (double)p.lpb);
                     }
                 }
             }

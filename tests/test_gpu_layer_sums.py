@@ -26,3 +26,22 @@ def test_few_to_many_workgroups(M):
         if first is None:
             first = got
     assert np.array_equal(got["acos_atom"], first["acos_atom"])       # (the last call repeats the first, bit for bit)
+
+
+def test_a_layer_beyond_binary32_spoils_only_its_own_result():
+    """Finite weights whose norms overflow give a NaN deficit, which takes 2^28 a step off a workgroup's sum (the lanes' 32-bit sums wrap): 5120 steps of it
+    go below -2^40.  The call that follows is as if there had been none."""
+    import torch
+    cx = sop.Context(0)                                               # (a context of its own)
+    fmt, g = sop.fmt_by_name("UE4M4"), 8
+    W, c = si.student_t_weights(64, 1032, 4.0, 7400), si.channel_norms(1032, 1.0, 7401)
+    ref = ops.pair_search(W, c, SETS[1], g, oracle_fmt(fmt))
+    Wt, ct = torch.from_numpy(W).cuda(), torch.from_numpy(c).cuda()
+    cx.set_alphabet(SETS[1])
+    big = torch.full((32768, 20480), 1e30, dtype=torch.bfloat16, device="cuda")
+    cb = torch.full((20480,), 1e10, dtype=torch.float32, device="cuda")
+    cx.pair_search(big, cb, g, fmt, emit=False)
+    for _ in range(2):
+        out = cx.pair_search(Wt, ct, g, fmt, emit=False)
+        assert np.max(np.abs(out.acos_atom.cpu().numpy() - ref.acos_atom)) <= 1e-6
+        assert np.max(np.abs(out.acos_pair.cpu().numpy()[:3] - ref.acos_pair)) <= 1e-6
