@@ -570,9 +570,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     // steps takes fewer (search_workgroups()).
     int evals = 0;                               // (a sign-negated copy under a signed word takes its original's candidates over)
     for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
-    // (3 e + 6: three times the cost of a step of e evaluations, since a workgroup of the present layer reduction costs about a third of the
-    // 10 ns the rule weighs it with: a row of one atom and 1531 steps 6.7 us -> 6.2, 169 small calls 1.3 % faster, none slower)
-    const long long wg = search_workgroups(p.total_units, std::min(c->n_cu, SOP_K_SEARCH_MAXWG), 3 * (emit ? 2 * evals : evals) + 6);
+    const long long wg = search_workgroups(p.total_units, std::min(c->n_cu, SOP_K_SEARCH_MAXWG), emit ? 2 * evals : evals);
     p.deal = p.total_units <= 4ll * SOP_K_SHORT_SHARE * c->n_cu ? 1u : 0u;
     p.units_q = (unsigned int)(p.total_units / wg); p.units_r = (unsigned int)(p.total_units % wg);
     p.grid_magic = grid_magic(wg);

@@ -136,21 +136,20 @@ struct LayerDesc {
 
 /* Workgroups of a search, one per compute unit at most, from whole steps per SIMD.  A step more on every SIMD costs about
  * 0.3 us + 0.1 us per evaluation (evaluations: codebooks times signs tried, twice that where planes are written), a workgroup
- * more 10 ns in the layer reduction (about 3 ns since the reduction counts its workgroups in the sums themselves: the launch states its evaluations
- * accordingly, see pair_search_impl).  Beyond SOP_K_SHORT_SHARE steps
- * a SIMD every compute unit has a workgroup.  Measured at 64 to 4500 steps over 31 kinds of call against every number of
- * workgroups that changes the steps per SIMD: 0.1 % above the best on average, 3 % at worst (one atom, 1024 steps: 8.5 us with
- * 86 workgroups, 9.7 with 256; six atoms, 1536: 13.6 with 192, 14.3 with 128 or 256; every plane of six signed ones, 1536: 24.3 with
- * 192, 33.7 with 128). */
+ * more about 10/3 ns in the layer reduction.  Beyond SOP_K_SHORT_SHARE steps a SIMD every compute unit has a workgroup.
+ * Measured at 64 to 8000 steps over 31 kinds of call, captured in a graph, against every number of workgroups that changes the steps per
+ * SIMD: 0.3 % above the best on average, 5.6 % at worst (one atom with every plane, 8000 steps: 14.3 us with 250 workgroups,
+ * 13.6 with 256; one atom, 771: 5.3 with 193, 5.6 with 97; 1024: 5.6 with 128, 5.4 with 256; six atoms, 1536: 9.8 with 192 or 256, 11.2 with 128;
+ * every plane of six signed ones, 1536: 21.5 with 192, 31.9 with 128). */
 #define SOP_K_SHORT_SHARE 8
 inline long long search_workgroups(long long steps, int n_cu, int evaluations)
 {
     const long long least = (steps + 4ll * n_cu - 1) / (4ll * n_cu);
     if (least > SOP_K_SHORT_SHARE) return n_cu;
-    long long best = 0, best_ns = 0;
+    long long best = 0, best_cost = 0;
     for (long long s = least; s <= SOP_K_SHORT_SHARE; ++s) {
-        const long long wg = (steps + 4 * s - 1) / (4 * s), ns = s * (300 + 100 * evaluations) + 10 * wg;
-        if (best == 0 || ns < best_ns) { best = wg; best_ns = ns; }
+        const long long wg = (steps + 4 * s - 1) / (4 * s), cost = s * (900 + 300 * evaluations) + 10 * wg;       // (in thirds of a nanosecond)
+        if (best == 0 || cost < best_cost) { best = wg; best_cost = cost; }
     }
     return best;
 }
