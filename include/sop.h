@@ -179,10 +179,9 @@ sop_status sop_prepare_scale(sop_ctx* ctx, sop_scale_fmt fmt, int layer_shift_k,
 /* sop_pair_search() for callers that cannot allocate: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments (without the workspace), same kernels, same results bit
  * for bit; the call itself calls no hipMalloc / hipFree and no allocating library routine.  What
- * sop_pair_search() keeps in memory of the context allocated on demand (the running sums and ticket
- * counters of the layer reduction, the table of (scale, reciprocal) per scale code) lives here in a
- * statically allocated device array of SOP_STATIC_SCRATCH_BYTES bytes that is part of the library's device
- * image: every GPU the library runs on holds one copy until the process ends.  A small kernel at the start
+ * sop_pair_search() keeps in memory of the context (the running sums of the layer reduction, the table
+ * of (scale, reciprocal) per scale code) lives here in a statically allocated device array of
+ * SOP_STATIC_SCRATCH_BYTES bytes that is part of the library's device image: every GPU the library runs on holds one copy until the process ends.  A small kernel at the start
  * of the call clears the sums and writes the scale table for (fmt, layer_shift_k); it is launched on
  * hip_stream before the search kernel (no memset node, so the pair may be captured into a graph).
  * Limit: the scale word may have at most SOP_STATIC_MAX_CODES magnitude codes (max_code < 2048, i.e.

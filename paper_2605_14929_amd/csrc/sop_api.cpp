@@ -51,11 +51,11 @@ static constexpr size_t kLsDone = kLsMax + 16 * SOP_K_LS_MAXREP;
 static constexpr size_t kLsWords = kLsDone + 17 * SOP_K_LS_DONE_STRIDE / 2;
 static constexpr int kMaxLayers = 1024;  // layers of one launch of the model-wide kernel (more are dealt with in several launches)
 static constexpr int kStabSlots = 160;   // (scale, reciprocal) tables kept on the device: more than the layer shifts one call can name (129)
-static constexpr size_t kSumsWords = SOP_K_REPL * SOP_K_NCOL + SOP_K_REPL + 1;   // one set of layer sums and tickets, in 64-bit words
+static constexpr size_t kSumsWords = SOP_K_REPL * SOP_K_NCOL;   // one set of layer sums, in 64-bit words
 static constexpr size_t kDdWords = SOP_K_DD_MAXBINS + (1 + SOP_K_DD_ROWS) * SOP_K_DD_DONE_STRIDE / 2;       // running histograms and ticket counters of the statistics passes, in 64-bit words
 
 // ---- scratch of the entry point that allocates nothing (sop_pair_search_static) ----
-// One set of layer sums with its ticket counters, then the (scale, reciprocal) table of the call's scale
+// One set of layer sums, then the (scale, reciprocal) table of the call's scale
 // word.  The array lives in the library's device image: every GPU the library runs on holds its own copy
 // at its own address until the process ends.  Host code never uses the array's name as an address: the
 // address on a device comes from hipGetSymbolAddress (static_scratch_of) and is what kernels are given.
@@ -82,7 +82,7 @@ static hipError_t static_scratch_of(int device, unsigned char** out)
     return hipSuccess;
 }
 
-// Start of a static call: the sums and tickets are cleared (an earlier call that did not finish may have left
+// Start of a static call: the sums are cleared (an earlier call that did not finish may have left
 // anything there) and the scale table of this call's scale word and layer shift is written:
 // value(q) * 2^-k (exact) and its IEEE reciprocal, the same values the host builds for sop_pair_search.
 __global__ void static_prologue_kernel(unsigned long long* sums, int n_words, float2* tab, int n_codes, int y, int bias, int k)
@@ -101,7 +101,7 @@ struct sop_ctx {
     int n_cu = 0;
     size_t lds_max = 0;                   // LDS one workgroup may use
     LayerDesc* d_ldesc = nullptr;         // [kMaxLayers] layer list of the model-wide kernel
-    unsigned long long* d_msums = nullptr; // its sums [kMaxLayers][SOP_K_REPL][SOP_K_NCOL] and tickets (zero between calls)
+    unsigned long long* d_msums = nullptr; // its sums [kMaxLayers][SOP_K_REPL][SOP_K_NCOL] and, behind them, its ticket counter (zero between calls)
     LayerDesc* h_ldesc[2] = {nullptr, nullptr};   // pinned staging for the layer list, used in turn
     hipEvent_t ldesc_copied[2] = {nullptr, nullptr};  // the copy out of each staging buffer has run
     bool ldesc_pending[2] = {false, false};
@@ -133,7 +133,7 @@ struct sop_ctx {
     int selm_set = 0;
     int selm_dirty[2] = {0, 0};           // planes of each set of the batched ranking's digit counts that hold counts
     SelMState* d_selstate = nullptr;      // [SOP_K_MAXA] what the passes of that ranking hand on, per score plane
-    unsigned long long* d_sums = nullptr; // two sets of [SOP_K_REPL][SOP_K_NCOL] layer sums followed by their ticket counters; zero between calls
+    unsigned long long* d_sums = nullptr; // two sets of [SOP_K_REPL][SOP_K_NCOL] layer sums; zero between calls
     hipStream_t lane_stream[kLanes] = {};   // sop_pair_search_layers deals the layers out to streams of its own
     hipEvent_t lane_event[kLanes + 1] = {};  // one per stream (join) and one for the fork
     float2* d_stab = nullptr;             // [kStabSlots][SOP_K_MAXTABCODES] (scale * 2^-k, reciprocal) tables, written by a kernel on first use
@@ -224,7 +224,7 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
         delete c;
         return hipfail(nullptr, e, "hipMalloc(rank counts of the sweep)");
     }
-    const size_t msums_bytes = sizeof(unsigned long long) * ((size_t)kMaxLayers * SOP_K_REPL * SOP_K_NCOL + SOP_K_REPL + 1);
+    const size_t msums_bytes = sizeof(unsigned long long) * ((size_t)kMaxLayers * SOP_K_REPL * SOP_K_NCOL + 1);
     if ((e = hipMalloc((void**)&c->d_ldesc, sizeof(LayerDesc) * kMaxLayers)) != hipSuccess ||
         (e = hipMalloc((void**)&c->d_msums, msums_bytes)) != hipSuccess || (e = hipMemset(c->d_msums, 0, msums_bytes)) != hipSuccess ||
         (e = hipHostMalloc((void**)&c->h_ldesc[0], sizeof(LayerDesc) * kMaxLayers, hipHostMallocDefault)) != hipSuccess ||
@@ -526,7 +526,6 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         p.pair_col[q] = (unsigned char)(na + i * (2 * na - i - 1) / 2 + (j - i - 1));
     }
     p.sums = use_static ? reinterpret_cast<unsigned long long*>(c->static_scratch) : c->d_sums + (size_t)sums_set * kSumsWords;
-    p.done = reinterpret_cast<unsigned int*>(p.sums + SOP_K_REPL * SOP_K_NCOL);
     p.acos_pair = c->n_pairs ? out->acos_pair : nullptr;
     p.acos_atom = out->acos_atom;
     p.sel_words = c->n_pairs ? out->sel_words : nullptr;
@@ -550,7 +549,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
     const size_t dyn_lds = (((size_t)p.n_bins * SOP_K_BIN_BYTES + 15) & ~(size_t)15) + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15) +
-                           2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_NCOL + search_slots(na)) * sizeof(unsigned long long);
+                           2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_OUT_WORDS + search_slots(na)) * sizeof(unsigned long long);
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds;
     hipError_t e = hipSuccess;
@@ -629,7 +628,7 @@ extern "C" sop_status sop_pair_search_layers(sop_ctx* c, const sop_layer* layers
     if ((reinterpret_cast<uintptr_t>(acos_pair_table) | reinterpret_cast<uintptr_t>(acos_atom_table)) & 7u)
         return fail(c, SOP_EINVAL, "sop_pair_search_layers: tables must be 8-byte aligned");
     // The layers go through the model-wide kernel: one launch works through a list of layers, its wavefronts
-    // passing from layer to layer without a pause (tables loaded once, tickets once), on the caller's stream.
+    // passing from layer to layer without a pause (tables loaded once, one ticket a workgroup), on the caller's stream.
     // Layers are grouped by their layer shift (the scale table in LDS belongs to one shift): a launch per
     // shift, and per kMaxLayers layers.  Where that kernel does not exist (alphabets of one or two atoms) or
     // the tables leave no room in LDS for the layers' sums, there is one kernel per layer, dealt out to two

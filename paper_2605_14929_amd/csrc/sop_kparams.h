@@ -6,6 +6,7 @@
 #define SOP_K_MAXA 8                 /* atoms                                        */
 #define SOP_K_MAXP 28                /* pairs i < j among SOP_K_MAXA atoms           */
 #define SOP_K_NCOL (SOP_K_MAXA + SOP_K_MAXP + 1)   /* sum columns: atoms, pairs, zero-norm lane count */
+#define SOP_K_OUT_WORDS ((SOP_K_MAXA + SOP_K_MAXP + 1) / 2)   /* 64-bit words of a list of the outputs, 32 bits each */
 #define SOP_K_FLUSH_STEPS 60         /* steps a lane's running sums are kept before they join the workgroup's (4 * 60 * 2^23 < 2^31) */
 #define SOP_K_REPL 8                 /* rows of layer sums (spread same-address atomics): replicas, the last one of a single layer's the totals of the others */
 #define SOP_K_MAXBINS 1024           /* bins of the element-search table                        */
@@ -102,7 +103,7 @@ struct KParams {
     // atomics (order-independent, so the result is reproducible); the workgroup that finishes last
     // turns them into the ACos outputs and leaves the sums (and the model-wide kernel's counter) at zero for the next call
     unsigned long long* sums;        // [SOP_K_REPL][SOP_K_NCOL]
-    unsigned int* done;              // workgroups finished (zero between calls; room for 1 + SOP_K_REPL words)
+    unsigned int* done;              // (model-wide kernel) workgroups finished (zero between calls)
     long long sum_max;               // (single search) the largest sum that a workgroup adds, sum_max(workgroups)
     double*   acos_pair;
     double*   acos_atom;

@@ -651,11 +651,11 @@ __device__ __forceinline__ void store_codes(const KParams& p, const Switches& sw
 
 // NA: atoms the kernel is unrolled for (2, 6 or 8).  OCC: wavefronts per SIMD the register budget is set
 // for; a workgroup is 4*OCC wavefronts and fills one compute unit on its own (one copy of the tables in
-// LDS per compute unit, one ticket per compute unit in the layer reduction).
+// LDS per compute unit, one addition per output and compute unit in the layer reduction).
 // MULTI: one launch works through a list of layers (model-wide call).  The workgroups stay, the tables are
 // loaded once, and every share's steps of all the layers form one sequence with one counter: a wavefront
 // passes from a layer to the next without waiting for anyone, adding what it holds to the finished layer's
-// sums in LDS on the way (one set of sums per layer of the launch); tickets and the conversion to ACos happen
+// sums in LDS on the way (one set of sums per layer of the launch); a ticket and the conversion to ACos happen
 // once, at the end of the launch, for all its layers.
 // SIGNMODE 0: the scale is positive; 1: both signs of the scale are tried and the better one kept
 // (signed scale word, absmax rule); 2: argmax rule, the rule fixes the sign.
@@ -681,11 +681,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     const size_t bins_bytes = ((size_t)p.n_bins * SOP_K_BIN_BYTES + 15) & ~(size_t)15;
     float2* s_tab = reinterpret_cast<float2*>(s_mem + bins_bytes);
     float4* s_gpar = reinterpret_cast<float4*>(s_mem + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
-    // reduction scratch: flag word, the final gather's totals, the workgroup's own totals (64-bit integers)
+    // reduction scratch: flag word (MULTI), list of outputs (not MULTI), the workgroup's own totals (64-bit integers)
     unsigned long long* s_red = reinterpret_cast<unsigned long long*>(s_gpar + 2 * SOP_K_MAXA);
     unsigned int* s_out = reinterpret_cast<unsigned int*>(s_red + 1);             // (not MULTI) output: its sum column, and from bit 8 its place in the table
     constexpr int NLIVE = search_cols(NA), NSLOT = search_slots(NA);              // sum columns of this variant: atoms, pairs, count column
-    unsigned long long* s_acc = s_red + 1 + SOP_K_NCOL;                           // [NSLOT] this workgroup's sums (MULTI: per layer)
+    unsigned long long* s_acc = s_red + 1 + SOP_K_OUT_WORDS;                     // [NSLOT] this workgroup's sums (MULTI: per layer)
     const int n_acc = MULTI ? p.n_layers * NSLOT : NSLOT;
     __shared__ unsigned int s_next[4];                                            // next step of each SIMD's share
     const uint32_t lds_neg = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_bins + SOP_K_BIN_NEGC;

@@ -1,7 +1,7 @@
 """The entry point that allocates nothing (sop_pair_search_static) against sop_pair_search: the same
 kernels with the layer sums and the scale table in the library's static device array, so every output
 must agree bit for bit.  Two calls in a row, the second on a smaller layer with another scale word, so
-that what the first call left in the array (sums, tickets, a longer scale table) would show."""
+that what the first call left in the array (sums, a longer scale table) would show."""
 import numpy as np
 import pytest
 
