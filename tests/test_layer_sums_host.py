@@ -3,6 +3,8 @@ every sum a layer can have."""
 import os
 import subprocess
 
+from test_gpu_layer_sums import ROWS_OF, SETS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SRC = r"""
@@ -60,9 +62,23 @@ int main()
 """
 
 
-def test_words_complete_and_clear_for_every_sum(tmp_path):
+def _build(tmp_path, text):
     src, exe = tmp_path / "s.cpp", tmp_path / "s"
-    src.write_text(SRC)
+    src.write_text(text)
     subprocess.check_call(["g++", "-std=c++17", "-fsanitize=undefined", "-fno-sanitize-recover", "-I", os.path.join(ROOT, "paper_2605_14929_amd", "csrc"), "-o", str(exe), str(src)])
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return str(exe)
+
+
+def test_words_complete_and_clear_for_every_sum(tmp_path):
+    r = subprocess.run([_build(tmp_path, SRC)], capture_output=True, text=True)
     assert r.stdout.strip() == "ok", r.stdout + r.stderr
+
+
+def test_the_rows_of_the_gpu_test_take_the_workgroups_it_names(tmp_path):
+    """A step a row (rows of 64 lanes are not folded: a fold wastes no fewer lanes than none), 256 compute units, one evaluation a codebook."""
+    asked = [(w, M, len(tabs)) for w, M in ROWS_OF.items() for tabs in SETS]
+    calls = "".join(f'std::printf("%lld\\n", search_workgroups({M}, 256, {e}));' for _, M, e in asked)
+    out = subprocess.run([_build(tmp_path, '#include <cstdio>\n#include "sop_kparams.h"\nint main() { ' + calls + " }")], capture_output=True, text=True, check=True).stdout
+    assert [int(x) for x in out.split()] == [w for w, _, _ in asked]
+    words = 7                                                         # (first-row words: the grids below, at and above one and two workgroups a word)
+    assert {words - 1, words, words + 1, 2 * words - 1, 2 * words, 2 * words + 1} <= set(ROWS_OF)
