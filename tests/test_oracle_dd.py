@@ -163,6 +163,30 @@ def test_library_host_fit_equals_the_oracle_fit():
     assert e.value.status == 3
 
 
+@pytest.mark.parametrize("H", [64, 1024, 4096])
+def test_fit_of_large_masses_equals_the_oracle_fit(H):
+    """The sums take 64 bits up to a total of (2^62 - 1) / H and 128 above, also where the total itself passes 64 bits: all below, at and above the
+    change, and at the largest counts there are."""
+    rng = np.random.default_rng(53)
+    init = OA.to_f32(OA.nf(4))
+    most = ((1 << 62) - 1) // H
+    for trial in range(6):
+        base = np.histogram(np.clip(0.4 * rng.standard_t(3, size=4000), -1, 1), bins=H, range=(-1, 1))[0].astype(object)
+        for total in (1, most // 2, most - 1, most, most + 1, 2 * most, H * most, 1 << 63, (1 << 64) - 1, 1 << 64, 3 << 64):
+            h = base * max(total // int(base.sum()), 1)
+            b = int(np.argmax(base))
+            if max(h) >= 1 << 63:
+                h = np.array([min(v, (1 << 63) - 1) for v in h], dtype=object)
+            elif total > 1 and h[b] + total - int(h.sum()) < 1 << 63:
+                h[b] += total - int(h.sum())                          # (the total to the unit)
+                assert int(h.sum()) == total
+            h = h.astype(np.int64)
+            mine = sop.sop_dd_fit(h, 16, 12, init)
+            assert np.array_equal(mine, DD.fit(h, 16, 12, init.astype(np.float64)).astype(np.float32)), (trial, total)
+    h = np.full(H, (1 << 63) - 1, dtype=np.int64)
+    assert np.array_equal(sop.sop_dd_fit(h, 16, 12, init), DD.fit(h, 16, 12, init.astype(np.float64)).astype(np.float32))
+
+
 def test_block_mask_equals_zeroing_the_other_blocks():
     W, c = _layer(M=40, K=512, seed=61)
     g = 16
