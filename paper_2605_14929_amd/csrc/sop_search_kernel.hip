@@ -1371,7 +1371,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // One store without a branch ends every path of a step: lanes without a word to store, or all of them, lie past the end the store is given
         // and are dropped by the hardware.  Behind a branch it may or may not be the last access, the compiler waits for every access in
         // flight, and a step began with a wait for memory's answer to the words of the one before (4096 x 11008, six atoms, rows from HBM:
-        // 73.7 us -> 70.5; ragged fp32 layer 22.1 -> 20.8).  (The planes of emit mode keep their branches: a range to set up for each costs
+        // 71.5 us -> 70.1, rows in cache 68.4 -> 68.1; fp32, 1531 x 5024, cosine metric, 20.8 -> 20.1).  (The planes of emit mode keep their branches: a range to set up for each costs
         // more than it saves, 4096 x 11008, two atoms, 67.8 us -> 72.7.)  32-bit words belong to more than sixteen pairs: of the two stores of eight atoms one
         // has nothing to store.
         unsigned int at = (unsigned int)lane;
@@ -1400,8 +1400,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // gets back that it holds the total: no ticket is taken and nothing is read afterwards.  Atomics to one address are served
         // one after the other (about 20 ns each), so a workgroup adds to one of seven words, chosen by its number, and the last of each adds
         // that total to the eighth: two round trips to memory on the last workgroup's path (sums, a ticket and the reading of the sums were
-        // three, with up to 256 tickets on one address; six atoms: 256 x 1024 10.3 us -> 9.5, 1024 x 4096 16.7 -> 13.8, 4096 x 11008
-        // 72.0 -> 69.8).  All adds are of integers: their order does not matter.
+        // three, with up to 256 tickets on one address; six atoms: 256 x 1024 10.1 us -> 9.4, 1024 x 4096 16.1 -> 13.4, 4096 x 11008
+        // 70.1 -> 68.4).  All adds are of integers: their order does not matter.
         // (Range of the sums beside their counts: SOP_K_SUM_MIN and sum_max().)
         // Lanes whose block had zero weighted norm (and lanes past the end of a row) added exactly 1 to every column; the count column
         // takes them out again.
