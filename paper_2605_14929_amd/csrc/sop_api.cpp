@@ -96,6 +96,8 @@ __global__ void static_prologue_kernel(unsigned long long* sums, int n_words, fl
     }
 }
 
+constexpr size_t kImgBytes = (size_t)SOP_K_PAIR_BIN_BYTES * SOP_K_MAXBINS;       // the largest image of an element-search table
+
 struct sop_ctx {
     int device = 0;
     int n_cu = 0;
@@ -111,6 +113,7 @@ struct sop_ctx {
     std::vector<std::vector<float>> tables;
     int pairs[2 * SOP_K_MAXP] = {0};
     // internal order: atoms of one scale group (equal endpoints) adjacent
+    unsigned int rec_bytes = 0;           // distance of the table's records
     int order[SOP_K_MAXA] = {0};          // internal index -> caller's index
     int gid[SOP_K_MAXA] = {0};            // scale group of the internal atom
     int mirror[SOP_K_MAXA] = {0};         // 1: the internal atom is the sign-negated copy of the one before it
@@ -119,9 +122,9 @@ struct sop_ctx {
     float bin_lo[SOP_K_MAXA] = {0}, bin_hi[SOP_K_MAXA] = {0};
     int nent[SOP_K_MAXA] = {0};
     int n_bins = 0;
-    BinRec* d_bins = nullptr;             // [MAXBINS] capacity: the context's own image of the element-search table
-    BinRec* d_bins_cur = nullptr;         // the image the searches read (d_bins, or an image inside a caller's workspace during sop_search_layer)
-    BinRec* h_bins = nullptr;             // pinned staging for table images of sop_search_layer (allocated at its first call)
+    char* d_bins = nullptr;               // (kImgBytes) the context's own image of the element-search table
+    char* d_bins_cur = nullptr;           // the image the searches read (d_bins, or an image inside a caller's workspace during sop_search_layer)
+    char* h_bins = nullptr;               // pinned staging for table images of sop_search_layer (allocated at its first call)
     char* h_res = nullptr;                // pinned staging for its results
     hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
     bool stage_pending = false;
@@ -187,7 +190,7 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
     if ((e = hipGetDeviceProperties(&prop, device)) != hipSuccess) { delete c; return hipfail(nullptr, e, "hipGetDeviceProperties"); }
     c->n_cu = prop.multiProcessorCount;
     c->lds_max = prop.sharedMemPerBlock;
-    if ((e = hipMalloc((void**)&c->d_bins, sizeof(BinRec) * SOP_K_MAXBINS)) != hipSuccess) { delete c; return hipfail(nullptr, e, "hipMalloc(table image)"); }
+    if ((e = hipMalloc((void**)&c->d_bins, kImgBytes)) != hipSuccess) { delete c; return hipfail(nullptr, e, "hipMalloc(table image)"); }
     if ((e = hipMalloc((void**)&c->d_sums, sizeof(unsigned long long) * kLanes * kSumsWords)) != hipSuccess ||
         (e = hipMemset(c->d_sums, 0, sizeof(unsigned long long) * kLanes * kSumsWords)) != hipSuccess) {
         (void)hipFree(c->d_bins); if (c->d_sums) (void)hipFree(c->d_sums);
@@ -291,25 +294,31 @@ static sop_status plan_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, 
 // Plan the alphabet and make it the context's current one.  d_img == nullptr: the context's own image, copied
 // synchronously.  Otherwise the image goes through the pinned buffer h_stage to d_img with a copy on `st`
 // (the host does not wait), and the searches launched from now on read d_img.
-static sop_status install_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, BinRec* d_img, BinRec* h_stage, hipStream_t st)
+static sop_status install_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, char* d_img, char* h_stage, hipStream_t st)
 {
     AlphabetPlan pl;
     if (sop_status s = plan_alphabet(c, atoms, n_atoms, pl)) return s;
+    // records as far apart as the reads of the atoms evaluated together want them (see BinRec)
+    bool together = false;
+    for (int i = 1; i < n_atoms; i += 2) together = together || pl.gid[i] == pl.gid[i - 1];
+    const size_t rec = together ? SOP_K_PAIR_BIN_BYTES : SOP_K_BIN_BYTES, img_bytes = pl.img.size() * rec;
     {
+        std::vector<char> own(d_img ? 0 : img_bytes);
+        char* const to = d_img ? h_stage : own.data();
+        for (size_t b = 0; b < pl.img.size(); ++b) {
+            std::memcpy(to + b * rec, &pl.img[b], sizeof(BinRec));
+            std::memset(to + b * rec + sizeof(BinRec), 0, rec - sizeof(BinRec));
+        }
         DeviceGuard guard(c->device);
         hipError_t e = guard.err;
-        if (e == hipSuccess) {
-            if (d_img) {
-                std::memcpy(h_stage, pl.img.data(), pl.img.size() * sizeof(BinRec));
-                e = hipMemcpyAsync(d_img, h_stage, pl.img.size() * sizeof(BinRec), hipMemcpyHostToDevice, st);
-            } else e = hipMemcpy(c->d_bins, pl.img.data(), pl.img.size() * sizeof(BinRec), hipMemcpyHostToDevice);
-        }
+        if (e == hipSuccess) e = d_img ? hipMemcpyAsync(d_img, to, img_bytes, hipMemcpyHostToDevice, st) : hipMemcpy(c->d_bins, to, img_bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hipfail(c, e, "upload of the table image");
     }
     c->d_bins_cur = d_img ? d_img : c->d_bins;
     c->tables.swap(pl.tabs);
     c->n_atoms = n_atoms;
     c->n_bins = pl.n_bins;
+    c->rec_bytes = (unsigned int)rec;
     for (int i = 0; i < n_atoms; ++i) {
         const std::vector<float>& L = c->tables[pl.order[i]];
         c->order[i] = pl.order[i]; c->gid[i] = pl.gid[i]; c->mirror[i] = pl.mirror[i]; c->selfsym[i] = pl.selfsym[i];
@@ -492,7 +501,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     p.M32 = (unsigned int)M;
     p.m_magic = M == 1 ? 0xFFFFFFFFu : (unsigned int)((1ull << 32) / (unsigned long long)M);
     p.A = A; p.P = c->n_pairs; p.lpb = lpb;
-    p.n_bins = c->n_bins;
+    p.n_bins = c->n_bins; p.rec_bytes = c->rec_bytes;
     p.man_bits = y; p.bias = bias; p.max_code = max_code; p.k = k;
     p.pow2k = std::ldexp(1.0f, k);
     p.sub_quantum = std::ldexp(1.0f, 1 - bias - y - k);
@@ -548,8 +557,14 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     int occ = 1, mode = 0;
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
-    const size_t dyn_lds = (((size_t)p.n_bins * SOP_K_BIN_BYTES + 15) & ~(size_t)15) + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15) +
-                           2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_OUT_WORDS + search_slots(na)) * sizeof(unsigned long long);
+    auto lds_of = [&](int n_codes) {
+        return (size_t)SOP_K_PERM_BYTES(na) + (size_t)p.n_bins * (emit ? SOP_K_WIDE_BIN_BYTES : p.rec_bytes) + (((size_t)n_codes * sizeof(float2) + 15) & ~(size_t)15) +
+               2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_OUT_WORDS + search_slots(na)) * sizeof(unsigned long long);
+    };
+    // (the bin table of 1024 bins with codes beside scale tables of 1000 codes and more: the kernel computes the scales then, to the same bits; 1 KiB is left
+    // for its own variables)
+    if (lds_of(p.n_tab_codes) + 1024 > c->lds_max) p.n_tab_codes = 0;
+    const size_t dyn_lds = lds_of(p.n_tab_codes);
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds;
     hipError_t e = hipSuccess;
@@ -1094,7 +1109,6 @@ extern "C" sop_status sop_pack_blocks(sop_ctx* c, int64_t M, int64_t K, int g, s
 
 // ------------------------------------------------------------------ the per-layer procedure (steps 1 to 4 and the sweep over p)
 namespace {
-constexpr size_t kImgBytes = sizeof(BinRec) * SOP_K_MAXBINS;
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct LayerWs {
     size_t rank, level, hist, tau, na, acos, bins, sc, codes, sel, total;
@@ -1201,8 +1215,8 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     }
     // whatever happens below, the context ends up reading its own image again, with no alphabet set
     struct Restore { sop_ctx* c; ~Restore() { c->d_bins_cur = c->d_bins; c->n_atoms = 0; c->n_pairs = 0; } } restore{c};
-    auto img = [&](int i) { return reinterpret_cast<BinRec*>(base + L.bins + (size_t)i * kImgBytes); };
-    auto himg = [&](int i) { return reinterpret_cast<BinRec*>(reinterpret_cast<char*>(c->h_bins) + (size_t)i * kImgBytes); };
+    auto img = [&](int i) { return reinterpret_cast<char*>(base) + L.bins + (size_t)i * kImgBytes; };
+    auto himg = [&](int i) { return c->h_bins + (size_t)i * kImgBytes; };
     double* d_acos = reinterpret_cast<double*>(base + L.acos);
     float* d_rank = reinterpret_cast<float*>(base + L.rank);
 

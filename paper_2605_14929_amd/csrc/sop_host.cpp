@@ -66,10 +66,9 @@ static bool build_bins(const std::vector<float>& L, float xl, float xh, float sc
         const bool used = j >= b_lo && j <= b_hi;                     // (the others are never addressed)
         if (used && c1 - c0 > 1) return false;
         const int a = used ? c0 : 0, b = used ? c1 : 0;
-        rec[j].thr[ia] = b > a ? mid[a] : inf;
-        rec[j].ylo[ia] = 0.5f * L[a];                // halves (exact: plan_alphabet refuses entries whose half is not)
-        rec[j].yhi[ia] = 0.5f * L[b];
-        rec[j].code_lo[ia] = a;
+        rec[j].val[ia][0] = 0.5f * L[a];             // halves (exact: plan_alphabet refuses entries whose half is not)
+        rec[j].val[ia][1] = b > a ? 0.5f * L[b] : inf;
+        rec[j].code_lo[ia] = (unsigned char)a;
     }
     return true;
 }
@@ -202,13 +201,11 @@ extern "C" sop_status sop_check_alphabet(const sop_atom* atoms, int n_atoms, int
             const int b = bin_of(x, pl.lo[i], pl.hi[i], pl.sc[i], pl.off[i]);
             if (b < 0 || b >= pl.n_bins) return false;
             const BinRec& r = pl.img[b];
-            const bool up = x > r.thr[i];
+            // (the table holds halves; the boundary is formed as their sum)
+            const volatile float thr = r.val[i][0] + r.val[i][1];
+            const bool up = x > thr;
             ++checked;
-            // (the table holds halves; the boundary formed as their sum must choose the same value wherever it is used)
-            const volatile float thr2 = r.ylo[i] + r.yhi[i];
-            const float v_up = x > thr2 ? r.yhi[i] : r.ylo[i];
-            if (v_up + v_up != L[code]) return false;
-            const float v = up ? r.yhi[i] : r.ylo[i];
+            const float v = r.val[i][up];
             return r.code_lo[i] + (up ? 1 : 0) == code && v + v == L[code];
         };
         bool ok = true;

@@ -11,11 +11,12 @@
 #define SOP_K_REPL 8                 /* rows of layer sums (spread same-address atomics): replicas, the last one of a single layer's the totals of the others */
 #define SOP_K_MAXBINS 1024           /* bins of the element-search table                        */
 #define SOP_K_MAXTABCODES 2048       /* scale codes whose (scale, reciprocal) pair is tabulated */
-#define SOP_K_BIN_WORDS (4 * SOP_K_MAXA + 1)   /* words of one bin record (odd: conflict-free banks)  */
-#define SOP_K_BIN_BYTES (4 * SOP_K_BIN_WORDS)
+#define SOP_K_BIN_BYTES (8 * (SOP_K_MAXA + 1))          /* a bin record (see BinRec) */
+#define SOP_K_PAIR_BIN_BYTES (8 * (SOP_K_MAXA + 2))     /* the same where atoms are evaluated two or four at a time */
+#define SOP_K_WIDE_BIN_BYTES (16 * (SOP_K_MAXA + 1))    /* the same in the LDS of kernels that write planes: values, their sum and the code of every atom */
 #define SOP_K_BIN_MAGIC 12582912.0f  /* 1.5 * 2^23: one unit in the last place is 1               */
 /* bits(MAGIC + v) = 0x4B400000 + v; the 24-bit multiply sees 0x400000 + v: subtract its product */
-#define SOP_K_BIN_NEGC (0u - 0x400000u * (unsigned)SOP_K_BIN_BYTES)
+#define SOP_K_BIN_NEGC(bytes) (0u - 0x400000u * (unsigned)(bytes))
 /* The bin table covers scaled weights from BIN_EXT * L[0] to BIN_EXT * L[N-1]: a block scale that
  * was rounded down (by at most a factor 1.5, in the subnormal range of the scale word) leaves every
  * scaled weight inside the table without a clamp.  Blocks whose scale saturated take a clamped path,
@@ -33,6 +34,10 @@ struct float2 { float x, y; };       /* (host-only translation units see the lau
 /* position of (i,j), i < j, in the lexicographic list of all pairs of SOP_K_MAXA atoms */
 SOP_K_HD constexpr int pair_index(int i, int j) { return i * (2 * SOP_K_MAXA - i - 1) / 2 + (j - i - 1); }
 
+/* Tables of 256 selector words that take the pairs from the order in which a search of na atoms forms them to the order requested, and their bytes */
+SOP_K_HD constexpr int search_perm_tables(int na) { return na == 2 ? 0 : (na * (na - 1) / 2 + 7) / 8; }
+#define SOP_K_PERM_BYTES(na) (search_perm_tables(na) * 1024)
+
 /* Sum columns of a variant unrolled for na atoms: atoms, pairs i < j of them (lexicographic), count of zero-norm lanes; and the same
  * rounded up to the four columns that a wavefront adds up together */
 SOP_K_HD constexpr int search_cols(int na) { return na + na * (na - 1) / 2 + 1; }
@@ -40,15 +45,18 @@ SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 *
 
 /* One bin of the element-search table.  For every atom the bin holds at most one code boundary.
  * The two values are stored HALVED (exactly; the element passes multiply by twice the block scale): the boundary
- * between two neighbouring entries then equals the binary32 sum of the two stored values, and the passes that only
- * choose between the values form it with one addition instead of reading it. */
+ * between two neighbouring entries then equals the binary32 sum of the two stored values, and the passes form it with
+ * one addition instead of reading it.  In a bin without a boundary the upper value is +infinity, and so is the sum: nothing
+ * lies above it or on it.
+ * One atom's values come with an 8-byte read of LDS, those of an even slot and the next with a 16-byte one.  An alphabet whose atoms are all evaluated one by one
+ * has its records 72 bytes apart, an odd number of 8-byte words: 32 neighbouring bins have an atom's values in 32 different pairs of LDS's 64 banks.  16-byte
+ * reads want records on 16-byte boundaries; an odd number of those, 80 bytes, puts 16 neighbouring bins into 16 different quadruples of banks.
+ * (72 bytes and ds_read2_b64 for two atoms: 4096 x 11008, six atoms, 1 to 2 % slower; 80 bytes for atoms one by one: five atoms of fitted codebooks 1 % slower.) */
 struct BinRec {
-    float thr[SOP_K_MAXA];      // the boundary inside the bin (+inf when there is none)
-    float ylo[SOP_K_MAXA];      // half of the codebook value at and below the boundary
-    float yhi[SOP_K_MAXA];      // half of the codebook value above the boundary
-    int   code_lo[SOP_K_MAXA];  // code at and below the boundary
-    int   pad;
+    float val[SOP_K_MAXA][2];            // half of the codebook value at and below the boundary, half of the one above it
+    unsigned char code_lo[SOP_K_MAXA];   // code at and below the boundary
 };
+static_assert(sizeof(BinRec) == SOP_K_BIN_BYTES && SOP_K_BIN_BYTES % 16 == 8 && SOP_K_PAIR_BIN_BYTES % 32 == 16 && SOP_K_WIDE_BIN_BYTES % 32 == 16 && SOP_K_MAXA % 2 == 0, "odd numbers of words");
 
 /* Atoms are handled in an internal order in which atoms with equal endpoints (one "scale group":
  * same ideal scale, same scale code, same scaled weights) are adjacent, and an atom that is the
@@ -57,7 +65,7 @@ struct KParams {
     // inputs
     const void*   W;
     const float*  c;
-    const BinRec* bins;              // [n_bins], atoms in internal order
+    const char*   bins;              // [n_bins] records (BinRec) rec_bytes apart, atoms in internal order
     const float2* stab;              // [n_tab_codes] (twice the scale value(q) * 2^-k, the scale's reciprocal), or null
     long long M, K, ldw;             // as the kernel walks the layer: rows may be folded (see Kc)
     long long Kc;                    // true row length.  When the rows lie back to back (ldw == K) and 64 lanes do not divide a
@@ -73,6 +81,7 @@ struct KParams {
     unsigned int M32, m_magic;       // M, and floor(2^32 / M) (2^32 - 1 for M = 1): step number -> (strip, row)
     int A, P, lpb;
     int n_bins;
+    unsigned int rec_bytes;          // SOP_K_BIN_BYTES or SOP_K_PAIR_BIN_BYTES
     int n_tab_codes;                 // 0: scale and reciprocal are computed arithmetically
     // scale word
     int man_bits, bias, max_code, k;

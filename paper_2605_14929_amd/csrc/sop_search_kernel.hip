@@ -11,9 +11,8 @@
 //
 // Every block is read from HBM exactly once.  LDS holds a table over uniform bins of the scaled
 // weight x: for every atom each bin contains at most one code boundary, so the nearest entry is a
-// table read and one compare.  A bin is a record of 33 words (boundary, half the lower value, half the
-// upper value and lower code of each of the 8 atoms, one word of padding; see read_rec for the halves):
-// the odd stride puts the same field of 32 consecutive bins into 32 different banks.  For scale words of
+// table read and one compare.  A bin is a record (BinRec) of half the lower and half the upper value of each of the 8 atoms; the boundary
+// is their sum.  For scale words of
 // up to 11 magnitude bits LDS also holds (twice the scale, the scale's reciprocal) of every scale code.
 //
 // Atoms with equal endpoints form a scale group: they share the ideal scale, the scale code and the
@@ -159,7 +158,7 @@ __device__ __forceinline__ ScalePrep prepare_scale(float pmax, float nmax, bool 
 template <int EPL, bool ARGMAX>
 __device__ __forceinline__ void prepare_sign(const float (&w)[EPL], float pmax, float nmax, bool negative, int a,
                                              const KParams& p, const Switches& sw, const float2* __restrict__ s_tab,
-                                             const float4* __restrict__ s_gpar, uint32_t lds_neg,
+                                             const float4* __restrict__ s_gpar, uint32_t lds_neg, uint32_t rec,
                                              int& q, float& ss, bool& nonzero, float (&x)[EPL], uint32_t (&boff)[EPL], bool& neg_out)
 {
     const float4 gp = s_gpar[2 * a];                   // (t+, -t-, bin scale, bin offset): same address in every lane
@@ -191,7 +190,7 @@ __device__ __forceinline__ void prepare_sign(const float (&w)[EPL], float pmax, 
         for (int i = 0; i < EPL; ++i) {
             x[i] = w[i] * rr;
             const float xc = __builtin_amdgcn_fmed3f(x[i], g2.x, g2.y);
-            boff[i] = __umul24(__float_as_uint(__fmaf_rn(xc, sc, off)), SOP_K_BIN_BYTES) + lds_neg;
+            boff[i] = __umul24(__float_as_uint(__fmaf_rn(xc, sc, off)), rec) + lds_neg;
         }
     } else {
 #pragma unroll
@@ -199,7 +198,7 @@ __device__ __forceinline__ void prepare_sign(const float (&w)[EPL], float pmax, 
             x[i] = w[i] * rr;
             // off carries 1.5*2^23, so the low mantissa bits of the sum are the bin number; one 24-bit
             // multiply-add turns them into the byte offset of the bin record
-            boff[i] = __umul24(__float_as_uint(__fmaf_rn(x[i], sc, off)), SOP_K_BIN_BYTES) + lds_neg;
+            boff[i] = __umul24(__float_as_uint(__fmaf_rn(x[i], sc, off)), rec) + lds_neg;
         }
     }
 }
@@ -208,22 +207,25 @@ __device__ __forceinline__ void prepare_sign(const float (&w)[EPL], float pmax, 
 // prepare_sign (a scale group's atoms share them), or formed on the spot from the weight and the scale's reciprocal
 // (signed scale words: the arrays of two signs would cost a wavefront per SIMD in registers, and with every atom
 // evaluated under two scales there is little left to share).  Same arithmetic either way.
-template <int EPL>
+// WIDE: the records are those of kernels that write planes (SOP_K_WIDE_BIN_BYTES).
+template <int EPL, bool WIDE_>
 struct ArrSrc {
+    static constexpr bool WIDE = WIDE_;
     const float (&x)[EPL];
     const uint32_t (&boff)[EPL];
     __device__ __forceinline__ void get(int i, float& xo, uint32_t& bo) const { xo = x[i]; bo = boff[i]; }
 };
-template <int EPL, bool CLAMP>
+template <int EPL, bool CLAMP, bool WIDE_>
 struct FlySrc {
+    static constexpr bool WIDE = WIDE_;
     const float (&w)[EPL];
     float rr, sc, off, lo, hi;
-    uint32_t lds_neg;
+    uint32_t lds_neg, rec;
     __device__ __forceinline__ void get(int i, float& xo, uint32_t& bo) const
     {
         xo = w[i] * rr;
         const float xc = CLAMP ? __builtin_amdgcn_fmed3f(xo, lo, hi) : xo;
-        bo = __umul24(__float_as_uint(__fmaf_rn(xc, sc, off)), SOP_K_BIN_BYTES) + lds_neg;
+        bo = __umul24(__float_as_uint(__fmaf_rn(xc, sc, off)), rec) + lds_neg;
     }
 };
 
@@ -250,30 +252,42 @@ struct RankSums {
     __device__ __forceinline__ float den() const { return EPL == 16 ? d0 + d1 : d0; }
 };
 
-// One bin record read: boundary, value below, value above (and the lower code when codes are wanted).
+// What an element pass reads of a bin record (BinRec): the halved values below and above the boundary, and the code below it when codes are wanted.
 // `addr` is the LDS byte address of the record and A the atom's slot in it: all reads are register + immediate offset.
 // The table holds HALF of each codebook value (exact: the host refuses entries whose half is not), and every
 // element pass multiplies by twice the block scale, which is the same product.  What that buys: the boundary
 // between two neighbouring entries, the binary64 mean rounded once to binary32, equals the binary32 sum of their
-// halves (one rounding of the same real number; the host checks it entry by entry), so a pass that needs the
-// boundary only to choose between the two values forms it with one addition instead of reading it.  LDS serves
-// 128 bytes a clock to the four SIMDs of a compute unit: with 12 bytes per weight and codebook the element passes
-// were bound by that, with 8 they are bound by the vector ALUs.  In a bin without a boundary both values are the
-// same entry, so the choice does not matter there; passes that form codes or look for scaled weights exactly on a
-// boundary (THR) read the stored boundary, which is +infinity in such bins.
-typedef __attribute__((address_space(3))) const float lds_cfloat;
-typedef __attribute__((address_space(3))) const int lds_cint;
+// halves (one rounding of the same real number; the host checks it entry by entry), so it is formed with one addition
+// instead of being read.  In a bin without a boundary the upper value, and with it the sum, is +infinity: no scaled weight lies above it or on it.
+// What bounds a pass is issue: a SIMD's four wavefronts get one instruction of any kind into about 2.4 cycles, and an LDS instruction takes
+// as much as one to two vector ones whatever it reads (64 vector instructions 150 cycles, with eight 4-, 8- or 16-byte reads among them 175 to 187).  LDS itself
+// serves two 4-byte reads (ds_read2_b32) of 64 lanes at random bins in 5.1 cycles, an 8-byte read in 2.9, a 16-byte one in 6.9.  So two atoms of one
+// group are read together with 16 bytes, and one alone with 8 (4-byte fields at 132-byte records before: 96 look-ups a step of six atoms, now 64).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const f32x2 lds_f32x2;
+typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+// Kernels that write planes hold for every atom of a bin its two values, their sum and the code below: a pass that forms codes takes all four
+// with one instruction.
 struct Rec { float thr, ylo, yhi; int clo; };
-template <bool THR, bool CODES>
+template <bool WIDE> __device__ __forceinline__ f32x2 read_pair(uint32_t addr, int a) { return ((lds_f32x2*)(size_t)addr)[WIDE ? 2 * a : a]; }
+// (lower, upper) of slots a and a + 1, a even
+template <bool WIDE> __device__ __forceinline__ f32x4 read_two(uint32_t addr, int a)
+{
+    if constexpr (!WIDE) return ((lds_f32x4*)(size_t)addr)[a / 2];
+    else { const f32x2 u = read_pair<WIDE>(addr, a), v = read_pair<WIDE>(addr, a + 1); return {u[0], u[1], v[0], v[1]}; }
+}
+template <bool WIDE, bool CODES>
 __device__ __forceinline__ Rec read_rec(uint32_t addr, int a)
 {
-    lds_cfloat* rp = (lds_cfloat*)(size_t)addr;
-    Rec r;
-    if (THR) r.thr = rp[a];
-    r.ylo = rp[SOP_K_MAXA + a]; r.yhi = rp[2 * SOP_K_MAXA + a];
-    if (!THR) r.thr = r.ylo + r.yhi;
-    r.clo = CODES ? ((lds_cint*)(size_t)addr)[3 * SOP_K_MAXA + a] : 0;
-    return r;
+    static_assert(!CODES || WIDE, "codes are formed where planes are written");
+    if constexpr (CODES) {
+        const f32x4 v = ((lds_f32x4*)(size_t)addr)[a];
+        return {v[2], v[0], v[1], __float_as_int(v[3])};
+    } else {
+        const f32x2 v = read_pair<WIDE>(addr, a);
+        return {v[0] + v[1], v[0], v[1], 0};
+    }
 }
 
 template <int EPL, bool CODES>
@@ -304,18 +318,20 @@ __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float
 #pragma unroll
         for (int j = 0; j < EPL / 4; ++j) codes[j] = 0;
     }
+    // (look-ups in flight: two where the variant of 8-element lanes with most sums has no registers for four)
+    constexpr int CH = EPL == 8 && CODES && RANK && METRIC == 2 ? 2 : 4;
 #pragma unroll
-    for (int i0 = 0; i0 < EPL; i0 += 4) {
-        Rec r[4];
-        float xe[4];
+    for (int i0 = 0; i0 < EPL; i0 += CH) {
+        Rec r[CH];
+        float xe[CH];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < CH; ++j) {
             uint32_t bo;
             src.get(i0 + j, xe[j], bo);
-            r[j] = read_rec<CODES || TIES, CODES>(bo, a);
+            r[j] = read_rec<SRC::WIDE, CODES>(bo, a);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < CH; ++j) {
             const int i = i0 + j;
             const bool up = xe[j] > r[j].thr;
             if constexpr (TIES) *tie |= __builtin_amdgcn_ballot_w64(xe[j] == r[j].thr);
@@ -353,7 +369,11 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
                                                     bool wide_codes, uint32_t (&codes)[EPL / 4])
 {
     static_assert(N == 1 || !CODES, "codes are formed atom by atom");
-    constexpr int CH = N > 2 || (N > 1 && RANK) ? 2 : 4;                  // elements whose look-ups are in flight
+    // Elements whose look-ups are in flight.  Atoms evaluated together ask for the next elements' look-ups before the ones at hand are used, at half as many
+    // elements a set (same registers; 28672 x 8192, seven atoms 8 % of a search, a model's layers 2 %).  One atom alone does not: five atoms of fitted codebooks, 4096 x 11008,
+    // 73.2 us against 75.1.
+    constexpr bool AHEAD = METRIC != 1 && !SRC::WIDE && N > 1;
+    constexpr int CH = AHEAD ? (N > 2 ? 1 : N > 1 ? 2 : 4) : N > 2 || (N > 1 && RANK) ? 2 : 4;
     float e0[N], e1[N], wd[N], ew[N];
     RankSums<EPL> rk[N];
 #pragma unroll
@@ -362,23 +382,45 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
 #pragma unroll
         for (int j = 0; j < EPL / 4; ++j) codes[j] = 0;
     }
-#pragma unroll
-    for (int i0 = 0; i0 < EPL; i0 += CH) {
-        Rec r[N][CH];
-        float xe[CH];
+    f32x4 r4[AHEAD ? 2 : 1][(N + 1) / 2][CH];
+    Rec r[N][CH];
+    float xe[AHEAD ? 2 : 1][CH];
+    auto ask = [&](int i0, int b) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
             uint32_t bo;
-            src.get(i0 + j, xe[j], bo);
+            src.get(i0 + j, xe[b][j], bo);
+            if constexpr (CODES) r[0][j] = read_rec<SRC::WIDE, true>(bo, a);
+            else if constexpr (N == 1) { const f32x2 v = read_pair<SRC::WIDE>(bo, a); r4[b][0][j] = {v[0], v[1], 0.0f, 0.0f}; }
+            else {
 #pragma unroll
-            for (int n = 0; n < N; ++n) r[n][j] = read_rec<CODES, CODES>(bo, a + n);
+                for (int n = 0; n < N; n += 2) r4[b][n / 2][j] = read_two<SRC::WIDE>(bo, a + n);
+            }
+        }
+    };
+    if constexpr (AHEAD) ask(0, 0);
+#pragma unroll
+    for (int i0 = 0; i0 < EPL; i0 += CH) {
+        const int b = AHEAD ? (i0 / CH) & 1 : 0;
+        if constexpr (AHEAD) {
+            if (i0 + CH < EPL) ask(i0 + CH, b ^ 1);
+            __builtin_amdgcn_sched_barrier(0);
+        } else ask(i0, 0);
+        if constexpr (!CODES) {
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+#pragma unroll
+                for (int j = 0; j < CH; ++j) {
+                    const float lo = r4[b][n / 2][j][n % 2 * 2], hi = r4[b][n / 2][j][n % 2 * 2 + 1];
+                    r[n][j] = {lo + hi, lo, hi, 0};
+                }
         }
 #pragma unroll
         for (int n = 0; n < N; ++n) {
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
                 const int i = i0 + j;
-                const bool up = xe[j] > r[n][j].thr;
+                const bool up = xe[b][j] > r[n][j].thr;
                 const float yv = up ? r[n][j].yhi : r[n][j].ylo;
                 if constexpr (ERR) {
                     const float d = __fmaf_rn(-ss, yv, w[i]);
@@ -434,7 +476,7 @@ __device__ __forceinline__ Sums eval_direct(const float (&w)[EPL], const float (
         for (int j = 0; j < 4; ++j) {
             uint32_t bo;
             src.get(i0 + j, xe[j], bo);
-            r[j] = read_rec<CODES || TIES, CODES>(bo, a);
+            r[j] = read_rec<SRC::WIDE, CODES>(bo, a);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -470,7 +512,7 @@ __device__ __forceinline__ Sums eval_direct(const float (&w)[EPL], const float (
 // (y is read as the table holds it, halved: the ratio does not change.)
 // LEAN: the products c w of the block statistics are formed again rather than kept for it in registers, and four look-ups are in
 // flight at a time.
-template <int EPL, int LPB, bool THR, bool LEAN, class SRC>
+template <int EPL, int LPB, bool LEAN, class SRC>
 __device__ __forceinline__ void direct_cosine_sums(const float (&cb)[EPL], const float (&w)[EPL], const SRC& src, bool nonzero, bool negative,
                                                    int a, float& ny_out, float& dy_out)
 {
@@ -480,7 +522,7 @@ __device__ __forceinline__ void direct_cosine_sums(const float (&cb)[EPL], const
         float xe;
         uint32_t bo;
         src.get(i, xe, bo);
-        const Rec r = read_rec<THR, false>(bo, a);
+        const Rec r = read_rec<SRC::WIDE, false>(bo, a);
         const float yv = xe > r.thr ? r.yhi : r.ylo;
         float wi = w[i];
         if constexpr (LEAN) asm volatile("" : "+v"(wi));
@@ -546,8 +588,95 @@ constexpr PairTab make_pair_tab()
 }
 constexpr PairTab kPairTab = make_pair_tab();
 template <int PI> struct PairOf { static constexpr int i = kPairTab.first[PI], j = kPairTab.second[PI]; };
+template <int V> struct ic { constexpr operator int() const { return V; } };      // a compile-time integer as an argument
 
-// Selector of pair PI and of all following pairs (i < j in internal order): bit `slot` of the
+// The pairs of a block by their errors' bit patterns, which order as the errors do (none is negative or a NaN).  The selector is "b strictly
+// better than a" for the caller's pair (a, b), and the internal order may have swapped the two, in which case internal j keeps the block on a tie:
+// pick_j = error[j] < error[i] + swapped, the borrow of a subtraction with a carry.  A pair adds the chosen atom's deficit to its running sum and
+// shifts its bit into `chain` by the carry of an addition; pair (i, j) ends at bit chain_bit(i, j).  Five instructions a pair and no test of
+// whether it is requested, where the general form takes eleven (scalar instructions and branches cost about as much issue time as vector ones).
+constexpr int chain_bit(int i, int j) { return j * (j - 1) / 2 + i; }
+// Up to three pairs (i, J) at once: a lane mask that a vector instruction writes may be read by another two instructions later at the earliest, which
+// three subtractions in a row are.  (The compiler makes more of either carry.)   SOPK_FIELD: offset and width of the pair's bit in `flips`.
+#define SOPK_FIELD(i, j) (pair_index(i, j) | 1 << 16)
+template <int J, int I>
+__device__ __forceinline__ void pairs_1(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    unsigned long long m0;
+    int t0;
+    asm("s_bfe_i64 %[m0], %[fl], %[f0]\n"
+        "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n s_nop 1\n"
+        "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n"
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]"
+        : [m0] "=&s"(m0), [t0] "=&v"(t0), [s0] "+v"(accp[pair_index(I, J)]), [ch] "+v"(chain)
+        : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [d0] "v"(dlt[I]), [f0] "n"(SOPK_FIELD(I, J)) : "scc");
+}
+// pairs (I, J) and (I - 1, J)
+template <int J, int I>
+__device__ __forceinline__ void pairs_2(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    unsigned long long m0, m1;
+    int t0, t1;
+    asm("s_bfe_i64 %[m0], %[fl], %[f0]\n s_bfe_i64 %[m1], %[fl], %[f1]\n"
+        "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n v_subb_co_u32 %[t1], %[m1], %[ej], %[e1], %[m1]\n s_nop 0\n"
+        "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n v_cndmask_b32 %[t1], %[d1], %[dj], %[m1]\n"
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]\n"
+        "v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]\n v_add_u32 %[s1], %[s1], %[t1]"
+        : [m0] "=&s"(m0), [m1] "=&s"(m1), [t0] "=&v"(t0), [t1] "=&v"(t1), [s0] "+v"(accp[pair_index(I, J)]), [s1] "+v"(accp[pair_index(I - 1, J)]), [ch] "+v"(chain)
+        : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [e1] "v"(score[I - 1]), [d0] "v"(dlt[I]), [d1] "v"(dlt[I - 1]),
+          [f0] "n"(SOPK_FIELD(I, J)), [f1] "n"(SOPK_FIELD(I - 1, J)) : "scc");
+}
+// pairs (I, J), (I - 1, J) and (I - 2, J)
+template <int J, int I>
+__device__ __forceinline__ void pairs_3(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    unsigned long long m0, m1, m2;
+    int t0, t1, t2;
+    asm("s_bfe_i64 %[m0], %[fl], %[f0]\n s_bfe_i64 %[m1], %[fl], %[f1]\n s_bfe_i64 %[m2], %[fl], %[f2]\n"
+        "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n v_subb_co_u32 %[t1], %[m1], %[ej], %[e1], %[m1]\n v_subb_co_u32 %[t2], %[m2], %[ej], %[e2], %[m2]\n"
+        "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n v_cndmask_b32 %[t1], %[d1], %[dj], %[m1]\n v_cndmask_b32 %[t2], %[d2], %[dj], %[m2]\n"
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]\n"
+        "v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]\n v_add_u32 %[s1], %[s1], %[t1]\n"
+        "v_addc_co_u32 %[ch], %[m2], %[ch], %[ch], %[m2]\n v_add_u32 %[s2], %[s2], %[t2]"
+        : [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [s0] "+v"(accp[pair_index(I, J)]),
+          [s1] "+v"(accp[pair_index(I - 1, J)]), [s2] "+v"(accp[pair_index(I - 2, J)]), [ch] "+v"(chain)
+        : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [e1] "v"(score[I - 1]), [e2] "v"(score[I - 2]),
+          [d0] "v"(dlt[I]), [d1] "v"(dlt[I - 1]), [d2] "v"(dlt[I - 2]), [f0] "n"(SOPK_FIELD(I, J)), [f1] "n"(SOPK_FIELD(I - 1, J)), [f2] "n"(SOPK_FIELD(I - 2, J)) : "scc");
+}
+#undef SOPK_FIELD
+// pairs (N - 1, J) .. (0, J) in this order
+template <int J, int N>
+__device__ __forceinline__ void pair_column(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    constexpr int done = N == 1 ? 1 : (N == 2 || N == 4) ? 2 : 3;
+    if constexpr (done == 1) pairs_1<J, N - 1>(flips, score, dlt, accp, chain);
+    else if constexpr (done == 2) pairs_2<J, N - 1>(flips, score, dlt, accp, chain);
+    else pairs_3<J, N - 1>(flips, score, dlt, accp, chain);
+    if constexpr (N > done) pair_column<J, N - done>(flips, score, dlt, accp, chain);
+}
+template <int J, int NA>
+__device__ __forceinline__ void ordered_pairs(int A, unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    // (a variant unrolled for six serves three atoms or more, one for eight seven or more)
+    if (J < (NA == 8 ? 7 : 3) || J < A) pair_column<J, J>(flips, score, dlt, accp, chain);
+    if constexpr (J > 1) ordered_pairs<J - 1, NA>(A, flips, score, dlt, accp, chain);
+}
+
+// Pair PI and the following ones where an error is a NaN: internal i keeps the block
+template <int PI, int NA>
+__device__ __forceinline__ void nan_pairs(const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+{
+    constexpr int i = PairOf<PI>::i, j = PairOf<PI>::j, c = chain_bit(i, j);
+    if constexpr (j < NA) {
+        if (((chain >> c) & 1u) && !(score[i] == score[i] && score[j] == score[j])) {
+            accp[PI] += dlt[i] - dlt[j];
+            chain ^= 1u << c;
+        }
+    }
+    if constexpr (PI + 1 < SOP_K_MAXP) nan_pairs<PI + 1, NA>(score, dlt, accp, chain);
+}
+
+// Selector of pair PI and of all following pairs (i < j in internal order), for every metric and alphabet: bit `slot` of the
 // block's selector word, and the chosen atom's deficit into the pair's running sum.
 template <int PI, int NA, int METRIC>
 __device__ __forceinline__ void all_pairs(const KParams& p, const Switches& sw, const float (&score)[SOP_K_MAXA],
@@ -624,8 +753,6 @@ __device__ __forceinline__ void widen(const RawBlk<BF16, EPL>& r, float (&w)[EPL
     }
 }
 
-template <int V> struct ic { constexpr operator int() const { return V; } };      // a compile-time integer as an argument
-
 // Ranking score of step 2 of the per-layer search: a decision quantity, formed in binary32 from the block's tree sums
 // num = <w,w^>_c, den = ||w^||_c^2 (chunks of 8, balanced tree) and wn = ||w||_c^2:
 // fl(fl(num / wn) * fl(|num| / den)), 1 for a block without weighted norm, 0 for a zero reconstruction
@@ -676,11 +803,15 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     constexpr bool SPLIT_RANK = EMIT && EPL == 8 && NA == 8;
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
-    // LDS: bin table | (scale, reciprocal) table | group parameters | reduction scratch
-    char* s_bins = s_mem;                                                         // [n_bins] records of 33 words
-    const size_t bins_bytes = ((size_t)p.n_bins * SOP_K_BIN_BYTES + 15) & ~(size_t)15;
-    float2* s_tab = reinterpret_cast<float2*>(s_mem + bins_bytes);
-    float4* s_gpar = reinterpret_cast<float4*>(s_mem + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
+    // LDS: selector bits | bin table | (scale, reciprocal) table | group parameters | reduction scratch
+    constexpr bool ORDERED = METRIC != 1 && NA != 2;                                // (a comparison of cosines is one of products)
+    constexpr int NPERM = search_perm_tables(NA);
+    uint32_t* const s_perm = reinterpret_cast<uint32_t*>(s_mem);                  // [NPERM][256] selector bits of eight bits of a chain of pairs
+    char* const s_bins = s_mem + SOP_K_PERM_BYTES(NA);                            // [n_bins] records
+    const uint32_t rec = EMIT ? SOP_K_WIDE_BIN_BYTES : p.rec_bytes;
+    const size_t bins_bytes = (size_t)p.n_bins * rec;
+    float2* s_tab = reinterpret_cast<float2*>(s_bins + bins_bytes);
+    float4* s_gpar = reinterpret_cast<float4*>(s_bins + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
     // reduction scratch: flag word (MULTI), list of outputs (not MULTI), the workgroup's own totals (64-bit integers)
     unsigned long long* s_red = reinterpret_cast<unsigned long long*>(s_gpar + 2 * SOP_K_MAXA);
     unsigned int* s_out = reinterpret_cast<unsigned int*>(s_red + 1);             // (not MULTI) output: its sum column, and from bit 8 its place in the table
@@ -688,7 +819,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     unsigned long long* s_acc = s_red + 1 + SOP_K_OUT_WORDS;                     // [NSLOT] this workgroup's sums (MULTI: per layer)
     const int n_acc = MULTI ? p.n_layers * NSLOT : NSLOT;
     __shared__ unsigned int s_next[4];                                            // next step of each SIMD's share
-    const uint32_t lds_neg = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_bins + SOP_K_BIN_NEGC;
+    const uint32_t lds_neg = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)s_bins + SOP_K_BIN_NEGC(rec);
 
     const int lane = threadIdx.x & 63;
     // the wavefront's number is the same in all its lanes: saying so keeps the row loop's counters
@@ -863,9 +994,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     }
     // Tables into LDS: the first 16 bytes of the bin table for four in flight per thread, the scale table and the group parameters are all asked
     // for before the first of them is waited for; a loop of one load, wait, one write would spend a round trip to L2 per word (the bin
-    // table has a multiple of four bins, so its size is a multiple of 16 bytes)
+    // table's records are multiples of 16 bytes)
     {
-        const int n16 = p.n_bins * (SOP_K_BIN_BYTES / 4) / 4, nt = p.n_tab_codes, tid = (int)threadIdx.x;
+        const int n16 = EMIT ? 0 : p.n_bins * (int)p.rec_bytes / 16, nt = p.n_tab_codes, tid = (int)threadIdx.x;
         const uint4* src = reinterpret_cast<const uint4*>(p.bins);
         uint4* dst = reinterpret_cast<uint4*>(s_bins);
         constexpr int NB = MULTI ? 1 : 2, NS = NB;      // words of the bin table and of the scale table in the first round
@@ -879,6 +1010,22 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         for (int j = 0; j < NS; ++j) { u[j] = make_float2(0.f, 0.f); if (j * NT < nt) u[j] = p.stab[min(tid + j * NT, nt - 1)]; }
         if (tid < 2 * SOP_K_MAXA) gp = reinterpret_cast<const float4*>(p.gpar)[tid];
         if (!MULTI && tid < p.A + p.P) s_out[tid] = tid < p.A ? (unsigned)tid | (unsigned)p.uidx[tid] << 8 : (unsigned)p.pair_col[tid - p.A] | (unsigned)(tid - p.A) << 8;
+        if constexpr (ORDERED) {
+            if (tid < 256) {
+                uint32_t v[NPERM];
+#pragma unroll
+                for (int k = 0; k < NPERM; ++k) v[k] = k == 0 ? p.flip_slots : 0u;
+#pragma unroll
+                for (int j = 1; j < NA; ++j)
+#pragma unroll
+                    for (int i = 0; i < j; ++i) {
+                        const int c = chain_bit(i, j), pi = pair_index(i, j);
+                        if ((p.pair_mask >> pi) & 1u) v[c / 8] ^= (uint32_t)((tid >> (c % 8)) & 1) << ((p.pair_slot_w[pi / 4] >> (8 * (pi % 4))) & 0xFF);
+                    }
+#pragma unroll
+                for (int k = 0; k < NPERM; ++k) s_perm[256 * k + tid] = v[k];
+            }
+        }
         if (tid < 4) s_next[tid] = dealt ? (unsigned int)OCC : 0u;
         for (int i = tid; i < n_acc; i += NT) s_acc[i] = 0ull;
 #pragma unroll
@@ -886,6 +1033,30 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 #pragma unroll
         for (int j = 0; j < NS; ++j) if (tid + j * NT < nt) s_tab[tid + j * NT] = u[j];
         if (tid < 2 * SOP_K_MAXA) s_gpar[tid] = gp;
+        if constexpr (EMIT) {
+            // two atoms of a bin a thread, four of them in flight: their values, the sums and the codes
+            const int n_two = p.n_bins * (SOP_K_MAXA / 2);
+            for (int i0 = tid; i0 < n_two; i0 += 4 * NT) {
+                f32x4 v[4];
+                uint16_t cd[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int i = min(i0 + j * NT, n_two - 1), q = i % (SOP_K_MAXA / 2);
+                    const BinRec& r = *reinterpret_cast<const BinRec*>(p.bins + (size_t)(i / (SOP_K_MAXA / 2)) * p.rec_bytes);
+                    { const float2 v0 = *reinterpret_cast<const float2*>(r.val[2 * q]), v1 = *reinterpret_cast<const float2*>(r.val[2 * q + 1]); v[j] = {v0.x, v0.y, v1.x, v1.y}; }
+                    cd[j] = *reinterpret_cast<const uint16_t*>(&r.code_lo[2 * q]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int i = i0 + j * NT, q = i % (SOP_K_MAXA / 2);
+                    if (i < n_two) {
+                        f32x4* const to = reinterpret_cast<f32x4*>(s_bins + (i / (SOP_K_MAXA / 2)) * rec) + 2 * q;
+                        to[0] = f32x4{v[j][0], v[j][1], v[j][0] + v[j][1], __int_as_float(cd[j] & 0xFF)};
+                        to[1] = f32x4{v[j][2], v[j][3], v[j][2] + v[j][3], __int_as_float(cd[j] >> 8)};
+                    }
+                }
+            }
+        }
         for (int i0 = tid + NB * NT; i0 < n16; i0 += 4 * NT) {
             uint4 v[4];
 #pragma unroll
@@ -939,6 +1110,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         asm volatile("" : "+s"(sw.A), "+s"(sw.pair_mask), "+s"(sw.flip_mask), "+s"(sw.gid), "+s"(sw.unit_tpos), "+s"(sw.unit_tneg), "+s"(sw.wide));
         if constexpr (SIGNED) asm volatile("" : "+s"(sw.mirror), "+s"(sw.selfsym));
         if constexpr (GROUPED) asm volatile("" : "+s"(sw.second));
+        unsigned long long flips = p.flip_mask;
+        if constexpr (ORDERED) asm volatile("" : "+s"(flips));
         const unsigned int cm32 = m, cs = strip;
         const long long cm = cm32;
         const unsigned int lanes_here = lanes_of(cs, MULTI ? lc_K : p.K);
@@ -1016,6 +1189,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // state of the current scale group: scale code, scale, scaled weights and the addresses of their bin records.
         // A signed scale word keeps the scale of both signs instead and forms scaled weights and addresses inside the
         // element pass (FlySrc): the arrays of two signs would cost 64 registers and with them a wavefront per SIMD.
+        // wave-uniform: some lane does not trust the residual form of an atom.  (A NaN error makes it so: see nan_pairs.)
+        bool any_weak = false;
         int gq = 0;
         float gss = 0.0f;                              // twice the scale (the table holds halved codebook values)
         bool gnz = false, gneg = false;
@@ -1083,11 +1258,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             auto pass = [&](auto n_, auto cl_, auto cd_, auto rk_, int a) __attribute__((always_inline)) {
                 constexpr int N = n_;
                 constexpr bool CL = cl_, CD = cd_, RK = rk_;
+                // (planes of six atoms: the forms of a pass stay apart; with their equal beginnings joined, as the compiler does, registers are spilled.  Planes of two
+                // have the registers and are faster joined, 4096 x 11008 67 us against 76)
+                if constexpr (EMIT && NA == 6) asm volatile("; %0" :: "n"(8 * N + 4 * CL + 2 * CD + RK));
                 const float4 gpar = s_gpar[2 * a];
                 float lo = 0.0f, hi = 0.0f;
                 if (CL) { const float4 g2 = s_gpar[2 * a + 1]; lo = g2.x; hi = g2.y; }
                 Sums sn[N];
-                eval_residual_group<EPL, METRIC, N, CD, RK && METRIC != 1, NA == 2, METRIC != 1 || EMIT>(w, cb, FlySrc<EPL, CL>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
+                eval_residual_group<EPL, METRIC, N, CD, RK && METRIC != 1, NA == 2 && (BF16 || !EMIT), METRIC != 1 || EMIT>(w, cb, FlySrc<EPL, CL, EMIT>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg, rec}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
 #pragma unroll
                 for (int n = 0; n < N; ++n) settle(a + n, sn[n], CD && want_codes);
             };
@@ -1140,15 +1318,18 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             }
             // the residual form is accurate while the reconstruction carries a fair share of the block's norm; otherwise
             // the whole wavefront recomputes the atom's cosine directly
+            any_weak = weak_atoms != 0u;
             while (__builtin_expect(weak_atoms != 0u, 0)) {
                 const int wa = __builtin_ctz(weak_atoms);
                 weak_atoms &= weak_atoms - 1u;
                 const ScalePrep sq = prepare_scale(pmax, nmax, false, wa, p, sw, s_tab, s_gpar);
                 const float4 gpar = s_gpar[2 * wa], g2 = s_gpar[2 * wa + 1];
                 float ny1, dy1;
-                direct_cosine_sums<EPL, LPB, EMIT, true>(cb, w, FlySrc<EPL, true>{w, sq.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg}, sq.nonzero, false, wa, ny1, dy1);
+                direct_cosine_sums<EPL, LPB, true>(cb, w, FlySrc<EPL, true, EMIT>{w, sq.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg, rec}, sq.nonzero, false, wa, ny1, dy1);
                 // (direct sums go with the raw norm, which is the scaled one times the inverse power of two, exactly)
-                const float wnr = nsc.wns * __uint_as_float((254u << 23) - __float_as_uint(nsc.sc));
+                float sc = nsc.sc;
+                asm volatile("" : "+v"(sc));               // (else the exponent that it was formed of is kept in a register for this)
+                const float wnr = nsc.wns * __uint_as_float((254u << 23) - __float_as_uint(sc));
                 const float rs = __frsqrt_rn(__fmaf_rn(wnr, dy1, 1.0e-37f));
                 const int ia = (int)__float_as_uint(__fmaf_rn(-ny1, rs, 3.0f)) - 0x40000000;
 #pragma unroll
@@ -1173,10 +1354,10 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                         spM = prepare_scale(pmax, nmax, true, a, p, sw, s_tab, s_gpar);
                     } else if constexpr (SIGNED) {
                         bool unused;
-                        prepare_sign<EPL, false>(w, pmax, nmax, false, a, p, sw, s_tab, s_gpar, lds_neg, spP.q, spP.ss, spP.nonzero, gx, gboff, unused);
-                        prepare_sign<EPL, false>(w, pmax, nmax, true, a, p, sw, s_tab, s_gpar, lds_neg, spM.q, spM.ss, spM.nonzero, gx2, gboff2, unused);
+                        prepare_sign<EPL, false>(w, pmax, nmax, false, a, p, sw, s_tab, s_gpar, lds_neg, rec, spP.q, spP.ss, spP.nonzero, gx, gboff, unused);
+                        prepare_sign<EPL, false>(w, pmax, nmax, true, a, p, sw, s_tab, s_gpar, lds_neg, rec, spM.q, spM.ss, spM.nonzero, gx2, gboff2, unused);
                     } else {
-                        prepare_sign<EPL, ARGMAX>(w, pmax, nmax, false, a, p, sw, s_tab, s_gpar, lds_neg, gq, gss, gnz, gx, gboff, gneg);
+                        prepare_sign<EPL, ARGMAX>(w, pmax, nmax, false, a, p, sw, s_tab, s_gpar, lds_neg, rec, gq, gss, gnz, gx, gboff, gneg);
                     }
                 }
                 const bool wide = EMIT && ((sw.wide >> a) & 1u);
@@ -1230,8 +1411,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                                     // the residual form is accurate while the reconstruction carries a fair share of the block's
                                     // norm; otherwise the whole wavefront recomputes this candidate's cosine sums directly
                                     if (__builtin_expect(__any(t.weak) != 0, 0)) {
-                                        direct_cosine_sums<EPL, LPB, true, LEAN>(cb, w, src, sp.nonzero, sgn, a, ny, dy);
+                                        direct_cosine_sums<EPL, LPB, LEAN>(cb, w, src, sp.nonzero, sgn, a, ny, dy);
                                         rawf = true;
+                                        any_weak = true;
                                     }
                                 }
                                 if constexpr (EMIT && METRIC == 1) { rn = t.ny; rd = t.dy; }
@@ -1239,12 +1421,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                             // the table covers a scale rounded down by up to the factor SOP_K_BIN_SAFE; beyond it (the scale word
                             // saturated) the whole wavefront clamps its scaled weights into the table's range
                             if constexpr (!FLY) {
-                                run(ArrSrc<EPL>{xarr, barr});
+                                run(ArrSrc<EPL, EMIT>{xarr, barr});
                             } else if (__builtin_expect(__any(sp.beyond) != 0, 0)) {
                                 const float4 g2 = s_gpar[2 * a + 1];       // (table range low, high, -, -)
-                                run(FlySrc<EPL, true>{w, sp.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg});
+                                run(FlySrc<EPL, true, EMIT>{w, sp.rr, gpar.z, gpar.w, g2.x, g2.y, lds_neg, rec});
                             } else {
-                                run(FlySrc<EPL, false>{w, sp.rr, gpar.z, gpar.w, 0.0f, 0.0f, lds_neg});
+                                run(FlySrc<EPL, false, EMIT>{w, sp.rr, gpar.z, gpar.w, 0.0f, 0.0f, lds_neg, rec});
                             }
                         };
                         eval_sign(spP, false, gx, gboff, err0, ny0, dy0, q0, raw0, codes0, rn0, rd0);
@@ -1300,15 +1482,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     }
                 } else if constexpr (METRIC == 1) {
                     // (emit mode without a code plane, as when only the ranking scores are wanted: the pass that forms no codes)
-                    if (!EMIT || p.codes) best = finish_direct<LPB>(eval_direct<EPL, EMIT, EMIT>(w, cb, ArrSrc<EPL>{gx, gboff}, gss, a, wide, codes));
-                    else best = finish_direct<LPB>(eval_direct<EPL, false, EMIT>(w, cb, ArrSrc<EPL>{gx, gboff}, gss, a, wide, codes));
+                    if (!EMIT || p.codes) best = finish_direct<LPB>(eval_direct<EPL, EMIT, EMIT>(w, cb, ArrSrc<EPL, EMIT>{gx, gboff}, gss, a, wide, codes));
+                    else best = finish_direct<LPB>(eval_direct<EPL, false, EMIT>(w, cb, ArrSrc<EPL, EMIT>{gx, gboff}, gss, a, wide, codes));
                     score[a] = best.dy > 0.0f ? best.ny * fabsf(best.ny) : 0.0f;
                     den[a] = best.dy > 0.0f ? best.dy : 1.0f;
                     raw = true;
                 } else {
-                    // (emit mode without a code plane, as when only the ranking scores are wanted: the pass that forms no codes
-                    // and reads no boundaries; the ranking score's sums are formed in the same pass)
-                    const ArrSrc<EPL> src{gx, gboff};
+                    // (emit mode without a code plane, as when only the ranking scores are wanted: the pass that forms no codes; the ranking score's sums are formed in the same pass)
+                    const ArrSrc<EPL, EMIT> src{gx, gboff};
                     Sums s;
                     if constexpr (!EMIT) s = eval_residual<EPL, METRIC, false>(w, cb, src, gss, a, wide, codes);
                     else if constexpr (SPLIT_RANK) {
@@ -1329,10 +1510,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                     // the block's norm; otherwise the whole wavefront recomputes this atom directly
                     if (__builtin_expect(__any(best.weak) != 0, 0)) {
                         float ny1, dy1;
-                        direct_cosine_sums<EPL, LPB, EMIT, LEAN>(cb, w, ArrSrc<EPL>{gx, gboff}, gnz, ARGMAX ? gneg : false, a, ny1, dy1);
+                        direct_cosine_sums<EPL, LPB, LEAN>(cb, w, ArrSrc<EPL, EMIT>{gx, gboff}, gnz, ARGMAX ? gneg : false, a, ny1, dy1);
                         best.ny = ny1;
                         best.dy = dy1;
                         raw = true;
+                        any_weak = true;
                     }
                     score[a] = best.err;
                 }
@@ -1365,8 +1547,24 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         }
         // ---- selector of every requested pair: one word per block ----
         uint32_t bits = 0;
-        all_pairs<0, NA, METRIC>(p, sw, score, den, dlt, accp, bits);
-        bits ^= p.flip_slots;
+        if constexpr (ORDERED) {
+            uint32_t chain = 0u;
+            ordered_pairs<NA - 1, NA>(sw.A, flips, score, dlt, accp, chain);
+            if (__builtin_expect(any_weak, 0)) {
+                bool nan = false;
+#pragma unroll
+                for (int a = 0; a < NA; ++a) nan = nan || score[a] != score[a];
+                if (__any(nan) != 0) nan_pairs<0, NA>(score, dlt, accp, chain);
+            }
+            // from the chain's order to the selector's, eight bits at a time (the table holds the swapped pairs' complement too)
+            if (MULTI ? lc_sel != nullptr : p.sel_words != nullptr) {
+#pragma unroll
+                for (int k = 0; k < NPERM; ++k) bits ^= s_perm[256 * k + ((chain >> (8 * k)) & 0xFFu)];
+            }
+        } else {
+            all_pairs<0, NA, METRIC>(p, sw, score, den, dlt, accp, bits);
+            bits ^= p.flip_slots;
+        }
         void* const sel_words = MULTI ? lc_sel : p.sel_words;
         // One store without a branch ends every path of a step: lanes without a word to store, or all of them, lie past the end the store is given
         // and are dropped by the hardware.  Behind a branch it may or may not be the last access, the compiler waits for every access in

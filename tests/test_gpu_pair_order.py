@@ -1,0 +1,87 @@
+"""The pair stage and the bin records at their edges: every number of atoms in orders that the kernel regroups, ties everywhere (the same codebook twice), part
+of the pairs in any order, errors beyond binary32; alphabets whose atoms are evaluated one by one, together, and with the largest tables."""
+import itertools
+
+import numpy as np
+import pytest
+
+import paper_2605_14929_amd as sop
+from oracle import atoms as OA, pairsearch as ops
+import sop_inputs as si
+from gpu_util import compare, oracle_fmt, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+NF, SH, NF5, SH5 = (OA.to_f32(t) for t in (OA.nf(4), OA.sh(4), OA.nf(5), OA.sh(5)))
+NEG = lambda t: OA.to_f32(-np.asarray(t, dtype=np.float64)[::-1])
+# copies before and after their originals, a codebook twice, groups mixed: the internal order swaps many pairs
+LONG = [SH, NF, NEG(NF5), NF, NEG(SH), NF5, NEG(NF), SH5]
+
+
+def _layer(M, K, seed):
+    W, c = si.student_t_weights(M, K, 4.0, seed), si.channel_norms(K, 1.0, seed + 1)
+    W[1, :64] = 0.0                                               # every atom ties
+    c[64:96] = 0.0                                                # errors are zero: every atom ties
+    return W, c
+
+
+@pytest.mark.parametrize("g", [8, 16, 32])
+@pytest.mark.parametrize("fmt", ["UE4M4", "E4M3"])
+@pytest.mark.parametrize("A", range(2, 9))
+def test_ties_and_swapped_pairs(A, fmt, g):
+    W, c = _layer(9, 1120, 8100 + A)
+    fmt = sop.fmt_by_name(fmt)
+    for tabs in (LONG[:A], LONG[:A][::-1]):
+        compare(run_gpu(W, c, tabs, g, fmt, emit=False), ops.pair_search(W, c, tabs, g, oracle_fmt(fmt)), A * (A - 1) // 2, emit=False)
+
+
+@pytest.mark.parametrize("metric", [sop.SEL_WSE, sop.SEL_MSE])
+@pytest.mark.parametrize("A", [3, 6, 7, 8])
+def test_part_of_the_pairs_in_any_order(A, metric):
+    W, c = _layer(6, 1120, 8200 + A)
+    fmt, tabs, rng = sop.fmt_by_name("UE4M4"), LONG[:A], np.random.default_rng(A)
+    pairs = list(itertools.combinations(range(A), 2))
+    for n in (1, 2, len(pairs) // 2, len(pairs)):
+        some = [pairs[i] for i in rng.permutation(len(pairs))[:n]]
+        got = run_gpu(W, c, tabs, 16, fmt, metric=metric, pairs=some, emit=False)
+        compare(got, ops.pair_search(W, c, tabs, 16, oracle_fmt(fmt), metric=metric, pairs=some), n, emit=False)
+
+
+def test_errors_beyond_binary32_tie():
+    """Errors of +infinity are equal; the blocks beside them are not touched."""
+    W, c = _layer(8, 512, 8300)
+    W[3:5] *= np.float32(1e25)
+    fmt = sop.fmt_by_name("UE4M4")
+    got, ref = run_gpu(W, c, LONG[:6], 16, fmt, emit=False), ops.pair_search(W, c, LONG[:6], 16, oracle_fmt(fmt))
+    assert np.array_equal(got["sel_words"], ref.sel_words)
+
+
+def _fine(n, step, seed):
+    """n entries from -1 to 1, the last but one three boundaries `step` apart: the finer the step, the more bins"""
+    t = np.sort(np.random.default_rng(seed).uniform(-0.9, 0.9, n - 5))
+    t = t[np.concatenate([[True], np.diff(t) > 2 * step])]
+    return np.concatenate([[-1.0], t, 0.93 + step * np.arange(3), [1.0]]).astype(np.float32)
+
+
+def _alphabet(steps, least_bins, scale):
+    """Three codebooks of a table of least_bins at least (the number hangs on where the boundaries fall between the bins as well)"""
+    for step in steps:
+        tabs = [OA.to_f32(_fine(n, step, seed) * f) for n, seed, f in zip((14, 13, 40), (1, 2, 3), scale)]
+        try:
+            if sop.sop_check_alphabet(tabs)[0] >= least_bins:
+                return tabs
+        except sop.SopError:
+            break                                                 # (closer than any table resolves)
+    raise AssertionError("no such table")
+
+
+@pytest.mark.parametrize("emit", [False, True])
+@pytest.mark.parametrize("steps,least_bins", [((0.02,), 64), (np.arange(0.0031, 0.0008, -2e-5), 1024)])
+@pytest.mark.parametrize("scale", [(1.0, 1.0, 1.0), (1.0, 0.96, 0.91)])
+def test_bin_records(scale, steps, least_bins, emit):
+    """Records of atoms together and of atoms one by one, tables up to the largest, with as many scale codes as are tabulated (the largest of both do not
+    fit into LDS where planes are written: the scales are computed)."""
+    tabs = _alphabet(steps, least_bins, scale)
+    fmt = sop.ScaleFmt(0, 4, 7, 12, -1, -1)                        # 2048 codes
+    W, c = _layer(8, 1120, 8400)
+    compare(run_gpu(W, c, tabs, 16, fmt, emit=emit), ops.pair_search(W, c, tabs, 16, oracle_fmt(fmt)), 3, emit=emit)
