@@ -801,6 +801,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // ranking sums in a pass of their own where eight atoms of 8-element lanes leave no registers for them in the one element pass (up to
     // 17 spilled; argmax rule, metric MSE, fp32, 4096 x 4096, every plane: 157 us in one pass, 127 in two)
     constexpr bool SPLIT_RANK = EMIT && EPL == 8 && NA == 8;
+    constexpr bool TOP_TEST = EMIT || (NA == 2 && SIGNMODE == 0 && EPL == 16);       // the row loop's test at its top (see there)
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
     // LDS: selector bits | bin table | (scale, reciprocal) table | group parameters | reduction scratch
@@ -1078,14 +1079,18 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     if (!dealt) first_row();
     int l_nxt = rq_l;                              // layer of the row in nxt
     int since_flush = 0;
-    // (the first row is waited for here: at the top of the loop the wait is then that of a step, whose row is older than its stores)
-    if (ok_cur) {
+    // The first row is waited for here: at the top of the loop the wait is then that of a step, whose row is older than its stores, which stay in
+    // flight.  The loop stands in the same branch: a way round the wait into the loop, which nothing ever takes, would make every step's wait one for the
+    // stores of the step before as well (two atoms under the argmax rule, lanes of eight bf16 weights: 1 to 3 %).  Where that way is joined with the loop's own
+    // test at its top by itself, and with planes, whose stores have branches of their own, the test stays there: positive scale, 2048 x 5504, one atom 11.9 us
+    // against 12.2, planes of two atoms under a signed word 2 to 4 %.
+    if (TOP_TEST || ok_cur) {
+    if (!TOP_TEST || ok_cur) {
 #pragma unroll
         for (int i = 0; i < (int)(sizeof(nxt.v) / sizeof(nxt.v[0])); ++i) asm volatile("" : "+v"(nxt.v[i].x), "+v"(nxt.v[i].y), "+v"(nxt.v[i].z), "+v"(nxt.v[i].w));
         norms_here();
     }
-
-    while (ok_cur) {
+    while (!TOP_TEST || ok_cur) {
         if constexpr (MULTI) {
             if (l_nxt != cl) {
                 // the arithmetic enters another layer: its channel norms are requested first, and while they
@@ -1586,6 +1591,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         ok_cur = ok_nxt;
         i_nxt = i_nn;
         if (++since_flush == SOP_K_FLUSH_STEPS) { flush(cl); since_flush = 0; }
+        if (!TOP_TEST && !ok_cur) break;
+    }
     }
 
     // ---- per-workgroup sums: what the lanes still hold joins the workgroup's integer sums in LDS ----

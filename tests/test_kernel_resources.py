@@ -37,3 +37,30 @@ def test_no_variant_spills(tmp_path):
             assert vgprs <= 512 // occ
             assert spilled == 0, ((bf16, epl, sign, metric, emit, na), spilled)
     assert seen == 576
+
+
+@pytest.mark.skipif(len(OBJECTS) != 6 or not shutil.which(f"{LLVM}/llvm-objdump"), reason="no objects of a build, or no tools to read them")
+def test_a_step_waits_for_its_row_and_not_for_the_stores_before(tmp_path):
+    """bf16 searches of one layer: the last wait before a step asks for the next row is the one for the row at hand (requested a step ago), and leaves that
+    step's selector stores in flight: one, with up to eight atoms two."""
+    def waits(obj):
+        d = tmp_path / os.path.basename(obj)
+        d.mkdir()
+        list(_kernels(obj, d))                                    # (leaves the code object in d)
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(d / "code")], capture_output=True, text=True, check=True).stdout
+        out = {}
+        for part in re.split(r"\n[0-9a-f]+ <", text)[1:]:
+            m = NAME.search(part.split(">")[0])
+            if not m or m.group(5) == "1" or m.group(8) == "1" or "s_barrier" not in part:
+                continue
+            lines = part.split("s_barrier")[1].split("\n")        # from the loaded tables to the end of the row loop
+            asks = [i for i, l in enumerate(lines) if "buffer_load_dwordx4" in l]
+            while len(asks) > 1 and asks[-1] - asks[-2] < 14:     # (the requests of one row)
+                asks.pop()
+            out[m.group(0), m.group(6)] = int(re.findall(r"vmcnt\((\d+)\)", "\n".join(lines[:asks[-1]]))[-1])
+        return out
+
+    found = {k: v for obj in OBJECTS if "search_1_" in obj for k, v in waits(obj).items()}
+    assert len(found) == 108
+    late = {k: v for k, v in found.items() if v != (2 if k[1] == "8" else 1)}
+    assert not late
