@@ -590,7 +590,7 @@ constexpr PairTab kPairTab = make_pair_tab();
 template <int PI> struct PairOf { static constexpr int i = kPairTab.first[PI], j = kPairTab.second[PI]; };
 template <int V> struct ic { constexpr operator int() const { return V; } };      // a compile-time integer as an argument
 
-// The pairs of a block by their errors' bit patterns, which order as the errors do (none is negative or a NaN).  The selector is "b strictly
+// The pairs of a block by their errors' bit patterns, which order as the errors do where none is below zero or a NaN (else see numbered_pairs).  The selector is "b strictly
 // better than a" for the caller's pair (a, b), and the internal order may have swapped the two, in which case internal j keeps the block on a tie:
 // pick_j = error[j] < error[i] + swapped, the borrow of a subtraction with a carry.  A pair adds the chosen atom's deficit to its running sum and
 // shifts its bit into `chain` by the carry of an addition; pair (i, j) ends at bit chain_bit(i, j).  Five instructions a pair and no test of
@@ -662,18 +662,20 @@ __device__ __forceinline__ void ordered_pairs(int A, unsigned long long flips, c
     if constexpr (J > 1) ordered_pairs<J - 1, NA>(A, flips, score, dlt, accp, chain);
 }
 
-// Pair PI and the following ones where an error is a NaN: internal i keeps the block
+// Pair PI and the following ones by the errors as numbers: what the chain took another way is put right.  (Errors below zero, which bit patterns order
+// the other way round; a NaN is not less than anything nor anything less than it, and internal i keeps the block.)
 template <int PI, int NA>
-__device__ __forceinline__ void nan_pairs(const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+__device__ __forceinline__ void numbered_pairs(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
 {
     constexpr int i = PairOf<PI>::i, j = PairOf<PI>::j, c = chain_bit(i, j);
     if constexpr (j < NA) {
-        if (((chain >> c) & 1u) && !(score[i] == score[i] && score[j] == score[j])) {
-            accp[PI] += dlt[i] - dlt[j];
+        const bool took_j = (chain >> c) & 1u, pick_j = score[j] < score[i] || (((flips >> PI) & 1u) && score[j] == score[i]);
+        if (took_j != pick_j) {
+            accp[PI] += pick_j ? dlt[j] - dlt[i] : dlt[i] - dlt[j];
             chain ^= 1u << c;
         }
     }
-    if constexpr (PI + 1 < SOP_K_MAXP) nan_pairs<PI + 1, NA>(score, dlt, accp, chain);
+    if constexpr (PI + 1 < SOP_K_MAXP) numbered_pairs<PI + 1, NA>(flips, score, dlt, accp, chain);
 }
 
 // Selector of pair PI and of all following pairs (i < j in internal order), for every metric and alphabet: bit `slot` of the
@@ -967,6 +969,16 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             cb[i] = t.x; cb[i + 1] = t.y; cb[i + 2] = t.z; cb[i + 3] = t.w;
         }
     };
+    // metric WSE: a norm below zero, which the interface rules out, may take errors below zero
+    unsigned int norms_below = 0u;                 // wave-uniform
+    auto look_at_norms = [&]() {
+        if constexpr (METRIC == 0 && ORDERED) {
+            float least = 0.0f;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) least = fminf(least, cb[i]);
+            norms_below = uni(__any(least < 0.0f) != 0);
+        }
+    };
     // (norms are waited for where they are asked for, not at their first use, which lies behind the request of the next row)
     auto norms_here = [&]() {
 #pragma unroll
@@ -1079,6 +1091,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     if (!dealt) first_row();
     int l_nxt = rq_l;                              // layer of the row in nxt
     int since_flush = 0;
+    if constexpr (TOP_TEST) look_at_norms();
     // The first row is waited for here: at the top of the loop the wait is then that of a step, whose row is older than its stores, which stay in
     // flight.  The loop stands in the same branch: a way round the wait into the loop, which nothing ever takes, would make every step's wait one for the
     // stores of the step before as well (two atoms under the argmax rule, lanes of eight bf16 weights: 1 to 3 %).  Where that way is joined with the loop's own
@@ -1090,6 +1103,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         for (int i = 0; i < (int)(sizeof(nxt.v) / sizeof(nxt.v[0])); ++i) asm volatile("" : "+v"(nxt.v[i].x), "+v"(nxt.v[i].y), "+v"(nxt.v[i].z), "+v"(nxt.v[i].w));
         norms_here();
     }
+    if constexpr (!TOP_TEST) look_at_norms();
     while (!TOP_TEST || ok_cur) {
         if constexpr (MULTI) {
             if (l_nxt != cl) {
@@ -1106,6 +1120,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 load_norms(lc_c, lc_Kc, (strip * 64u + (unsigned int)lane) * EPL, (unsigned int)lane < lanes_of(strip, lc_K));
                 if (left >= 0) flush(left);
                 norms_here();
+                look_at_norms();
                 since_flush = 0;
             }
         }
@@ -1125,6 +1140,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             cur_strip = cs;
             load_norms(MULTI ? lc_c : p.c, MULTI ? lc_Kc : (unsigned int)p.Kc, (cs * 64u + (unsigned int)lane) * EPL, valid);
             norms_here();
+            look_at_norms();
         }
         // ---- the block: one read from HBM, requested one step ahead ----
         float w[EPL];
@@ -1194,8 +1210,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // state of the current scale group: scale code, scale, scaled weights and the addresses of their bin records.
         // A signed scale word keeps the scale of both signs instead and forms scaled weights and addresses inside the
         // element pass (FlySrc): the arrays of two signs would cost 64 registers and with them a wavefront per SIMD.
-        // wave-uniform: some lane does not trust the residual form of an atom.  (A NaN error makes it so: see nan_pairs.)
-        bool any_weak = false;
+        // wave-uniform: an error may be below zero (then so is a norm) or a NaN (then no lane trusts the residual form of its atom)
+        unsigned int odd = norms_below;
         int gq = 0;
         float gss = 0.0f;                              // twice the scale (the table holds halved codebook values)
         bool gnz = false, gneg = false;
@@ -1323,7 +1339,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             }
             // the residual form is accurate while the reconstruction carries a fair share of the block's norm; otherwise
             // the whole wavefront recomputes the atom's cosine directly
-            any_weak = weak_atoms != 0u;
+            odd |= weak_atoms;
             while (__builtin_expect(weak_atoms != 0u, 0)) {
                 const int wa = __builtin_ctz(weak_atoms);
                 weak_atoms &= weak_atoms - 1u;
@@ -1418,7 +1434,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                                     if (__builtin_expect(__any(t.weak) != 0, 0)) {
                                         direct_cosine_sums<EPL, LPB, LEAN>(cb, w, src, sp.nonzero, sgn, a, ny, dy);
                                         rawf = true;
-                                        any_weak = true;
+                                        odd = 1u;
                                     }
                                 }
                                 if constexpr (EMIT && METRIC == 1) { rn = t.ny; rd = t.dy; }
@@ -1519,7 +1535,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                         best.ny = ny1;
                         best.dy = dy1;
                         raw = true;
-                        any_weak = true;
+                        odd = 1u;
                     }
                     score[a] = best.err;
                 }
@@ -1555,11 +1571,11 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         if constexpr (ORDERED) {
             uint32_t chain = 0u;
             ordered_pairs<NA - 1, NA>(sw.A, flips, score, dlt, accp, chain);
-            if (__builtin_expect(any_weak, 0)) {
-                bool nan = false;
+            if (__builtin_expect(odd != 0u, 0)) {
+                bool some = false;
 #pragma unroll
-                for (int a = 0; a < NA; ++a) nan = nan || score[a] != score[a];
-                if (__any(nan) != 0) nan_pairs<0, NA>(score, dlt, accp, chain);
+                for (int a = 0; a < NA; ++a) some = some || !(score[a] >= 0.0f);
+                if (__any(some) != 0) numbered_pairs<0, NA>(flips, score, dlt, accp, chain);
             }
             // from the chain's order to the selector's, eight bits at a time (the table holds the swapped pairs' complement too)
             if (MULTI ? lc_sel != nullptr : p.sel_words != nullptr) {

@@ -85,3 +85,33 @@ def test_bin_records(scale, steps, least_bins, emit):
     fmt = sop.ScaleFmt(0, 4, 7, 12, -1, -1)                        # 2048 codes
     W, c = _layer(8, 1120, 8400)
     compare(run_gpu(W, c, tabs, 16, fmt, emit=emit), ops.pair_search(W, c, tabs, 16, oracle_fmt(fmt)), 3, emit=emit)
+
+
+@pytest.mark.parametrize("g", [8, 16, 32])
+@pytest.mark.parametrize("fmt,rule", [("UE4M4", 0), ("E4M3", 0), ("E4M3", 1)])
+@pytest.mark.parametrize("A", [3, 6, 8])
+def test_errors_below_zero_and_errors_that_are_no_numbers(A, fmt, rule, g):
+    """Norms that the interface rules out and nothing checks: the errors are compared as numbers all the same (below zero where a norm is), whatever the
+    pairs' order, and the blocks beside them are not touched.  A NaN beats nothing and loses to nothing: the block stays with the atom that comes
+    first inside the kernel, which a block of nothing but NaNs tells for every pair."""
+    W, c = _layer(9, 1120, 8500 + A)
+    c[128:640] *= np.where(np.random.default_rng(A).random(512) < 0.3, -1.0, 1.0).astype(np.float32)
+    c[704] = np.nan
+    c[832] = np.inf
+    W[::2, 832] = 0.0                                             # (infinity times a residual of zero)
+    fmt = sop.fmt_by_name(fmt)
+    pairs = list(itertools.combinations(range(A), 2))
+    swapped = 0
+    for tabs in (LONG[:A], LONG[:A][::-1]):
+        for some in (pairs, pairs[::-1], pairs[1::3]):
+            got = run_gpu(W, c, tabs, g, fmt, pairs=some, scale_rule=rule, emit=False)["sel_words"]
+            ref = ops.pair_search(W, c, tabs, g, oracle_fmt(fmt), pairs=some, scale_rule=rule)
+            first = got[704 // g]
+            swapped |= int(first)
+            want = ref.sel_words.copy()
+            for q, (a, b) in enumerate(some):
+                nan = np.isnan(ref.blk_err[a]) | np.isnan(ref.blk_err[b])
+                assert nan[704 // g] and nan.sum() >= 9
+                want[nan] = want[nan] & ~np.uint32(1 << q) | first & np.uint32(1 << q)
+            assert np.array_equal(got, want)
+    assert A == 3 or swapped
