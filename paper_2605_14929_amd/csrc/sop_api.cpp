@@ -532,6 +532,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
         p.pair_mask |= 1u << pi;
         if (ia > ib) { p.flip_mask |= 1u << pi; p.flip_slots |= 1u << q; }
         p.pair_slot_w[pi / 4] |= (unsigned)q << (8 * (pi % 4));
+        p.chain_sel[chain_bit(i, j)] = 1u << q;
         p.pair_col[q] = (unsigned char)(na + i * (2 * na - i - 1) / 2 + (j - i - 1));
     }
     p.sums = use_static ? reinterpret_cast<unsigned long long*>(c->static_scratch) : c->d_sums + (size_t)sums_set * kSumsWords;

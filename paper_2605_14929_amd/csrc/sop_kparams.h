@@ -33,6 +33,8 @@ struct float2 { float x, y; };       /* (host-only translation units see the lau
 
 /* position of (i,j), i < j, in the lexicographic list of all pairs of SOP_K_MAXA atoms */
 SOP_K_HD constexpr int pair_index(int i, int j) { return i * (2 * SOP_K_MAXA - i - 1) / 2 + (j - i - 1); }
+/* bit of pair (i,j), i < j, in the chain in which a search of more than two atoms forms the pairs (metrics WSE and MSE) */
+SOP_K_HD constexpr int chain_bit(int i, int j) { return j * (j - 1) / 2 + i; }
 
 /* Tables of 256 selector words that take the pairs from the order in which a search of na atoms forms them to the order requested, and their bytes */
 SOP_K_HD constexpr int search_perm_tables(int na) { return na == 2 ? 0 : (na * (na - 1) / 2 + 7) / 8; }
@@ -106,6 +108,7 @@ struct KParams {
     unsigned int flip_slots;                          // bit q: output pair q is such a swapped pair
     // (byte arrays sit on 8-byte boundaries so that the kernels fetch them with scalar loads)
     unsigned int pair_slot_w[SOP_K_MAXP / 4];          // byte pi%4 of word pi/4: output index of pair pi = pair_index(i,j)
+    unsigned int chain_sel[(SOP_K_MAXP + 7) / 8 * 8];  // bit of the selector word that bit chain_bit(i,j) of a chain of pairs becomes, 0: not requested
     alignas(8) unsigned char pair_col[SOP_K_MAXP + 4]; // sum column of output pair o (in the variant's own numbering, see search_cols)
     // outputs
     // layer sums of 1-cos in fixed point (2^-22 units): every workgroup adds its share with integer

@@ -595,7 +595,6 @@ template <int V> struct ic { constexpr operator int() const { return V; } };    
 // pick_j = error[j] < error[i] + swapped, the borrow of a subtraction with a carry.  A pair adds the chosen atom's deficit to its running sum and
 // shifts its bit into `chain` by the carry of an addition; pair (i, j) ends at bit chain_bit(i, j).  Five instructions a pair and no test of
 // whether it is requested, where the general form takes eleven (scalar instructions and branches cost about as much issue time as vector ones).
-constexpr int chain_bit(int i, int j) { return j * (j - 1) / 2 + i; }
 // Up to three pairs (i, J) at once: a lane mask that a vector instruction writes may be read by another two instructions later at the earliest, which
 // three subtractions in a row are.  (The compiler makes more of either carry.)   SOPK_FIELD: offset and width of the pair's bit in `flips`.
 #define SOPK_FIELD(i, j) (pair_index(i, j) | 1 << 16)
@@ -1023,20 +1022,16 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         for (int j = 0; j < NS; ++j) { u[j] = make_float2(0.f, 0.f); if (j * NT < nt) u[j] = p.stab[min(tid + j * NT, nt - 1)]; }
         if (tid < 2 * SOP_K_MAXA) gp = reinterpret_cast<const float4*>(p.gpar)[tid];
         if (!MULTI && tid < p.A + p.P) s_out[tid] = tid < p.A ? (unsigned)tid | (unsigned)p.uidx[tid] << 8 : (unsigned)p.pair_col[tid - p.A] | (unsigned)(tid - p.A) << 8;
+        // (256 threads a table; a word of selector bits for every bit of the chain comes from the host, and an entry takes those of its set bits: two instructions a
+        // bit.  With the words formed here, pair by pair, by the first 256 threads, this was 0.3 us of every launch of six atoms and 1.0 us of eight.)
         if constexpr (ORDERED) {
-            if (tid < 256) {
-                uint32_t v[NPERM];
+            if (MULTI || p.sel_words) {
+                for (int k = wv >> 2; k < NPERM; k += OCC) {
+                    uint32_t v = 0u;
 #pragma unroll
-                for (int k = 0; k < NPERM; ++k) v[k] = k == 0 ? p.flip_slots : 0u;
-#pragma unroll
-                for (int j = 1; j < NA; ++j)
-#pragma unroll
-                    for (int i = 0; i < j; ++i) {
-                        const int c = chain_bit(i, j), pi = pair_index(i, j);
-                        if ((p.pair_mask >> pi) & 1u) v[c / 8] ^= (uint32_t)((tid >> (c % 8)) & 1) << ((p.pair_slot_w[pi / 4] >> (8 * (pi % 4))) & 0xFF);
-                    }
-#pragma unroll
-                for (int k = 0; k < NPERM; ++k) s_perm[256 * k + tid] = v[k];
+                    for (int i = 0; i < 8; ++i) v |= (uint32_t)__builtin_amdgcn_sbfe(tid, i, 1) & p.chain_sel[8 * k + i];
+                    s_perm[256 * k + (tid & 255)] = k == 0 ? v ^ p.flip_slots : v;
+                }
             }
         }
         if (tid < 4) s_next[tid] = dealt ? (unsigned int)OCC : 0u;
