@@ -558,14 +558,8 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     int occ = 1, mode = 0;
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
-    auto lds_of = [&](int n_codes) {
-        return (size_t)SOP_K_PERM_BYTES(na) + (size_t)p.n_bins * (emit ? SOP_K_WIDE_BIN_BYTES : p.rec_bytes) + (((size_t)n_codes * sizeof(float2) + 15) & ~(size_t)15) +
-               2 * SOP_K_MAXA * sizeof(float4) + (1 + SOP_K_OUT_WORDS + search_slots(na)) * sizeof(unsigned long long);
-    };
-    // (the bin table of 1024 bins with codes beside scale tables of 1000 codes and more: the kernel computes the scales then, to the same bits; 1 KiB is left
-    // for its own variables)
-    if (lds_of(p.n_tab_codes) + 1024 > c->lds_max) p.n_tab_codes = 0;
-    const size_t dyn_lds = lds_of(p.n_tab_codes);
+    p.n_tab_codes = search_tab_codes(na, p.n_bins, emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes, p.n_tab_codes, c->lds_max);
+    const size_t dyn_lds = search_lds(na, p.n_bins, emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes, p.n_tab_codes);
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds;
     hipError_t e = hipSuccess;

@@ -1,6 +1,7 @@
 // Launch parameters shared by the host side of the library and its kernels (passed by value).
 #ifndef SOP_KPARAMS_H
 #define SOP_KPARAMS_H
+#include <stddef.h>
 #include <stdint.h>
 
 #define SOP_K_MAXA 8                 /* atoms                                        */
@@ -13,7 +14,7 @@
 #define SOP_K_MAXTABCODES 2048       /* scale codes whose (scale, reciprocal) pair is tabulated */
 #define SOP_K_BIN_BYTES (8 * (SOP_K_MAXA + 1))          /* a bin record (see BinRec) */
 #define SOP_K_PAIR_BIN_BYTES (8 * (SOP_K_MAXA + 2))     /* the same where atoms are evaluated two or four at a time */
-#define SOP_K_WIDE_BIN_BYTES (16 * (SOP_K_MAXA + 1))    /* the same in the LDS of kernels that write planes: values, their sum and the code of every atom */
+#define SOP_K_WIDE_BIN_BYTES(na) (16 * ((na) + 1))       /* the same in the LDS of kernels that write planes (unrolled for na atoms): values, their sum and the code of every atom */
 #define SOP_K_BIN_MAGIC 12582912.0f  /* 1.5 * 2^23: one unit in the last place is 1               */
 /* bits(MAGIC + v) = 0x4B400000 + v; the 24-bit multiply sees 0x400000 + v: subtract its product */
 #define SOP_K_BIN_NEGC(bytes) (0u - 0x400000u * (unsigned)(bytes))
@@ -58,7 +59,7 @@ struct BinRec {
     float val[SOP_K_MAXA][2];            // half of the codebook value at and below the boundary, half of the one above it
     unsigned char code_lo[SOP_K_MAXA];   // code at and below the boundary
 };
-static_assert(sizeof(BinRec) == SOP_K_BIN_BYTES && SOP_K_BIN_BYTES % 16 == 8 && SOP_K_PAIR_BIN_BYTES % 32 == 16 && SOP_K_WIDE_BIN_BYTES % 32 == 16 && SOP_K_MAXA % 2 == 0, "odd numbers of words");
+static_assert(sizeof(BinRec) == SOP_K_BIN_BYTES && SOP_K_BIN_BYTES % 16 == 8 && SOP_K_PAIR_BIN_BYTES % 32 == 16 && SOP_K_WIDE_BIN_BYTES(2) % 32 == 16 && SOP_K_MAXA % 2 == 0, "odd numbers of words");
 
 /* Atoms are handled in an internal order in which atoms with equal endpoints (one "scale group":
  * same ideal scale, same scale code, same scaled weights) are adjacent, and an atom that is the
@@ -166,6 +167,15 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
     }
     return best;
 }
+
+/* LDS of a search unrolled for na atoms, beside the kernel's own variables (below 1 KiB): selector tables, bin records, scale table, group parameters, outputs and sums */
+inline size_t search_lds(int na, int n_bins, int rec_bytes, int n_codes)
+{
+    return (size_t)SOP_K_PERM_BYTES(na) + (size_t)n_bins * rec_bytes + (((size_t)n_codes * 8 + 15) & ~(size_t)15) + 2 * SOP_K_MAXA * 16 + (1 + SOP_K_OUT_WORDS + search_slots(na)) * 8;
+}
+/* Scale codes tabulated: all of them, or none where the table does not fit beside the bins and the kernel computes the scales instead, to the same bits: planes of seven
+ * or eight atoms with 1024 bins beside more than about 1300 codes (seven atoms, 4096 x 11008, 2048 codes: 267 us; such planes of three atoms, which fit, 106.) */
+inline int search_tab_codes(int na, int n_bins, int rec_bytes, int n_codes, size_t lds_max) { return search_lds(na, n_bins, rec_bytes, n_codes) + 1024 > lds_max ? 0 : n_codes; }
 
 /* Layer sums of a single search.  A word of them counts in its top bits the workgroups that have added to it (units of 2^56 in the first
  * SOP_K_REPL - 1 rows, of 2^60 in the last one, which takes those rows' totals).  A sum must never reach into its count or borrow from it,

@@ -810,7 +810,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     constexpr int NPERM = search_perm_tables(NA);
     uint32_t* const s_perm = reinterpret_cast<uint32_t*>(s_mem);                  // [NPERM][256] selector bits of eight bits of a chain of pairs
     char* const s_bins = s_mem + SOP_K_PERM_BYTES(NA);                            // [n_bins] records
-    const uint32_t rec = EMIT ? SOP_K_WIDE_BIN_BYTES : p.rec_bytes;
+    const uint32_t rec = EMIT ? SOP_K_WIDE_BIN_BYTES(NA) : p.rec_bytes;
     const size_t bins_bytes = (size_t)p.n_bins * rec;
     float2* s_tab = reinterpret_cast<float2*>(s_bins + bins_bytes);
     float4* s_gpar = reinterpret_cast<float4*>(s_bins + bins_bytes + (((size_t)p.n_tab_codes * sizeof(float2) + 15) & ~(size_t)15));
@@ -1015,6 +1015,23 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         uint4 t[NB];
         float2 u[NS];
         float4 gp = make_float4(0.f, 0.f, 0.f, 0.f);
+        // planes: two atoms of a bin a thread, of the atoms that the variant is unrolled for; their values, the sums and the codes
+        const int n_two = EMIT ? p.n_bins * (NA / 2) : 0;
+        f32x4 two_v = {0.0f, 0.0f, 0.0f, 0.0f};
+        uint32_t two_c = 0u;
+        auto ask_two = [&](int i, f32x4& v, uint32_t& cd) {
+            const int q = i % (NA / 2);
+            const BinRec& r = *reinterpret_cast<const BinRec*>(p.bins + (size_t)(i / (NA / 2)) * p.rec_bytes);
+            const float2 v0 = *reinterpret_cast<const float2*>(r.val[2 * q]), v1 = *reinterpret_cast<const float2*>(r.val[2 * q + 1]);
+            v = {v0.x, v0.y, v1.x, v1.y};
+            cd = *reinterpret_cast<const uint16_t*>(&r.code_lo[2 * q]);
+        };
+        auto put_two = [&](int i, const f32x4& v, uint32_t cd) {
+            f32x4* const to = reinterpret_cast<f32x4*>(s_bins + (i / (NA / 2)) * rec) + 2 * (i % (NA / 2));
+            to[0] = f32x4{v[0], v[1], v[0] + v[1], __int_as_float((int)(cd & 0xFFu))};
+            to[1] = f32x4{v[2], v[3], v[2] + v[3], __int_as_float((int)(cd >> 8))};
+        };
+        if constexpr (EMIT) ask_two(min(tid, n_two - 1), two_v, two_c);
         // (a uniform test skips what is not there; indices past the end read the last word again)
 #pragma unroll
         for (int j = 0; j < NB; ++j) { t[j] = make_uint4(0, 0, 0, 0); if (j * NT < n16) t[j] = src[min(tid + j * NT, n16 - 1)]; }
@@ -1042,27 +1059,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         for (int j = 0; j < NS; ++j) if (tid + j * NT < nt) s_tab[tid + j * NT] = u[j];
         if (tid < 2 * SOP_K_MAXA) s_gpar[tid] = gp;
         if constexpr (EMIT) {
-            // two atoms of a bin a thread, four of them in flight: their values, the sums and the codes
-            const int n_two = p.n_bins * (SOP_K_MAXA / 2);
-            for (int i0 = tid; i0 < n_two; i0 += 4 * NT) {
+            if (tid < n_two) put_two(tid, two_v, two_c);
+            for (int i0 = tid + NT; i0 < n_two; i0 += 4 * NT) {
                 f32x4 v[4];
-                uint16_t cd[4];
+                uint32_t cd[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = min(i0 + j * NT, n_two - 1), q = i % (SOP_K_MAXA / 2);
-                    const BinRec& r = *reinterpret_cast<const BinRec*>(p.bins + (size_t)(i / (SOP_K_MAXA / 2)) * p.rec_bytes);
-                    { const float2 v0 = *reinterpret_cast<const float2*>(r.val[2 * q]), v1 = *reinterpret_cast<const float2*>(r.val[2 * q + 1]); v[j] = {v0.x, v0.y, v1.x, v1.y}; }
-                    cd[j] = *reinterpret_cast<const uint16_t*>(&r.code_lo[2 * q]);
-                }
+                for (int j = 0; j < 4; ++j) ask_two(min(i0 + j * NT, n_two - 1), v[j], cd[j]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = i0 + j * NT, q = i % (SOP_K_MAXA / 2);
-                    if (i < n_two) {
-                        f32x4* const to = reinterpret_cast<f32x4*>(s_bins + (i / (SOP_K_MAXA / 2)) * rec) + 2 * q;
-                        to[0] = f32x4{v[j][0], v[j][1], v[j][0] + v[j][1], __int_as_float(cd[j] & 0xFF)};
-                        to[1] = f32x4{v[j][2], v[j][3], v[j][2] + v[j][3], __int_as_float(cd[j] >> 8)};
-                    }
-                }
+                for (int j = 0; j < 4; ++j) if (i0 + j * NT < n_two) put_two(i0 + j * NT, v[j], cd[j]);
             }
         }
         for (int i0 = tid + NB * NT; i0 < n16; i0 += 4 * NT) {
