@@ -345,12 +345,13 @@ __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float
             if constexpr (RANK) rk.add(i, w[i], cb[i], ss, yv);
             put_code<EPL, CODES>(codes, i, (uint32_t)r[j].clo + (up ? 1u : 0u), wide_codes);
         }
-        // (one chunk's look-ups in flight at a time where the pass keeps many sums: a register budget, not an order)
+        // (one chunk's look-ups in flight at a time where the pass keeps many sums: a register budget, not an order.  With codes beside the tie test as well: the
+        // elements' lane masks would otherwise push a hundred constants of the row loop out of the scalar registers, 33 with the barrier)
         if constexpr (RANK) {
             asm volatile("" : "+v"(e0), "+v"(e1), "+v"(wd), "+v"(rk.n0), "+v"(rk.n1), "+v"(rk.d0), "+v"(rk.d1));
             if constexpr (METRIC == 2) asm volatile("" : "+v"(ew));
-            __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (RANK || (CODES && TIES && EPL == 16)) __builtin_amdgcn_sched_barrier(0);
     }
     Sums s;
     s.err = EPL == 16 ? e0 + e1 : e0;
