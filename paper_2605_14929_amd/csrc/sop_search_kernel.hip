@@ -365,7 +365,7 @@ __device__ __forceinline__ Sums eval_residual(const float (&w)[EPL], const float
 // table address are formed once per element, used for every atom and dropped, so no array of either is ever held.  Same
 // arithmetic, in the same order, as eval_residual (metrics WSE and MSE) or eval_direct (metric COS; ERR: with the error sum).  CODES: one
 // atom (N = 1).
-template <int EPL, int METRIC, int N, bool CODES, bool RANK, bool KEEPCW, bool ERR, class SRC>
+template <int EPL, int METRIC, int N, bool CODES, bool RANK, int KEEPCW, bool ERR, class SRC>
 __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const float (&cb)[EPL], const SRC& src, float ss, int a, Sums (&out)[N],
                                                     bool wide_codes, uint32_t (&codes)[EPL / 4])
 {
@@ -374,7 +374,7 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
     // elements a set (same registers; 28672 x 8192, seven atoms 8 % of a search, a model's layers 2 %).  One atom alone does not: five atoms of fitted codebooks, 4096 x 11008,
     // 73.2 us against 75.1.
     constexpr bool AHEAD = METRIC != 1 && !SRC::WIDE && N > 1;
-    constexpr int CH = AHEAD ? (N > 2 ? 1 : N > 1 ? 2 : 4) : N > 2 || (N > 1 && RANK) ? 2 : 4;
+    constexpr int CH = AHEAD ? (N > 2 ? 1 : 2) : N > 2 || (N > 1 && RANK) ? 2 : 4;
     float e0[N], e1[N], wd[N], ew[N];
     RankSums<EPL> rk[N];
 #pragma unroll
@@ -433,7 +433,7 @@ __device__ __forceinline__ void eval_residual_group(const float (&w)[EPL], const
                 }
                 if constexpr (RANK || METRIC == 1) {
                     float wi = w[i];
-                    if constexpr (!KEEPCW) asm volatile("" : "+v"(wi));       // (c w is formed again for every atom rather than kept: 16 registers)
+                    if (i >= KEEPCW) asm volatile("" : "+v"(wi));             // (c w is formed again for every atom rather than kept: a register an element)
                     rk[n].add(i, wi, cb[i], ss, yv);
                 }
                 put_code<EPL, CODES>(codes, i, (uint32_t)r[n][j].clo + (up ? 1u : 0u), wide_codes);
@@ -1285,8 +1285,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 const float4 gpar = s_gpar[2 * a];
                 float lo = 0.0f, hi = 0.0f;
                 if (CL) { const float4 g2 = s_gpar[2 * a + 1]; lo = g2.x; hi = g2.y; }
+                // Products c w of the statistics kept for the passes with ranking or direct cosine sums: all of them where two atoms leave registers for them; fp32
+                // planes of two atoms have room for ten, with metric MSE for eight (up to five registers spilled with more; formed again for every atom, with none
+                // kept: 4096 x 11008, every plane, 83.5 us, with ten 78.5; bf16 65.6 with all).
+                constexpr int keep_cw = NA != 2 ? 0 : BF16 || !EMIT || METRIC == 1 ? EPL : METRIC == 2 ? 8 : 10;
                 Sums sn[N];
-                eval_residual_group<EPL, METRIC, N, CD, RK && METRIC != 1, NA == 2 && (BF16 || !EMIT), METRIC != 1 || EMIT>(w, cb, FlySrc<EPL, CL, EMIT>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg, rec}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
+                eval_residual_group<EPL, METRIC, N, CD, RK && METRIC != 1, keep_cw, METRIC != 1 || EMIT>(w, cb, FlySrc<EPL, CL, EMIT>{w, sp.rr, gpar.z, gpar.w, lo, hi, lds_neg, rec}, sp.ss, a, sn, EMIT && ((sw.wide >> a) & 1u), codes);
 #pragma unroll
                 for (int n = 0; n < N; ++n) settle(a + n, sn[n], CD && want_codes);
             };
