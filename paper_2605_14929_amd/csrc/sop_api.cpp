@@ -558,8 +558,9 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     int occ = 1, mode = 0;
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
-    p.n_tab_codes = search_tab_codes(na, p.n_bins, emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes, p.n_tab_codes, c->lds_max);
-    const size_t dyn_lds = search_lds(na, p.n_bins, emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes, p.n_tab_codes);
+    const int lds_rec = emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes;
+    p.n_tab_codes = search_tab_codes(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes, c->lds_max);
+    const size_t dyn_lds = search_lds(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes);
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds;
     hipError_t e = hipSuccess;

@@ -37,9 +37,8 @@ SOP_K_HD constexpr int pair_index(int i, int j) { return i * (2 * SOP_K_MAXA - i
 /* bit of pair (i,j), i < j, in the chain in which a search of more than two atoms forms the pairs (metrics WSE and MSE) */
 SOP_K_HD constexpr int chain_bit(int i, int j) { return j * (j - 1) / 2 + i; }
 
-/* Tables of 256 selector words that take the pairs from the order in which a search of na atoms forms them to the order requested, and their bytes */
-SOP_K_HD constexpr int search_perm_tables(int na) { return na == 2 ? 0 : (na * (na - 1) / 2 + 7) / 8; }
-#define SOP_K_PERM_BYTES(na) (search_perm_tables(na) * 1024)
+/* Tables of 256 selector words that take the pairs from the order of a chain to the order requested (metrics WSE and MSE, more than two atoms) */
+SOP_K_HD constexpr int search_perm_tables(int na, bool cosine) { return na == 2 || cosine ? 0 : (na * (na - 1) / 2 + 7) / 8; }
 
 /* Sum columns of a variant unrolled for na atoms: atoms, pairs i < j of them (lexicographic), count of zero-norm lanes; and the same
  * rounded up to the four columns that a wavefront adds up together */
@@ -169,13 +168,13 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
 }
 
 /* LDS of a search unrolled for na atoms, beside the kernel's own variables (below 1 KiB): selector tables, bin records, scale table, group parameters, outputs and sums */
-inline size_t search_lds(int na, int n_bins, int rec_bytes, int n_codes)
+inline size_t search_lds(int na, bool cosine, int n_bins, int rec_bytes, int n_codes)
 {
-    return (size_t)SOP_K_PERM_BYTES(na) + (size_t)n_bins * rec_bytes + (((size_t)n_codes * 8 + 15) & ~(size_t)15) + 2 * SOP_K_MAXA * 16 + (1 + SOP_K_OUT_WORDS + search_slots(na)) * 8;
+    return (size_t)search_perm_tables(na, cosine) * 1024 + (size_t)n_bins * rec_bytes + (((size_t)n_codes * 8 + 15) & ~(size_t)15) + 2 * SOP_K_MAXA * 16 + (1 + SOP_K_OUT_WORDS + search_slots(na)) * 8;
 }
 /* Scale codes tabulated: all of them, or none where the table does not fit beside the bins and the kernel computes the scales instead, to the same bits: planes of seven
  * or eight atoms with 1024 bins beside more than about 1300 codes (seven atoms, 4096 x 11008, 2048 codes: 267 us; such planes of three atoms, which fit, 106.) */
-inline int search_tab_codes(int na, int n_bins, int rec_bytes, int n_codes, size_t lds_max) { return search_lds(na, n_bins, rec_bytes, n_codes) + 1024 > lds_max ? 0 : n_codes; }
+inline int search_tab_codes(int na, bool cosine, int n_bins, int rec_bytes, int n_codes, size_t lds_max) { return search_lds(na, cosine, n_bins, rec_bytes, n_codes) + 1024 > lds_max ? 0 : n_codes; }
 
 /* Layer sums of a single search.  A word of them counts in its top bits the workgroups that have added to it (units of 2^56 in the first
  * SOP_K_REPL - 1 rows, of 2^60 in the last one, which takes those rows' totals).  A sum must never reach into its count or borrow from it,

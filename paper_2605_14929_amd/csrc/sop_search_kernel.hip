@@ -807,10 +807,10 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
     extern __shared__ __align__(16) char s_mem[];
     // LDS: selector bits | bin table | (scale, reciprocal) table | group parameters | reduction scratch
-    constexpr bool ORDERED = METRIC != 1 && NA != 2;                                // (a comparison of cosines is one of products)
-    constexpr int NPERM = search_perm_tables(NA);
+    constexpr int NPERM = search_perm_tables(NA, METRIC == 1);                      // (a comparison of cosines is one of products: no chain)
+    constexpr bool ORDERED = NPERM != 0;
     uint32_t* const s_perm = reinterpret_cast<uint32_t*>(s_mem);                  // [NPERM][256] selector bits of eight bits of a chain of pairs
-    char* const s_bins = s_mem + SOP_K_PERM_BYTES(NA);                            // [n_bins] records
+    char* const s_bins = s_mem + NPERM * 1024;                                    // [n_bins] records
     const uint32_t rec = EMIT ? SOP_K_WIDE_BIN_BYTES(NA) : p.rec_bytes;
     const size_t bins_bytes = (size_t)p.n_bins * rec;
     float2* s_tab = reinterpret_cast<float2*>(s_bins + bins_bytes);
