@@ -37,6 +37,12 @@ static int bin_of(float x, float xl, float xh, float sc, float off)
     return (int)(f2u(t) - f2u(SOP_K_BIN_MAGIC));
 }
 
+// Bins of a table: the smallest count that resolves the alphabet.  Even, so that a table of 72-byte records is whole 16-byte words, in which the kernels copy it and
+// behind which what follows it in LDS is aligned.
+static constexpr int kBinCounts[] = {16, 24, 32, 40, 48, 56, 64, 80, 96, 112, 128, 160, 192, 256, 384, 512, 768, 1024};
+static constexpr bool even_counts() { for (int n : kBinCounts) if (n % 2 || n > SOP_K_MAXBINS) return false; return true; }
+static_assert(even_counts(), "bin tables are whole 16-byte words");
+
 // Fill atom slot `ia` of the bin records for the table range [xl, xh] (wider than the atom: values
 // beyond the atom's endpoints take its first / last entry); false when some bin would hold two code
 // boundaries or the binning leaves [0, n_bins).
@@ -97,8 +103,8 @@ sop_status soph::plan_alphabet(std::string* err, const sop_atom* atoms, int n_at
             const volatile float h = 0.5f * L[j];
             if (h + h != L[j]) return planfail(err, SOP_EATOM, "atom entry too small: a non-zero entry must be at least 2^-125 in magnitude");
         }
-        // The search kernels that write no codes form a code boundary as the binary32 sum of its neighbours' halves
-        // instead of reading it.  That sum is the boundary (the binary64 mean rounded once to binary32): both round the
+        // The search kernels form a code boundary as the binary32 sum of its neighbours' halves: the table stores none.
+        // That sum is the boundary (the binary64 mean rounded once to binary32): both round the
         // same real number once, the binary64 mean being exact whenever its low bits can matter.  Checked, not assumed:
         for (int j = 0; j + 1 < N; ++j) {
             const volatile float hs = 0.5f * L[j] + 0.5f * L[j + 1];
@@ -155,7 +161,6 @@ sop_status soph::plan_alphabet(std::string* err, const sop_atom* atoms, int n_at
     // smallest bin count for which every bin of every atom holds at most one code boundary.  The
     // table spans SOP_K_BIN_EXT times the atom's range, so that a block whose scale was rounded down
     // needs no clamp.
-    static const int kBinCounts[] = {16, 24, 32, 40, 48, 56, 64, 80, 96, 112, 128, 160, 192, 256, 384, 512, 768, 1024};
     for (int nb : kBinCounts) {
         pl.img.assign((size_t)nb, BinRec{});
         bool ok = true;

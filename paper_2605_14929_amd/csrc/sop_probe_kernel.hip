@@ -122,8 +122,8 @@ __global__ __launch_bounds__(1024) void issue_probe_kernel(float* __restrict__ o
 // Calibration kernel: the element pass of the search kernel on its own (kinds 15..18 of the issue probe).  Per
 // iteration a lane runs six passes ("atoms") over 16 elements held in registers: a table look-up in LDS at a bin that
 // differs from lane to lane (records of 33 words, fields apart by the atom count; 256 bins), the choice between the two values
-// read, residual fma, c*d, error fma, cosine-sum fma.  It tells what the look-ups cost beside the arithmetic: LDS serves
-// 128 bytes a clock to the four SIMDs of a compute unit.
+// read, residual fma, c*d, error fma, cosine-sum fma.  It tells what the look-ups cost beside the arithmetic: a
+// two-address 4-byte read of 64 lanes takes a compute unit 5.1 cycles (100 bytes a clock), an 8-byte one 2.9.
 //   MODE 0  12-byte look-up: boundary, value below, value above            (6 vector instructions per element)
 //   MODE 1   8-byte look-up: the two values, boundary = their sum          (7 with one two-address read; the search kernel's records hold the two values side by side)
 //   MODE 2  no look-up, the arithmetic of MODE 1 on register values        (7)

@@ -595,7 +595,10 @@ template <int V> struct ic { constexpr operator int() const { return V; } };    
 // better than a" for the caller's pair (a, b), and the internal order may have swapped the two, in which case internal j keeps the block on a tie:
 // pick_j = error[j] < error[i] + swapped, the borrow of a subtraction with a carry.  A pair adds the chosen atom's deficit to its running sum and
 // shifts its bit into `chain` by the carry of an addition; pair (i, j) ends at bit chain_bit(i, j).  Five instructions a pair and no test of
-// whether it is requested, where the general form takes eleven (scalar instructions and branches cost about as much issue time as vector ones).
+// whether it is requested, where the general form takes eleven (scalar instructions and branches cost about as much issue time as vector ones).  Pairs that are
+// not requested are formed as well and go nowhere.  That costs a list of one pair (4096 x 4096, six atoms: unsigned 30.2 us either way, signed word 40.8 pair by pair
+// and 43.1 in the chain, all fifteen 43.7 and 43.1), but a second form beside the chain for short lists made the chain's own step 1 % slower and gained one
+// pair 1 to 2 %, and tests that leave out columns without a requested pair cost every other list 0.5 to 1 %.
 // Up to three pairs (i, J) at once: a lane mask that a vector instruction writes may be read by another two instructions later at the earliest, which
 // three subtractions in a row are.  (The compiler makes more of either carry.)   SOPK_FIELD: offset and width of the pair's bit in `flips`.
 #define SOPK_FIELD(i, j) (pair_index(i, j) | 1 << 16)
@@ -1005,9 +1008,8 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
             load_norms(p.c, (unsigned int)p.Kc, (strip * 64u + (unsigned int)lane) * EPL, (unsigned int)lane < lanes_of(strip, p.K));
         }
     }
-    // Tables into LDS: the first 16 bytes of the bin table for four in flight per thread, the scale table and the group parameters are all asked
-    // for before the first of them is waited for; a loop of one load, wait, one write would spend a round trip to L2 per word (the bin
-    // table's records are multiples of 16 bytes)
+    // Tables into LDS: the first words of the bin table, of the scale table and the group parameters are all asked for before the first of them is waited
+    // for; a loop of one load, wait, one write would spend a round trip to L2 per word.  (A table has an even number of bins: whole 16-byte words.)
     {
         const int n16 = EMIT ? 0 : p.n_bins * (int)p.rec_bytes / 16, nt = p.n_tab_codes, tid = (int)threadIdx.x;
         const uint4* src = reinterpret_cast<const uint4*>(p.bins);
