@@ -8,7 +8,7 @@ import pytest
 import paper_2605_14929_amd as sop
 from oracle import atoms as OA, pairsearch as ops
 import sop_inputs as si
-from gpu_util import compare, oracle_fmt, run_gpu
+from gpu_util import compare, ctx, oracle_fmt, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -18,33 +18,65 @@ NEG = lambda t: OA.to_f32(-np.asarray(t, dtype=np.float64)[::-1])
 LONG = [SH, NF, NEG(NF5), NF, NEG(SH), NF5, NEG(NF), SH5]
 
 
-def _layer(M, K, seed):
+def _layer(M, K, seed, bf16=False):
     W, c = si.student_t_weights(M, K, 4.0, seed), si.channel_norms(K, 1.0, seed + 1)
+    if bf16:
+        W = si.generate.bf16_round(W)
     W[1, :64] = 0.0                                               # every atom ties
     c[64:96] = 0.0                                                # errors are zero: every atom ties
     return W, c
 
 
+@pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("g", [8, 16, 32])
-@pytest.mark.parametrize("fmt", ["UE4M4", "E4M3"])
+@pytest.mark.parametrize("fmt,rule", [("UE4M4", 0), ("E4M3", 0), ("E4M3", 1)])
 @pytest.mark.parametrize("A", range(2, 9))
-def test_ties_and_swapped_pairs(A, fmt, g):
-    W, c = _layer(9, 1120, 8100 + A)
+def test_ties_and_swapped_pairs(A, fmt, rule, g, bf16):
+    W, c = _layer(9, 1120, 8100 + A, bf16)
     fmt = sop.fmt_by_name(fmt)
     for tabs in (LONG[:A], LONG[:A][::-1]):
-        compare(run_gpu(W, c, tabs, g, fmt, emit=False), ops.pair_search(W, c, tabs, g, oracle_fmt(fmt)), A * (A - 1) // 2, emit=False)
+        got = run_gpu(W, c, tabs, g, fmt, scale_rule=rule, bf16=bf16, emit=False)
+        compare(got, ops.pair_search(W, c, tabs, g, oracle_fmt(fmt), scale_rule=rule), A * (A - 1) // 2, emit=False)
 
 
-@pytest.mark.parametrize("metric", [sop.SEL_WSE, sop.SEL_MSE])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("metric", [sop.SEL_WSE, sop.SEL_MSE, sop.SEL_COS])
 @pytest.mark.parametrize("A", [3, 6, 7, 8])
-def test_part_of_the_pairs_in_any_order(A, metric):
-    W, c = _layer(6, 1120, 8200 + A)
+def test_part_of_the_pairs_in_any_order(A, metric, bf16):
+    W, c = _layer(6, 1120, 8200 + A, bf16)
     fmt, tabs, rng = sop.fmt_by_name("UE4M4"), LONG[:A], np.random.default_rng(A)
     pairs = list(itertools.combinations(range(A), 2))
     for n in (1, 2, len(pairs) // 2, len(pairs)):
         some = [pairs[i] for i in rng.permutation(len(pairs))[:n]]
-        got = run_gpu(W, c, tabs, 16, fmt, metric=metric, pairs=some, emit=False)
+        got = run_gpu(W, c, tabs, 16, fmt, metric=metric, pairs=some, bf16=bf16, emit=False)
         compare(got, ops.pair_search(W, c, tabs, 16, oracle_fmt(fmt), metric=metric, pairs=some), n, emit=False)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("A", [3, 6, 8])
+def test_selectors_of_several_layers(A, bf16):
+    """The model-wide call: layers of several shapes with selector words and without, ties, copies in the internal order and part of the pairs in an order of
+    their own; each layer as in a search of its own, and as the oracle has it."""
+    import torch
+    fmt, tabs, rng = sop.fmt_by_name("UE4M4"), LONG[:A][::-1], np.random.default_rng(A)
+    pairs = list(itertools.combinations(range(A), 2))
+    some = [pairs[i] for i in rng.permutation(len(pairs))[:max(2, len(pairs) * 2 // 3)]]
+    data = [_layer(M, K, 8600 + i, bf16) for i, (M, K) in enumerate([(9, 1120), (3, 2048), (33, 160), (8, 1120)])]
+    cx = ctx()
+    cx.set_alphabet(tabs)
+    cx.set_pairs(some)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    layers = [(torch.from_numpy(W).cuda().to(dt), torch.from_numpy(c).cuda()) for W, c in data]
+    wide = len(some) > 16
+    for want_sel in (True, False):
+        acos, atoms, words = cx.pair_search_layers(layers, 16, fmt, want_sel=want_sel)
+        torch.cuda.synchronize()
+        for i, (W, c) in enumerate(data):
+            ref = ops.pair_search(W, c, tabs, 16, oracle_fmt(fmt), pairs=some)
+            assert np.max(np.abs(acos[i].cpu().numpy() - ref.acos_pair)) <= 1e-6 and np.max(np.abs(atoms[i].cpu().numpy() - ref.acos_atom)) <= 1e-6
+            if want_sel:
+                got = words[i].cpu().numpy()
+                assert np.array_equal(got.view(np.uint16 if got.dtype == np.int16 else np.uint32).astype(np.uint32).reshape(-1), ref.sel_words)
 
 
 def test_errors_beyond_binary32_tie():
