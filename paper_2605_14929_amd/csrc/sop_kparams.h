@@ -108,7 +108,6 @@ struct KParams {
     unsigned int flip_slots;                          // bit q: output pair q is such a swapped pair
     // (byte arrays sit on 8-byte boundaries so that the kernels fetch them with scalar loads)
     unsigned int pair_slot_w[SOP_K_MAXP / 4];          // byte pi%4 of word pi/4: output index of pair pi = pair_index(i,j)
-    unsigned int chain_sel[(SOP_K_MAXP + 7) / 8 * 8];  // bit of the selector word that bit chain_bit(i,j) of a chain of pairs becomes, 0: not requested
     alignas(8) unsigned char pair_col[SOP_K_MAXP + 4]; // sum column of output pair o (in the variant's own numbering, see search_cols)
     // outputs
     // layer sums of 1-cos in fixed point (2^-22 units): every workgroup adds its share with integer
@@ -130,6 +129,7 @@ struct KParams {
     // [n_layers][SOP_K_REPL][SOP_K_NCOL], acos_pair / acos_atom are tables with rows of P / A values (a layer names its row)
     const struct LayerDesc* layers;
     int n_layers;
+    unsigned int chain_sel[(SOP_K_MAXP + 7) / 8 * 8];  // (last: only the searches that chain their pairs read it) bit of the selector word that bit chain_bit(i,j) of a chain of pairs becomes, 0: not requested
 };
 
 /* One layer of a model-wide launch (72 bytes, read with scalar loads) */
