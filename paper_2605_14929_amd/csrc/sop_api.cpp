@@ -559,10 +559,11 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
     const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
     const int lds_rec = emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes;
-    p.n_tab_codes = search_tab_codes(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes, c->lds_max);
-    const size_t dyn_lds = search_lds(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes);
+    const size_t sums_lds = lane_sums_in_lds(dtype == SOP_BF16, epl, sign_mode, (int)metric, emit != 0, na, false) ? lane_sums_bytes(na) : 0;
+    p.n_tab_codes = search_tab_codes(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes, c->lds_max - sums_lds);
+    const size_t dyn_lds = search_lds(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes) + sums_lds;
     if (p_out) *p_out = p;
-    if (lds_out) *lds_out = dyn_lds;
+    if (lds_out) *lds_out = dyn_lds - sums_lds;          // (the model-wide kernel keeps its lanes' sums in registers)
     hipError_t e = hipSuccess;
     if (c->occ_blocks[vi] == 0 || c->occ_lds[vi] != dyn_lds) {
         if (dyn_lds > 48 * 1024) {
@@ -581,7 +582,8 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     int evals = 0;                               // (a sign-negated copy under a signed word takes its original's candidates over)
     for (int i = 0; i < A; ++i) evals += sign_mode != 1 ? 1 : c->mirror[i] ? 0 : 2;
     const long long wg = search_workgroups(p.total_units, std::min(c->n_cu, SOP_K_SEARCH_MAXWG), emit ? 2 * evals : evals);
-    p.deal = p.total_units <= 4ll * SOP_K_SHORT_SHARE * c->n_cu ? 1u : 0u;
+    occ = search_waves(occ, p.total_units, wg);
+    p.deal = search_deal(na, emit != 0, p.total_units, c->n_cu) ? (unsigned int)occ : 0u;
     p.units_q = (unsigned int)(p.total_units / wg); p.units_r = (unsigned int)(p.total_units % wg);
     p.grid_magic = grid_magic(wg);
     p.sum_max = sum_max((unsigned int)wg);

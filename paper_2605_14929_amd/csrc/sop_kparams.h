@@ -45,6 +45,20 @@ SOP_K_HD constexpr int search_perm_tables(int na, bool cosine) { return na == 2 
 SOP_K_HD constexpr int search_cols(int na) { return na + na * (na - 1) / 2 + 1; }
 SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 * 4; }
 
+/* Searches of one layer that keep their lanes' running sums in LDS rather than in registers: 22 registers less for six atoms, 37 for eight, where that is
+ * a wavefront more per SIMD (see occ_for(); an add is one instruction either way, and the adds of a wavefront meet no other lane's word).  Measured, registers -> LDS,
+ * 4096 x 4096 and 4096 x 11008, bf16, g = 16: six atoms under a signed word 43.1 us -> 38.4 and 95.3 -> 89.1 (145 registers, now 126: three wavefronts, now four), by
+ * the cosine 43.6 -> 37.7 and 99.6 -> 90.8; seven 39.4 -> 35.4 and 88.7 -> 83.1, eight 45.2 -> 40.8 and 101.9 -> 96.2 (143 -> 109), under a signed word 72.6 -> 61.8 and
+ * 175 -> 143.8 (two wavefronts, now three); argmax rule 33.1 -> 30.2 and 74.0 -> 70.9; fp32, six atoms 35.5 -> 33.4 and 77.8 -> 74.0; 28672 x 8192, seven 475 -> 425.
+ * Where the sums are not what holds a wavefront back they stay in registers: six atoms of bf16 weights (four wavefronts as it is), one or two, planes, 8-element lanes, MSE under a
+ * signed word or the argmax rule (six spill up to 113 registers at four wavefronts), and the model-wide kernel, whose wavefronts of a SIMD are in different layers at a time. */
+SOP_K_HD constexpr bool lane_sums_in_lds(bool bf16, int epl, int sign_mode, int metric, bool emit, int na, bool multi)
+{
+    return !multi && !emit && epl == 16 && na != 2 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);
+}
+/* LDS of these sums: four sets (one a SIMD) of 64 words a column, on a 16-byte boundary */
+SOP_K_HD constexpr size_t lane_sums_bytes(int na) { return (size_t)4 * search_slots(na) * 64 * 4 + 8; }
+
 /* One bin of the element-search table.  For every atom the bin holds at most one code boundary.
  * The two values are stored HALVED (exactly; the element passes multiply by twice the block scale): the boundary
  * between two neighbouring entries then equals the binary32 sum of the two stored values, and the passes form it with
@@ -166,6 +180,20 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
     }
     return best;
 }
+
+/* Wavefronts per SIMD of such a launch, of a variant built for occ.  A share of eight steps, two for each of four wavefronts, takes longer than with three wavefronts, which
+ * end one after the other (5024 columns, 7.2 to 8 steps a SIMD: six atoms 19.0 us -> 17.9, cosine metric 20.8 -> 19.4, fp32 18.9 -> 18.1, one atom 9.2 -> 8.6; six
+ * under a signed word 23.9 -> 23.6).  Other shares do not (5, 6 and 7 steps: 4 to 10 % slower with three wavefronts; 9 to 17: 1 to 5 %). */
+inline int search_waves(int occ, long long steps, long long wg)
+{
+    const long long most = ((steps + wg - 1) / wg + 3) / 4;          /* steps of the longest share */
+    return occ == 4 && most == 8 ? occ - 1 : occ;
+}
+
+/* Are the wavefronts' first steps dealt out, and their rows asked for ahead of the tables?  In short shares, always (see search_kernel).  In longer ones
+ * searches of more than two atoms gain 0.3 to 0.7 us a call by it (2048 x 5120, six under a signed word 27.2 us -> 26.5, eight 28.0 -> 27.3, fp32 26.8 -> 25.8; 4096 x 11008, seven 80.8 ->
+ * 80.2), one or two atoms and the searches that write planes lose 0.1 to 0.4. */
+inline bool search_deal(int na, bool emit, long long steps, int n_cu) { return steps <= 4ll * SOP_K_SHORT_SHARE * n_cu || (na > 2 && !emit); }
 
 /* LDS of a search unrolled for na atoms, beside the kernel's own variables (below 1 KiB): selector tables, bin records, scale table, group parameters, outputs and sums */
 inline size_t search_lds(int na, bool cosine, int n_bins, int rec_bytes, int n_codes)

@@ -591,6 +591,34 @@ constexpr PairTab kPairTab = make_pair_tab();
 template <int PI> struct PairOf { static constexpr int i = kPairTab.first[PI], j = kPairTab.second[PI]; };
 template <int V> struct ic { constexpr operator int() const { return V; } };      // a compile-time integer as an argument
 
+// Running sums of 1 - cos in units of 2^-22 (integers: exact, so their order does not matter): atoms, pairs, and the number of steps in which
+// the lane's block had zero norm.
+// IN_LDS: not in the lane's registers but in LDS (lane_sums_in_lds()), where the wavefronts that share a SIMD's steps add to one set of 64 words a column, each lane to the word of
+// its number.  An add is one instruction either way.  Every wavefront empties its set after SOP_K_FLUSH_STEPS steps of its own, so a word never holds
+// more than that many steps of each of four wavefronts: 240 of at most 2^23.
+typedef __attribute__((address_space(3))) int lds_int;
+template <bool IN_LDS, int NA>
+struct LaneSums {
+    static constexpr bool in_lds = IN_LDS;
+    int a[IN_LDS ? 1 : SOP_K_MAXA], p[IN_LDS ? 1 : SOP_K_MAXP], z;
+    uint32_t at;                                   // LDS byte address of the lane's word of column 0
+    static __device__ __forceinline__ constexpr int pair_col(int pi) { return NA + kPairTab.first[pi] * (2 * NA - kPairTab.first[pi] - 1) / 2 + kPairTab.second[pi] - kPairTab.first[pi] - 1; }
+    __device__ __forceinline__ void clear()
+    {
+        z = 0;
+        if constexpr (!IN_LDS) {
+#pragma unroll
+            for (int i = 0; i < SOP_K_MAXA; ++i) a[i] = 0;
+#pragma unroll
+            for (int i = 0; i < SOP_K_MAXP; ++i) p[i] = 0;
+        }
+    }
+    __device__ __forceinline__ lds_int* word(int col) const { return (lds_int*)(size_t)at + 64 * col; }
+    __device__ __forceinline__ void add(int col, int v) const { __hip_atomic_fetch_add(word(col), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+    __device__ __forceinline__ void atom(int i, int v) { if constexpr (IN_LDS) add(i, v); else a[i] += v; }
+    __device__ __forceinline__ void pair(int pi, int v) { if constexpr (IN_LDS) add(pair_col(pi), v); else p[pi] += v; }
+};
+
 // The pairs of a block by their errors' bit patterns, which order as the errors do where none is below zero or a NaN (else see numbered_pairs).  The selector is "b strictly
 // better than a" for the caller's pair (a, b), and the internal order may have swapped the two, in which case internal j keeps the block on a tie:
 // pick_j = error[j] < error[i] + swapped, the borrow of a subtraction with a carry.  A pair adds the chosen atom's deficit to its running sum and
@@ -602,91 +630,93 @@ template <int V> struct ic { constexpr operator int() const { return V; } };    
 // Up to three pairs (i, J) at once: a lane mask that a vector instruction writes may be read by another two instructions later at the earliest, which
 // three subtractions in a row are.  (The compiler makes more of either carry.)   SOPK_FIELD: offset and width of the pair's bit in `flips`.
 #define SOPK_FIELD(i, j) (pair_index(i, j) | 1 << 16)
-template <int J, int I>
-__device__ __forceinline__ void pairs_1(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int J, int I, class SUMS>
+__device__ __forceinline__ void pairs_1(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     unsigned long long m0;
     int t0;
     asm("s_bfe_i64 %[m0], %[fl], %[f0]\n"
         "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n s_nop 1\n"
         "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n"
-        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]"
-        : [m0] "=&s"(m0), [t0] "=&v"(t0), [s0] "+v"(accp[pair_index(I, J)]), [ch] "+v"(chain)
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]"
+        : [m0] "=&s"(m0), [t0] "=&v"(t0), [ch] "+v"(chain)
         : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [d0] "v"(dlt[I]), [f0] "n"(SOPK_FIELD(I, J)) : "scc");
+    sums.pair(pair_index(I, J), t0);
 }
 // pairs (I, J) and (I - 1, J)
-template <int J, int I>
-__device__ __forceinline__ void pairs_2(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int J, int I, class SUMS>
+__device__ __forceinline__ void pairs_2(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     unsigned long long m0, m1;
     int t0, t1;
     asm("s_bfe_i64 %[m0], %[fl], %[f0]\n s_bfe_i64 %[m1], %[fl], %[f1]\n"
         "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n v_subb_co_u32 %[t1], %[m1], %[ej], %[e1], %[m1]\n s_nop 0\n"
         "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n v_cndmask_b32 %[t1], %[d1], %[dj], %[m1]\n"
-        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]\n"
-        "v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]\n v_add_u32 %[s1], %[s1], %[t1]"
-        : [m0] "=&s"(m0), [m1] "=&s"(m1), [t0] "=&v"(t0), [t1] "=&v"(t1), [s0] "+v"(accp[pair_index(I, J)]), [s1] "+v"(accp[pair_index(I - 1, J)]), [ch] "+v"(chain)
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]"
+        : [m0] "=&s"(m0), [m1] "=&s"(m1), [t0] "=&v"(t0), [t1] "=&v"(t1), [ch] "+v"(chain)
         : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [e1] "v"(score[I - 1]), [d0] "v"(dlt[I]), [d1] "v"(dlt[I - 1]),
           [f0] "n"(SOPK_FIELD(I, J)), [f1] "n"(SOPK_FIELD(I - 1, J)) : "scc");
+    sums.pair(pair_index(I, J), t0);
+    sums.pair(pair_index(I - 1, J), t1);
 }
 // pairs (I, J), (I - 1, J) and (I - 2, J)
-template <int J, int I>
-__device__ __forceinline__ void pairs_3(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int J, int I, class SUMS>
+__device__ __forceinline__ void pairs_3(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     unsigned long long m0, m1, m2;
     int t0, t1, t2;
     asm("s_bfe_i64 %[m0], %[fl], %[f0]\n s_bfe_i64 %[m1], %[fl], %[f1]\n s_bfe_i64 %[m2], %[fl], %[f2]\n"
         "v_subb_co_u32 %[t0], %[m0], %[ej], %[e0], %[m0]\n v_subb_co_u32 %[t1], %[m1], %[ej], %[e1], %[m1]\n v_subb_co_u32 %[t2], %[m2], %[ej], %[e2], %[m2]\n"
         "v_cndmask_b32 %[t0], %[d0], %[dj], %[m0]\n v_cndmask_b32 %[t1], %[d1], %[dj], %[m1]\n v_cndmask_b32 %[t2], %[d2], %[dj], %[m2]\n"
-        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_add_u32 %[s0], %[s0], %[t0]\n"
-        "v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]\n v_add_u32 %[s1], %[s1], %[t1]\n"
-        "v_addc_co_u32 %[ch], %[m2], %[ch], %[ch], %[m2]\n v_add_u32 %[s2], %[s2], %[t2]"
-        : [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [s0] "+v"(accp[pair_index(I, J)]),
-          [s1] "+v"(accp[pair_index(I - 1, J)]), [s2] "+v"(accp[pair_index(I - 2, J)]), [ch] "+v"(chain)
+        "v_addc_co_u32 %[ch], %[m0], %[ch], %[ch], %[m0]\n v_addc_co_u32 %[ch], %[m1], %[ch], %[ch], %[m1]\n v_addc_co_u32 %[ch], %[m2], %[ch], %[ch], %[m2]"
+        : [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [ch] "+v"(chain)
         : [fl] "s"(flips), [ej] "v"(score[J]), [dj] "v"(dlt[J]), [e0] "v"(score[I]), [e1] "v"(score[I - 1]), [e2] "v"(score[I - 2]),
           [d0] "v"(dlt[I]), [d1] "v"(dlt[I - 1]), [d2] "v"(dlt[I - 2]), [f0] "n"(SOPK_FIELD(I, J)), [f1] "n"(SOPK_FIELD(I - 1, J)), [f2] "n"(SOPK_FIELD(I - 2, J)) : "scc");
+    sums.pair(pair_index(I, J), t0);
+    sums.pair(pair_index(I - 1, J), t1);
+    sums.pair(pair_index(I - 2, J), t2);
 }
 #undef SOPK_FIELD
 // pairs (N - 1, J) .. (0, J) in this order
-template <int J, int N>
-__device__ __forceinline__ void pair_column(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int J, int N, class SUMS>
+__device__ __forceinline__ void pair_column(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     constexpr int done = N == 1 ? 1 : (N == 2 || N == 4) ? 2 : 3;
-    if constexpr (done == 1) pairs_1<J, N - 1>(flips, score, dlt, accp, chain);
-    else if constexpr (done == 2) pairs_2<J, N - 1>(flips, score, dlt, accp, chain);
-    else pairs_3<J, N - 1>(flips, score, dlt, accp, chain);
-    if constexpr (N > done) pair_column<J, N - done>(flips, score, dlt, accp, chain);
+    if constexpr (done == 1) pairs_1<J, N - 1>(flips, score, dlt, sums, chain);
+    else if constexpr (done == 2) pairs_2<J, N - 1>(flips, score, dlt, sums, chain);
+    else pairs_3<J, N - 1>(flips, score, dlt, sums, chain);
+    if constexpr (N > done) pair_column<J, N - done>(flips, score, dlt, sums, chain);
 }
-template <int J, int NA>
-__device__ __forceinline__ void ordered_pairs(int A, unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int J, int NA, class SUMS>
+__device__ __forceinline__ void ordered_pairs(int A, unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     // (a variant unrolled for six serves three atoms or more, one for eight seven or more)
-    if (J < (NA == 8 ? 7 : 3) || J < A) pair_column<J, J>(flips, score, dlt, accp, chain);
-    if constexpr (J > 1) ordered_pairs<J - 1, NA>(A, flips, score, dlt, accp, chain);
+    if (J < (NA == 8 ? 7 : 3) || J < A) pair_column<J, J>(flips, score, dlt, sums, chain);
+    if constexpr (J > 1) ordered_pairs<J - 1, NA>(A, flips, score, dlt, sums, chain);
 }
 
 // Pair PI and the following ones by the errors as numbers: what the chain took another way is put right.  (Errors below zero, which bit patterns order
 // the other way round; a NaN is not less than anything nor anything less than it, and internal i keeps the block.)
-template <int PI, int NA>
-__device__ __forceinline__ void numbered_pairs(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], int (&accp)[SOP_K_MAXP], uint32_t& chain)
+template <int PI, int NA, class SUMS>
+__device__ __forceinline__ void numbered_pairs(unsigned long long flips, const float (&score)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA], SUMS& sums, uint32_t& chain)
 {
     constexpr int i = PairOf<PI>::i, j = PairOf<PI>::j, c = chain_bit(i, j);
     if constexpr (j < NA) {
         const bool took_j = (chain >> c) & 1u, pick_j = score[j] < score[i] || (((flips >> PI) & 1u) && score[j] == score[i]);
         if (took_j != pick_j) {
-            accp[PI] += pick_j ? dlt[j] - dlt[i] : dlt[i] - dlt[j];
+            sums.pair(PI, pick_j ? dlt[j] - dlt[i] : dlt[i] - dlt[j]);
             chain ^= 1u << c;
         }
     }
-    if constexpr (PI + 1 < SOP_K_MAXP) numbered_pairs<PI + 1, NA>(flips, score, dlt, accp, chain);
+    if constexpr (PI + 1 < SOP_K_MAXP) numbered_pairs<PI + 1, NA>(flips, score, dlt, sums, chain);
 }
 
 // Selector of pair PI and of all following pairs (i < j in internal order), for every metric and alphabet: bit `slot` of the
 // block's selector word, and the chosen atom's deficit into the pair's running sum.
-template <int PI, int NA, int METRIC>
+template <int PI, int NA, int METRIC, class SUMS>
 __device__ __forceinline__ void all_pairs(const KParams& p, const Switches& sw, const float (&score)[SOP_K_MAXA],
                                           const float (&den)[SOP_K_MAXA], const int (&dlt)[SOP_K_MAXA],
-                                          int (&accp)[SOP_K_MAXP], uint32_t& bits)
+                                          SUMS& sums, uint32_t& bits)
 {
     constexpr int i = PairOf<PI>::i, j = PairOf<PI>::j;
     static_assert(pair_index(i, j) == PI, "pair enumeration");
@@ -704,14 +734,14 @@ __device__ __forceinline__ void all_pairs(const KParams& p, const Switches& sw, 
             const unsigned long long le = __builtin_amdgcn_ballot_w64(METRIC == 1 ? lhs >= rhs : lhs <= rhs);
             const bool pick_j = __builtin_amdgcn_inverse_ballot_w64(flip ? le : lt);
             const int chosen = pick_j ? dj : di;
-            accp[PI] += chosen;
+            sums.pair(PI, chosen);
             // bit = "internal j taken"; for swapped pairs the caller's selector is its complement, put
             // right by one xor with the mask of swapped pairs after the last pair
             const int slot = (p.pair_slot_w[PI / 4] >> (8 * (PI % 4))) & 0xFF;
             bits |= (pick_j ? 1u : 0u) << slot;
         }
     }
-    if constexpr (PI + 1 < SOP_K_MAXP) all_pairs<PI + 1, NA, METRIC>(p, sw, score, den, dlt, accp, bits);
+    if constexpr (PI + 1 < SOP_K_MAXP) all_pairs<PI + 1, NA, METRIC>(p, sw, score, den, dlt, sums, bits);
 }
 
 // The weights one lane reads per step, as they come from memory
@@ -802,12 +832,14 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     // the direct cosine sums outside the grouped passes: in the form that keeps registers low for the variants that are short of them
     // (the others have some left, and the form's scheduling fences cost the signed eight-atom search a sixth: 4096 x 4096, 77 us
     // -> 92; the signed one-atom search with every plane, g = 32, takes 33.4 us with it and 35.0 without)
+    constexpr bool LSUM = lane_sums_in_lds(BF16, EPL, SIGNMODE, METRIC, EMIT, NA, MULTI);
     constexpr bool LEAN = NA == 6 || (NA == 2 && EMIT);
     // ranking sums in a pass of their own where eight atoms of 8-element lanes leave no registers for them in the one element pass (up to
     // 17 spilled; argmax rule, metric MSE, fp32, 4096 x 4096, every plane: 157 us in one pass, 127 in two)
     constexpr bool SPLIT_RANK = EMIT && EPL == 8 && NA == 8;
     constexpr bool TOP_TEST = EMIT || (NA == 2 && SIGNMODE == 0 && EPL == 16);       // the row loop's test at its top (see there)
-    constexpr int NT = 256 * OCC, NW = 4 * OCC;                                   // threads, wavefronts of the workgroup
+    // wavefronts per SIMD, threads of the workgroup (a launch of short shares may have one wavefront less than the variant is built for, see search_waves())
+    const int waves = !MULTI && OCC == 4 && p.deal ? (int)p.deal : OCC, NT = 256 * waves;
     extern __shared__ __align__(16) char s_mem[];
     // LDS: selector bits | bin table | (scale, reciprocal) table | group parameters | reduction scratch
     constexpr int NPERM = search_perm_tables(NA, METRIC == 1);                      // (a comparison of cosines is one of products: no chain)
@@ -900,13 +932,9 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         st = q; row = r;
     };
 
-    // running sums of 1 - cos in units of 2^-22 (integers: exact, so their order does not matter): atoms,
-    // pairs, and the number of steps in which the lane's block had zero norm
-    int acca[SOP_K_MAXA], accp[SOP_K_MAXP], accz = 0;
-#pragma unroll
-    for (int i = 0; i < SOP_K_MAXA; ++i) acca[i] = 0;
-#pragma unroll
-    for (int i = 0; i < SOP_K_MAXP; ++i) accp[i] = 0;
+    LaneSums<LSUM, NA> sums;
+    sums.clear();
+    if constexpr (LSUM) sums.at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(char*)(s_acc + NSLOT + 1) + (uint32_t)((simd * NSLOT * 64 + lane) * 4);
     // Lane sums of every column, exact.  Four columns at a time: exchanges of half and quarter wavefronts (gfx950's lane swaps)
     // leave one column's sums over four lanes in each row of 16 lanes, the row is added up with data-parallel-primitive moves
     // (quads, half rows, rows: every lane of the row then holds the column's sum), and the first lane of each row adds it to
@@ -929,17 +957,35 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     auto fold_halves = [](int a, int b) -> int { const auto t = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false); return (int)(t[0] + t[1]); };
     auto fold_rows = [](int a, int b) -> int { const auto t = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false); return (int)(t[0] + t[1]); };
     int cl = MULTI ? -1 : 0;                       // the layer the arithmetic is in
+    // (LSUM: four columns' words, of any size, cut at bit 15 before the folds: below 2^18 for four words each)
+    auto join = [&](const int (&lo)[4], const int (&hi)[4], unsigned long long* dst, int fl) {
+        const int rl = row_sum(fold_rows(fold_halves(lo[0], lo[2]), fold_halves(lo[1], lo[3])));
+        const int rh = row_sum(fold_rows(fold_halves(hi[0], hi[2]), fold_halves(hi[1], hi[3])));
+        if ((fl & 15) == 0) atomicAdd(dst, (unsigned long long)(((long long)rh << 15) + (long long)rl));
+    };
     auto flush = [&](int layer) {
         int fl = lane;
         asm volatile("" : "+v"(fl));                 // (the address is formed here, not kept in a register through the row loop)
         unsigned long long* dst = s_acc + (MULTI ? layer * NSLOT : 0) + (fl >> 4);
         int val[NSLOT], n = 0;                       // the live columns of this variant (compile-time list)
+        if constexpr (LSUM) {
+            // (what the other wavefronts of the SIMD added goes along)
+            sums.add(NLIVE - 1, sums.z << 22); sums.z = 0;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) { val[n++] = acca[i]; acca[i] = 0; }
+            for (int j = 0; j < NSLOT; j += 4) {
+                int lo[4], hi[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { hi[i] = __hip_atomic_exchange(sums.word(j + i), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); lo[i] = hi[i] & 0x7FFF; hi[i] >>= 15; }
+                join(lo, hi, dst + j, fl);
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) { val[n++] = sums.a[i]; sums.a[i] = 0; }
 #pragma unroll
         for (int i = 0; i < SOP_K_MAXP; ++i)
-            if (kPairTab.second[i] < NA) { val[n++] = accp[i]; accp[i] = 0; }
-        val[n++] = accz << 22; accz = 0;
+            if (kPairTab.second[i] < NA) { val[n++] = sums.p[i]; sums.p[i] = 0; }
+        val[n++] = sums.z << 22; sums.z = 0;
 #pragma unroll
         for (int i = NLIVE; i < NSLOT; ++i) val[i] = 0;
 #pragma unroll
@@ -987,10 +1033,10 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
 #pragma unroll
         for (int i = 0; i < EPL; ++i) asm volatile("" : "+v"(cb[i]));
     };
-    // Short shares: the first step of each wavefront is its own and the others come from the counter (all from the counter, the first
+    // Where they are dealt out, the first step of each wavefront is its own and the others come from the counter (all from the counter, the first
     // two steps of a share went to its first wavefront, one after the other, while the others had none: six atoms, 1536 steps, 16.4 us
-    // -> 13.6), and its row and channel norms are asked for ahead of everything else.  Long ones take every step from the counter:
-    // wavefronts that start in step stay in step, and use the units by turns less well (six model layers of 2048 x 2048: 57 us ->
+    // -> 13.6), and its row and channel norms are asked for ahead of everything else.  For which launches: search_deal().  The model-wide kernel takes every step
+    // from the counter: wavefronts that start in step stay in step, and use the units by turns less well (six model layers of 2048 x 2048: 57 us ->
     // 59 with the first steps dealt out).
     const bool dealt = !MULTI && p.deal;
     unsigned int i_cur = 0u;
@@ -1046,7 +1092,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         // bit.  With the words formed here, pair by pair, by the first 256 threads, this was 0.3 us of every launch of six atoms and 1.0 us of eight.)
         if constexpr (ORDERED) {
             if (MULTI || p.sel_words) {
-                for (int k = wv >> 2; k < NPERM; k += OCC) {
+                for (int k = wv >> 2; k < NPERM; k += waves) {
                     uint32_t v = 0u;
 #pragma unroll
                     for (int i = 0; i < 8; ++i) v |= (uint32_t)__builtin_amdgcn_sbfe(tid, i, 1) & p.chain_sel[8 * k + i];
@@ -1054,8 +1100,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 }
             }
         }
-        if (tid < 4) s_next[tid] = dealt ? (unsigned int)OCC : 0u;
+        if (tid < 4) s_next[tid] = dealt ? (unsigned int)waves : 0u;
         for (int i = tid; i < n_acc; i += NT) s_acc[i] = 0ull;
+        if constexpr (LSUM) {
+            static_assert((2 + SOP_K_OUT_WORDS + NSLOT) % 2 == 0, "16-byte words");
+            for (int i = tid; i < 4 * NSLOT * 16; i += NT) reinterpret_cast<uint4*>(s_acc + NSLOT + 1)[i] = make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
         for (int j = 0; j < NB; ++j) if (tid + j * NT < n16) dst[tid + j * NT] = t[j];
 #pragma unroll
@@ -1191,7 +1241,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         pmax = valid ? pmax : 1.0f;
         nmax = valid ? nmax : 1.0f;
         const float wn = group_sum<LPB>(EPL == 16 ? wn0 + wn1 : wn0);
-        accz += wn > 0.0f ? 0 : 1;
+        sums.z += wn > 0.0f ? 0 : 1;
         // power of two that brings ||w||^2 into [1, 2) (exponent fields 1 .. 253: norms within 2^-126 .. 2^126)
         NormScale nsc;
         {
@@ -1259,7 +1309,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 }
                 const float rs = __frsqrt_rn(__fmaf_rn(nsc.wns, t.dy, 1.0e-37f));
                 dlt[a] = (int)__float_as_uint(__fmaf_rn(-t.ny, rs, 3.0f)) - 0x40000000;
-                acca[a] += dlt[a];
+                sums.atom(a, dlt[a]);
                 if (__builtin_expect(__any(t.weak) != 0, 0)) weak_atoms |= 1u << a;
                 if constexpr (EMIT) {
                     const long long ua = p.uidx[a];
@@ -1361,7 +1411,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 const int ia = (int)__float_as_uint(__fmaf_rn(-ny1, rs, 3.0f)) - 0x40000000;
 #pragma unroll
                 for (int a = 0; a < NA; ++a)
-                    if (a == wa) { acca[a] += ia - dlt[a]; dlt[a] = ia; }
+                    if (a == wa) { sums.atom(a, ia - dlt[a]); dlt[a] = ia; }
                 if constexpr (EMIT) {
                     if (p.blk_cos && leader) p.blk_cos[(long long)p.uidx[wa] * p.Nb + blk] = wnr > 0.0f ? 1.0f - __fmaf_rn(-ny1, rs, 1.0f) : 1.0f;
                 }
@@ -1557,7 +1607,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 const float rs = __frsqrt_rn(__fmaf_rn((raw && METRIC != 1) ? wn : nsc.wns, best.dy, 1.0e-37f));
                 const int ia = (int)__float_as_uint(__fmaf_rn(-best.ny, rs, 3.0f)) - 0x40000000;
                 dlt[a] = ia;
-                acca[a] += ia;
+                sums.atom(a, ia);
                 if (EMIT) {
                     const long long ua = p.uidx[a];
                     if (p.codes && valid) store_codes<EPL>(p, sw, a, cm, (long long)(cs * 64u + (unsigned int)lane) * EPL, codes);
@@ -1576,12 +1626,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
         uint32_t bits = 0;
         if constexpr (ORDERED) {
             uint32_t chain = 0u;
-            ordered_pairs<NA - 1, NA>(sw.A, flips, score, dlt, accp, chain);
+            ordered_pairs<NA - 1, NA>(sw.A, flips, score, dlt, sums, chain);
             if (__builtin_expect(odd != 0u, 0)) {
                 bool some = false;
 #pragma unroll
                 for (int a = 0; a < NA; ++a) some = some || !(score[a] >= 0.0f);
-                if (__any(some) != 0) numbered_pairs<0, NA>(flips, score, dlt, accp, chain);
+                if (__any(some) != 0) numbered_pairs<0, NA>(flips, score, dlt, sums, chain);
             }
             // from the chain's order to the selector's, eight bits at a time (the table holds the swapped pairs' complement too)
             if (MULTI ? lc_sel != nullptr : p.sel_words != nullptr) {
@@ -1589,7 +1639,7 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
                 for (int k = 0; k < NPERM; ++k) bits ^= s_perm[256 * k + ((chain >> (8 * k)) & 0xFFu)];
             }
         } else {
-            all_pairs<0, NA, METRIC>(p, sw, score, den, dlt, accp, bits);
+            all_pairs<0, NA, METRIC>(p, sw, score, den, dlt, sums, bits);
             bits ^= p.flip_slots;
         }
         void* const sel_words = MULTI ? lc_sel : p.sel_words;
@@ -1618,7 +1668,24 @@ __global__ __launch_bounds__(256 * OCC, 1) void search_kernel(const KParams p)
     }
 
     // ---- per-workgroup sums: what the lanes still hold joins the workgroup's integer sums in LDS ----
-    if (!MULTI || cl >= 0) flush(cl);
+    if constexpr (LSUM) {
+        sums.add(NLIVE - 1, sums.z << 22);
+        __syncthreads();
+        static_assert(NSLOT / 4 <= (OCC == 4 ? 12 : 4 * OCC), "a wavefront for every four columns");
+        if (wv < NSLOT / 4) {                                    // (four columns of all four SIMDs' words)
+            const lds_int* const from = (lds_int*)(size_t)(sums.at - (uint32_t)(simd * NSLOT * 256)) + wv * 256;
+            int v[4][4], lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[q][i] = from[q * NSLOT * 64 + 64 * i];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { lo[i] += v[q][i] & 0x7FFF; hi[i] += v[q][i] >> 15; }
+            join(lo, hi, s_acc + wv * 4 + (lane >> 4), lane);
+        }
+    } else if (!MULTI || cl >= 0) flush(cl);
     __syncthreads();
     const int tid = wv * 64 + lane;                // (not kept through the row loop)
     if constexpr (!MULTI) {
@@ -1733,6 +1800,7 @@ namespace {
 // plane 84 -> 72.7, fp32 4096 x 4096, six atoms 43.2 -> 37.4; the model-wide search of six atoms (bf16) spills a register at four wavefronts.
 constexpr int occ_for(bool bf16, int epl, int sign_mode, bool emit, int na, int metric, bool multi)
 {
+    if (lane_sums_in_lds(bf16, epl, sign_mode, metric, emit, na, multi)) return (na == 8 && sign_mode != 0) || (sign_mode == 2 && metric == 1) ? 3 : 4;      // (109 to 128 registers; 126 to 168)
     if (epl == 8) {
         if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;
         if (sign_mode == 1) return emit ? 2 : 3;
