@@ -144,8 +144,8 @@ struct sop_ctx {
     unsigned long long stab_clock = 0;
     int scale_rule = 0;                   // 0: absmax, 1: argmax
     unsigned char* static_scratch = nullptr;   // this device's copy of sop_static_scratch (looked up by sop_create)
-    int occ_blocks[864];                  // resident workgroups per CU of each kernel variant (0 = unknown)
-    size_t occ_lds[864];
+    int occ_blocks[1728];                 // resident workgroups per CU of each kernel variant (0 = unknown)
+    size_t occ_lds[1728];
     std::string err;
 };
 
@@ -556,10 +556,16 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     }
     const int sign_mode = c->scale_rule == 1 ? 2 : w;
     int occ = 1, mode = 0;
-    const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0, &occ, &mode);
-    const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, 0);
-    const int lds_rec = emit ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes;
-    const size_t sums_lds = lane_sums_in_lds(dtype == SOP_BF16, epl, sign_mode, (int)metric, emit != 0, na, false) ? lane_sums_bytes(na) : 0;
+    int planes = emit ? SOP_K_PLANES_ALL : SOP_K_PLANES_NONE;
+    if (emit && !p.scale_code && !p.codes && !p.blk_cos && !(p.blk_rank && p.blk_err)) {
+        const int one = p.blk_rank ? SOP_K_PLANES_RANK : SOP_K_PLANES_ERR;
+        if (one_plane_variants(epl, sign_mode, (int)metric, na, one)) planes = one;
+    }
+    const int ask = planes == SOP_K_PLANES_ALL ? 0 : planes;
+    const void* fn = sopk_search_kernel(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, ask, &occ, &mode);
+    const int vi = sopk_variant_index(dtype == SOP_BF16, g, sign_mode, (int)metric, emit, na_class, ask);
+    const int lds_rec = planes == SOP_K_PLANES_ALL ? SOP_K_WIDE_BIN_BYTES(na) : (int)p.rec_bytes;
+    const size_t sums_lds = lane_sums_in_lds(dtype == SOP_BF16, epl, sign_mode, (int)metric, planes, na, false) ? lane_sums_bytes(na) : 0;
     p.n_tab_codes = search_tab_codes(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes, c->lds_max - sums_lds);
     const size_t dyn_lds = search_lds(na, metric == SOP_SEL_COS, p.n_bins, lds_rec, p.n_tab_codes) + sums_lds;
     if (p_out) *p_out = p;

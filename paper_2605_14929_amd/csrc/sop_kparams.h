@@ -45,6 +45,20 @@ SOP_K_HD constexpr int search_perm_tables(int na, bool cosine) { return na == 2 
 SOP_K_HD constexpr int search_cols(int na) { return na + na * (na - 1) / 2 + 1; }
 SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 * 4; }
 
+/* Per-block planes that a variant of the search can write: none; any of them; the ranking scores or the block errors and no other.
+ * The variants of one plane are those of the searches that a program makes for a plane alone (metric WSE, lanes of 16 weights): the ranking scores of up to six atoms, the first pass of the
+ * per-layer procedure, and the errors of one or two under a positive scale, the comparison of weight formats.  They form no codes, need no 16-byte records and keep no
+ * pointers of planes that are not there, which is a wavefront more per SIMD, and store without a branch.  4096 x 11008, bf16, ranking scores of six atoms 130 us (any plane) -> 113,
+ * of two 49.8 -> 44.4, under a signed word (whose codes were formed to no end) 272 -> 165 and 105 -> 86 (g = 64); fp32 174 -> 121; 28672 x 8192, errors of one atom 149 -> 121. */
+#define SOP_K_PLANES_NONE 0
+#define SOP_K_PLANES_ALL 1
+#define SOP_K_PLANES_RANK 3
+#define SOP_K_PLANES_ERR 4
+SOP_K_HD constexpr bool one_plane_variants(int epl, int sign_mode, int metric, int na, int planes)
+{
+    return epl == 16 && metric == 0 && na != 8 && (planes == SOP_K_PLANES_RANK ? sign_mode != 2 : na == 2 && sign_mode == 0);
+}
+
 /* Searches of one layer that keep their lanes' running sums in LDS rather than in registers: 22 registers less for six atoms, 37 for eight, where that is
  * a wavefront more per SIMD (see occ_for(); an add is one instruction either way, and the adds of a wavefront meet no other lane's word).  Measured, registers -> LDS,
  * 4096 x 4096 and 4096 x 11008, bf16, g = 16: six atoms under a signed word 43.1 us -> 38.4 and 95.3 -> 89.1 (145 registers, now 126: three wavefronts, now four), by
@@ -52,9 +66,10 @@ SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 *
  * 175 -> 143.8 (two wavefronts, now three); argmax rule 33.1 -> 30.2 and 74.0 -> 70.9; fp32, six atoms 35.5 -> 33.4 and 77.8 -> 74.0; 28672 x 8192, seven 475 -> 425.
  * Where the sums are not what holds a wavefront back they stay in registers: six atoms of bf16 weights (four wavefronts as it is), one or two, planes, 8-element lanes, MSE under a
  * signed word or the argmax rule (six spill up to 113 registers at four wavefronts), and the model-wide kernel, whose wavefronts of a SIMD are in different layers at a time. */
-SOP_K_HD constexpr bool lane_sums_in_lds(bool bf16, int epl, int sign_mode, int metric, bool emit, int na, bool multi)
+SOP_K_HD constexpr bool lane_sums_in_lds(bool bf16, int epl, int sign_mode, int metric, int planes, int na, bool multi)
 {
-    return !multi && !emit && epl == 16 && na != 2 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);
+    if (planes == SOP_K_PLANES_RANK) return na == 6;
+    return !multi && planes == SOP_K_PLANES_NONE && epl == 16 && na != 2 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);
 }
 /* LDS of these sums: four sets (one a SIMD) of 64 words a column, on a 16-byte boundary */
 SOP_K_HD constexpr size_t lane_sums_bytes(int na) { return (size_t)4 * search_slots(na) * 64 * 4 + 8; }

@@ -8,7 +8,7 @@
 SOPK_DECL(0, 0) SOPK_DECL(0, 1) SOPK_DECL(0, 2) SOPK_DECL(1, 0) SOPK_DECL(1, 1) SOPK_DECL(1, 2)
 #undef SOPK_DECL
 
-// mode: 0 one layer, 2 a list of layers; *mode_out tells which was given (0 where the one asked for does not exist)
+// mode: 0 one layer, 2 a list of layers, SOP_K_PLANES_RANK or SOP_K_PLANES_ERR one layer and that plane only; *mode_out tells which was given (0 where the one asked for does not exist)
 extern "C" const void* sopk_search_kernel(int is_bf16, int g, int sign_mode, int metric, int emit, int na_class, int mode, int* occ, int* mode_out)
 {
     if (is_bf16) {
@@ -24,7 +24,7 @@ extern "C" const void* sopk_search_kernel(int is_bf16, int g, int sign_mode, int
 extern "C" int sopk_variant_index(int is_bf16, int g, int sign_mode, int metric, int emit, int na_class, int mode)
 {
     const int gi = g == 8 ? 0 : g == 16 ? 1 : g == 32 ? 2 : 3;
-    return ((((((is_bf16 ? 1 : 0) * 4 + gi) * 3 + sign_mode) * 3 + metric) * 2 + (emit ? 1 : 0)) * 3 + na_class) * 2 + (mode ? 1 : 0);
+    return ((((((is_bf16 ? 1 : 0) * 4 + gi) * 3 + sign_mode) * 3 + metric) * 2 + (emit ? 1 : 0)) * 3 + na_class) * 4 + (mode == 0 ? 0 : mode - 1);
 }
 
 // n_wg workgroups of 256 * occ threads
