@@ -33,7 +33,7 @@ extern "C" hipError_t sopk_sum_launch(const LsParams* p, void* stream);
 extern "C" hipError_t sopk_issue_probe_launch(int kind, int n_wg, int n_threads, int iters, float a, float b, float* out, void* stream);
 extern "C" hipError_t sopk_probe_launch(const void* x, long long n16, unsigned int* out, void* stream);
 extern "C" hipError_t sopk_sel_launch(const SelParams* p, int n_wg_count, int n_wg, void* stream);
-extern "C" hipError_t sopk_selm_launch(const SelMParams* p, int n_wg_count, int n_wg, void* stream);
+extern "C" hipError_t sopk_selm_launch(const SelMParams* p, int n_wg_count, int n_wg_next, int n_wg, void* stream);
 extern "C" hipError_t sopk_pack_launch(const PackParams* p, void* stream);
 
 namespace {
@@ -985,6 +985,9 @@ extern "C" sop_status sop_sum_f32(sop_ctx* c, const float* x, int64_t n, double*
 }
 
 // ------------------------------------------------------------------ block ranking and pools (step 2)
+static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t n_blocks, const int64_t* n_top, int n_levels,
+                                        int higher_is_better, uint8_t* level, float* tau, int64_t* n_a, int n_planes, void* stream);
+
 extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_blocks, int64_t n_top, int higher_is_better,
                                     uint8_t* pool_b, float* tau, int64_t* n_a, void* stream)
 {
@@ -995,6 +998,8 @@ extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_bl
     if (!aligned16(score)) return fail(c, SOP_EINVAL, "sop_partition: score must be 16-byte aligned");
     if ((reinterpret_cast<uintptr_t>(pool_b) & 3u) || (reinterpret_cast<uintptr_t>(tau) & 3u) || (reinterpret_cast<uintptr_t>(n_a) & 7u))
         return fail(c, SOP_EINVAL, "sop_partition: pool_b and tau must be 4-byte aligned, n_a 8-byte aligned");
+    // (the passes of several thresholds: from where they are faster whatever the scores, see SOP_K_SEL_ONE_MAX)
+    if (n_blocks > SOP_K_SEL_ONE_MAX) return partition_levels_impl(c, score, n_blocks, &n_top, 1, higher_is_better, pool_b, tau, n_a, 1, stream);
     SelParams p;
     std::memset(&p, 0, sizeof(p));
     p.score = score; p.n = n_blocks; p.n_top = n_top; p.higher = higher_is_better ? 1 : 0; p.all_b = n_top == 0;
@@ -1047,9 +1052,10 @@ static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t 
     // all planes no more than are resident at once (two of 1024 threads per compute unit): a second, half-empty round of
     // workgroups cost six planes a quarter of the pass
     const int n_wg_count = (int)std::min<long long>(std::max(std::min(c->n_cu / 2, 2 * c->n_cu / std::max(n_planes, 1)), 1), cquads);
+    const int n_wg_next = (int)std::min<long long>(std::max(std::min(c->n_cu, 2 * c->n_cu / std::max(n_planes, 1)), 1), cquads);      // (few of whose counts are not zero)
     DeviceGuard guard(c->device);
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
-    hipError_t e = sopk_selm_launch(&p, n_wg_count, n_wg, stream);
+    hipError_t e = sopk_selm_launch(&p, n_wg_count, n_wg_next, n_wg, stream);
     if (e != hipSuccess) return hipfail(c, e, "kernel launch");
     c->selm_dirty[c->selm_set ^ 1] = 0;
     if (any) { c->selm_dirty[c->selm_set] = std::max(c->selm_dirty[c->selm_set], n_planes); c->selm_set ^= 1; }

@@ -345,10 +345,20 @@ struct LsParams {
     uint16_t* codes;                 // optional [M*K] index into the ascending signed grid
 };
 
-/* Ranking of the blocks by a per-block score (exact selection of the score of a given rank) */
-#define SOP_K_SEL_THREADS 256         /* pool-mask kernel */
+/* Ranking of the blocks by a per-block score (exact selection of the scores of given ranks: nested pools) */
+#define SOP_K_SEL_THREADS 256         /* pool-mask and level kernels */
 #define SOP_K_CNT_THREADS 1024        /* counting kernels */
-#define SOP_K_SEL_BINS 2048          /* 11 + 11 + 10 bits of the 32-bit key over three passes */
+#define SOP_K_SEL_MAXLEV 8
+#define SOP_K_SEL_FINE 8192          /* bins of 256 keys for the scores in [7/8, 1) in the first pass */
+#define SOP_K_SEL_BINS1 (2048 - 1 + SOP_K_SEL_FINE)     /* bins of the first pass */
+#define SOP_K_SEL_BINS1_PAD ((SOP_K_SEL_BINS1 + SOP_K_CNT_THREADS - 1) / SOP_K_CNT_THREADS * SOP_K_CNT_THREADS)
+#define SOP_K_SEL_BINS 2048          /* one threshold: bins of a pass (11 + 11 + 10 bits of the 32-bit key); several: bins of a threshold in the second and third pass */
+#define SOP_K_SEL_DONE (SOP_K_SEL_BINS1_PAD + 2 * SOP_K_SEL_MAXLEV * SOP_K_SEL_BINS)      /* tickets of the passes, a 128-byte line each */
+#define SOP_K_SELM_WORDS (SOP_K_SEL_DONE + 3 * 32)      /* one set of counts and tickets of a plane */
+/* One threshold of one plane of at most SOP_K_SEL_ONE_MAX scores goes through three passes of 11, 11 and 10 bits, whose digits every workgroup of the next finds for
+ * itself: no pass ends in a ticket.  Against the passes of several thresholds, 2.8 M scores: cosines 29.1 us and 26.7, errors (spread over many binades) 28.7 and
+ * 37.7; 0.7 M 21.2 and 21.2, 20.2 and 29.2; 14.7 M 94 and 60, 92 and 78. */
+#define SOP_K_SEL_ONE_MAX (8 << 20)
 struct SelParams {
     const float* score;              // [n]
     long long n, n_top;              // 1 <= n_top <= n (n_top == 0: all_b)
@@ -361,16 +371,15 @@ struct SelParams {
     long long* n_a;                  // [1] blocks that stay in the first pool
 };
 
-/* Ranking with several thresholds at once (the sweep over the partition parameter p): nested pools */
-#define SOP_K_SEL_MAXLEV 8
-#define SOP_K_SELM_WORDS ((1 + 2 * SOP_K_SEL_MAXLEV) * SOP_K_SEL_BINS)   /* one set of digit counts */
-/* what the passes of such a ranking hand on, per score plane (written by a one-workgroup kernel after each counting pass) */
+/* what the passes hand on, per score plane (written by the last workgroup of a pass) */
 struct SelMState {
     unsigned int prefix[SOP_K_SEL_MAXLEV];       // digits of every threshold's key fixed so far
+    unsigned int mask[SOP_K_SEL_MAXLEV];         // their bits; all: the key is known, or every block ranks worse
     unsigned int rank_in[SOP_K_SEL_MAXLEV];      // rank wanted among the keys with those digits
     unsigned int above[SOP_K_SEL_MAXLEV];        // keys above those digits
     int alias[SOP_K_SEL_MAXLEV];                 // first threshold with the same digits so far (its histogram is the one used)
-    unsigned long long tkey[SOP_K_SEL_MAXLEV];   // after the last pass: the threshold's key (2^32: every block ranks worse)
+    unsigned int open;                           // bit t: threshold t has a histogram of its own in the next pass
+    unsigned long long tkey[SOP_K_SEL_MAXLEV];   // the threshold's key (2^32: every block ranks worse)
 };
 struct SelMParams {
     const float* score;              // [n]
@@ -378,7 +387,7 @@ struct SelMParams {
     int higher;                      // 1: a larger score ranks better
     int n_levels;                    // thresholds, 1 .. SOP_K_SEL_MAXLEV
     long long n_top[SOP_K_SEL_MAXLEV];   // non-decreasing sizes of the first pool (0: every block goes to the second pool)
-    unsigned int* hist;              // pass 0: [SOP_K_SEL_BINS]; pass 1: [MAXLEV][BINS]; pass 2: [MAXLEV][BINS] (zero when the call starts)
+    unsigned int* hist;              // first pass [SOP_K_SEL_BINS1_PAD], second and third [MAXLEV][BINS], tickets (zero when the call starts)
     unsigned int* hist_other;        // the set the next call counts into: cleared by this call
     unsigned char* level;            // [n] number of thresholds the block ranks strictly worse than
     float* tau;                      // [n_levels] threshold scores
