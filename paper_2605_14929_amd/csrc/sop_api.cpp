@@ -125,7 +125,9 @@ struct sop_ctx {
     char* d_bins = nullptr;               // (kImgBytes) the context's own image of the element-search table
     char* d_bins_cur = nullptr;           // the image the searches read (d_bins, or an image inside a caller's workspace during sop_search_layer)
     char* h_bins = nullptr;               // pinned staging for table images of sop_search_layer (allocated at its first call)
-    char* h_res = nullptr;                // pinned staging for its results
+    char* h_res = nullptr;                // pinned memory that its kernels write their results to: histograms, then ACos values
+    char* d_res = nullptr;                // the same as kernels address it
+    hipEvent_t pass_done[SOP_LAYER_MAX_ATOMS] = {};     // its histogram passes
     hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
     bool stage_pending = false;
     unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
@@ -145,7 +147,7 @@ struct sop_ctx {
     int scale_rule = 0;                   // 0: absmax, 1: argmax
     unsigned char* static_scratch = nullptr;   // this device's copy of sop_static_scratch (looked up by sop_create)
     int occ_blocks[1728];                 // resident workgroups per CU of each kernel variant (0 = unknown)
-    size_t occ_lds[1728];
+    size_t occ_lds[1728];                 // ... with this much LDS, the most asked for yet
     std::string err;
 };
 
@@ -268,6 +270,7 @@ extern "C" sop_status sop_destroy(sop_ctx* c)
         if (c->h_bins) (void)hipHostFree(c->h_bins);
         if (c->h_res) (void)hipHostFree(c->h_res);
         if (c->stage_done) (void)hipEventDestroy(c->stage_done);
+        for (hipEvent_t ev : c->pass_done) if (ev) (void)hipEventDestroy(ev);
         for (hipStream_t s : c->lane_stream) if (s) (void)hipStreamDestroy(s);
         for (hipEvent_t ev : c->lane_event) if (ev) (void)hipEventDestroy(ev);
         if (c->d_stab) (void)hipFree(c->d_stab);
@@ -291,41 +294,63 @@ static sop_status plan_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, 
     return s == SOP_OK ? s : fail(c, s, err);
 }
 
-// Plan the alphabet and make it the context's current one.  d_img == nullptr: the context's own image, copied
-// synchronously.  Otherwise the image goes through the pinned buffer h_stage to d_img with a copy on `st`
-// (the host does not wait), and the searches launched from now on read d_img.
-static sop_status install_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, char* d_img, char* h_stage, hipStream_t st)
+// An alphabet planned, its table image formed
+struct Planned { AlphabetPlan pl; int n_atoms = 0; size_t rec = 0, bytes = 0; };
+
+// records as far apart as the reads of the atoms evaluated together want them (see BinRec)
+static sop_status plan_image(sop_ctx* c, const sop_atom* atoms, int n_atoms, Planned& q)
 {
-    AlphabetPlan pl;
-    if (sop_status s = plan_alphabet(c, atoms, n_atoms, pl)) return s;
-    // records as far apart as the reads of the atoms evaluated together want them (see BinRec)
+    if (sop_status s = plan_alphabet(c, atoms, n_atoms, q.pl)) return s;
     bool together = false;
-    for (int i = 1; i < n_atoms; i += 2) together = together || pl.gid[i] == pl.gid[i - 1];
-    const size_t rec = together ? SOP_K_PAIR_BIN_BYTES : SOP_K_BIN_BYTES, img_bytes = pl.img.size() * rec;
-    {
-        std::vector<char> own(d_img ? 0 : img_bytes);
-        char* const to = d_img ? h_stage : own.data();
-        for (size_t b = 0; b < pl.img.size(); ++b) {
-            std::memcpy(to + b * rec, &pl.img[b], sizeof(BinRec));
-            std::memset(to + b * rec + sizeof(BinRec), 0, rec - sizeof(BinRec));
-        }
-        DeviceGuard guard(c->device);
-        hipError_t e = guard.err;
-        if (e == hipSuccess) e = d_img ? hipMemcpyAsync(d_img, to, img_bytes, hipMemcpyHostToDevice, st) : hipMemcpy(c->d_bins, to, img_bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) return hipfail(c, e, "upload of the table image");
+    for (int i = 1; i < n_atoms; i += 2) together = together || q.pl.gid[i] == q.pl.gid[i - 1];
+    q.n_atoms = n_atoms;
+    q.rec = together ? SOP_K_PAIR_BIN_BYTES : SOP_K_BIN_BYTES;
+    q.bytes = q.pl.img.size() * q.rec;
+    return SOP_OK;
+}
+
+static void write_image(const Planned& q, char* to)
+{
+    for (size_t b = 0; b < q.pl.img.size(); ++b) {
+        std::memcpy(to + b * q.rec, &q.pl.img[b], sizeof(BinRec));
+        std::memset(to + b * q.rec + sizeof(BinRec), 0, q.rec - sizeof(BinRec));
     }
-    c->d_bins_cur = d_img ? d_img : c->d_bins;
-    c->tables.swap(pl.tabs);
-    c->n_atoms = n_atoms;
-    c->n_bins = pl.n_bins;
-    c->rec_bytes = (unsigned int)rec;
-    for (int i = 0; i < n_atoms; ++i) {
-        const std::vector<float>& L = c->tables[pl.order[i]];
-        c->order[i] = pl.order[i]; c->gid[i] = pl.gid[i]; c->mirror[i] = pl.mirror[i]; c->selfsym[i] = pl.selfsym[i];
+}
+
+// the planned alphabet becomes the context's current one; the searches launched from now on read its image at d_img
+static void adopt(sop_ctx* c, Planned& q, char* d_img)
+{
+    c->d_bins_cur = d_img;
+    c->tables.swap(q.pl.tabs);
+    c->n_atoms = q.n_atoms;
+    c->n_bins = q.pl.n_bins;
+    c->rec_bytes = (unsigned int)q.rec;
+    for (int i = 0; i < q.n_atoms; ++i) {
+        const std::vector<float>& L = c->tables[q.pl.order[i]];
+        c->order[i] = q.pl.order[i]; c->gid[i] = q.pl.gid[i]; c->mirror[i] = q.pl.mirror[i]; c->selfsym[i] = q.pl.selfsym[i];
         c->tpos[i] = L.back(); c->tneg[i] = -L.front(); c->nent[i] = (int)L.size();
-        c->bin_sc[i] = pl.sc[i]; c->bin_off[i] = pl.off[i]; c->bin_lo[i] = pl.lo[i]; c->bin_hi[i] = pl.hi[i];
+        c->bin_sc[i] = q.pl.sc[i]; c->bin_off[i] = q.pl.off[i]; c->bin_lo[i] = q.pl.lo[i]; c->bin_hi[i] = q.pl.hi[i];
     }
     default_pairs(c);                      // (the occupancy cache is keyed by variant and LDS size: it stays valid)
+}
+
+// Plan the alphabet and make it the context's current one.  d_img == nullptr: the context's own image, copied
+// synchronously.  Otherwise the image goes through the pinned buffer h_stage to d_img with a copy on `st`
+// (the host does not wait).
+static sop_status install_alphabet(sop_ctx* c, const sop_atom* atoms, int n_atoms, char* d_img, char* h_stage, hipStream_t st)
+{
+    Planned q;
+    if (sop_status s = plan_image(c, atoms, n_atoms, q)) return s;
+    std::vector<char> own(d_img ? 0 : q.bytes);
+    char* const to = d_img ? h_stage : own.data();
+    write_image(q, to);
+    {
+        DeviceGuard guard(c->device);
+        hipError_t e = guard.err;
+        if (e == hipSuccess) e = d_img ? hipMemcpyAsync(d_img, to, q.bytes, hipMemcpyHostToDevice, st) : hipMemcpy(c->d_bins, to, q.bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return hipfail(c, e, "upload of the table image");
+    }
+    adopt(c, q, d_img ? d_img : c->d_bins);
     return SOP_OK;
 }
 
@@ -571,7 +596,7 @@ static sop_status pair_search_impl(sop_ctx* c, const void* W, sop_dtype dtype, i
     if (p_out) *p_out = p;
     if (lds_out) *lds_out = dyn_lds - sums_lds;          // (the model-wide kernel keeps its lanes' sums in registers)
     hipError_t e = hipSuccess;
-    if (c->occ_blocks[vi] == 0 || c->occ_lds[vi] != dyn_lds) {
+    if (c->occ_blocks[vi] == 0 || c->occ_lds[vi] < dyn_lds) {
         if (dyn_lds > 48 * 1024) {
             e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds);
             if (e != hipSuccess) return hipfail(c, e, "hipFuncSetAttribute(dynamic LDS)");
@@ -727,7 +752,7 @@ extern "C" sop_status sop_pair_search_layers(sop_ctx* c, const sop_layer* layers
                     p.acos_pair = c->n_pairs > 0 ? acos_pair_table : nullptr;
                     p.acos_atom = acos_atom_table;
                     const size_t dyn_lds = lds0 + (size_t)n * per_layer;
-                    if (c->occ_blocks[vi] == 0 || c->occ_lds[vi] != dyn_lds) {
+                    if (c->occ_blocks[vi] == 0 || c->occ_lds[vi] < dyn_lds) {
                         if (dyn_lds > 48 * 1024 && (e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds)) != hipSuccess)
                             return hipfail(c, e, "hipFuncSetAttribute(dynamic LDS)");
                         int nb = 0;
@@ -1121,7 +1146,7 @@ extern "C" sop_status sop_pack_blocks(sop_ctx* c, int64_t M, int64_t K, int g, s
 namespace {
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct LayerWs {
-    size_t rank, level, hist, tau, na, acos, bins, sc, codes, sel, total;
+    size_t rank, level, tau, na, acos, bins, sc, codes, sel, total;
     int n_img;
 };
 // An alphabet of more than eight atoms is covered by several searches of at most eight atoms each (the kernel unrolls over
@@ -1132,7 +1157,7 @@ constexpr int kAcosPer = SOP_K_MAXP + SOP_K_MAXA;          // doubles per such s
 // acos region, in doubles: kFixedMax searches of the fixed alphabet, then per atom a: 8 pairs (a, L_b(p_j))
 constexpr int kAcosFit = kFixedMax * kAcosPer;
 constexpr int kAcosAll = kAcosFit + SOP_LAYER_MAX_ATOMS * 8;
-LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int n_p, int bins, int pack)
+LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int pack)
 {
     const size_t Nb = (size_t)(M * (K / g));
     LayerWs w;
@@ -1140,10 +1165,9 @@ LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int n_p, int bins, int pack
     auto take = [&](size_t bytes) { const size_t o = off; off += up256(bytes); return o; };
     w.rank = take((size_t)A * Nb * sizeof(float));
     w.level = take((size_t)A * up256(Nb));
-    w.hist = take((size_t)A * std::max(n_p, 1) * bins * sizeof(long long));
     w.tau = take((size_t)SOP_LAYER_MAX_ATOMS * SOP_K_SEL_MAXLEV * sizeof(float));
     w.na = take((size_t)SOP_LAYER_MAX_ATOMS * SOP_K_SEL_MAXLEV * sizeof(long long));
-    w.acos = take((size_t)kAcosAll * sizeof(double));
+    w.acos = take((size_t)kAcosPer * sizeof(double));      // (the winner's own; the candidates' go to pinned host memory)
     w.n_img = kFixedMax + A + 2;                       // the searches of the fixed alphabet, one per atom's sweep, one spare, the winner
     w.bins = take((size_t)w.n_img * kImgBytes);
     w.sc = take(pack ? 2 * Nb * sizeof(uint16_t) : 0);
@@ -1176,7 +1200,7 @@ extern "C" sop_status sop_search_layer_workspace(sop_ctx* c, int64_t M, int64_t 
     if (!bytes) return fail(c, SOP_EINVAL, "sop_search_layer_workspace: bytes is NULL");
     if (sop_status s = shape_check(c, M, K, g)) return s;
     if (sop_status s = layer_opts_check(c, n_atoms, o)) return s;
-    *bytes = layer_ws(M, K, g, n_atoms, o->n_p, o->n_p ? o->fit_bins : 64, o->pack).total;
+    *bytes = layer_ws(M, K, g, n_atoms, o->pack).total;
     return SOP_OK;
 }
 
@@ -1192,7 +1216,7 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     const int A = n_atoms, n_p = o->n_p, bins = n_p ? o->fit_bins : 64;
     if (A < 2 && n_p == 0) return fail(c, SOP_EINVAL, "sop_search_layer: one atom and no sweep leave no pair to examine");
     if (o->pack && (!words || !payload)) return fail(c, SOP_EINVAL, "sop_search_layer: packing needs words_dev and payload_dev");
-    const LayerWs L = layer_ws(M, K, g, A, n_p, bins, o->pack);
+    const LayerWs L = layer_ws(M, K, g, A, o->pack);
     if (!ws || ws_bytes < L.total) return fail(c, SOP_ENOMEM, "sop_search_layer: workspace too small (see sop_search_layer_workspace)");
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return fail(c, SOP_EINVAL, "sop_search_layer: workspace must be 256-byte aligned");
     for (int a = 0; a < A; ++a)
@@ -1216,6 +1240,7 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     if (!c->h_bins) {
         if ((e = hipHostMalloc((void**)&c->h_bins, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, hipHostMallocDefault)) != hipSuccess ||
             (e = hipHostMalloc((void**)&c->h_res, res_bytes, hipHostMallocDefault)) != hipSuccess ||
+            (e = hipHostGetDevicePointer((void**)&c->d_res, c->h_res, 0)) != hipSuccess ||
             (e = hipEventCreateWithFlags(&c->stage_done, hipEventDisableTiming)) != hipSuccess)
             return hipfail(c, e, "pinned staging of sop_search_layer");
     }
@@ -1223,11 +1248,20 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         if ((e = hipEventSynchronize(c->stage_done)) != hipSuccess) return hipfail(c, e, "hipEventSynchronize(staging)");
         c->stage_pending = false;
     }
-    // whatever happens below, the context ends up reading its own image again, with no alphabet set
-    struct Restore { sop_ctx* c; ~Restore() { c->d_bins_cur = c->d_bins; c->n_atoms = 0; c->n_pairs = 0; } } restore{c};
+    // whatever happens below, the context ends up reading its own image again, with no alphabet set, and the next call waits for what this one has put on
+    // the stream before it writes to the staging buffers
+    struct Restore {
+        sop_ctx* c; hipStream_t st;
+        ~Restore() { c->d_bins_cur = c->d_bins; c->n_atoms = 0; c->n_pairs = 0; c->stage_pending = hipEventRecord(c->stage_done, st) == hipSuccess; }
+    } restore{c, st};
     auto img = [&](int i) { return reinterpret_cast<char*>(base) + L.bins + (size_t)i * kImgBytes; };
     auto himg = [&](int i) { return c->h_bins + (size_t)i * kImgBytes; };
-    double* d_acos = reinterpret_cast<double*>(base + L.acos);
+    // histograms and ACos values are written by the kernels straight into pinned host memory (a copy at their end cost 4 us and a gap of 11 on the stream)
+    const size_t hist_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long);
+    const long long* h_hist = reinterpret_cast<const long long*>(c->h_res);
+    const double* h_acos = reinterpret_cast<const double*>(c->h_res + hist_bytes);
+    long long* d_hist = reinterpret_cast<long long*>(c->d_res);
+    double* d_acos = reinterpret_cast<double*>(c->d_res + hist_bytes);
     float* d_rank = reinterpret_cast<float*>(base + L.rank);
 
     // ---- step 1 for every atom, and every pair of fixed atoms: searches of at most eight atoms each, those of the two
@@ -1273,7 +1307,7 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         const double v = std::floor(o->p_percent[j] * (double)Nb / 100.0 + 0.5);      // nearest count, halves up
         tops[j] = v < 0.0 ? 0 : (v > (double)Nb ? Nb : (int64_t)v);
     }
-    long long* d_hist = reinterpret_cast<long long*>(base + L.hist);
+    int n_passes = 0, pass_of[SOP_LAYER_MAX_ATOMS] = {0};
     if (n_p) {
         // all atoms' planes are ranked by the same four launches when they lie back to back with whole float4s (N_b
         // a multiple of four); the level planes are N_b bytes apart then
@@ -1294,23 +1328,27 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
                                                              reinterpret_cast<int64_t*>(base + L.na), 1, stream)) return s;
             if (sop_status s = dd_histogram_impl(c, W, dtype, M, K, ldw, o->weighted_fit ? cn : nullptr, g, bins, 1, d_level + a * lstride, n_p,
                                                  reinterpret_cast<int64_t*>(d_hist + (size_t)a * n_p * bins), stream, na, (int64_t)lstride)) return s;
+            if ((!c->pass_done[n_passes] && (e = hipEventCreateWithFlags(&c->pass_done[n_passes], hipEventDisableTiming)) != hipSuccess) ||
+                (e = hipEventRecord(c->pass_done[n_passes], st)) != hipSuccess) return hipfail(c, e, "event of a histogram pass");
+            for (int b = a; b < a + na; ++b) pass_of[b] = n_passes;
+            ++n_passes;
         }
     }
-    long long* h_hist = reinterpret_cast<long long*>(c->h_res);
-    double* h_acos = reinterpret_cast<double*>(c->h_res + (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long));
-    if (n_p) {
-        if ((e = hipMemcpyAsync(h_hist, d_hist, (size_t)A * n_p * bins * sizeof(long long), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "copy of the pool histograms");
-    }
-    // ---- the fits (host), and step 4 for one atom's whole sweep per search: alphabet (a, L_b(p_0), L_b(p_1), ...) ----
+    // ---- the fits (host), and step 4 for one atom's whole sweep per search: alphabet (a, L_b(p_0), L_b(p_1), ...).  A pass's atoms are fitted while the
+    //      GPU works on the passes behind it, and their tables go up in one copy ahead of their searches (4096 x 11008, six atoms, three passes: the GPU waited 70 to 90 us
+    //      for the first fits after the last pass, and 4.6 us for a copy before every search) ----
     std::vector<std::vector<float>> fitted((size_t)A * std::max(n_p, 1));
     std::vector<int> slot_of((size_t)A * std::max(n_p, 1), -1);       // position of (a, j) in the acos region, -1: candidate dropped
     int spare_uses = 0;
-    auto score = [&](int a, const std::vector<int>& js, int image, int out_base) -> sop_status {
+    size_t img_used = (size_t)fx.size() * kImgBytes;                  // (images of the sweeps, one behind the other)
+    auto plan = [&](int a, const std::vector<int>& js, Planned& q) -> sop_status {
         std::vector<sop_atom> al(1 + js.size());
         al[0] = atoms[a];
         for (size_t i = 0; i < js.size(); ++i) { al[1 + i].n_entries = o->fit_entries; al[1 + i].values = fitted[(size_t)a * n_p + js[i]].data(); }
-        if (sop_status s = install_alphabet(c, al.data(), (int)al.size(), img(image), himg(image), st)) return s;
+        return plan_image(c, al.data(), (int)al.size(), q);
+    };
+    auto score = [&](int a, const std::vector<int>& js, Planned& q, char* d_img, int out_base) -> sop_status {
+        adopt(c, q, d_img);
         int pr[2 * SOP_K_MAXA];
         for (size_t i = 0; i < js.size(); ++i) { pr[2 * i] = 0; pr[2 * i + 1] = 1 + (int)i; }
         if (sop_status s = sop_set_pairs(c, pr, (int)js.size())) return s;
@@ -1321,39 +1359,68 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         for (size_t i = 0; i < js.size(); ++i) slot_of[(size_t)a * n_p + js[i]] = out_base + (int)i;
         return SOP_OK;
     };
-    for (int a = 0; a < A && n_p; ++a) {
-        std::vector<int> js;
-        for (int j = 0; j < n_p; ++j) {
-            const long long* h = h_hist + ((size_t)a * n_p + j) * bins;
-            bool any = false;
-            for (int b = 0; b < bins && !any; ++b) any = h[b] != 0;
-            std::vector<float>& Lb = fitted[(size_t)a * n_p + j];
-            Lb.assign(o->fit_entries, 0.0f);
-            sop_status fs = SOP_OK;
-            if (!any) Lb = init;                                   // an empty pool: the start grid stands in
-            else if (o->fit_grid) {
-                std::vector<int> chosen(o->fit_entries);
-                fs = sop_dd_fit_grid(reinterpret_cast<const int64_t*>(h), bins, o->fit_grid, o->n_fit_grid, o->fit_entries, chosen.data(), nullptr);
-                if (fs == SOP_OK) for (int t = 0; t < o->fit_entries; ++t) Lb[t] = (float)o->fit_grid[chosen[t]];
-            } else fs = sop_dd_fit(reinterpret_cast<const int64_t*>(h), bins, o->fit_entries, o->fit_iters, init.data(), Lb.data());
-            if (fs == SOP_OK) js.push_back(j);
-            else if (fs != SOP_EATOM) return fail(c, fs, std::string("sop_search_layer: fit: ") + soph::host_last_error());
+    for (int a0 = 0; a0 < A && n_p;) {
+        int a1 = a0;
+        while (a1 < A && pass_of[a1] == pass_of[a0]) ++a1;
+        if ((e = hipEventSynchronize(c->pass_done[pass_of[a0]])) != hipSuccess) return hipfail(c, e, "hipEventSynchronize(histogram pass)");
+        struct Sweep { int a; std::vector<int> js; Planned q; size_t at; bool whole; };
+        std::vector<Sweep> sweeps;
+        const size_t up0 = img_used;
+        for (int a = a0; a < a1; ++a) {
+            Sweep w;
+            w.a = a;
+            for (int j = 0; j < n_p; ++j) {
+                const long long* h = h_hist + ((size_t)a * n_p + j) * bins;
+                bool any = false;
+                for (int b = 0; b < bins && !any; ++b) any = h[b] != 0;
+                std::vector<float>& Lb = fitted[(size_t)a * n_p + j];
+                Lb.assign(o->fit_entries, 0.0f);
+                sop_status fs = SOP_OK;
+                if (!any) Lb = init;                                   // an empty pool: the start grid stands in
+                else if (o->fit_grid) {
+                    std::vector<int> chosen(o->fit_entries);
+                    fs = sop_dd_fit_grid(reinterpret_cast<const int64_t*>(h), bins, o->fit_grid, o->n_fit_grid, o->fit_entries, chosen.data(), nullptr);
+                    if (fs == SOP_OK) for (int t = 0; t < o->fit_entries; ++t) Lb[t] = (float)o->fit_grid[chosen[t]];
+                } else fs = sop_dd_fit(reinterpret_cast<const int64_t*>(h), bins, o->fit_entries, o->fit_iters, init.data(), Lb.data());
+                if (fs == SOP_OK) w.js.push_back(j);
+                else if (fs != SOP_EATOM) return fail(c, fs, std::string("sop_search_layer: fit: ") + soph::host_last_error());
+            }
+            if (w.js.empty()) continue;
+            const sop_status s = plan(a, w.js, w.q);
+            if (s != SOP_OK && s != SOP_EATOM) return s;
+            w.whole = s == SOP_OK;
+            w.at = img_used;
+            if (w.whole) {
+                write_image(w.q, c->h_bins + w.at);
+                img_used = up256(img_used + w.q.bytes);
+            }
+            sweeps.push_back(std::move(w));
         }
-        if (js.empty()) continue;
-        sop_status s = score(a, js, kFixedMax + a, kAcosFit + 8 * a);
-        if (s == SOP_EATOM && js.size() > 1) {
+        if (img_used > up0 && (e = hipMemcpyAsync(base + L.bins + up0, c->h_bins + up0, img_used - up0, hipMemcpyHostToDevice, st)) != hipSuccess)
+            return hipfail(c, e, "upload of the table images");
+        for (Sweep& w : sweeps) {
+            if (w.whole) {
+                if (sop_status s = score(w.a, w.js, w.q, base + L.bins + w.at, kAcosFit + 8 * w.a)) return s;
+                continue;
+            }
             // some fitted codebook cannot be searched next to the others (entries too closely spaced for the
             // element-search table): the candidates are scored one by one, through one spare image, and
             // those that fail alone are dropped
-            for (size_t i = 0; i < js.size(); ++i) {
+            for (size_t i = 0; w.js.size() > 1 && i < w.js.size(); ++i) {
+                const std::vector<int> one(1, w.js[i]);
+                Planned q;
+                const sop_status s = plan(w.a, one, q);
+                if (s == SOP_EATOM) continue;
+                if (s != SOP_OK) return s;
                 if (spare_uses++ && (e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "hipStreamSynchronize");
-                s = score(a, std::vector<int>(1, js[i]), kFixedMax + A, kAcosFit + 8 * a + (int)i);
-                if (s != SOP_OK && s != SOP_EATOM) return s;
+                write_image(q, himg(kFixedMax + A));
+                if ((e = hipMemcpyAsync(img(kFixedMax + A), himg(kFixedMax + A), q.bytes, hipMemcpyHostToDevice, st)) != hipSuccess) return hipfail(c, e, "upload of the table image");
+                if (sop_status t = score(w.a, one, q, img(kFixedMax + A), kAcosFit + 8 * w.a + (int)i)) return t;
             }
-        } else if (s != SOP_OK && s != SOP_EATOM) return s;
+        }
+        a0 = a1;
     }
-    if ((e = hipMemcpyAsync(h_acos, d_acos, (size_t)(kAcosFit + 8 * A) * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "copy of the ACos values");
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "wait for the ACos values");
     // ---- the best (L_a, p, L_b): the largest layer ACos, the first one among equals (fixed pairs in their
     //      order, then atom by atom, p by p) ----
     std::memset(res, 0, sizeof(*res));
@@ -1400,12 +1467,10 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         const size_t plane_a = two[0].n_entries <= 16 ? (size_t)(M * K / 2) : (size_t)(M * K);
         sop_outputs out;
         std::memset(&out, 0, sizeof(out));
-        out.acos_pair = d_acos; out.scale_code = sc; out.codes = codes; out.sel_words = base + L.sel;
+        out.acos_pair = reinterpret_cast<double*>(base + L.acos); out.scale_code = sc; out.codes = codes; out.sel_words = base + L.sel;
         if (sop_status s = pair_search_impl(c, W, dtype, M, K, ldw, cn, g, fmt, k, metric, nullptr, 0, &out, stream, true)) return s;
         if (sop_status s = sop_pack_blocks(c, M, K, g, fmt, sc, codes, two[0].n_entries, sc + Nb, codes + plane_a, two[1].n_entries,
                                            base + L.sel, 2, 0, words, payload, &res->n_bits, stream)) return s;
     }
-    if ((e = hipEventRecord(c->stage_done, st)) != hipSuccess) return hipfail(c, e, "hipEventRecord");
-    c->stage_pending = true;
     return SOP_OK;
 }
