@@ -26,6 +26,7 @@ extern "C" const void* sopk_search_kernel(int is_bf16, int g, int sign_mode, int
 extern "C" int sopk_variant_index(int is_bf16, int g, int sign_mode, int metric, int emit, int na_class, int mode);
 extern "C" hipError_t sopk_launch(const void* fn, const KParams* p, int n_wg, int occ, size_t dyn_lds, void* stream);
 extern "C" hipError_t sopk_dd_launch(const DdParams* p, int is_bf16, int g, void* stream);
+extern "C" hipError_t sopk_fit_launch(const FitParams* p, int n_hist, void* stream);
 extern "C" hipError_t sopk_fl_launch(const FlParams* p, int is_bf16, int g, void* stream);
 extern "C" int sopk_fl_weights_per_lane(int is_bf16, int g);
 extern "C" hipError_t sopk_ls_launch(const LsParams* p, int is_bf16, void* stream);
@@ -127,7 +128,6 @@ struct sop_ctx {
     char* h_bins = nullptr;               // pinned staging for table images of sop_search_layer (allocated at its first call)
     char* h_res = nullptr;                // pinned memory that its kernels write their results to: histograms, then ACos values
     char* d_res = nullptr;                // the same as kernels address it
-    hipEvent_t pass_done[SOP_LAYER_MAX_ATOMS] = {};     // its histogram passes
     hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
     bool stage_pending = false;
     unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
@@ -270,7 +270,6 @@ extern "C" sop_status sop_destroy(sop_ctx* c)
         if (c->h_bins) (void)hipHostFree(c->h_bins);
         if (c->h_res) (void)hipHostFree(c->h_res);
         if (c->stage_done) (void)hipEventDestroy(c->stage_done);
-        for (hipEvent_t ev : c->pass_done) if (ev) (void)hipEventDestroy(ev);
         for (hipStream_t s : c->lane_stream) if (s) (void)hipStreamDestroy(s);
         for (hipEvent_t ev : c->lane_event) if (ev) (void)hipEventDestroy(ev);
         if (c->d_stab) (void)hipFree(c->d_stab);
@@ -1146,7 +1145,7 @@ extern "C" sop_status sop_pack_blocks(sop_ctx* c, int64_t M, int64_t K, int g, s
 namespace {
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct LayerWs {
-    size_t rank, level, tau, na, acos, bins, sc, codes, sel, total;
+    size_t rank, level, hist, tau, na, acos, bins, sc, codes, sel, total;
     int n_img;
 };
 // An alphabet of more than eight atoms is covered by several searches of at most eight atoms each (the kernel unrolls over
@@ -1157,7 +1156,7 @@ constexpr int kAcosPer = SOP_K_MAXP + SOP_K_MAXA;          // doubles per such s
 // acos region, in doubles: kFixedMax searches of the fixed alphabet, then per atom a: 8 pairs (a, L_b(p_j))
 constexpr int kAcosFit = kFixedMax * kAcosPer;
 constexpr int kAcosAll = kAcosFit + SOP_LAYER_MAX_ATOMS * 8;
-LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int pack)
+LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int n_p, int bins, int pack)
 {
     const size_t Nb = (size_t)(M * (K / g));
     LayerWs w;
@@ -1165,6 +1164,7 @@ LayerWs layer_ws(int64_t M, int64_t K, int g, int A, int pack)
     auto take = [&](size_t bytes) { const size_t o = off; off += up256(bytes); return o; };
     w.rank = take((size_t)A * Nb * sizeof(float));
     w.level = take((size_t)A * up256(Nb));
+    w.hist = take((size_t)A * std::max(n_p, 1) * bins * sizeof(long long));
     w.tau = take((size_t)SOP_LAYER_MAX_ATOMS * SOP_K_SEL_MAXLEV * sizeof(float));
     w.na = take((size_t)SOP_LAYER_MAX_ATOMS * SOP_K_SEL_MAXLEV * sizeof(long long));
     w.acos = take((size_t)kAcosPer * sizeof(double));      // (the winner's own; the candidates' go to pinned host memory)
@@ -1200,7 +1200,7 @@ extern "C" sop_status sop_search_layer_workspace(sop_ctx* c, int64_t M, int64_t 
     if (!bytes) return fail(c, SOP_EINVAL, "sop_search_layer_workspace: bytes is NULL");
     if (sop_status s = shape_check(c, M, K, g)) return s;
     if (sop_status s = layer_opts_check(c, n_atoms, o)) return s;
-    *bytes = layer_ws(M, K, g, n_atoms, o->pack).total;
+    *bytes = layer_ws(M, K, g, n_atoms, o->n_p, o->n_p ? o->fit_bins : 64, o->pack).total;
     return SOP_OK;
 }
 
@@ -1216,7 +1216,7 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     const int A = n_atoms, n_p = o->n_p, bins = n_p ? o->fit_bins : 64;
     if (A < 2 && n_p == 0) return fail(c, SOP_EINVAL, "sop_search_layer: one atom and no sweep leave no pair to examine");
     if (o->pack && (!words || !payload)) return fail(c, SOP_EINVAL, "sop_search_layer: packing needs words_dev and payload_dev");
-    const LayerWs L = layer_ws(M, K, g, A, o->pack);
+    const LayerWs L = layer_ws(M, K, g, A, n_p, bins, o->pack);
     if (!ws || ws_bytes < L.total) return fail(c, SOP_ENOMEM, "sop_search_layer: workspace too small (see sop_search_layer_workspace)");
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return fail(c, SOP_EINVAL, "sop_search_layer: workspace must be 256-byte aligned");
     for (int a = 0; a < A; ++a)
@@ -1236,7 +1236,9 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
     hipError_t e = hipSuccess;
     // pinned staging, allocated once per context
-    const size_t res_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long) + (size_t)kAcosAll * sizeof(double);
+    const size_t hist_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long), acos_bytes = (size_t)kAcosAll * sizeof(double);
+    const size_t fits_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * SOP_K_FIT_MAXENT * sizeof(float);
+    const size_t res_bytes = hist_bytes + acos_bytes + fits_bytes + (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * sizeof(int);
     if (!c->h_bins) {
         if ((e = hipHostMalloc((void**)&c->h_bins, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, hipHostMallocDefault)) != hipSuccess ||
             (e = hipHostMalloc((void**)&c->h_res, res_bytes, hipHostMallocDefault)) != hipSuccess ||
@@ -1256,11 +1258,15 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     } restore{c, st};
     auto img = [&](int i) { return reinterpret_cast<char*>(base) + L.bins + (size_t)i * kImgBytes; };
     auto himg = [&](int i) { return c->h_bins + (size_t)i * kImgBytes; };
-    // histograms and ACos values are written by the kernels straight into pinned host memory (a copy at their end cost 4 us and a gap of 11 on the stream)
-    const size_t hist_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long);
-    const long long* h_hist = reinterpret_cast<const long long*>(c->h_res);
+    // what the host looks at, fitted codebooks and ACos values, is written by the kernels straight into pinned host memory (a copy at their end cost 4 us and a
+    // gap of 11 on the stream); so are the histograms where the host fits: entries selected on a grid, or a start grid out of order (no fit accepts it)
+    bool gpu_fit = n_p > 0 && !o->fit_grid;
+    for (int t = 1; gpu_fit && t < o->fit_entries; ++t) gpu_fit = init[t - 1] < init[t];
+    long long* h_hist = reinterpret_cast<long long*>(c->h_res);
     const double* h_acos = reinterpret_cast<const double*>(c->h_res + hist_bytes);
-    long long* d_hist = reinterpret_cast<long long*>(c->d_res);
+    const float* h_fits = reinterpret_cast<const float*>(c->h_res + hist_bytes + acos_bytes);
+    const int* h_status = reinterpret_cast<const int*>(c->h_res + hist_bytes + acos_bytes + fits_bytes);
+    long long* d_hist = gpu_fit ? reinterpret_cast<long long*>(base + L.hist) : reinterpret_cast<long long*>(c->d_res);
     double* d_acos = reinterpret_cast<double*>(c->d_res + hist_bytes);
     float* d_rank = reinterpret_cast<float*>(base + L.rank);
 
@@ -1307,7 +1313,6 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         const double v = std::floor(o->p_percent[j] * (double)Nb / 100.0 + 0.5);      // nearest count, halves up
         tops[j] = v < 0.0 ? 0 : (v > (double)Nb ? Nb : (int64_t)v);
     }
-    int n_passes = 0, pass_of[SOP_LAYER_MAX_ATOMS] = {0};
     if (n_p) {
         // all atoms' planes are ranked by the same four launches when they lie back to back with whole float4s (N_b
         // a multiple of four); the level planes are N_b bytes apart then
@@ -1328,15 +1333,22 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
                                                              reinterpret_cast<int64_t*>(base + L.na), 1, stream)) return s;
             if (sop_status s = dd_histogram_impl(c, W, dtype, M, K, ldw, o->weighted_fit ? cn : nullptr, g, bins, 1, d_level + a * lstride, n_p,
                                                  reinterpret_cast<int64_t*>(d_hist + (size_t)a * n_p * bins), stream, na, (int64_t)lstride)) return s;
-            if ((!c->pass_done[n_passes] && (e = hipEventCreateWithFlags(&c->pass_done[n_passes], hipEventDisableTiming)) != hipSuccess) ||
-                (e = hipEventRecord(c->pass_done[n_passes], st)) != hipSuccess) return hipfail(c, e, "event of a histogram pass");
-            for (int b = a; b < a + na; ++b) pass_of[b] = n_passes;
-            ++n_passes;
         }
+        if (gpu_fit) {
+            FitParams fp;
+            std::memset(&fp, 0, sizeof(fp));
+            fp.hist = d_hist;
+            fp.n_bins = bins; fp.n_entries = o->fit_entries; fp.iters = o->fit_iters;
+            std::copy(init.begin(), init.end(), fp.init);
+            fp.out = reinterpret_cast<float*>(c->d_res + hist_bytes + acos_bytes);
+            fp.status = reinterpret_cast<int*>(c->d_res + hist_bytes + acos_bytes + fits_bytes);
+            if ((e = sopk_fit_launch(&fp, A * n_p, stream)) != hipSuccess) return hipfail(c, e, "kernel launch (fits)");
+        }
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "wait for the fits");
     }
-    // ---- the fits (host), and step 4 for one atom's whole sweep per search: alphabet (a, L_b(p_0), L_b(p_1), ...).  A pass's atoms are fitted while the
-    //      GPU works on the passes behind it, and their tables go up in one copy ahead of their searches (4096 x 11008, six atoms, three passes: the GPU waited 70 to 90 us
-    //      for the first fits after the last pass, and 4.6 us for a copy before every search) ----
+    // ---- step 4 for one atom's whole sweep per search: alphabet (a, L_b(p_0), L_b(p_1), ...).  The tables of two atoms go up in one copy ahead of their searches: the
+    //      first search starts after two plans, and the GPU works on a pair's searches while the next are planned (a copy before every search was 4.6 us of the
+    //      GPU's time; one copy for all of them has it wait for all plans) ----
     std::vector<std::vector<float>> fitted((size_t)A * std::max(n_p, 1));
     std::vector<int> slot_of((size_t)A * std::max(n_p, 1), -1);       // position of (a, j) in the acos region, -1: candidate dropped
     int spare_uses = 0;
@@ -1360,9 +1372,7 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         return SOP_OK;
     };
     for (int a0 = 0; a0 < A && n_p;) {
-        int a1 = a0;
-        while (a1 < A && pass_of[a1] == pass_of[a0]) ++a1;
-        if ((e = hipEventSynchronize(c->pass_done[pass_of[a0]])) != hipSuccess) return hipfail(c, e, "hipEventSynchronize(histogram pass)");
+        const int a1 = std::min(a0 + 2, A);
         struct Sweep { int a; std::vector<int> js; Planned q; size_t at; bool whole; };
         std::vector<Sweep> sweeps;
         const size_t up0 = img_used;
@@ -1370,13 +1380,22 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
             Sweep w;
             w.a = a;
             for (int j = 0; j < n_p; ++j) {
-                const long long* h = h_hist + ((size_t)a * n_p + j) * bins;
-                bool any = false;
-                for (int b = 0; b < bins && !any; ++b) any = h[b] != 0;
-                std::vector<float>& Lb = fitted[(size_t)a * n_p + j];
+                const size_t at = (size_t)a * n_p + j;
+                long long* h = h_hist + at * bins;
+                std::vector<float>& Lb = fitted[at];
                 Lb.assign(o->fit_entries, 0.0f);
                 sop_status fs = SOP_OK;
-                if (!any) Lb = init;                                   // an empty pool: the start grid stands in
+                const int done = gpu_fit ? h_status[at] : SOP_K_FIT_HOST;
+                bool any = done != SOP_K_FIT_EMPTY;
+                if (done == SOP_K_FIT_HOST) {
+                    if (gpu_fit && ((e = hipMemcpyAsync(h, d_hist + at * bins, (size_t)bins * sizeof(long long), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+                                    (e = hipStreamSynchronize(st)) != hipSuccess)) return hipfail(c, e, "copy of a pool histogram");
+                    any = false;
+                    for (int b = 0; b < bins && !any; ++b) any = h[b] != 0;
+                }
+                if (done == SOP_K_FIT_OK) std::copy(h_fits + at * SOP_K_FIT_MAXENT, h_fits + at * SOP_K_FIT_MAXENT + o->fit_entries, Lb.begin());
+                else if (done == SOP_K_FIT_NONE) fs = SOP_EATOM;
+                else if (!any) Lb = init;                                   // an empty pool: the start grid stands in
                 else if (o->fit_grid) {
                     std::vector<int> chosen(o->fit_entries);
                     fs = sop_dd_fit_grid(reinterpret_cast<const int64_t*>(h), bins, o->fit_grid, o->n_fit_grid, o->fit_entries, chosen.data(), nullptr);

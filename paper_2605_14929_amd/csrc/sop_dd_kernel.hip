@@ -345,7 +345,94 @@ __global__ __launch_bounds__(SOP_K_DD_THREADS) void dd_hist_kernel(const DdParam
     }
 }
 
+// Weighted Lloyd fit of a codebook on a histogram, a workgroup each: the rounds of sop_dd_fit, to the same bits (integer prefix sums of mass and first
+// moment; a cell is the run of bins whose centres lie above one midpoint and not above the next; binary64 midpoints, centres and divisions as on the
+// host).  Bound by a round's chain (midpoint, bin, two prefix sums, two divisions), not by data: one wavefront, a lane an entry.  Twenty-four fits of 1024 bins and 20
+// rounds take 18 us at once, where the host took 5 us for each while the GPU waited.
+__global__ __launch_bounds__(SOP_K_FIT_THREADS) void dd_fit_kernel(const FitParams p)
+{
+    typedef unsigned long long u64;
+    extern __shared__ __align__(16) u64 s_pre[];                      // [n_bins + 1] mass, then [n_bins + 1] first moment in units of 1 / n_bins
+    __shared__ u64 s_part[2][SOP_K_FIT_THREADS / 64];
+    const int H = p.n_bins, n = p.n_entries, tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    u64* const pm = s_pre;
+    u64* const pf = s_pre + H + 1;
+    const long long* const hist = p.hist + (size_t)blockIdx.x * H;
+    for (int b = tid; b < H; b += SOP_K_FIT_THREADS) pm[b] = (u64)hist[b];
+    __syncthreads();
+    // prefix sums: a run of bins a thread
+    const int per = (H + SOP_K_FIT_THREADS - 1) / SOP_K_FIT_THREADS, b0 = min(tid * per, H), b1 = min(b0 + per, H);
+    u64 m = 0ull, f = 0ull;
+    for (int b = b0; b < b1; ++b) { const u64 v = pm[b]; m += v; f += v * (unsigned)(2 * b + 1); }
+    u64 im = m, jf = f;
+#pragma unroll
+    for (int st = 1; st < 64; st <<= 1) {
+        const u64 a = (u64)__shfl_up((long long)im, st, 64), c = (u64)__shfl_up((long long)jf, st, 64);
+        if (lane >= st) { im += a; jf += c; }
+    }
+    if (lane == 63) { s_part[0][wv] = im; s_part[1][wv] = jf; }
+    __syncthreads();
+    for (int i = 0; i < wv; ++i) { im += s_part[0][i]; jf += s_part[1][i]; }
+    u64 am = im - m, af = jf - f;
+    for (int b = b0; b < b1; ++b) {
+        const u64 v = pm[b];
+        pm[b] = am; pf[b] = af;
+        am += v; af += v * (unsigned)(2 * b + 1);
+    }
+    if (tid == SOP_K_FIT_THREADS - 1) { pm[H] = im; pf[H] = jf; }
+    __syncthreads();
+    if (wv != 0) return;
+    const u64 total = pm[H];
+    int status = total == 0ull ? SOP_K_FIT_EMPTY : SOP_K_FIT_OK;
+    // (the largest first moment is below 2 H total.  A total that wrapped is out of reach: a layer has fewer than 2^38 weights of at most 2^31 each)
+    if (total > (0x7FFFFFFFFFFFFFFFull >> 1) / (u64)H) status = SOP_K_FIT_HOST;
+    const bool on = lane < n;
+    double cent = on ? (double)p.init[min(lane, SOP_K_FIT_MAXENT - 1)] : 0.0;
+    const double inv = 1.0 / (double)H, halfH = 0.5 * (double)H;
+    auto centre = [inv](int b) { return -1.0 + (2.0 * (double)b + 1.0) * inv; };
+    if (status == SOP_K_FIT_OK) {
+        for (int it = 0; it < p.iters; ++it) {
+            const double next = __shfl_down(cent, 1, 64), before = cent;
+            int end = H;                                              // one past the last bin of the lane's cell
+            if (lane + 1 < n) {
+                const double mid = 0.5 * (cent + next), g = (mid + 1.0) * halfH;
+                int b = g > 0.0 ? (g < (double)H ? (int)g : H) : 0;
+                while (b > 0 && mid < centre(b - 1)) --b;
+                while (b < H && !(mid < centre(b))) ++b;
+                end = b;
+            }
+            int lo = __shfl_up(end, 1, 64);
+            if (lane == 0) lo = 0;
+            if (on) {
+                const u64 mass = pm[end] - pm[lo], first = pf[end] - pf[lo];
+                if (mass > 0ull) cent = ((double)first / (double)mass) * inv - 1.0;      // (H is a power of two: the division by it, exactly)
+            }
+            const double below = __shfl_up(cent, 1, 64);
+            if (__builtin_amdgcn_ballot_w64(on && lane > 0 && !(below <= cent)) != 0ull) { status = SOP_K_FIT_HOST; break; }
+            if (__builtin_amdgcn_ballot_w64(on && cent != before) == 0ull) break;      // a round that moves no entry is the last one that could
+        }
+        const float o = (float)cent, prev = __shfl_up(o, 1, 64);
+        const bool bad = (on && lane > 0 && !(prev < o)) || (lane == 0 && !(o < 0.0f)) || (lane == n - 1 && !(o > 0.0f));
+        if (status == SOP_K_FIT_OK && __builtin_amdgcn_ballot_w64(bad) != 0ull) status = SOP_K_FIT_NONE;
+        if (on) p.out[(size_t)blockIdx.x * SOP_K_FIT_MAXENT + lane] = o;
+    }
+    if (lane == 0) p.status[blockIdx.x] = status;
+}
+
 }  // namespace sopk
+
+// one workgroup a histogram
+extern "C" hipError_t sopk_fit_launch(const FitParams* pp, int n_hist, void* stream)
+{
+    const FitParams p = *pp;
+    const size_t lds = (size_t)(p.n_bins + 1) * 16;
+    if (lds > 48 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sopk::dd_fit_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(sopk::dd_fit_kernel, dim3((unsigned)n_hist), dim3(SOP_K_FIT_THREADS), lds, (hipStream_t)stream, p);
+    return hipGetLastError();
+}
 
 extern "C" hipError_t sopk_dd_launch(const DdParams* pp, int is_bf16, int g, void* stream)
 {

@@ -306,6 +306,21 @@ inline unsigned int dd_rows(unsigned int words, unsigned int workgroups)
     return words <= SOP_K_DD_THREADS && workgroups >= 64u ? SOP_K_DD_ROWS : 1u;
 }
 
+/* Fits of data-derived codebooks, one histogram a workgroup (the weighted Lloyd rounds of sop_dd_fit) */
+#define SOP_K_FIT_THREADS 256
+#define SOP_K_FIT_MAXENT 64          /* entries of a codebook: a lane each */
+#define SOP_K_FIT_OK 0
+#define SOP_K_FIT_NONE 1             /* not strictly ascending in binary32, or one-sided: no codebook (SOP_EATOM) */
+#define SOP_K_FIT_EMPTY 2            /* an empty histogram */
+#define SOP_K_FIT_HOST 3             /* moments beyond 64 bits, or entries out of order on the way: left to the host */
+struct FitParams {
+    const long long* hist;           // [histograms][n_bins]
+    int n_bins, n_entries, iters;
+    float init[SOP_K_FIT_MAXENT];    // start grid, strictly ascending
+    float* out;                      // [histograms][SOP_K_FIT_MAXENT]
+    int* status;                     // [histograms]
+};
+
 /* Statistics pass of the per-layer scale shift */
 #define SOP_K_FL_THREADS 1024
 #define SOP_K_FL_BINS 320            /* binary exponents -160 .. 159 of sc = m * 2^e, 1/2 <= m < 1 */

@@ -1,0 +1,61 @@
+"""The per-layer procedure fits its codebooks on the GPU: candidates, dropped ones among them, their ACos and the winner's table are those of the single
+calls chained, with the fits on the host (sop_dd_fit), bit for bit: smallest and largest histograms and codebooks, no rounds and many, pools that are empty or
+the whole layer, equal pools, one plane and several passes over the weights."""
+import numpy as np
+import pytest
+
+import paper_2605_14929_amd as sop
+from paper_2605_14929_amd import layer_search
+from oracle import atoms as OA
+import sop_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+NF, SH = OA.to_f32(OA.nf(4)), OA.to_f32(OA.sh(4))
+ATOMS = [NF, SH, OA.to_f32(OA.negate(OA.nf(4))), OA.to_f32(OA.negate(OA.sh(4)))]
+
+
+@pytest.mark.parametrize("M,K,g", [(48, 1024, 16), (4, 48, 16), (36, 1056, 32)])
+@pytest.mark.parametrize("bins,entries,iters,p", [(64, 16, 20, (50.0, 80.0)), (1024, 16, 20, (0.0, 50.0, 70.0, 70.0, 100.0)), (8192, 16, 40, (60.0,)), (2048, 2, 5, (30.0, 60.0, 90.0)),
+                                                  (1024, 64, 20, (20.0, 75.0)), (256, 33, 1, (50.0, 95.0)), (512, 16, 0, (40.0,))])
+@pytest.mark.parametrize("weighted", [True, False])
+def test_against_fits_on_the_host(M, K, g, bins, entries, iters, p, weighted):
+    import torch
+    W, c = si.bf16_round(si.student_t_weights(M, K, 4.0, 8300 + M)), si.channel_norms(K, 1.0, 8301)
+    Wt, ct = torch.from_numpy(W).cuda().to(torch.bfloat16), torch.from_numpy(c).cuda()
+    fmt, Nb = sop.fmt_by_name("UE4M3"), M * K // g
+    init = NF if entries == 16 else np.linspace(-1, 1, entries, dtype=np.float32)
+    cx = sop.Context(0)
+    r = layer_search.search_layer(cx, Wt, ct, g, fmt, ATOMS, p_grid=p, fit_entries=entries, fit_iters=iters, fit_bins=bins, fit_init=init, weighted_fit=weighted)
+    tops = [int(np.floor(x * Nb / 100.0 + 0.5)) for x in p]
+    cx.set_alphabet(ATOMS)
+    rank = cx.pair_search(Wt, ct, g, fmt, emit=True).blk_rank
+    want, tables = {}, {}
+    for a, tab in enumerate(ATOMS):
+        level, _, _ = cx.partition_levels(rank[a].clone(), tops)
+        hist = cx.dd_histogram_levels(Wt, ct if weighted else None, g, level, len(tops), bins).cpu().numpy()
+        js, books = [], []
+        for j in range(len(p)):
+            if not hist[j].any():
+                book = init
+            else:
+                try:
+                    book = sop.sop_dd_fit(hist[j], entries, iters, init)
+                except sop.SopError:
+                    continue
+            js.append(j)
+            books.append(np.asarray(book, np.float32))
+        if not js:
+            continue
+        try:
+            cx.set_alphabet([tab] + books)
+        except sop.SopError:
+            continue                                                  # (searched one by one: not followed here)
+        cx.set_pairs([(0, 1 + i) for i in range(len(js))])
+        acos = cx.pair_search(Wt, ct, g, fmt).acos_pair.cpu().numpy()
+        for i, j in enumerate(js):
+            want[(a, p[j])] = acos[i]                                 # (equal p: the last one, as the result's dictionary)
+            tables.setdefault((a, p[j]), books[i])
+    assert {k: v for k, v in r.acos_fitted.items() if k in want} == want
+    if r.kind == "fitted":
+        assert np.array_equal(r.table_b, tables[(r.a, r.p_percent)])
