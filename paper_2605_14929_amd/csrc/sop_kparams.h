@@ -64,12 +64,15 @@ SOP_K_HD constexpr bool one_plane_variants(int epl, int sign_mode, int metric, i
  * 4096 x 4096 and 4096 x 11008, bf16, g = 16: six atoms under a signed word 43.1 us -> 38.4 and 95.3 -> 89.1 (145 registers, now 126: three wavefronts, now four), by
  * the cosine 43.6 -> 37.7 and 99.6 -> 90.8; seven 39.4 -> 35.4 and 88.7 -> 83.1, eight 45.2 -> 40.8 and 101.9 -> 96.2 (143 -> 109), under a signed word 72.6 -> 61.8 and
  * 175 -> 143.8 (two wavefronts, now three); argmax rule 33.1 -> 30.2 and 74.0 -> 70.9; fp32, six atoms 35.5 -> 33.4 and 77.8 -> 74.0; 28672 x 8192, seven 475 -> 425.
- * Where the sums are not what holds a wavefront back they stay in registers: six atoms of bf16 weights (four wavefronts as it is), one or two, planes, 8-element lanes, MSE under a
+ * Lanes of 8 elements, six under a signed word and all of eight, three wavefronts, now four: 4096 x 11008, g = 8, 120 -> 105 and 130 -> 116.
+ * Where the sums are not what holds a wavefront back they stay in registers: six atoms of bf16 weights (four wavefronts as it is), most of one or two, planes, MSE of 16-element lanes under a
  * signed word or the argmax rule (six spill up to 113 registers at four wavefronts), and the model-wide kernel, whose wavefronts of a SIMD are in different layers at a time. */
 SOP_K_HD constexpr bool lane_sums_in_lds(bool bf16, int epl, int sign_mode, int metric, int planes, int na, bool multi)
 {
     if (planes == SOP_K_PLANES_RANK) return na == 6;
-    return !multi && planes == SOP_K_PLANES_NONE && epl == 16 && na != 2 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);
+    if (epl == 8) return !multi && planes == SOP_K_PLANES_NONE && (na == 8 || (na == 6 && sign_mode == 1));
+    if (na == 2) return planes == SOP_K_PLANES_NONE && sign_mode == 1 && !bf16 && metric == 0;      // (one register short of four wavefronts)
+    return !multi && planes == SOP_K_PLANES_NONE && epl == 16 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);
 }
 /* LDS of these sums: four sets (one a SIMD) of 64 words a column, on a 16-byte boundary */
 SOP_K_HD constexpr size_t lane_sums_bytes(int na) { return (size_t)4 * search_slots(na) * 64 * 4 + 8; }

@@ -856,17 +856,17 @@ constexpr int occ_for(bool bf16, int epl, int sign_mode, int planes, int na, int
     const bool emit = planes == SOP_K_PLANES_ALL;
     if (planes == SOP_K_PLANES_ERR) return 4;
     if (planes == SOP_K_PLANES_RANK) return sign_mode == 0 ? 4 : bf16 || na == 2 ? 3 : 2;
-    if (lane_sums_in_lds(bf16, epl, sign_mode, metric, planes, na, multi)) return (na == 8 && sign_mode != 0) || (sign_mode == 2 && metric == 1) ? 3 : 4;      // (109 to 128 registers; 126 to 168)
+    if (lane_sums_in_lds(bf16, epl, sign_mode, metric, planes, na, multi)) return epl == 16 && ((na == 8 && sign_mode != 0) || (sign_mode == 2 && metric == 1)) ? 3 : 4;      // (109 to 128 registers; 126 to 168)
     if (epl == 8) {
         if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;
-        if (sign_mode == 1) return emit ? 2 : 3;
+        if (sign_mode == 1) return emit ? 2 : multi && na == 6 && metric == 0 ? 4 : 3;
         return (emit || na == 8) ? 3 : 4;
     }
     if (sign_mode == 0) {
         if (!emit) return na == 8 || (na == 6 && metric == 1 && multi) ? 3 : (na == 2 || bf16) ? 4 : 3;
         return na == 2 || (na == 6 && bf16 && metric != 1) ? 3 : 2;
     }
-    if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : 3;
+    if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : sign_mode == 1 && (epl == 8 || metric != 2) ? 4 : 3;      // (signed: 104 to 128 registers, MSE a few more; 4096 x 11008, two atoms, 61.7 us at three wavefronts, 56.9 at four, one 38.0 and 34.6)
     if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 && metric != 1) ? 2 : 3;
     if (emit) return 2;
     return (na == 8 || metric == 1) ? 2 : 3;        // (argmax rule) the cosine metric keeps two more sums per candidate alive

@@ -60,6 +60,15 @@ def test_short_and_middling_shares(rows, tabs, fmt, metric, rule, f32):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows", [1, 733, 900])                      # (lanes of eight weights: ten steps a row)
+@pytest.mark.parametrize("tabs,fmt,metric,rule", [(SIX, "E4M3", sop.SEL_WSE, sop.SCALE_ABSMAX), (EIGHT, "UE4M4", sop.SEL_MSE, sop.SCALE_ABSMAX), (EIGHT, "E4M3", sop.SEL_COS, sop.SCALE_ABSMAX),
+                                                  (EIGHT[:7], "E4M3", sop.SEL_WSE, sop.SCALE_ARGMAX)])
+def test_lanes_of_eight_weights(rows, tabs, fmt, metric, rule):
+    import torch
+    against_pairs(rows, 5024, 8, torch.bfloat16, tabs, fmt, metric, rule, pairs={(0, 1), (1, 5), (2, 3), (0, len(tabs) - 1)})
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("tabs,fmt", [(EIGHT[:7], "UE4M4"), (SIX, "E4M3")])
 def test_words_emptied_on_the_way(tabs, fmt):
     """More than 60 steps a wavefront on 256 compute units: 4 * 256 * 4 * 60 steps of 1024 weights and some."""
