@@ -46,17 +46,18 @@ SOP_K_HD constexpr int search_cols(int na) { return na + na * (na - 1) / 2 + 1; 
 SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 * 4; }
 
 /* Per-block planes that a variant of the search can write: none; any of them; the ranking scores or the block errors and no other.
- * The variants of one plane are those of the searches that a program makes for a plane alone (metric WSE, lanes of 16 weights): the ranking scores of up to six atoms, the first pass of the
+ * The variants of one plane are those of the searches that a program makes for a plane alone (metric WSE): the ranking scores of up to six atoms, the first pass of the
  * per-layer procedure, and the errors of one or two under a positive scale, the comparison of weight formats.  They form no codes, need no 16-byte records and keep no
  * pointers of planes that are not there, which is a wavefront more per SIMD, and store without a branch.  4096 x 11008, bf16, ranking scores of six atoms 130 us (any plane) -> 113,
- * of two 49.8 -> 44.4, under a signed word (whose codes were formed to no end) 272 -> 165 and 105 -> 86 (g = 64); fp32 174 -> 121; 28672 x 8192, errors of one atom 149 -> 121. */
+ * of two 49.8 -> 44.4, under a signed word (whose codes were formed to no end) 272 -> 165 and 105 -> 86 (g = 64); fp32 174 -> 121; 28672 x 8192, errors of one atom 149 -> 121;
+ * lanes of eight weights, ranking scores of six atoms 161 -> 126, under a signed word 286 -> 157. */
 #define SOP_K_PLANES_NONE 0
 #define SOP_K_PLANES_ALL 1
 #define SOP_K_PLANES_RANK 3
 #define SOP_K_PLANES_ERR 4
 SOP_K_HD constexpr bool one_plane_variants(int epl, int sign_mode, int metric, int na, int planes)
 {
-    return epl == 16 && metric == 0 && na != 8 && (planes == SOP_K_PLANES_RANK ? sign_mode != 2 : na == 2 && sign_mode == 0);
+    return metric == 0 && na != 8 && (planes == SOP_K_PLANES_RANK ? sign_mode != 2 : epl == 16 && na == 2 && sign_mode == 0);
 }
 
 /* Searches of one layer that keep their lanes' running sums in LDS rather than in registers: 22 registers less for six atoms, 37 for eight, where that is
@@ -69,7 +70,7 @@ SOP_K_HD constexpr bool one_plane_variants(int epl, int sign_mode, int metric, i
  * signed word or the argmax rule (six spill up to 113 registers at four wavefronts), and the model-wide kernel, whose wavefronts of a SIMD are in different layers at a time. */
 SOP_K_HD constexpr bool lane_sums_in_lds(bool bf16, int epl, int sign_mode, int metric, int planes, int na, bool multi)
 {
-    if (planes == SOP_K_PLANES_RANK) return na == 6;
+    if (planes == SOP_K_PLANES_RANK) return na == 6 && (epl == 16 || sign_mode == 1);
     if (epl == 8) return !multi && planes == SOP_K_PLANES_NONE && (na == 8 || (na == 6 && sign_mode == 1));
     if (na == 2) return planes == SOP_K_PLANES_NONE && sign_mode == 1 && !bf16 && metric == 0;      // (one register short of four wavefronts)
     return !multi && planes == SOP_K_PLANES_NONE && epl == 16 && !(sign_mode == 0 && na == 6 && bf16) && !(sign_mode != 0 && na == 6 && metric == 2);

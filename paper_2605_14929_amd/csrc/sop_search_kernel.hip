@@ -855,7 +855,7 @@ constexpr int occ_for(bool bf16, int epl, int sign_mode, int planes, int na, int
 {
     const bool emit = planes == SOP_K_PLANES_ALL;
     if (planes == SOP_K_PLANES_ERR) return 4;
-    if (planes == SOP_K_PLANES_RANK) return sign_mode == 0 ? 4 : bf16 || na == 2 ? 3 : 2;
+    if (planes == SOP_K_PLANES_RANK) return sign_mode == 0 || epl == 8 ? 4 : bf16 || na == 2 ? 3 : 2;
     if (lane_sums_in_lds(bf16, epl, sign_mode, metric, planes, na, multi)) return epl == 16 && ((na == 8 && sign_mode != 0) || (sign_mode == 2 && metric == 1)) ? 3 : 4;      // (109 to 128 registers; 126 to 168)
     if (epl == 8) {
         if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;

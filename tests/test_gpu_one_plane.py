@@ -16,7 +16,7 @@ SETS = {1: [NF], 2: [NF, NEG], 3: [NF, SH, OWN], 6: [NF, SH, NEG, OA.to_f32(OA.n
 
 
 @pytest.mark.parametrize("M,K,pad", [(1, 64, 0), (3, 1088, 0), (37, 1024, 8), (700, 4160, 24)])
-@pytest.mark.parametrize("g", [16, 32, 64])
+@pytest.mark.parametrize("g", [8, 16, 32, 64])
 @pytest.mark.parametrize("fmt", ["UE4M4", "E4M3", "saturating", "saturating signed"])
 @pytest.mark.parametrize("f32", [False, True])
 def test_one_plane_against_all(M, K, pad, g, fmt, f32):
