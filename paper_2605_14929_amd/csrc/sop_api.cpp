@@ -134,9 +134,7 @@ struct sop_ctx {
     unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] rows of the running DD histogram and, behind them, the counters of finished workgroups; zero between calls
     unsigned int* d_sel = nullptr;        // [2][3][SOP_K_SEL_BINS] two sets of digit counts of the block ranking: a call counts into set sel_set and clears the other
     int sel_set = 0;
-    unsigned int* d_selm = nullptr;       // [2][SOP_K_MAXA][SOP_K_SELM_WORDS] two sets of digit counts of the ranking with several thresholds (one per score plane of a launch)
-    int selm_set = 0;
-    int selm_dirty[2] = {0, 0};           // planes of each set of the batched ranking's digit counts that hold counts
+    unsigned int* d_selm = nullptr;       // [SOP_K_MAXA][SOP_K_SELM_WORDS] bin counts of the ranking with several thresholds, per score plane of a launch (zero between calls)
     SelMState* d_selstate = nullptr;      // [SOP_K_MAXA] what the passes of that ranking hand on, per score plane
     unsigned long long* d_sums = nullptr; // two sets of [SOP_K_REPL][SOP_K_NCOL] layer sums; zero between calls
     hipStream_t lane_stream[kLanes] = {};   // sop_pair_search_layers deals the layers out to streams of its own
@@ -222,8 +220,8 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
         delete c;
         return hipfail(nullptr, e, "hipMalloc(scale tables)");
     }
-    if ((e = hipMalloc((void**)&c->d_selm, sizeof(unsigned int) * 2 * SOP_K_MAXA * SOP_K_SELM_WORDS)) != hipSuccess ||
-        (e = hipMemset(c->d_selm, 0, sizeof(unsigned int) * 2 * SOP_K_MAXA * SOP_K_SELM_WORDS)) != hipSuccess ||
+    if ((e = hipMalloc((void**)&c->d_selm, sizeof(unsigned int) * SOP_K_MAXA * SOP_K_SELM_WORDS)) != hipSuccess ||
+        (e = hipMemset(c->d_selm, 0, sizeof(unsigned int) * SOP_K_MAXA * SOP_K_SELM_WORDS)) != hipSuccess ||
         (e = hipMalloc((void**)&c->d_selstate, sizeof(SelMState) * SOP_K_MAXA)) != hipSuccess) {
         (void)hipFree(c->d_bins); (void)hipFree(c->d_sums); (void)hipFree(c->d_ddacc); (void)hipFree(c->d_ls); (void)hipFree(c->d_sel); (void)hipFree(c->d_stab); if (c->d_selm) (void)hipFree(c->d_selm);
         delete c;
@@ -1061,12 +1059,10 @@ static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t 
     SelMParams p;
     std::memset(&p, 0, sizeof(p));
     p.score = score; p.n = n_blocks; p.higher = higher_is_better ? 1 : 0; p.n_levels = n_levels;
-    bool any = false;
-    for (int j = 0; j < n_levels; ++j) { p.n_top[j] = n_top[j]; any = any || n_top[j] != 0; }
-    p.hist = c->d_selm + (c->selm_set ? (size_t)SOP_K_MAXA * SOP_K_SELM_WORDS : 0); p.hist_other = c->d_selm + (c->selm_set ? 0 : (size_t)SOP_K_MAXA * SOP_K_SELM_WORDS);
+    for (int j = 0; j < n_levels; ++j) p.n_top[j] = n_top[j];
+    p.hist = c->d_selm;
     p.level = level; p.tau = tau; p.n_a = reinterpret_cast<long long*>(n_a);
     p.n_planes = n_planes;
-    p.n_clear = c->selm_dirty[c->selm_set ^ 1];
     p.state = c->d_selstate;
     if (n_planes > 1 && (n_blocks & 3)) return fail(c, SOP_EINVAL, "ranking of several planes: the number of blocks must be a multiple of four");
     const long long quads = std::max<long long>((n_blocks / 4 + SOP_K_SEL_THREADS - 1) / SOP_K_SEL_THREADS, 1);
@@ -1081,8 +1077,6 @@ static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t 
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
     hipError_t e = sopk_selm_launch(&p, n_wg_count, n_wg_next, n_wg, stream);
     if (e != hipSuccess) return hipfail(c, e, "kernel launch");
-    c->selm_dirty[c->selm_set ^ 1] = 0;
-    if (any) { c->selm_dirty[c->selm_set] = std::max(c->selm_dirty[c->selm_set], n_planes); c->selm_set ^= 1; }
     return SOP_OK;
 }
 

@@ -406,8 +406,7 @@ struct SelMParams {
     int higher;                      // 1: a larger score ranks better
     int n_levels;                    // thresholds, 1 .. SOP_K_SEL_MAXLEV
     long long n_top[SOP_K_SEL_MAXLEV];   // non-decreasing sizes of the first pool (0: every block goes to the second pool)
-    unsigned int* hist;              // first pass [SOP_K_SEL_BINS1_PAD], second and third [MAXLEV][BINS], tickets (zero when the call starts)
-    unsigned int* hist_other;        // the set the next call counts into: cleared by this call
+    unsigned int* hist;              // first pass [SOP_K_SEL_BINS1_PAD], second and third [MAXLEV][BINS], tickets (zero when the call starts; its last kernel clears them)
     unsigned char* level;            // [n] number of thresholds the block ranks strictly worse than
     float* tau;                      // [n_levels] threshold scores
     long long* n_a;                  // [n_levels] blocks at least as good as the threshold
@@ -415,8 +414,6 @@ struct SelMParams {
     // several score planes in one launch (blockIdx.y names the plane): plane q reads score + q * n, counts into
     // hist + q * SOP_K_SELM_WORDS and writes level + q * n, tau / n_a + q * SOP_K_SEL_MAXLEV
     int n_planes;
-    int n_clear;                     // planes of hist_other that hold counts (the calls that counted into that set may have
-                                     // had more planes than this one): all of them are cleared
 };
 
 /* Packing of scale words and code payloads */

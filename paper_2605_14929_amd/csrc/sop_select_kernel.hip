@@ -462,13 +462,9 @@ __global__ __launch_bounds__(SOP_K_SEL_THREADS) void rank_level_kernel(const Sel
         const long long i = (n4 << 2) + threadIdx.x;
         p.level[i] = (unsigned char)level_of(p.score[i]);
     }
-    // the other set of digit counts is cleared for the next call: every plane that holds counts, which can be more
-    // planes than this launch has (a launch over fewer planes follows one over more)
-    for (unsigned int cq = blockIdx.y; cq < (unsigned int)pp.n_clear; cq += gridDim.y) {
-        unsigned int* dst = pp.hist_other + (size_t)cq * SOP_K_SELM_WORDS;
-        for (long long gi = (long long)blockIdx.x * SOP_K_SEL_THREADS + threadIdx.x; gi < SOP_K_SELM_WORDS; gi += (long long)gridDim.x * SOP_K_SEL_THREADS)
-            dst[gi] = 0u;
-    }
+    // counts and tickets, which nothing reads any more (the thresholds are in the state), are zero again for the next call or the next replay of this one
+    for (long long gi = (long long)blockIdx.x * SOP_K_SEL_THREADS + threadIdx.x; gi < SOP_K_SELM_WORDS; gi += (long long)gridDim.x * SOP_K_SEL_THREADS)
+        p.hist[gi] = 0u;
 }
 
 // no first pool wanted of any threshold: the defaults (every block ranks worse)

@@ -59,3 +59,28 @@ def test_against_sorted_keys(kind, higher):
         pool, tau, n_a = [x.cpu().numpy() for x in cx.partition(t, (n + 1) // 2, higher)]
         thr = order[(n + 1) // 2 - 1]
         assert np.array_equal(pool, k < thr) and n_a[0] == np.count_nonzero(k >= thr)
+
+
+def test_replays_of_a_captured_call():
+    """A call leaves its counts at zero itself: a graph of one ranking gives the same again and again, with new scores and with other calls between."""
+    import torch
+    rng = np.random.default_rng(6)
+    cx = sop.Context(0)
+    for n, tops in ((70004, [100, 35002, 60000]), (9_000_003, [4_500_001])):
+        t = torch.from_numpy(scores("both", n, rng)).cuda()
+        cx.partition_levels(t, tops)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            out = cx.partition_levels(t, tops) if len(tops) > 1 else cx.partition(t, tops[0])
+        for i in range(4):
+            t.copy_(torch.from_numpy(scores("both" if i & 1 else "inside", n, rng)))
+            graph.replay()
+            torch.cuda.synchronize()
+            got = [x.cpu().numpy() for x in out]
+            if i == 2:
+                cx.partition_levels(t, [5, n])
+            want = [x.cpu().numpy() for x in (cx.partition_levels(t, tops) if len(tops) > 1 else cx.partition(t, tops[0]))]
+            assert all(np.array_equal(a, b) for a, b in zip(got, want)), (n, i)
+            k = np.sort(keys(t.cpu().numpy(), True))[::-1]
+            assert [int(v) for v in got[2]] == [int(np.count_nonzero(k >= k[m - 1])) for m in tops], (n, i)
