@@ -500,8 +500,9 @@ sop_status sop_search_layer_workspace(sop_ctx* ctx, int64_t M, int64_t K, int g,
  * (1..16) codebooks; workspace_dev: DEVICE, 256-byte aligned, at least sop_search_layer_workspace() bytes;
  * result: HOST; words_dev / payload_dev: DEVICE outputs of the packing as in sop_pack_blocks() (pack only: N_b
  * uint16 and N_b * g*n/8 bytes with n = bits of the larger of the two codebooks; the scale word needs a metabit).
- * The call queues its kernels on hip_stream and waits for the stream twice (the pool histograms are fitted on the
- * host; the ACos values decide the winner); the packing is queued and not waited for.  It replaces the context's
+ * The call queues its kernels on hip_stream and waits for the stream twice (the fitted codebooks become the searches'
+ * tables; the ACos values decide the winner); the packing is queued and not waited for.  Free fits run on the GPU,
+ * selections among fit_grid's values on the host.  It replaces the context's
  * alphabet and pair list: afterwards the context has no alphabet set.  The first call on a context allocates
  * pinned host staging (a few MB).  Calls on one context must not overlap. */
 sop_status sop_search_layer(sop_ctx* ctx, const void* W_dev, sop_dtype dtype, int64_t M, int64_t K, int64_t ldw, const float* c_dev,
