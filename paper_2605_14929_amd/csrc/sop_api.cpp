@@ -1188,6 +1188,24 @@ sop_status layer_opts_check(sop_ctx* c, int n_atoms, const sop_layer_opts* o)
 }
 }  // namespace
 
+// Pinned staging of the per-layer procedure.  All of it or nothing: kernels write through d_res, so a context never shows a part of a set-up that failed.
+static hipError_t stage_setup(sop_ctx* c, size_t bins_bytes, size_t res_bytes)
+{
+    char *bins = nullptr, *res = nullptr, *dev = nullptr;
+    hipEvent_t done = nullptr;
+    hipError_t e = hipHostMalloc((void**)&bins, bins_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&res, res_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&dev, res, 0);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        if (bins) (void)hipHostFree(bins);
+        if (res) (void)hipHostFree(res);
+        return e;
+    }
+    c->h_bins = bins; c->h_res = res; c->d_res = dev; c->stage_done = done;
+    return hipSuccess;
+}
+
 extern "C" sop_status sop_search_layer_workspace(sop_ctx* c, int64_t M, int64_t K, int g, int n_atoms, const sop_layer_opts* o, size_t* bytes)
 {
     if (!c) return SOP_EINVAL;
@@ -1233,13 +1251,8 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     const size_t hist_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long), acos_bytes = (size_t)kAcosAll * sizeof(double);
     const size_t fits_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * SOP_K_FIT_MAXENT * sizeof(float);
     const size_t res_bytes = hist_bytes + acos_bytes + fits_bytes + (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * sizeof(int);
-    if (!c->h_bins) {
-        if ((e = hipHostMalloc((void**)&c->h_bins, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, hipHostMallocDefault)) != hipSuccess ||
-            (e = hipHostMalloc((void**)&c->h_res, res_bytes, hipHostMallocDefault)) != hipSuccess ||
-            (e = hipHostGetDevicePointer((void**)&c->d_res, c->h_res, 0)) != hipSuccess ||
-            (e = hipEventCreateWithFlags(&c->stage_done, hipEventDisableTiming)) != hipSuccess)
-            return hipfail(c, e, "pinned staging of sop_search_layer");
-    }
+    if (!c->stage_done && (e = stage_setup(c, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, res_bytes)) != hipSuccess)
+        return hipfail(c, e, "pinned staging of sop_search_layer");
     if (c->stage_pending) {                            // an earlier call's copies out of the staging buffers have run?
         if ((e = hipEventSynchronize(c->stage_done)) != hipSuccess) return hipfail(c, e, "hipEventSynchronize(staging)");
         c->stage_pending = false;
