@@ -504,7 +504,8 @@ sop_status sop_search_layer_workspace(sop_ctx* ctx, int64_t M, int64_t K, int g,
  * tables; the ACos values decide the winner); the packing is queued and not waited for.  Free fits run on the GPU,
  * selections among fit_grid's values on the host.  It replaces the context's
  * alphabet and pair list: afterwards the context has no alphabet set.  The first call on a context allocates
- * pinned host staging (a few MB).  Calls on one context must not overlap. */
+ * pinned host staging (a few MB).  As it waits, a call on a stream that is being captured is refused (SOP_EHIP) before it queues anything.
+ * Calls on one context must not overlap. */
 sop_status sop_search_layer(sop_ctx* ctx, const void* W_dev, sop_dtype dtype, int64_t M, int64_t K, int64_t ldw, const float* c_dev,
                             int g, sop_scale_fmt fmt, int layer_shift_k, sop_metric metric, const sop_atom* atoms, int n_atoms,
                             const sop_layer_opts* opts, void* workspace_dev, size_t workspace_bytes, sop_layer_result* result,

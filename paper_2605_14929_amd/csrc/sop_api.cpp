@@ -128,8 +128,8 @@ struct sop_ctx {
     char* h_bins = nullptr;               // pinned staging for table images of sop_search_layer (allocated at its first call)
     char* h_res = nullptr;                // pinned memory that its kernels write their results to: histograms, then ACos values
     char* d_res = nullptr;                // the same as kernels address it
-    hipEvent_t stage_done = nullptr;      // the last copy out of h_bins has run
-    bool stage_pending = false;
+    hipEvent_t stage_done = nullptr;      // what the last call of sop_search_layer put on its stream has run
+    enum { kStageFree, kStagePending, kStageUnmarked } stage = kStageFree;      // nothing to wait for; stage_done; work is on the way that no event stands behind
     unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
     unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] rows of the running DD histogram and, behind them, the counters of finished workgroups; zero between calls
     unsigned int* d_sel = nullptr;        // [2][3][SOP_K_SEL_BINS] two sets of digit counts of the block ranking: a call counts into set sel_set and clears the other
@@ -1253,15 +1253,27 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     const size_t res_bytes = hist_bytes + acos_bytes + fits_bytes + (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * sizeof(int);
     if (!c->stage_done && (e = stage_setup(c, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, res_bytes)) != hipSuccess)
         return hipfail(c, e, "pinned staging of sop_search_layer");
-    if (c->stage_pending) {                            // an earlier call's copies out of the staging buffers have run?
-        if ((e = hipEventSynchronize(c->stage_done)) != hipSuccess) return hipfail(c, e, "hipEventSynchronize(staging)");
-        c->stage_pending = false;
+    // (the call waits for its stream: refused before anything of it becomes part of a graph, or an event of one)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if ((e = hipStreamIsCapturing(st, &capturing)) != hipSuccess) return hipfail(c, e, "hipStreamIsCapturing");
+    if (capturing != hipStreamCaptureStatusNone) return fail(c, SOP_EHIP, "sop_search_layer: the call waits for its stream, which is being captured");
+    if (c->stage != sop_ctx::kStageFree) {             // an earlier call's copies out of the staging buffers and writes to them have run?
+        e = c->stage == sop_ctx::kStagePending ? hipEventSynchronize(c->stage_done) : hipDeviceSynchronize();
+        if (e != hipSuccess) return hipfail(c, e, "wait for the call before (staging)");
+        c->stage = sop_ctx::kStageFree;
     }
     // whatever happens below, the context ends up reading its own image again, with no alphabet set, and the next call waits for what this one has put on
     // the stream before it writes to the staging buffers
     struct Restore {
-        sop_ctx* c; hipStream_t st;
-        ~Restore() { c->d_bins_cur = c->d_bins; c->n_atoms = 0; c->n_pairs = 0; c->stage_pending = hipEventRecord(c->stage_done, st) == hipSuccess; }
+        sop_ctx* c; hipStream_t st; bool marked = false;
+        hipError_t mark()
+        {
+            const hipError_t e = hipEventRecord(c->stage_done, st);
+            c->stage = e == hipSuccess ? sop_ctx::kStagePending : sop_ctx::kStageUnmarked;
+            marked = true;
+            return e;
+        }
+        ~Restore() { c->d_bins_cur = c->d_bins; c->n_atoms = 0; c->n_pairs = 0; if (!marked) (void)mark(); }
     } restore{c, st};
     auto img = [&](int i) { return reinterpret_cast<char*>(base) + L.bins + (size_t)i * kImgBytes; };
     auto himg = [&](int i) { return c->h_bins + (size_t)i * kImgBytes; };
@@ -1498,5 +1510,6 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
         if (sop_status s = sop_pack_blocks(c, M, K, g, fmt, sc, codes, two[0].n_entries, sc + Nb, codes + plane_a, two[1].n_entries,
                                            base + L.sel, 2, 0, words, payload, &res->n_bits, stream)) return s;
     }
+    if ((e = restore.mark()) != hipSuccess) return hipfail(c, e, "hipEventRecord");
     return SOP_OK;
 }

@@ -25,6 +25,8 @@ static std::string g_fail;                 // the next call of this function fai
 static int g_fail_after = 0;               // ... after so many that do not
 static int g_searches_outside = 0;         // searches whose results would go to memory that nobody allocated
 static int g_events = 0;                   // events alive
+static bool g_capturing = false;           // the stream is being captured
+static std::string g_log;                  // waits ('e' event, 's' stream, 'd' device) and uploads from pinned memory ('u') in their order
 static bool fails(const char* fn)
 {
     if (g_fail != fn || g_fail_after-- > 0) return false;
@@ -64,15 +66,30 @@ hipError_t hipHostFree(void* p) { CHECK(g_pinned.erase(static_cast<char*>(p)) ==
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned int) { if (fails("hipHostGetDevicePointer")) return hipErrorInvalidValue; *d = h; return hipSuccess; }
 hipError_t hipMemset(void* p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { if (inside(g_pinned, s)) g_log += 'u'; std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { static char scratch[1 << 16]; *p = scratch; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 1; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned int) { if (fails("hipEventCreateWithFlags")) return hipErrorOutOfMemory; *e = reinterpret_cast<hipEvent_t>(new int(0)); ++g_events; return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<int*>(e); --g_events; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { return e ? hipSuccess : hipErrorInvalidHandle; }
-hipError_t hipEventSynchronize(hipEvent_t e) { return e ? hipSuccess : hipErrorInvalidHandle; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+// (an event recorded on a stream that is being captured stands for no work of the GPU: it can't be waited for)
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+{
+    if (!e) return hipErrorInvalidHandle;
+    if (fails("hipEventRecord")) return hipErrorOutOfMemory;
+    *reinterpret_cast<int*>(e) = g_capturing;
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e)
+{
+    if (!e) return hipErrorInvalidHandle;
+    if (*reinterpret_cast<int*>(e)) return hipErrorCapturedEvent;
+    g_log += 'e';
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { if (g_capturing) return hipErrorStreamCaptureUnsupported; g_log += 's'; return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { if (g_capturing) return hipErrorStreamCaptureUnsupported; g_log += 'd'; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* st) { *g = *b = dim3(1, 1, 1); *s = 0; *st = nullptr; return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3 block, void** args, size_t, hipStream_t)
@@ -135,11 +152,47 @@ static void setup_fails(const char* fn, int after)
     CHECK(g_pinned.empty() && g_device.empty() && g_events == 0);
 }
 
+// no event could be recorded behind a call's work: the call says so where nothing else went wrong, and the next one waits for all of it before it writes to the staging buffers
+static void record_fails(bool call_fails)
+{
+    sop_ctx* c = nullptr;
+    CHECK(sop_create(&c, 0) == SOP_OK);
+    Layer l(c);
+    CHECK(l.call(c) == SOP_OK);
+    g_fail = "hipEventRecord"; g_fail_after = 0;
+    CHECK(l.call(c, call_fails ? 100 : 0) == (call_fails ? SOP_EFMT : SOP_EHIP));
+    CHECK(g_fail.empty());
+    g_log.clear();
+    CHECK(l.call(c) == SOP_OK);
+    CHECK(g_log[0] == 'd');
+    g_log.clear();
+    CHECK(l.call(c) == SOP_OK);
+    CHECK(g_log[0] == 'e');
+    CHECK(sop_destroy(c) == SOP_OK);
+}
+
+// a call on a stream that is being captured is refused, whatever else is wrong with it, and leaves the context as it was
+static void captured(int shift)
+{
+    sop_ctx* c = nullptr;
+    CHECK(sop_create(&c, 0) == SOP_OK);
+    Layer l(c);
+    CHECK(l.call(c) == SOP_OK);
+    g_capturing = true;
+    CHECK(l.call(c, shift) != SOP_OK);
+    g_capturing = false;
+    CHECK(l.call(c) == SOP_OK);
+    CHECK(l.call(c) == SOP_OK);
+    CHECK(sop_destroy(c) == SOP_OK);
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "setup") setup_fails(argv[2], std::atoi(argv[3]));
-    else { std::printf("usage: %s setup FUNCTION CALLS_BEFORE\n", argv[0]); return 2; }
+    else if (what == "record") record_fails(std::atoi(argv[2]) != 0);
+    else if (what == "captured") captured(std::atoi(argv[2]));
+    else { std::printf("usage: %s setup FUNCTION CALLS_BEFORE | record CALL_FAILS | captured SHIFT\n", argv[0]); return 2; }
     if (failures) return 1;
     std::printf("procedure ok\n");
     return 0;

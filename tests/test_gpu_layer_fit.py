@@ -59,3 +59,27 @@ def test_against_fits_on_the_host(M, K, g, bins, entries, iters, p, weighted):
     assert {k: v for k, v in r.acos_fitted.items() if k in want} == want
     if r.kind == "fitted":
         assert np.array_equal(r.table_b, tables[(r.a, r.p_percent)])
+
+
+def test_a_captured_call_is_refused_and_the_graph_stays_good():
+    """A refused call, with good arguments or with bad ones, adds nothing to the graph being captured, and the context serves the next call."""
+    import torch
+    W, c = si.bf16_round(si.student_t_weights(48, 1024, 4.0, 8310)), si.channel_norms(1024, 1.0, 8311)
+    Wt, ct = torch.from_numpy(W).cuda().to(torch.bfloat16), torch.from_numpy(c).cuda()
+    cx, x = sop.Context(0), torch.zeros(64, device="cuda")
+    call = lambda k=0: layer_search.search_layer(cx, Wt, ct, 16, sop.fmt_by_name("UE4M3"), ATOMS, p_grid=(50.0, 80.0), k=k)
+    want = call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        x.add_(1.0)
+        for k in (0, 100):                                           # (100: out of range, otherwise found by the first search)
+            with pytest.raises(sop.SopError):
+                call(k)
+        x.add_(1.0)
+    for i in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (x == 2.0 * (i + 1)).all()
+        got = call()
+        assert got.acos == want.acos and got.acos_fitted == want.acos_fitted

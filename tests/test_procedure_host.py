@@ -24,3 +24,13 @@ def _run(program, *args):
 @pytest.mark.parametrize("step", [("hipHostMalloc", 0), ("hipHostMalloc", 1), ("hipHostGetDevicePointer", 0), ("hipEventCreateWithFlags", 0)])
 def test_a_failed_setup_is_made_up_for_by_the_next_call(program, step):
     _run(program, "setup", step[0], str(step[1]))
+
+
+@pytest.mark.parametrize("call_fails", [0, 1])
+def test_work_that_no_event_stands_behind_is_waited_for(program, call_fails):
+    _run(program, "record", str(call_fails))
+
+
+@pytest.mark.parametrize("shift", [0, 100])                      # (100: out of range, found by the first search)
+def test_a_captured_call_is_refused_and_leaves_nothing(program, shift):
+    _run(program, "captured", str(shift))
