@@ -358,8 +358,12 @@ __global__ __launch_bounds__(SOP_K_FIT_THREADS) void dd_fit_kernel(const FitPara
     u64* const pm = s_pre;
     u64* const pf = s_pre + H + 1;
     const long long* const hist = p.hist + (size_t)blockIdx.x * H;
-    for (int b = tid; b < H; b += SOP_K_FIT_THREADS) pm[b] = (u64)hist[b];
-    __syncthreads();
+    // The largest first moment is below 2 H times the total mass, so the sums are exact in 64 bits where the total is at most `most`.  No bin may exceed it either (a negative
+    // one does), or the total itself could wrap to something small: a weight's mass is up to 2^31 - 1, and 2^33 of those, 16 GiB of bf16, fit this GPU
+    const u64 most = (0x7FFFFFFFFFFFFFFFull >> 1) / (u64)H;
+    int beyond = 0;
+    for (int b = tid; b < H; b += SOP_K_FIT_THREADS) { const u64 v = (u64)hist[b]; pm[b] = v; beyond |= v > most ? 1 : 0; }
+    beyond = __syncthreads_or(beyond);
     // prefix sums: a run of bins a thread
     const int per = (H + SOP_K_FIT_THREADS - 1) / SOP_K_FIT_THREADS, b0 = min(tid * per, H), b1 = min(b0 + per, H);
     u64 m = 0ull, f = 0ull;
@@ -383,9 +387,7 @@ __global__ __launch_bounds__(SOP_K_FIT_THREADS) void dd_fit_kernel(const FitPara
     __syncthreads();
     if (wv != 0) return;
     const u64 total = pm[H];
-    int status = total == 0ull ? SOP_K_FIT_EMPTY : SOP_K_FIT_OK;
-    // (the largest first moment is below 2 H total.  A total that wrapped is out of reach: a layer has fewer than 2^38 weights of at most 2^31 each)
-    if (total > (0x7FFFFFFFFFFFFFFFull >> 1) / (u64)H) status = SOP_K_FIT_HOST;
+    int status = beyond || total > most ? SOP_K_FIT_HOST : total == 0ull ? SOP_K_FIT_EMPTY : SOP_K_FIT_OK;
     const bool on = lane < n;
     double cent = on ? (double)p.init[min(lane, SOP_K_FIT_MAXENT - 1)] : 0.0;
     const double inv = 1.0 / (double)H, halfH = 0.5 * (double)H;

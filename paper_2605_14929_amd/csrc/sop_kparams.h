@@ -316,7 +316,7 @@ inline unsigned int dd_rows(unsigned int words, unsigned int workgroups)
 #define SOP_K_FIT_OK 0
 #define SOP_K_FIT_NONE 1             /* not strictly ascending in binary32, or one-sided: no codebook (SOP_EATOM) */
 #define SOP_K_FIT_EMPTY 2            /* an empty histogram */
-#define SOP_K_FIT_HOST 3             /* moments beyond 64 bits, or entries out of order on the way: left to the host */
+#define SOP_K_FIT_HOST 3             /* moments that 64 bits may not hold, a negative bin, or entries out of order on the way: left to the host */
 struct FitParams {
     const long long* hist;           // [histograms][n_bins]
     int n_bins, n_entries, iters;

@@ -83,3 +83,42 @@ def test_a_captured_call_is_refused_and_the_graph_stays_good():
         assert (x == 2.0 * (i + 1)).all()
         got = call()
         assert got.acos == want.acos and got.acos_fitted == want.acos_fitted
+
+
+@pytest.mark.parametrize("bins", [64, 1024, 8192])
+def test_fits_that_64_bits_may_not_hold_are_left_to_the_host(bins):
+    """The fitting kernel on histograms at the edges of its range: a total mass of 2^62 / bins is fitted, to the host's bits; one more, bins that wrap the total
+    to something small or to nothing, and negative ones are not."""
+    import ctypes as C
+    import torch
+
+    class FitParams(C.Structure):
+        _fields_ = [("hist", C.c_void_p), ("n_bins", C.c_int), ("n_entries", C.c_int), ("iters", C.c_int), ("init", C.c_float * 64), ("out", C.c_void_p), ("status", C.c_void_p)]
+
+    OK, EMPTY, HOST = 0, 2, 3
+    most = ((1 << 63) - 1 >> 1) // bins
+    x = (2.0 * np.arange(bins) + 1.0) / bins - 1.0
+    bell = np.floor(np.exp(-4.0 * x * x) / np.exp(-4.0 * x * x).sum() * most * 0.999).astype(np.int64)
+    full, over, small, nothing, negative, empty, right = [bell.copy() for _ in range(7)]
+    full[bins // 2] += most - int(full.sum())
+    over[bins // 2] += most + 1 - int(over.sum())
+    small[:] = np.maximum(bell >> 20, 1)
+    small[[1, 5, bins - 9, bins - 2]] = 1 << 62                       # (the total is 2^64 and a little)
+    nothing[:] = 0
+    nothing[[3, bins - 7]] = -(1 << 63)
+    negative[bins // 3] = -1
+    empty[:] = 0
+    right[:bins // 2] = 0
+    hist = np.stack([full, over, small, nothing, negative, empty, right])
+    want = [OK, HOST, HOST, HOST, HOST, EMPTY, OK]
+    entries = 16
+    t = torch.from_numpy(hist).cuda()
+    out, status = torch.zeros((len(want), 64), device="cuda"), torch.full((len(want),), -1, dtype=torch.int32, device="cuda")
+    p = FitParams(t.data_ptr(), bins, entries, 20, (C.c_float * 64)(*NF), out.data_ptr(), status.data_ptr())
+    launch = sop.lib().sopk_fit_launch
+    launch.argtypes = [C.POINTER(FitParams), C.c_int, C.c_void_p]
+    assert launch(C.byref(p), len(want), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert status.tolist() == want
+    for i in (0, 6):
+        assert np.array_equal(out[i, :entries].cpu().numpy(), np.asarray(sop.sop_dd_fit(hist[i], entries, 20, NF), np.float32))
