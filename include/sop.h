@@ -501,8 +501,9 @@ sop_status sop_search_layer_workspace(sop_ctx* ctx, int64_t M, int64_t K, int g,
  * result: HOST; words_dev / payload_dev: DEVICE outputs of the packing as in sop_pack_blocks() (pack only: N_b
  * uint16 and N_b * g*n/8 bytes with n = bits of the larger of the two codebooks; the scale word needs a metabit).
  * The call queues its kernels on hip_stream and waits for the stream twice (the fitted codebooks become the searches'
- * tables; the ACos values decide the winner); the packing is queued and not waited for.  Free fits run on the GPU,
- * selections among fit_grid's values on the host.  It replaces the context's
+ * tables; the ACos values decide the winner); the packing is queued and not waited for.  Free fits run on the GPU, selections among fit_grid's
+ * values on the host; so are free fits of pools whose mass exceeds 2^62 / fit_bins (more than 2^29 weights of the largest norm at 8192 bins), for
+ * which the call waits a third time.  It replaces the context's
  * alphabet and pair list: afterwards the context has no alphabet set.  The first call on a context allocates
  * pinned host staging (a few MB).  As it waits, a call on a stream that is being captured is refused (SOP_EHIP) before it queues anything.
  * Calls on one context must not overlap. */

@@ -1364,6 +1364,10 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
             if ((e = sopk_fit_launch(&fp, A * n_p, stream)) != hipSuccess) return hipfail(c, e, "kernel launch (fits)");
         }
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return hipfail(c, e, "wait for the fits");
+        // (fits that the kernel left to the host: all histograms come over, here, where the stream is empty, and not one by one behind the searches below)
+        if (gpu_fit && std::find(h_status, h_status + A * n_p, SOP_K_FIT_HOST) != h_status + A * n_p &&
+            ((e = hipMemcpyAsync(h_hist, d_hist, (size_t)A * n_p * bins * sizeof(long long), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+             (e = hipStreamSynchronize(st)) != hipSuccess)) return hipfail(c, e, "copy of the pool histograms");
     }
     // ---- step 4 for one atom's whole sweep per search: alphabet (a, L_b(p_0), L_b(p_1), ...).  The tables of two atoms go up in one copy ahead of their searches: the
     //      first search starts after two plans, and the GPU works on a pair's searches while the next are planned (a copy before every search was 4.6 us of the
@@ -1407,8 +1411,6 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
                 const int done = gpu_fit ? h_status[at] : SOP_K_FIT_HOST;
                 bool any = done != SOP_K_FIT_EMPTY;
                 if (done == SOP_K_FIT_HOST) {
-                    if (gpu_fit && ((e = hipMemcpyAsync(h, d_hist + at * bins, (size_t)bins * sizeof(long long), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-                                    (e = hipStreamSynchronize(st)) != hipSuccess)) return hipfail(c, e, "copy of a pool histogram");
                     any = false;
                     for (int b = 0; b < bins && !any; ++b) any = h[b] != 0;
                 }

@@ -122,3 +122,18 @@ def test_fits_that_64_bits_may_not_hold_are_left_to_the_host(bins):
     assert status.tolist() == want
     for i in (0, 6):
         assert np.array_equal(out[i, :entries].cpu().numpy(), np.asarray(sop.sop_dd_fit(hist[i], entries, 20, NF), np.float32))
+
+
+@pytest.mark.parametrize("M,bins,p", [(512, 8192, (20.0,)), (1024, 4096, (20.0, 95.0))])
+def test_fits_left_to_the_host_within_the_procedure(M, bins, p, monkeypatch):
+    """Norms so small that every weight has the largest mass there is: the first pool's total exceeds what the kernel fits (the second's of the last case does not),
+    and its histogram comes to the host."""
+    import torch
+    K = 1024
+    norms = np.full(K, 1e-36, np.float32)
+    Wt = torch.from_numpy(si.bf16_round(si.student_t_weights(M, K, 4.0, 8300 + M))).cuda().to(torch.bfloat16)
+    total = int(sop.Context(0).dd_histogram(Wt, torch.from_numpy(norms).cuda(), 16, bins).cpu().numpy().sum())
+    most = (1 << 62) // bins
+    assert [total * (100 - x) / 100 > most for x in p] == [x < 50 for x in p]
+    monkeypatch.setattr(si, "channel_norms", lambda *a: norms)
+    test_against_fits_on_the_host(M, K, 16, bins, 16, 20, p, True)
