@@ -97,6 +97,7 @@ __global__ void static_prologue_kernel(unsigned long long* sums, int n_words, fl
     }
 }
 
+constexpr size_t kSelWords = 3 * SOP_K_SEL_BINS + 4;
 constexpr size_t kImgBytes = (size_t)SOP_K_PAIR_BIN_BYTES * SOP_K_MAXBINS;       // the largest image of an element-search table
 
 struct sop_ctx {
@@ -132,8 +133,7 @@ struct sop_ctx {
     enum { kStageFree, kStagePending, kStageUnmarked } stage = kStageFree;      // nothing to wait for; stage_done; work is on the way that no event stands behind
     unsigned long long* d_ls = nullptr;   // [kLsWords] scratch of the layer-scope passes; zero between calls
     unsigned long long* d_ddacc = nullptr; // [SOP_K_DD_MAXBINS] rows of the running DD histogram and, behind them, the counters of finished workgroups; zero between calls
-    unsigned int* d_sel = nullptr;        // [2][3][SOP_K_SEL_BINS] two sets of digit counts of the block ranking: a call counts into set sel_set and clears the other
-    int sel_set = 0;
+    unsigned int* d_sel = nullptr;        // [kSelWords] digit counts of the block ranking and, behind them, what its last pass hands on (see SelParams)
     unsigned int* d_selm = nullptr;       // [SOP_K_MAXA][SOP_K_SELM_WORDS] bin counts of the ranking with several thresholds, per score plane of a launch (zero between calls)
     SelMState* d_selstate = nullptr;      // [SOP_K_MAXA] what the passes of that ranking hand on, per score plane
     unsigned long long* d_sums = nullptr; // two sets of [SOP_K_REPL][SOP_K_NCOL] layer sums; zero between calls
@@ -209,8 +209,8 @@ extern "C" sop_status sop_create(sop_ctx** out, int device)
         delete c;
         return hipfail(nullptr, e, "hipMalloc(partials)");
     }
-    if ((e = hipMalloc((void**)&c->d_sel, sizeof(unsigned int) * (6 * SOP_K_SEL_BINS))) != hipSuccess ||
-        (e = hipMemset(c->d_sel, 0, sizeof(unsigned int) * (6 * SOP_K_SEL_BINS))) != hipSuccess) {
+    if ((e = hipMalloc((void**)&c->d_sel, sizeof(unsigned int) * kSelWords)) != hipSuccess ||
+        (e = hipMemset(c->d_sel, 0, sizeof(unsigned int) * kSelWords)) != hipSuccess) {
         (void)hipFree(c->d_bins); (void)hipFree(c->d_sums); (void)hipFree(c->d_ddacc); (void)hipFree(c->d_ls); if (c->d_sel) (void)hipFree(c->d_sel);
         delete c;
         return hipfail(nullptr, e, "hipMalloc(rank counts)");
@@ -1025,7 +1025,7 @@ extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_bl
     SelParams p;
     std::memset(&p, 0, sizeof(p));
     p.score = score; p.n = n_blocks; p.n_top = n_top; p.higher = higher_is_better ? 1 : 0; p.all_b = n_top == 0;
-    p.hist = c->d_sel + (c->sel_set ? 3 * SOP_K_SEL_BINS : 0); p.hist_other = c->d_sel + (c->sel_set ? 0 : 3 * SOP_K_SEL_BINS);
+    p.hist = c->d_sel; p.found = c->d_sel + 3 * SOP_K_SEL_BINS;
     p.pool_b = pool_b; p.tau = tau; p.n_a = reinterpret_cast<long long*>(n_a);
     const long long quads = std::max<long long>((n_blocks / 4 + SOP_K_SEL_THREADS - 1) / SOP_K_SEL_THREADS, 1);
     const int n_wg = (int)std::min<long long>((long long)c->n_cu * 4, quads);
@@ -1035,7 +1035,6 @@ extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_bl
     const int n_wg_count = (int)std::min<long long>(std::max(c->n_cu / 2, 1), cquads);
     hipError_t e = sopk_sel_launch(&p, n_wg_count, n_wg, stream);
     if (e != hipSuccess) return hipfail(c, e, "kernel launch");
-    if (!p.all_b) c->sel_set ^= 1;
     return SOP_OK;
 }
 

@@ -383,8 +383,8 @@ struct SelParams {
     long long n, n_top;              // 1 <= n_top <= n (n_top == 0: all_b)
     int higher;                      // 1: a larger score ranks better
     int all_b;                       // 1: every block goes to the second pool
-    unsigned int* hist;              // [3][SOP_K_SEL_BINS] digit counts of the passes (zero when the call starts)
-    unsigned int* hist_other;        // [3][SOP_K_SEL_BINS] the set the next call counts into: cleared by this call
+    unsigned int* hist;              // [3][SOP_K_SEL_BINS] digit counts of the passes (the first two are zero between calls, the last one is cleared by the first pass)
+    unsigned int* found;             // [3] what the last pass hands to the split: digits of the first two passes in place, rank wanted among the keys with them, keys above them
     unsigned char* pool_b;           // [n] 1 = ranked strictly worse than the threshold
     float* tau;                      // [1] the threshold score
     long long* n_a;                  // [1] blocks that stay in the first pool

@@ -17,8 +17,8 @@
 //   a pass is the read of the scores and, for few of them, five round trips to memory one after the other (state, scores, sums, ticket, totals).  Three passes of 11, 11 and
 //   10 bits whatever the scores, with a kernel after each that found the digits, against these, 2.8 M scores, four thresholds: six planes 109 us -> 66, one plane 51 -> 31 (scores spread
 //   over many binades, where the third pass counts: 56.6 -> 47.6); 98 304 scores 31.8 -> 20.9; 14.7 M 134 -> 69.
-// Counts are integers added with atomics, so every result is exact and reproducible.  The context holds two sets of histograms:
-// a call counts into one and clears the other, which the next call then counts into.
+// Counts are integers added with atomics, so every result is exact and reproducible.  Every call leaves the counts that the next one adds to at zero itself, so a captured call can
+// be replayed: each is cleared by a kernel of the call in which no workgroup reads it any more, or none yet.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -118,8 +118,12 @@ __global__ __launch_bounds__(SOP_K_CNT_THREADS) void rank_count_kernel(const Sel
         if (PASS >= 2) {
             const Digit f1 = find_digit(p.hist + SOP_K_SEL_BINS, f0.rank_in, &s_found, s_wave);
             prefix |= (uint32_t)f1.digit << 10; pmask = 0xFFFFFC00u;
+            // (what the split kernel goes on from: it reads the first two histograms no more, and clears them)
+            if (blockIdx.x == 0 && threadIdx.x == 0) { p.found[0] = prefix; p.found[1] = f1.rank_in; p.found[2] = f0.above + f1.above; }
         }
     }
+    if (PASS == 0)                                                  // the last pass's counts of the call before, which nothing reads any more
+        for (int i = (int)(blockIdx.x * SOP_K_CNT_THREADS + threadIdx.x); i < SOP_K_SEL_BINS; i += (int)gridDim.x * SOP_K_CNT_THREADS) p.hist[2 * SOP_K_SEL_BINS + i] = 0u;
     __syncthreads();
     const bool higher = p.higher != 0;
     const long long n4 = p.n >> 2;
@@ -154,13 +158,11 @@ __global__ __launch_bounds__(SOP_K_SEL_THREADS) void rank_split_kernel(const Sel
     unsigned int n_a = 0;
     float tau = higher ? __uint_as_float(0x7F800000u) : __uint_as_float(0xFF800000u);
     if (!p.all_b) {
-        const Digit f0 = find_digit(p.hist, (unsigned int)p.n_top, &s_found, s_wave);
-        const Digit f1 = find_digit(p.hist + SOP_K_SEL_BINS, f0.rank_in, &s_found, s_wave);
-        const Digit f2 = find_digit(p.hist + 2 * SOP_K_SEL_BINS, f1.rank_in, &s_found, s_wave);
-        tkey = ((uint32_t)f0.digit << 21) | ((uint32_t)f1.digit << 10) | (uint32_t)f2.digit;
+        const Digit f2 = find_digit(p.hist + 2 * SOP_K_SEL_BINS, p.found[1], &s_found, s_wave);
+        tkey = p.found[0] | (uint32_t)f2.digit;
         tau = key_score(tkey, higher);
         // keys above tau's, plus every key equal to it
-        n_a = f0.above + f1.above + f2.above + p.hist[2 * SOP_K_SEL_BINS + f2.digit];
+        n_a = p.found[2] + f2.above + p.hist[2 * SOP_K_SEL_BINS + f2.digit];
     }
     const long long n4 = p.n >> 2;
     const float4* s4 = reinterpret_cast<const float4*>(p.score);
@@ -181,10 +183,9 @@ __global__ __launch_bounds__(SOP_K_SEL_THREADS) void rank_split_kernel(const Sel
         p.pool_b[i] = p.all_b ? 1 : (rank_key(p.score[i], higher) < tkey ? 1 : 0);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) { *p.tau = tau; *p.n_a = (long long)n_a; }
-    // clear the other set of histograms (the one the previous call counted into; nothing reads it
-    // now) for the next call: no workgroup has to wait for the others
-    for (long long gi = (long long)blockIdx.x * SOP_K_SEL_THREADS + threadIdx.x; gi < 3 * SOP_K_SEL_BINS; gi += (long long)gridDim.x * SOP_K_SEL_THREADS)
-        p.hist_other[gi] = 0u;
+    // the first two histograms are zero for the next call (the last one is cleared by its first kernel: every workgroup of this one reads it)
+    for (long long gi = (long long)blockIdx.x * SOP_K_SEL_THREADS + threadIdx.x; !p.all_b && gi < 2 * SOP_K_SEL_BINS; gi += (long long)gridDim.x * SOP_K_SEL_THREADS)
+        p.hist[gi] = 0u;
 }
 
 // ---- several thresholds at once (the sweep over the partition parameter: nested pools), several planes ----

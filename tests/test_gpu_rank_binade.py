@@ -84,3 +84,32 @@ def test_replays_of_a_captured_call():
             assert all(np.array_equal(a, b) for a, b in zip(got, want)), (n, i)
             k = np.sort(keys(t.cpu().numpy(), True))[::-1]
             assert [int(v) for v in got[2]] == [int(np.count_nonzero(k >= k[m - 1])) for m in tops], (n, i)
+
+
+@pytest.mark.parametrize("n", [7, 4099, 70004, 2_818_048])
+def test_replays_of_a_captured_call_with_one_threshold(n):
+    """The same for the three passes of a single threshold, with other calls of other sizes, and calls without a first pool, between the replays."""
+    import torch
+    rng = np.random.default_rng(7)
+    cx = sop.Context(0)
+    top = (n + 1) // 2
+    t = torch.from_numpy(scores("both", n, rng)).cuda()
+    cx.partition(t, top)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = cx.partition(t, top)
+    for i in range(5):
+        s = scores(("both", "inside", "wide", "one bin", "special")[i], n, rng)
+        t.copy_(torch.from_numpy(s))
+        graph.replay()
+        torch.cuda.synchronize()
+        pool, tau, n_a = [x.cpu().numpy() for x in out]
+        k = keys(s, True)
+        thr = np.sort(k)[::-1][top - 1]
+        assert np.array_equal(pool, k < thr) and n_a[0] == np.count_nonzero(k >= thr) and keys(tau, True)[0] == thr, (n, i)
+        if i == 1:
+            cx.partition(t, 0)
+        if i == 2:
+            cx.partition(t, n)
+            cx.partition(t[:max(n // 3, 1)], 1, False)
