@@ -66,3 +66,28 @@ def test_metric_mse_against_wse_with_every_plane_of_eight_atoms(rule):
     fmt = "E4M3" if rule else "UE4M4"
     wse, mse = (_best_ms(8, fmt, 8, m, torch.float32, emit=True, rule=rule) for m in (sop.SEL_WSE, sop.SEL_MSE))
     assert mse < 1.1 * wse, (wse, mse)
+
+
+def _median_us(run, n=20):
+    import torch
+    times = []
+    for _ in range(7):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(n):
+            run()
+        e1.record()
+        e1.synchronize()
+        times.append(e0.elapsed_time(e1) / n * 1e3)
+    return sorted(times)[3]
+
+
+def test_ranking_of_scores_of_which_half_are_equal():
+    # 100 us against 91 measured; 160 against 91 where lanes that share a bin were counted one by one unless all of them did, 147 against 114 in the three passes before
+    import torch
+    cx, n = ctx(), 14_680_064
+    u = torch.rand(n, generator=torch.Generator(device="cuda").manual_seed(6), device="cuda")
+    spread, half = 0.75 + 0.1249 * u, torch.where(u < 0.5, 0.8, 0.5 + 0.5 * u)
+    tops = [int(n * f) for f in (0.5, 0.7, 0.85, 0.95)]
+    a, b = (_median_us(lambda: cx.partition_levels(s, tops)) for s in (spread, half))
+    assert b < 1.35 * a, (a, b)
