@@ -1010,18 +1010,9 @@ extern "C" sop_status sop_sum_f32(sop_ctx* c, const float* x, int64_t n, double*
 static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t n_blocks, const int64_t* n_top, int n_levels,
                                         int higher_is_better, uint8_t* level, float* tau, int64_t* n_a, int n_planes, void* stream);
 
-extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_blocks, int64_t n_top, int higher_is_better,
-                                    uint8_t* pool_b, float* tau, int64_t* n_a, void* stream)
+// one threshold, by the three passes of its own (arguments checked)
+static sop_status rank_one(sop_ctx* c, const float* score, int64_t n_blocks, int64_t n_top, int higher_is_better, uint8_t* pool_b, float* tau, int64_t* n_a, void* stream)
 {
-    if (!c) return SOP_EINVAL;
-    if (!score || !pool_b || !tau || !n_a) return fail(c, SOP_EINVAL, "sop_partition: score, pool_b, tau and n_a must not be NULL");
-    if (n_blocks < 1 || n_blocks > 0x7FFFFFFFll) return fail(c, SOP_ESHAPE, "sop_partition: n_blocks must lie in 1 .. 2^31-1");
-    if (n_top < 0 || n_top > n_blocks) return fail(c, SOP_EINVAL, "sop_partition: n_top must lie in 0 .. n_blocks");
-    if (!aligned16(score)) return fail(c, SOP_EINVAL, "sop_partition: score must be 16-byte aligned");
-    if ((reinterpret_cast<uintptr_t>(pool_b) & 3u) || (reinterpret_cast<uintptr_t>(tau) & 3u) || (reinterpret_cast<uintptr_t>(n_a) & 7u))
-        return fail(c, SOP_EINVAL, "sop_partition: pool_b and tau must be 4-byte aligned, n_a 8-byte aligned");
-    // (the passes of several thresholds: from where they are faster whatever the scores, see SOP_K_SEL_ONE_MAX)
-    if (n_blocks > SOP_K_SEL_ONE_MAX) return partition_levels_impl(c, score, n_blocks, &n_top, 1, higher_is_better, pool_b, tau, n_a, 1, stream);
     SelParams p;
     std::memset(&p, 0, sizeof(p));
     p.score = score; p.n = n_blocks; p.n_top = n_top; p.higher = higher_is_better ? 1 : 0; p.all_b = n_top == 0;
@@ -1036,6 +1027,20 @@ extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_bl
     hipError_t e = sopk_sel_launch(&p, n_wg_count, n_wg, stream);
     if (e != hipSuccess) return hipfail(c, e, "kernel launch");
     return SOP_OK;
+}
+
+extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_blocks, int64_t n_top, int higher_is_better,
+                                    uint8_t* pool_b, float* tau, int64_t* n_a, void* stream)
+{
+    if (!c) return SOP_EINVAL;
+    if (!score || !pool_b || !tau || !n_a) return fail(c, SOP_EINVAL, "sop_partition: score, pool_b, tau and n_a must not be NULL");
+    if (n_blocks < 1 || n_blocks > 0x7FFFFFFFll) return fail(c, SOP_ESHAPE, "sop_partition: n_blocks must lie in 1 .. 2^31-1");
+    if (n_top < 0 || n_top > n_blocks) return fail(c, SOP_EINVAL, "sop_partition: n_top must lie in 0 .. n_blocks");
+    if (!aligned16(score)) return fail(c, SOP_EINVAL, "sop_partition: score must be 16-byte aligned");
+    if ((reinterpret_cast<uintptr_t>(pool_b) & 3u) || (reinterpret_cast<uintptr_t>(tau) & 3u) || (reinterpret_cast<uintptr_t>(n_a) & 7u))
+        return fail(c, SOP_EINVAL, "sop_partition: pool_b and tau must be 4-byte aligned, n_a 8-byte aligned");
+    if (!sel_three_passes(n_blocks, n_top == 0)) return partition_levels_impl(c, score, n_blocks, &n_top, 1, higher_is_better, pool_b, tau, n_a, 1, stream);
+    return rank_one(c, score, n_blocks, n_top, higher_is_better, pool_b, tau, n_a, stream);
 }
 
 // n_planes score planes of n_blocks scores each, back to back, ranked in the same launches (the per-layer

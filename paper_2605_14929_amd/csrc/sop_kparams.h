@@ -378,6 +378,9 @@ struct LsParams {
  * itself: no pass ends in a ticket.  Against the passes of several thresholds, 2.8 M scores: cosines 29.1 us and 26.7, errors (spread over many binades) 28.7 and
  * 37.7; 0.7 M 21.2 and 21.2, 20.2 and 29.2; 14.7 M 94 and 60, 92 and 78. */
 #define SOP_K_SEL_ONE_MAX (8 << 20)
+/* Does a ranking go through these three passes?  With no first pool wanted there is nothing to count and its split kernel writes the whole mask without a look at the scores
+ * (14.7 M 10.2 us; 17.9 by the level kernel, which reads them). */
+inline bool sel_three_passes(long long n, bool none) { return none || n <= SOP_K_SEL_ONE_MAX; }
 struct SelParams {
     const float* score;              // [n]
     long long n, n_top;              // 1 <= n_top <= n (n_top == 0: all_b)

@@ -91,3 +91,11 @@ def test_ranking_of_scores_of_which_half_are_equal():
     tops = [int(n * f) for f in (0.5, 0.7, 0.85, 0.95)]
     a, b = (_median_us(lambda: cx.partition_levels(s, tops)) for s in (spread, half))
     assert b < 1.35 * a, (a, b)
+
+
+def test_ranking_without_a_first_pool_reads_no_scores():
+    # the mask of 14.7 M blocks takes what that of 2.8 M takes (a launch); 1.75 times as long by the kernel that reads the scores
+    import torch
+    cx, s = ctx(), torch.rand(14_680_064, device="cuda")
+    few, many = (_median_us(lambda: cx.partition(t, 0), 50) for t in (s[:2_818_048], s))
+    assert many < 1.4 * few, (few, many)
