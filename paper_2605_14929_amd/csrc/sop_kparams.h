@@ -375,12 +375,15 @@ struct LsParams {
 #define SOP_K_SEL_DONE (SOP_K_SEL_BINS1_PAD + 2 * SOP_K_SEL_MAXLEV * SOP_K_SEL_BINS)      /* tickets of the passes, a 128-byte line each */
 #define SOP_K_SELM_WORDS (SOP_K_SEL_DONE + 3 * 32)      /* one set of counts and tickets of a plane */
 /* One threshold of one plane of at most SOP_K_SEL_ONE_MAX scores goes through three passes of 11, 11 and 10 bits, whose digits every workgroup of the next finds for
- * itself: no pass ends in a ticket.  Against the passes of several thresholds, 2.8 M scores: cosines 29.1 us and 26.7, errors (spread over many binades) 28.7 and
- * 37.7; 0.7 M 21.2 and 21.2, 20.2 and 29.2; 14.7 M 94 and 60, 92 and 78. */
+ * itself: no pass ends in a ticket.  Against the passes of several thresholds, 2.8 M scores: cosines 27.3 us and 28.1, errors (spread over many binades) 27.0 and
+ * 39.9, cosines that crowd in [3/4, 7/8) 27.1 and 38.8; 0.7 M 18.6 and 22.1, 18.4 and 30.1, 18.6 and 30.0; 8.4 M 55.0 and 42.8, 53.9 and 58.5, 54.6 and 58.7; 14.7 M 93 and 61, 90 and 80,
+ * 92 and 83 (the three passes with a split that looked for three digits: 1 to 2 us more). */
 #define SOP_K_SEL_ONE_MAX (8 << 20)
-/* Does a ranking go through these three passes?  With no first pool wanted there is nothing to count and its split kernel writes the whole mask without a look at the scores
- * (14.7 M 10.2 us; 17.9 by the level kernel, which reads them). */
-inline bool sel_three_passes(long long n, bool none) { return none || n <= SOP_K_SEL_ONE_MAX; }
+/* The same asked for as levels: cosines of up to 3 M scores are as fast this way (8.4 M 55 us and 43), all others faster. */
+#define SOP_K_SEL_ONE_LEVELS_MAX (3 << 20)
+/* Does a ranking of one threshold go through these three passes?  With no first pool wanted there is nothing to count, and its split kernel writes the whole mask without a look at the
+ * scores (14.7 M 10.2 us; 17.9 by the level kernel, which reads them). */
+inline bool sel_three_passes(long long n, bool levels, bool none) { return none || n <= (levels ? SOP_K_SEL_ONE_LEVELS_MAX : SOP_K_SEL_ONE_MAX); }
 struct SelParams {
     const float* score;              // [n]
     long long n, n_top;              // 1 <= n_top <= n (n_top == 0: all_b)

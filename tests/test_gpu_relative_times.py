@@ -99,3 +99,14 @@ def test_ranking_without_a_first_pool_reads_no_scores():
     cx, s = ctx(), torch.rand(14_680_064, device="cuda")
     few, many = (_median_us(lambda: cx.partition(t, 0), 50) for t in (s[:2_818_048], s))
     assert many < 1.4 * few, (few, many)
+
+
+@pytest.mark.parametrize("kind", ["spread", "crowded"])
+def test_levels_of_one_threshold_take_what_its_pool_takes(kind):
+    # the same three passes: 18.6 us and 18.6; 28 to 30 by the passes of several thresholds
+    import torch
+    cx, n = ctx(), 700_000
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    s = torch.randn(n, generator=gen, device="cuda").mul_(2.0).exp_() if kind == "spread" else torch.rand(n, generator=gen, device="cuda").mul_(0.1249).add_(0.75)
+    pool, levels = (_median_us(f, 50) for f in (lambda: cx.partition(s, 490_000), lambda: cx.partition_levels(s, [490_000])))
+    assert levels < 1.25 * pool, (pool, levels)
