@@ -1039,7 +1039,7 @@ extern "C" sop_status sop_partition(sop_ctx* c, const float* score, int64_t n_bl
     if (!aligned16(score)) return fail(c, SOP_EINVAL, "sop_partition: score must be 16-byte aligned");
     if ((reinterpret_cast<uintptr_t>(pool_b) & 3u) || (reinterpret_cast<uintptr_t>(tau) & 3u) || (reinterpret_cast<uintptr_t>(n_a) & 7u))
         return fail(c, SOP_EINVAL, "sop_partition: pool_b and tau must be 4-byte aligned, n_a 8-byte aligned");
-    if (!sel_three_passes(n_blocks, false, n_top == 0)) return partition_levels_impl(c, score, n_blocks, &n_top, 1, higher_is_better, pool_b, tau, n_a, 1, stream);
+    if (!sel_three_passes(n_blocks, false, higher_is_better != 0, n_top == 0)) return partition_levels_impl(c, score, n_blocks, &n_top, 1, higher_is_better, pool_b, tau, n_a, 1, stream);
     return rank_one(c, score, n_blocks, n_top, higher_is_better, pool_b, tau, n_a, stream);
 }
 
@@ -1060,7 +1060,7 @@ static sop_status partition_levels_impl(sop_ctx* c, const float* score, int64_t 
     if (!aligned16(score)) return fail(c, SOP_EINVAL, "sop_partition_levels: score must be 16-byte aligned");
     if ((reinterpret_cast<uintptr_t>(level) & 3u) || (reinterpret_cast<uintptr_t>(tau) & 3u) || (reinterpret_cast<uintptr_t>(n_a) & 7u))
         return fail(c, SOP_EINVAL, "sop_partition_levels: level_dev and tau must be 4-byte aligned, n_a 8-byte aligned");
-    if (n_levels == 1 && n_planes == 1 && sel_three_passes(n_blocks, true, n_top[0] == 0))        // (a pool mask is the levels of one threshold)
+    if (n_levels == 1 && n_planes == 1 && sel_three_passes(n_blocks, true, higher_is_better != 0, n_top[0] == 0))        // (a pool mask is the levels of one threshold)
         return rank_one(c, score, n_blocks, n_top[0], higher_is_better, level, tau, n_a, stream);
     SelMParams p;
     std::memset(&p, 0, sizeof(p));

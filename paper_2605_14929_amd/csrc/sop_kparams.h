@@ -379,11 +379,14 @@ struct LsParams {
  * 39.9, cosines that crowd in [3/4, 7/8) 27.1 and 38.8; 0.7 M 18.6 and 22.1, 18.4 and 30.1, 18.6 and 30.0; 8.4 M 55.0 and 42.8, 53.9 and 58.5, 54.6 and 58.7; 14.7 M 93 and 61, 90 and 80,
  * 92 and 83 (the three passes with a split that looked for three digits: 1 to 2 us more). */
 #define SOP_K_SEL_ONE_MAX (8 << 20)
+/* Scores of which the smaller is the better are errors and no cosines: the line lies where both ways take them as long (8.4 M 54.1 us and 59.1, 9.4 M 63.2 and 63.1, 10.4 M
+ * 68.2 and 66.5; spread over the whole range of binary32, 50.2 and 57.1, 59.3 and 61.4, 63.5 and 65.1). */
+#define SOP_K_SEL_ONE_ERR_MAX (9 << 20)
 /* The same asked for as levels: cosines of up to 3 M scores are as fast this way (8.4 M 55 us and 43), all others faster. */
 #define SOP_K_SEL_ONE_LEVELS_MAX (3 << 20)
 /* Does a ranking of one threshold go through these three passes?  With no first pool wanted there is nothing to count, and its split kernel writes the whole mask without a look at the
  * scores (14.7 M 10.2 us; 17.9 by the level kernel, which reads them). */
-inline bool sel_three_passes(long long n, bool levels, bool none) { return none || n <= (levels ? SOP_K_SEL_ONE_LEVELS_MAX : SOP_K_SEL_ONE_MAX); }
+inline bool sel_three_passes(long long n, bool levels, bool higher, bool none) { return none || n <= (levels ? SOP_K_SEL_ONE_LEVELS_MAX : higher ? SOP_K_SEL_ONE_MAX : SOP_K_SEL_ONE_ERR_MAX); }
 struct SelParams {
     const float* score;              // [n]
     long long n, n_top;              // 1 <= n_top <= n (n_top == 0: all_b)
