@@ -64,3 +64,42 @@ def test_a_step_waits_for_its_row_and_not_for_the_stores_before(tmp_path):
     assert len(found) == 108
     late = {k: v for k, v in found.items() if v != (2 if k[1] == "8" else 1)}
     assert not late
+
+
+PLANE = re.compile(r"plane_kernelILb(\d)ELi(\d+)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E")
+
+
+@pytest.mark.skipif(len(OBJECTS) != 6 or not shutil.which(f"{LLVM}/llvm-objdump"), reason="no objects of a build, or no tools to read them")
+def test_no_variant_of_one_plane_spills(tmp_path):
+    """The searches that write one plane: no spilled vector register, no access to scratch memory (the frame that some of them reserve for scalar registers is kept in
+    lanes of vector registers), and for bf16 weights the last wait before a step asks for its next row is not one for every store in flight."""
+    seen = 0
+    for obj in OBJECTS:
+        list(_kernels(obj, tmp_path))                                # (leaves the code object)
+        code = str(tmp_path / "code")
+        notes = subprocess.run([f"{LLVM}/llvm-readobj", "--notes", code], capture_output=True, text=True, check=True).stdout
+        limits = {}
+        for part in re.split(r"\n\s+- \.a", notes)[1:]:
+            f = dict(re.findall(r"\.?(\w+):\s+(\S+)", part))
+            m = PLANE.search(f.get("symbol", ""))
+            if m:
+                limits[m.group(0)] = m
+                assert int(f["vgpr_count"]) <= 512 // int(m.group(8)), m.group(0)
+                assert int(f["vgpr_spill_count"]) == 0, m.group(0)
+        if not limits:
+            continue
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", code], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"\n[0-9a-f]+ <", text)[1:]:
+            m = PLANE.search(part.split(">")[0])
+            if not m or "s_barrier" not in part:
+                continue
+            assert "scratch_" not in part, m.group(0)
+            seen += 1
+            if m.group(1) == "0":
+                continue
+            lines = part.split("s_barrier")[1].split("\n")            # from the loaded tables to the end of the row loop
+            asks = [i for i, l in enumerate(lines) if "buffer_load_dwordx4" in l]
+            while len(asks) > 1 and asks[-1] - asks[-2] < 14:         # (the requests of one row)
+                asks.pop()
+            assert int(re.findall(r"vmcnt\((\d+)\)", "\n".join(lines[:asks[-1]]))[-1]) > 0, m.group(0)
+    assert seen == 38
