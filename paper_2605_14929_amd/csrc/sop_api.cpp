@@ -127,7 +127,7 @@ struct sop_ctx {
     char* d_bins = nullptr;               // (kImgBytes) the context's own image of the element-search table
     char* d_bins_cur = nullptr;           // the image the searches read (d_bins, or an image inside a caller's workspace during sop_search_layer)
     char* h_bins = nullptr;               // pinned staging for table images of sop_search_layer (allocated at its first call)
-    char* h_res = nullptr;                // pinned memory that its kernels write their results to: histograms, then ACos values
+    char* h_res = nullptr;                // pinned memory that its kernels write their results to: histograms, ACos values, fitted codebooks and their states
     char* d_res = nullptr;                // the same as kernels address it
     hipEvent_t stage_done = nullptr;      // what the last call of sop_search_layer put on its stream has run
     enum { kStageFree, kStagePending, kStageUnmarked } stage = kStageFree;      // nothing to wait for; stage_done; work is on the way that no event stands behind

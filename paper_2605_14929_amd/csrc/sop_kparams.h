@@ -50,7 +50,10 @@ SOP_K_HD constexpr int search_slots(int na) { return (search_cols(na) + 3) / 4 *
  * per-layer procedure, and the errors of one or two under a positive scale, the comparison of weight formats.  They form no codes, need no 16-byte records and keep no
  * pointers of planes that are not there, which is a wavefront more per SIMD, and store without a branch.  4096 x 11008, bf16, ranking scores of six atoms 130 us (any plane) -> 113,
  * of two 49.8 -> 44.4, under a signed word (whose codes were formed to no end) 272 -> 165 and 105 -> 86 (g = 64); fp32 174 -> 121; 28672 x 8192, errors of one atom 149 -> 121;
- * lanes of eight weights, ranking scores of six atoms 161 -> 126, under a signed word 286 -> 157. */
+ * lanes of eight weights, ranking scores of six atoms 161 -> 126, under a signed word 286 -> 157.
+ * Other planes alone (and the ranking scores of a procedure with seven or more atoms, of the argmax rule or the other metrics) come from the kernel of any plane.  By their registers they would gain
+ * as well (bf16, g = 16: ranking scores of eight atoms 154, three wavefronts where any plane leaves two; errors of six 126, four and not three): they are left out for the library's size
+ * and build time, of which every such kind takes a kernel more per block size and weight type (these 38 take 1.3 MB). */
 #define SOP_K_PLANES_NONE 0
 #define SOP_K_PLANES_ALL 1
 #define SOP_K_PLANES_RANK 3
@@ -128,7 +131,8 @@ struct KParams {
     unsigned int gid_w;                            // 4 bits per atom: its scale group (atoms of a group are adjacent)
     unsigned int second_mask;                      // odd bit a: atoms a-1 and a are of one scale group (evaluated together, also where planes but no codes
                                                    // are written); bits 2 and 6: atoms 0..3 and 4..7 are (evaluated together in search mode)
-    unsigned int deal;                             // 1: the shares are short (SOP_K_SHORT_SHARE), their wavefronts' first steps are dealt out
+    unsigned int deal;                             // (one layer) not 0: the wavefronts' first steps are dealt out (search_deal()), and this is the launch's wavefronts per SIMD, which the
+                                                   // kernel takes its number of threads from: never 0 where search_waves() gives fewer than the variant is built for
     unsigned int mirror_mask;                      // bit a: atom a is the sign-negated copy of atom a-1 (signed scale words take its candidates over)
     unsigned int selfsym_mask;                     // bit a: atom a is its own sign-negated copy
     alignas(8) unsigned char nent[SOP_K_MAXA];     // entries of the atom
@@ -201,8 +205,10 @@ inline long long search_workgroups(long long steps, int n_cu, int evaluations)
 }
 
 /* Wavefronts per SIMD of such a launch, of a variant built for occ.  A share of eight steps, two for each of four wavefronts, takes longer than with three wavefronts, which
- * end one after the other (5024 columns, 7.2 to 8 steps a SIMD: six atoms 19.0 us -> 17.9, cosine metric 20.8 -> 19.4, fp32 18.9 -> 18.1, one atom 9.2 -> 8.6; six
- * under a signed word 23.9 -> 23.6).  Other shares do not (5, 6 and 7 steps: 4 to 10 % slower with three wavefronts; 9 to 17: 1 to 5 %). */
+ * end one after the other (7.03 to 8 steps a SIMD in layers of 1024, 2048, 4096, 5024, 5632, 8192, 11008 and 16384 columns, four wavefronts -> three: six atoms 18.7 - 19.5 us -> 17.8 - 18.6, of
+ * fp32 weights 18.3 - 20.7 -> 17.6 - 19.4, by the cosine of fp32 weights 18.0 - 20.7 -> 17.0 - 19.0, seven 21.2 - 21.9 -> 20.7 - 21.3, one 8.8 - 9.8 -> 8.5 - 9.4, two 10.9 - 11.9 -> 10.4 - 11.4; six under a
+ * signed word 23.6 - 24.5 -> 23.4 - 24.0).  Other shares do not (7 steps and a few more than 8, six, seven and six signed atoms: 2 to 10 % slower with three wavefronts, one and two atoms within 4 % either way;
+ * 5024 columns, 5 and 6 steps: 4 to 10 %, 9 to 17: 1 to 5 %). */
 inline int search_waves(int occ, long long steps, long long wg)
 {
     const long long most = ((steps + wg - 1) / wg + 3) / 4;          /* steps of the longest share */

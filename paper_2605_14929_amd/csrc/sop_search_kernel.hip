@@ -842,12 +842,12 @@ __global__ __launch_bounds__(256 * OCC, 1) void plane_kernel(const KParams p)
 
 // ---- kernel table of this part ----
 namespace {
-// Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling (the
-// signed cosine search, with its chunks of look-ups kept apart, at three: 4096 x 4096, six atoms, g = 16, bf16, 47.8 us against 51.6
-// with 18 to 61 registers spilled, fp32 52.8 at three against 59.5 at two, eight atoms 67.6 against 76.8).  The passes that
+// Wavefronts per SIMD each variant is built for (512 / occ registers a lane): as many as its registers allow without spilling.  (With the lanes' sums in registers: the
+// signed cosine search, its chunks of look-ups kept apart, 4096 x 4096, six atoms, g = 16, bf16, three wavefronts 47.8 us against 51.6
+// with 18 to 61 registers spilled, fp32 52.8 at three against 59.5 at two, eight atoms 67.6 against 76.8; in LDS, see lane_sums_in_lds(), they fit one more.)  The passes that
 // evaluate a scale group's atoms together (16 elements a lane, positive scale) hold neither scaled weights
 // nor table addresses and fit one wavefront more than the others: the headline layer (4096 x 11008, six atoms) takes 75.7 us at
-// four against 78.4 with the arrays at three, a 28672 x 8192 layer with seven atoms 530 us at three against 640 at two.  fp32
+// four against 78.4 with the arrays at three, a 28672 x 8192 layer with seven atoms 530 us at three against 640 at two (425 at four, sums in LDS).  fp32
 // weights keep 8 more registers of requested rows: one wavefront less where that is the difference.  Metric COS, from the arrays of one
 // atom at a time at two wavefronts: 4096 x 11008, bf16, 2 / 4 / 6 / 7 atoms 40.2 / 76.3 / 96.6 / 112 us -> 37.6 / 59.6 / 83 / 104.5, two atoms with every
 // plane 84 -> 72.7, fp32 4096 x 4096, six atoms 43.2 -> 37.4; the model-wide search of six atoms (bf16) spills a register at four wavefronts.
@@ -859,14 +859,14 @@ constexpr int occ_for(bool bf16, int epl, int sign_mode, int planes, int na, int
     if (lane_sums_in_lds(bf16, epl, sign_mode, metric, planes, na, multi)) return epl == 16 && ((na == 8 && sign_mode != 0) || (sign_mode == 2 && metric == 1)) ? 3 : 4;      // (109 to 128 registers; 126 to 168)
     if (epl == 8) {
         if (na == 2) return (sign_mode == 1 && emit) ? 3 : 4;
-        if (sign_mode == 1) return emit ? 2 : multi && na == 6 && metric == 0 ? 4 : 3;
+        if (sign_mode == 1) return emit ? 2 : multi && na == 6 && metric == 0 ? 4 : 3;      // (model-wide, g = 8, at three wavefronts and at four: eight layers of 4096 x 4096, six atoms, bf16 380 us and 328, fp32 387 and 337)
         return (emit || na == 8) ? 3 : 4;
     }
     if (sign_mode == 0) {
         if (!emit) return na == 8 || (na == 6 && metric == 1 && multi) ? 3 : (na == 2 || bf16) ? 4 : 3;
         return na == 2 || (na == 6 && bf16 && metric != 1) ? 3 : 2;
     }
-    if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : sign_mode == 1 && (epl == 8 || metric != 2) ? 4 : 3;      // (signed: 104 to 128 registers, MSE a few more; 4096 x 11008, two atoms, 61.7 us at three wavefronts, 56.9 at four, one 38.0 and 34.6)
+    if (na == 2) return emit ? (sign_mode == 1 && metric != 1 && bf16 ? 3 : 2) : sign_mode == 1 && metric != 2 ? 4 : 3;      // (signed: 104 to 128 registers, MSE a few more; 4096 x 11008, two atoms, 61.7 us at three wavefronts, 56.9 at four, one 38.0 and 34.6)
     if (sign_mode == 1) return emit ? (na == 8 ? 1 : 2) : (na == 8 && metric != 1) ? 2 : 3;
     if (emit) return 2;
     return (na == 8 || metric == 1) ? 2 : 3;        // (argmax rule) the cosine metric keeps two more sums per candidate alive
