@@ -1253,16 +1253,16 @@ extern "C" sop_status sop_search_layer(sop_ctx* c, const void* W, sop_dtype dtyp
     DeviceGuard guard(c->device);
     if (guard.err != hipSuccess) return hipfail(c, guard.err, "hipSetDevice");
     hipError_t e = hipSuccess;
+    // (the call waits for its stream: refused before anything of it becomes part of a graph, or an event of one, and before an allocation ends the capture)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if ((e = hipStreamIsCapturing(st, &capturing)) != hipSuccess) return hipfail(c, e, "hipStreamIsCapturing");
+    if (capturing != hipStreamCaptureStatusNone) return fail(c, SOP_EHIP, "sop_search_layer: the call waits for its stream, which is being captured");
     // pinned staging, allocated once per context
     const size_t hist_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_K_DD_MAXBINS * sizeof(long long), acos_bytes = (size_t)kAcosAll * sizeof(double);
     const size_t fits_bytes = (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * SOP_K_FIT_MAXENT * sizeof(float);
     const size_t res_bytes = hist_bytes + acos_bytes + fits_bytes + (size_t)SOP_LAYER_MAX_ATOMS * SOP_LAYER_MAX_P * sizeof(int);
     if (!c->stage_done && (e = stage_setup(c, (size_t)(kFixedMax + SOP_LAYER_MAX_ATOMS + 2) * kImgBytes, res_bytes)) != hipSuccess)
         return hipfail(c, e, "pinned staging of sop_search_layer");
-    // (the call waits for its stream: refused before anything of it becomes part of a graph, or an event of one)
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if ((e = hipStreamIsCapturing(st, &capturing)) != hipSuccess) return hipfail(c, e, "hipStreamIsCapturing");
-    if (capturing != hipStreamCaptureStatusNone) return fail(c, SOP_EHIP, "sop_search_layer: the call waits for its stream, which is being captured");
     if (c->stage != sop_ctx::kStageFree) {             // an earlier call's copies out of the staging buffers and writes to them have run?
         e = c->stage == sop_ctx::kStagePending ? hipEventSynchronize(c->stage_done) : hipDeviceSynchronize();
         if (e != hipSuccess) return hipfail(c, e, "wait for the call before (staging)");

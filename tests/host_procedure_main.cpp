@@ -26,6 +26,7 @@ static int g_fail_after = 0;               // ... after so many that do not
 static int g_searches_outside = 0;         // searches whose results would go to memory that nobody allocated
 static int g_events = 0;                   // events alive
 static bool g_capturing = false;           // the stream is being captured
+static bool g_broken = false;              // ... and a call that no capture allows has been made (it ends the capture)
 static std::string g_log;                  // waits ('e' event, 's' stream, 'd' device) and uploads from pinned memory ('u') in their order
 static bool fails(const char* fn)
 {
@@ -61,7 +62,7 @@ const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) { *p = take(g_device, n); return hipSuccess; }
 hipError_t hipFree(void* p) { CHECK(g_device.erase(static_cast<char*>(p)) == 1); free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { if (fails("hipHostMalloc")) return hipErrorOutOfMemory; *p = take(g_pinned, n); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int) { if (g_capturing) { g_broken = true; return hipErrorStreamCaptureUnsupported; } if (fails("hipHostMalloc")) return hipErrorOutOfMemory; *p = take(g_pinned, n); return hipSuccess; }
 hipError_t hipHostFree(void* p) { CHECK(g_pinned.erase(static_cast<char*>(p)) == 1); free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned int) { if (fails("hipHostGetDevicePointer")) return hipErrorInvalidValue; *d = h; return hipSuccess; }
 hipError_t hipMemset(void* p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
@@ -87,8 +88,8 @@ hipError_t hipEventSynchronize(hipEvent_t e)
     g_log += 'e';
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { if (g_capturing) return hipErrorStreamCaptureUnsupported; g_log += 's'; return hipSuccess; }
-hipError_t hipDeviceSynchronize(void) { if (g_capturing) return hipErrorStreamCaptureUnsupported; g_log += 'd'; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { if (g_capturing) { g_broken = true; return hipErrorStreamCaptureUnsupported; } g_log += 's'; return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { if (g_capturing) { g_broken = true; return hipErrorStreamCaptureUnsupported; } g_log += 'd'; return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* st) { *g = *b = dim3(1, 1, 1); *s = 0; *st = nullptr; return hipSuccess; }
@@ -171,15 +172,16 @@ static void record_fails(bool call_fails)
     CHECK(sop_destroy(c) == SOP_OK);
 }
 
-// a call on a stream that is being captured is refused, whatever else is wrong with it, and leaves the context as it was
-static void captured(int shift)
+// a call on a stream that is being captured is refused, whatever else is wrong with it and also as a context's first, and leaves capture and context as they were
+static void captured(int shift, bool first)
 {
     sop_ctx* c = nullptr;
     CHECK(sop_create(&c, 0) == SOP_OK);
     Layer l(c);
-    CHECK(l.call(c) == SOP_OK);
+    if (!first) CHECK(l.call(c) == SOP_OK);
     g_capturing = true;
     CHECK(l.call(c, shift) != SOP_OK);
+    CHECK(!g_broken);
     g_capturing = false;
     CHECK(l.call(c) == SOP_OK);
     CHECK(l.call(c) == SOP_OK);
@@ -191,8 +193,8 @@ int main(int argc, char** argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "setup") setup_fails(argv[2], std::atoi(argv[3]));
     else if (what == "record") record_fails(std::atoi(argv[2]) != 0);
-    else if (what == "captured") captured(std::atoi(argv[2]));
-    else { std::printf("usage: %s setup FUNCTION CALLS_BEFORE | record CALL_FAILS | captured SHIFT\n", argv[0]); return 2; }
+    else if (what == "captured") captured(std::atoi(argv[2]), std::atoi(argv[3]) != 0);
+    else { std::printf("usage: %s setup FUNCTION CALLS_BEFORE | record CALL_FAILS | captured SHIFT FIRST\n", argv[0]); return 2; }
     if (failures) return 1;
     std::printf("procedure ok\n");
     return 0;

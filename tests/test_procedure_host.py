@@ -31,6 +31,7 @@ def test_work_that_no_event_stands_behind_is_waited_for(program, call_fails):
     _run(program, "record", str(call_fails))
 
 
+@pytest.mark.parametrize("first", [0, 1])
 @pytest.mark.parametrize("shift", [0, 100])                      # (100: out of range, found by the first search)
-def test_a_captured_call_is_refused_and_leaves_nothing(program, shift):
-    _run(program, "captured", str(shift))
+def test_a_captured_call_is_refused_and_leaves_nothing(program, shift, first):
+    _run(program, "captured", str(shift), str(first))
